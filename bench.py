@@ -536,7 +536,7 @@ def bench_short_conv(args, w, sla, si, torch, np) -> int:
         "data": "synthetic",
         "config": {
             "workload": f"{w.name}: short convolution + SiLU over [B={w.B}, T={w.T}, C={C}] {w.dtype}, {taps} taps, fp32 weights",
-            "kernel": f"sla_short_conv_silu_kernel<{'true' if w.dtype == 'bf16' else 'false'}, {taps}>",
+            "kernel": f"sla_feature_map_kernel<{'true' if w.dtype == 'bf16' else 'false'}, {taps}, 0>",
         },
         "roofline": {
             "bound": "hbm",

@@ -6,11 +6,19 @@
 //   * the Gated DeltaNet blocks' feature map (Sec. 5.1, Model Configuration: short convolution, then SiLU), with
 //     an optional division of every head's vector by sqrt(sum of squares + eps), forward and backward.
 //
-// All of it streams: a thread owns eight adjacent channels (16 bytes of a token row), a wave covers 1 KB of every
+// All of it streams, but the feature map is bound by the vector pipes as much as by memory: about 130 (backward 265)
+// instructions per eight channels and token.  Hence U tokens' loads in flight, whose registers are reloaded where they
+// are read, shifts of the window by unrolling instead of moves, and the reciprocal in sigmoidf().  bf16, B=8 T=4096
+// 2048 channels: forward with L2 65 -> 58 us (268 MB, 4.6 TB/s), without 55 -> 44 us, backward 125 -> 102 us (402 MB,
+// 3.9 TB/s; 227 registers: two wavefronts per SIMD).  The device's own copy of the same tensor takes 37 us.
+//
+// A thread owns eight adjacent channels (16 bytes of a token row), a wave covers 1 KB of every
 // row it touches.  Sums over tokens (dW, dw) are taken in two deterministic stages: every thread leaves the sum
 // over its own tokens in the workspace, a second kernel adds those partial sums in a fixed order.  No atomics.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "sla.h"
 
@@ -22,7 +30,8 @@ typedef __attribute__((ext_vector_type(4))) uint32_t gu4;
 typedef __attribute__((ext_vector_type(4))) float gf4;
 
 constexpr int kGThreads = 256;
-constexpr int kSeg = 64;  // tokens per thread of the convolution kernels
+// Tokens per thread of the convolution kernels (multiples of 4): see segment_length().
+constexpr int kSegMax = 64, kSegMin = 16;
 constexpr float kLog2e = 1.4426950408889634f;
 
 template <bool BF16>
@@ -87,17 +96,49 @@ __device__ __forceinline__ float head_allsum(float s) {
     return s;
 }
 
-__device__ __forceinline__ float sigmoidf(float s) { return 1.f / (1.f + __builtin_amdgcn_exp2f(-s * kLog2e)); }
+// 1 / (1 + e^-s): the hardware reciprocal with one Newton step, 7 instructions where the IEEE division alone takes 10.
+// An infinite e^-s makes the step 0 * inf; fmaxf drops that NaN, and the result is the 0 it should be.  (A NaN s gives
+// 0 here; every use multiplies by s.)
+__device__ __forceinline__ float sigmoidf(float s) {
+    const float d = 1.f + __builtin_amdgcn_exp2f(-s * kLog2e), r = __builtin_amdgcn_rcpf(d);
+    return fmaxf(__builtin_fmaf(__builtin_fmaf(-d, r, 1.f), r, r), 0.f);
+}
+
+// Eight adjacent elements as loaded: a load in flight keeps four registers (bf16; fp32: eight) until it is used.
+template <bool BF16>
+struct Raw8 {
+    gu4 v[BF16 ? 1 : 2];
+    __device__ __forceinline__ void load(const void* x, size_t off) {
+        if constexpr (BF16) {
+            v[0] = *(const gu4*)((const uint16_t*)x + off);
+        } else {
+            v[0] = *(const gu4*)((const float*)x + off);
+            v[1] = *(const gu4*)((const float*)x + off + 4);
+        }
+    }
+    __device__ __forceinline__ void get(float* f) const {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if constexpr (BF16) {
+                f[2 * i] = __uint_as_float(v[0][i] << 16);
+                f[2 * i + 1] = __uint_as_float(v[0][i] & 0xffff0000u);
+            } else {
+                f[i] = __uint_as_float(v[0][i]);
+                f[4 + i] = __uint_as_float(v[1][i]);
+            }
+        }
+    }
+};
 
 // ------------------------------------------------------------------------------------------------------------
 // Feature map with the L2 option: y = silu(conv(x)), then every head (LPH lanes x 8 channels) divided by
-// sqrt(sum of squares + eps).  LPH = 0: no normalisation.  Thread -> (batch row, 64-token segment, 8 channels);
+// sqrt(sum of squares + eps).  LPH = 0: no normalisation.  Thread -> (batch row, segment of tokens, 8 channels);
 // the lanes of a head sit in one 16-lane row and walk the same tokens in step.
 // ------------------------------------------------------------------------------------------------------------
 template <bool BF16, int K, int LPH>
 __global__ __launch_bounds__(kGThreads) void sla_feature_map_kernel(const void* x, const float* w, void* y, int B, int T,
-                                                                     int C, float eps) {
-    const int groups = C / 8, segs = (T + kSeg - 1) / kSeg;
+                                                                     int C, int seg_len, float eps) {
+    const int groups = C / 8, segs = (T + seg_len - 1) / seg_len;
     const size_t idx = (size_t)blockIdx.x * kGThreads + threadIdx.x;
     const size_t total = (size_t)B * segs * groups;
     // threads past the end repeat the last one (so that the cross-lane sums stay defined) and store nothing
@@ -109,7 +150,7 @@ __global__ __launch_bounds__(kGThreads) void sla_feature_map_kernel(const void* 
     for (int c = 0; c < 8; ++c)
 #pragma unroll
         for (int i = 0; i < K; ++i) wt[i][c] = w[(size_t)(8 * cg + c) * K + i];
-    const int t0 = seg * kSeg, t1 = min(T, t0 + kSeg);
+    const int t0 = seg * seg_len, t1 = min(T, t0 + seg_len);
     const size_t row0 = (size_t)b * T;
     float hist[K][8];
 #pragma unroll
@@ -122,19 +163,21 @@ __global__ __launch_bounds__(kGThreads) void sla_feature_map_kernel(const void* 
             for (int c = 0; c < 8; ++c) hist[i + 1][c] = 0.f;
         }
     }
+    // U tokens in flight: each register set is loaded again with the token U later as soon as it has been read, also
+    // past the segment's end (the token is clamped; nothing is made of it)
     constexpr int U = 4;
-    for (int tb = t0; tb < t0 + kSeg; tb += U) {  // every lane of a row runs the same trip count
-        float in[U][8];
+    Raw8<BF16> in[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) ld8<BF16>(x, (row0 + min(tb + u, t1 - 1)) * C + 8 * cg, in[u]);
+    for (int u = 0; u < U; ++u) in[u].load(x, (row0 + min(t0 + u, T - 1)) * C + 8 * cg);
+    for (int tb = t0; tb < t0 + seg_len; tb += U) {  // every lane of a row runs the same trip count
 #pragma unroll
         for (int u = 0; u < U; ++u) {
 #pragma unroll
             for (int i = 0; i < K - 1; ++i)
 #pragma unroll
                 for (int c = 0; c < 8; ++c) hist[i][c] = hist[i + 1][c];
-#pragma unroll
-            for (int c = 0; c < 8; ++c) hist[K - 1][c] = in[u][c];
+            in[u].get(hist[K - 1]);
+            in[u].load(x, (row0 + min(tb + U + u, T - 1)) * C + 8 * cg);
             float out[8], ss = 0.f;
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
@@ -158,15 +201,15 @@ __global__ __launch_bounds__(kGThreads) void sla_feature_map_kernel(const void* 
 // Its backward.  With s the convolution, a = silu(s), r = (sum_head a^2 + eps)^-1/2, y = a r:
 //     da = r dy - a r^3 sum_head(a dy),   ds = da sigmoid(s) (1 + s (1 - sigmoid(s))),
 //     dx[u] = sum_i w[i] ds[u + (K-1) - i],   dw[i] = sum_t ds[t] x[t - (K-1) + i].
-// A thread recomputes s for its 64 tokens and for the K-1 tokens after them (whose ds reaches back into its
+// A thread recomputes s for its tokens and for the K-1 tokens after them (whose ds reaches back into its
 // segment), keeps the last K values of ds, and writes dx[u] once ds[u + K - 1] is known.  Its share of dw (own
 // tokens only) goes to part[(b * segs + seg)][channel][tap].
 // ------------------------------------------------------------------------------------------------------------
 template <bool BF16, int K, int LPH>
 __global__ __launch_bounds__(kGThreads) void sla_feature_map_bwd_kernel(const void* x, const float* w, const void* dy,
                                                                          void* dx, float* part, int B, int T, int C,
-                                                                         float eps) {
-    const int groups = C / 8, segs = (T + kSeg - 1) / kSeg;
+                                                                         int seg_len, float eps) {
+    const int groups = C / 8, segs = (T + seg_len - 1) / seg_len;
     const size_t idx = (size_t)blockIdx.x * kGThreads + threadIdx.x;
     const size_t total = (size_t)B * segs * groups;
     const bool live = idx < total;
@@ -177,7 +220,7 @@ __global__ __launch_bounds__(kGThreads) void sla_feature_map_bwd_kernel(const vo
     for (int c = 0; c < 8; ++c)
 #pragma unroll
         for (int i = 0; i < K; ++i) wt[i][c] = w[(size_t)(8 * cg + c) * K + i];
-    const int t0 = seg * kSeg, t1 = min(T, t0 + kSeg);
+    const int t0 = seg * seg_len, t1 = min(T, t0 + seg_len);
     const size_t row0 = (size_t)b * T;
     float hist[K][8];  // hist[i] = x[t - (K-1) + i]
 #pragma unroll
@@ -199,20 +242,17 @@ __global__ __launch_bounds__(kGThreads) void sla_feature_map_bwd_kernel(const vo
             dsh[i][c] = 0.f;
             dwacc[i][c] = 0.f;
         }
-    // tokens t0 .. t0 + 63 + (K-1): beyond min(T, ...) the cotangent is zero (nothing flows back from there)
-    for (int t = t0; t < t0 + kSeg + K - 1; ++t) {
-        const bool inside = t < T;               // a real token (maybe of the next segment)
-        const bool own = t < t1;                 // a token of this thread's segment
-        const int tc = min(t, T - 1);
-        float xin[8], g[8];
-        ld8<BF16>(x, (row0 + tc) * C + 8 * cg, xin);
-        ld8<BF16>(dy, (row0 + tc) * C + 8 * cg, g);
+    // One token: its gradient with respect to the convolution's output, its share of dw if OWN, and dx of the token
+    // K-1 before it.  Tokens past the sequence carry no cotangent.
+    auto token = [&](int t, auto own, const Raw8<BF16>& xr, const Raw8<BF16>& gr) __attribute__((always_inline)) {
+        const bool inside = t < T;  // a real token (maybe of the next segment)
+        float g[8];
 #pragma unroll
         for (int i = 0; i < K - 1; ++i)
 #pragma unroll
             for (int c = 0; c < 8; ++c) hist[i][c] = hist[i + 1][c];
-#pragma unroll
-        for (int c = 0; c < 8; ++c) hist[K - 1][c] = xin[c];
+        xr.get(hist[K - 1]);
+        gr.get(g);
         float s[8], sg[8], a[8], ss = 0.f, ag = 0.f;
 #pragma unroll
         for (int c = 0; c < 8; ++c) {
@@ -243,24 +283,46 @@ __global__ __launch_bounds__(kGThreads) void sla_feature_map_bwd_kernel(const vo
         for (int c = 0; c < 8; ++c) {
             const float ds = inside ? da[c] * sg[c] * (1.f + s[c] * (1.f - sg[c])) : 0.f;
             dsh[K - 1][c] = ds;
-            if (own) {
+            if constexpr (decltype(own)::value) {
 #pragma unroll
                 for (int i = 0; i < K; ++i) dwacc[i][c] += ds * hist[i][c];
             }
         }
         // dx[u] for u = t - (K-1): ds[u + (K-1) - i] = dsh[K-1-i]
         const int u = t - (K - 1);
-        if (live && u >= t0 && u < t1) {
-            float o[8];
+        float o[8];
 #pragma unroll
-            for (int c = 0; c < 8; ++c) {
-                float acc = 0.f;
+        for (int c = 0; c < 8; ++c) {
+            float acc = 0.f;
 #pragma unroll
-                for (int i = 0; i < K; ++i) acc += wt[i][c] * dsh[K - 1 - i][c];
-                o[c] = acc;
-            }
-            st8<BF16, true>(dx, (row0 + u) * C + 8 * cg, o);
+            for (int i = 0; i < K; ++i) acc += wt[i][c] * dsh[K - 1 - i][c];
+            o[c] = acc;
         }
+        if (live && u >= t0 && u < t1) st8<BF16, true>(dx, (row0 + u) * C + 8 * cg, o);
+    };
+    // U tokens in flight, as in the forward
+    constexpr int U = BF16 ? 4 : 2;
+    Raw8<BF16> xr[U], gr[U];
+    auto fetch = [&](int n, int t) __attribute__((always_inline)) {
+        const size_t at = (row0 + min(t, T - 1)) * C + 8 * cg;
+        xr[n].load(x, at);
+        gr[n].load(dy, at);
+    };
+#pragma unroll
+    for (int n = 0; n < U; ++n) fetch(n, t0 + n);
+    for (int tb = t0; tb < t0 + seg_len; tb += U) {
+#pragma unroll
+        for (int n = 0; n < U; ++n) {
+            const Raw8<BF16> xn = xr[n], gn = gr[n];
+            fetch(n, tb + U + n);
+            token(tb + n, std::true_type{}, xn, gn);
+        }
+    }
+    // the K-1 tokens after the segment: their ds reaches back into it
+#pragma unroll
+    for (int n = 0; n < K - 1; ++n) {
+        if (n >= U) fetch(n % U, t0 + seg_len + n);
+        token(t0 + seg_len + n, std::false_type{}, xr[n % U], gr[n % U]);
     }
     if (live) {
         float* p = part + ((size_t)(b * segs + seg) * C + 8 * cg) * K;
@@ -351,14 +413,14 @@ __global__ __launch_bounds__(kGThreads) void sla_gate_logits_bwd_kernel(const vo
 
 template <bool BF16, int K>
 int feature_map_lph(int lph, bool bwd, dim3 grid, hipStream_t st, const void* x, const float* w, const void* dy, void* out,
-                    float* part, int B, int T, int C, float eps) {
+                    float* part, int B, int T, int C, int seg, float eps) {
 #define SLA_FM(LPH)                                                                                                  \
     if (bwd)                                                                                                         \
         hipLaunchKernelGGL((sla_feature_map_bwd_kernel<BF16, K, LPH>), grid, dim3(kGThreads), 0, st, x, w, dy, out,  \
-                           part, B, T, C, eps);                                                                      \
+                           part, B, T, C, seg, eps);                                                                      \
     else                                                                                                             \
         hipLaunchKernelGGL((sla_feature_map_kernel<BF16, K, LPH>), grid, dim3(kGThreads), 0, st, x, w, out, B, T, C, \
-                           eps);                                                                                     \
+                           seg, eps);                                                                                     \
     break;
     switch (lph) {
         case 0: SLA_FM(0)
@@ -373,12 +435,12 @@ int feature_map_lph(int lph, bool bwd, dim3 grid, hipStream_t st, const void* x,
 
 template <bool BF16>
 int feature_map_taps(int taps, int lph, bool bwd, dim3 grid, hipStream_t st, const void* x, const float* w, const void* dy,
-                     void* out, float* part, int B, int T, int C, float eps) {
+                     void* out, float* part, int B, int T, int C, int seg, float eps) {
     switch (taps) {
-        case 1: return feature_map_lph<BF16, 1>(lph, bwd, grid, st, x, w, dy, out, part, B, T, C, eps);
-        case 2: return feature_map_lph<BF16, 2>(lph, bwd, grid, st, x, w, dy, out, part, B, T, C, eps);
-        case 3: return feature_map_lph<BF16, 3>(lph, bwd, grid, st, x, w, dy, out, part, B, T, C, eps);
-        case 4: return feature_map_lph<BF16, 4>(lph, bwd, grid, st, x, w, dy, out, part, B, T, C, eps);
+        case 1: return feature_map_lph<BF16, 1>(lph, bwd, grid, st, x, w, dy, out, part, B, T, C, seg, eps);
+        case 2: return feature_map_lph<BF16, 2>(lph, bwd, grid, st, x, w, dy, out, part, B, T, C, seg, eps);
+        case 3: return feature_map_lph<BF16, 3>(lph, bwd, grid, st, x, w, dy, out, part, B, T, C, seg, eps);
+        case 4: return feature_map_lph<BF16, 4>(lph, bwd, grid, st, x, w, dy, out, part, B, T, C, seg, eps);
         default: return SLA_ERR_UNSUPPORTED;
     }
 }
@@ -389,29 +451,59 @@ int sum_partials(const float* part, float* out, size_t stride, int nparts, hipSt
     return hipGetLastError() == hipSuccess ? SLA_OK : SLA_ERR_HIP;
 }
 
+// Tokens per thread.  64 while that leaves two wavefronts per SIMD (131072 threads): a segment re-reads the K-1 tokens
+// before it, and the backward also recomputes the K-1 tokens after it.  With fewer, a thread's walk is a serial chain
+// of about 0.3 us (backward 0.65 us) a token whatever else the chip does, so it is cut: B=4 T=777 640 channels, forward
+// 24.9 -> 9.6 us, backward 46.6 -> 20.0 us, 64 against 16.  `least`: the shortest the caller allows.
+int segment_length(int B, int T, int C, int least) {
+    int seg = kSegMax;
+    while (seg > least && (size_t)B * ((T + seg - 1) / seg) * (C / 8) < 131072) seg /= 2;
+    return seg;
+}
+
+// The backward's shortest segment: a bound on the partial sums of dw (which the workspace holds) that does not depend
+// on the channels: long batches have wavefronts enough with segments of 64 at any usual width.
+int backward_least(int B, int T) {
+    const size_t rows = (size_t)B * T;
+    return rows >= 131072 ? kSegMax : rows >= 32768 ? 32 : kSegMin;
+}
+
 }  // namespace
 
-// Segments of 64 tokens per batch row: the number of partial sums of dw is B times this.
-size_t feature_map_partials(int B, int T) { return (size_t)B * ((T + kSeg - 1) / kSeg); }
+// Partial sums of dw the workspace has room for: one per batch row and segment of the shortest length.
+size_t feature_map_partials(int B, int T) {
+    const int least = backward_least(B, T);
+    return (size_t)B * ((T + least - 1) / least);
+}
 
 int launch_feature_map(int dtype, int B, int T, int C, int taps, int head_width, float eps, const void* x, const float* w,
                        void* y, hipStream_t stream) {
-    const size_t threads = feature_map_partials(B, T) * (C / 8);
+    const int seg = segment_length(B, T, C, kSegMin);
+    const size_t threads = (size_t)B * ((T + seg - 1) / seg) * (C / 8);
     const dim3 grid((unsigned)((threads + kGThreads - 1) / kGThreads));
     if (dtype == SLA_BF16)
-        return feature_map_taps<true>(taps, head_width / 8, false, grid, stream, x, w, nullptr, y, nullptr, B, T, C, eps);
-    return feature_map_taps<false>(taps, head_width / 8, false, grid, stream, x, w, nullptr, y, nullptr, B, T, C, eps);
+        return feature_map_taps<true>(taps, head_width / 8, false, grid, stream, x, w, nullptr, y, nullptr, B, T, C, seg,
+                                      eps);
+    return feature_map_taps<false>(taps, head_width / 8, false, grid, stream, x, w, nullptr, y, nullptr, B, T, C, seg,
+                                   eps);
+}
+
+// The feature map without the normalisation.
+int launch_short_conv_silu(int dtype, int B, int T, int C, int taps, const void* x, const float* w, void* y,
+                           hipStream_t stream) {
+    return launch_feature_map(dtype, B, T, C, taps, 0, 0.f, x, w, y, stream);
 }
 
 int launch_feature_map_backward(int dtype, int B, int T, int C, int taps, int head_width, float eps, const void* x,
                                 const float* w, const void* dy, void* dx, float* dw, float* workspace,
                                 hipStream_t stream) {
-    const size_t nparts = feature_map_partials(B, T), threads = nparts * (C / 8);
+    const int seg = segment_length(B, T, C, backward_least(B, T));
+    const size_t nparts = (size_t)B * ((T + seg - 1) / seg), threads = nparts * (C / 8);
     const dim3 grid((unsigned)((threads + kGThreads - 1) / kGThreads));
     const int rc = dtype == SLA_BF16 ? feature_map_taps<true>(taps, head_width / 8, true, grid, stream, x, w, dy, dx,
-                                                              workspace, B, T, C, eps)
+                                                              workspace, B, T, C, seg, eps)
                                      : feature_map_taps<false>(taps, head_width / 8, true, grid, stream, x, w, dy, dx,
-                                                               workspace, B, T, C, eps);
+                                                               workspace, B, T, C, seg, eps);
     if (rc != SLA_OK) return rc;
     return sum_partials(workspace, dw, (size_t)C * taps, (int)nparts, stream);
 }

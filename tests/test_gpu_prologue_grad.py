@@ -107,3 +107,41 @@ def test_prologue_and_mixer_gradients_chain():
     assert rel_err(_host(gr["dq"]), ref["dq"] + pq) <= 2e-2
     assert rel_err(_host(gr["dk"]), ref["dk"] + pk) <= 2e-2
     assert rel_err(_host(dwq), rwq) <= 2e-2 and rel_err(_host(dwk), rwk) <= 2e-2
+
+
+@pytest.mark.parametrize("C", [1024, 2048])
+def test_feature_map_segment_lengths_agree(C):
+    """How many tokens a thread walks depends on the size of the batch (here 32 and 64, a row alone: 16); every token's
+    arithmetic is the same, so rows of a batch equal the rows run alone, bit for bit; dw differs by summation order."""
+    import torch
+
+    import paper_2602_01744_amd as sla
+
+    B, T = 40, 1090
+    gen = torch.Generator(device="cuda").manual_seed(3300 + C)
+    x, dy = (torch.randn(B, T, C, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    w = torch.randn(C, 4, generator=gen, device="cuda") * 0.5
+    y = sla.short_conv_silu_l2(x, w, 128)
+    dx, dw = sla.short_conv_silu_l2_backward(x, w, dy, 128)
+    rows = [sla.short_conv_silu_l2_backward(x[b : b + 1], w, dy[b : b + 1], 128) for b in range(B)]
+    for b in range(B):
+        assert torch.equal(sla.short_conv_silu_l2(x[b : b + 1], w, 128)[0], y[b])
+        assert torch.equal(rows[b][0][0], dx[b])
+    total = torch.stack([r[1].double() for r in rows]).sum(0)
+    assert float((dw.double() - total).abs().max() / total.abs().max()) <= 1e-5
+
+
+def test_feature_map_saturates():
+    """SiLU far out: exactly 0 (not NaN) where e^-s overflows, s itself on the other side; gradients 0 and dy."""
+    import torch
+
+    import paper_2602_01744_amd as sla
+
+    x = torch.tensor([-3e38, -1e4, -100.0, 100.0, 1e4, 3e38, 0.0, -0.0], device="cuda").repeat(1, 5, 1)
+    w = torch.ones(8, 1, device="cuda")
+    dy = torch.full_like(x, 2.0)
+    want = torch.where(x > 0, x, torch.zeros_like(x))
+    assert torch.equal(sla.short_conv_silu(x, w), want)
+    dx, _ = sla.short_conv_silu_l2_backward(x, w, dy)
+    assert torch.equal(dx[..., :6], torch.where(x > 0, dy, torch.zeros_like(x))[..., :6])
+    assert torch.equal(dx[..., 6:], torch.ones_like(dx[..., 6:]))
