@@ -2,11 +2,27 @@
 // (batch, head), the constant-memory inference form (Sec. 3.2, Recurrent Implementation; derived in Appendix A).
 //
 // The step reads and rewrites the whole state, 2 * dk * dv * 4 bytes per head against O(dk * dv) flops: it is
-// HBM-bound, so the kernel is a streaming read-modify-write.  One workgroup of 256 threads per (batch, head);
-// thread (rg, c4) owns four adjacent value columns of the rows rg, rg + NRG, rg + 2 NRG, ...: a wave touches
-// whole 512-byte (dv = 128) row segments, every thread has all of its 16-byte loads in flight at once
-// (64 KB per workgroup), and the state tile stays in registers between the read and the write -- also for the
-// delta rule, whose write depends on a reduction (k S) over the whole tile.
+// HBM-bound, so the kernel is a streaming read-modify-write.  A workgroup of 256 threads owns DS adjacent value
+// columns of one (batch, head): no step of the recurrence mixes value columns, so the slices are independent.
+// Thread (rg, c4) owns four adjacent columns of the rows rg, rg + NRG, rg + 2 NRG, ...; every load of the workgroup
+// (logits or projection, q, k, decay, v, then the state) is issued in the order of use before anything waits, and the
+// state stays in registers between the read and the write -- also for the delta rule, whose write depends on a
+// reduction (k S) over the whole slice.  Sums over rows meet by shuffles inside a wave and through LDS between the four
+// waves.  The slices of a head run on one XCD.
+// Slice width: 64 columns (8 state rows per thread at dk = 128).  32 while 64 give at most 256 workgroups: the call is
+// then one round of loads and stores whose length is the rows per thread (64 / 32 columns, us: B=1 H=4 128 x 256 fused
+// 3.8 / 3.7, B=4 H=16 128 x 128 5.0 / 4.9); from there on 32 pays for twice the q, k, decay and gate loads (B=32 H=32
+// 64 x 64 fused 9.2 / 11.2), and 128 and more have fewer wavefronts per compute unit (B=64 H=16 128 x 256 49.9 / 52.4).
+// Kernel time in us against one workgroup per (batch, head) and the gates' loads behind the state's, the earlier form
+// (bf16, graph of 48 steps; "far": over several states, so that they come from HBM, "near": one state, which the
+// memory-side cache holds):
+//     B  H  dk x dv                      near           far
+//     1  4  128 x 256 GLA, fused      6.2 ->  3.7
+//     1  16 128 x 128 delta rule      4.8 ->  3.8
+//     64 16 128 x 128 delta rule     23.0 -> 21.6   30.9 -> 28.1 (4.8 TB/s)
+//     64 16 128 x 128 GLA, fused     21.8 -> 22.4   29.8 -> 29.2
+//     64 16 128 x 256 delta rule     50.2 -> 41.0   64.0 -> 51.7 (5.2 TB/s)
+//     256 32 32 x 64  GLA            23.2 -> 22.4   28.4 -> 26.2
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -33,7 +49,7 @@ struct DArgs {
     const float* beta;
     float* state;
     void* out;
-    int B, H;
+    int B, H, dv;
 };
 
 __device__ __forceinline__ float dec_exp(float x) { return __builtin_amdgcn_exp2f(x * kDecLog2e); }
@@ -76,55 +92,93 @@ __device__ __forceinline__ uint32_t dec_pack_bf16(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, t);
 }
 
-// softmax over the H logits of one batch row, evaluated for head h (Eq. 4); every lane of the wave returns it
-__device__ __forceinline__ float decode_gate(const float* logits, int H, int h, int lane) {
-    const float x = lane < H ? logits[lane] : -INFINITY;
+// softmax over the H logits of one batch row, lane i holding logit i (lanes past H: -inf), evaluated for head h (Eq. 4);
+// every lane of the wave returns it
+__device__ __forceinline__ float decode_gate(float x, int H, int h, int lane) {
     float m = x;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
-    float s = lane < H ? dec_exp(x - m) : 0.f;
+    const float e = lane < H ? dec_exp(x - m) : 0.f;
+    float s = e;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
-    return dec_exp(logits[h] - m) / s;
+    return __shfl(e, h) / s;
 }
 
-template <bool BF16, int VAR, int DK, int DV>
+// Sum over the row groups that share a wave (lanes NC4 apart hold the same columns), left in all of them.
+template <int NC4>
+__device__ __forceinline__ float wave_rows_sum(float x) {
+#pragma unroll
+    for (int o = NC4; o < 64; o <<= 1) x += __shfl_xor(x, o);
+    return x;
+}
+
+// One workgroup: `DS` adjacent value columns (slice blockIdx.x % slices) of one (batch, head).
+template <bool BF16, int VAR, int DK, int DS>
 __global__ __launch_bounds__(kDecThreads) void sla_decode_kernel(const DArgs a) {
-    constexpr int NC4 = DV / 4;            // threads along a row
-    constexpr int NRG = kDecThreads / NC4; // row groups
-    constexpr int RPT = DK / NRG;          // rows per thread
-    static_assert(DK % NRG == 0 && RPT >= 1, "rows divide among the row groups");
-    __shared__ float red[NRG][DV];  // per-row-group partial sums over the state rows
+    constexpr int NC4 = DS / 4;             // threads along a row of the slice
+    constexpr int NRG = kDecThreads / NC4;  // row groups
+    constexpr int RPT = DK / NRG;           // rows per thread
+    constexpr int NW = kDecThreads / 64;
+    static_assert(NC4 <= 64 && DK % NRG == 0 && RPT >= 1, "rows divide among the row groups, a row lies in one wave");
+    __shared__ float red[NW][DS];  // per-wave partial sums over the state rows
 
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int bh = blockIdx.x, b = bh / a.H, h = bh % a.H;
-    const int c4 = tid % NC4, rg = tid / NC4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // workgroups go round-robin over the eight XCDs: the slices of a head, which share its rows' memory pages and its
+    // vectors, are placed on one of them
+    const int slices = a.dv / DS, place = blockIdx.x >> 3, slice = place % slices;
+    const int bh = (place / slices) * 8 + (blockIdx.x & 7), b = bh / a.H, h = bh % a.H;
+    if (bh >= a.B * a.H) return;
+    const int c4 = tid % NC4, rg = tid / NC4, row4 = a.dv / 4;
 
-    // the state tile of this thread: issue every load before anything waits for one (the gates, which need a
-    // round trip of their own, are formed while these are in flight)
-    d_f32x4* srow = (d_f32x4*)(a.state + (size_t)bh * DK * DV) + c4;
+    // Loads come back in the order they were issued, so what the gates are made of goes first: they are then formed
+    // while the state tile and the token's vectors, all issued before anything waits, are still on their way.
+    constexpr int TPH = DK >= 64 ? 16 : 8, EPT = DK / TPH;  // fused projection: threads per head, elements per thread
+    const int sub = tid % TPH;
+    int h2 = tid / TPH;
+    float xq[EPT], xk[EPT], wq[EPT], wk[EPT], lq = -INFINITY, lk = -INFINITY;
+    auto load_projection = [&]() __attribute__((always_inline)) {
+        const size_t at = ((size_t)b * a.H + h2) * DK + sub * EPT, wat = (size_t)h2 * DK + sub * EPT;
+        load_run<BF16, EPT>(a.q, at, xq);
+        load_run<false, EPT>(a.wq, wat, wq);
+        if (a.wk) {
+            load_run<BF16, EPT>(a.k, at, xk);
+            load_run<false, EPT>(a.wk, wat, wk);
+        }
+    };
+    if (a.wq) {
+        if (h2 < a.H) load_projection();
+    } else if (lane < a.H) {
+        lq = a.ql[(size_t)b * a.H + lane];
+        if (a.kl) lk = a.kl[(size_t)b * a.H + lane];
+    }
+    d_f32x4* srow = (d_f32x4*)(a.state + (size_t)bh * DK * a.dv + slice * DS) + c4;
+    float qd[RPT], kd[RPT], ad[RPT];
+#pragma unroll
+    for (int i = 0; i < RPT; ++i) {
+        const size_t d = (size_t)bh * DK + rg + NRG * i;
+        qd[i] = load_elem<BF16>(a.q, d);
+        kd[i] = load_elem<BF16>(a.k, d);
+        if constexpr (VAR == SLA_GLA) ad[i] = load_elem<BF16>(a.ld, d);
+    }
+    float v4[4], ld_scalar = 0.f, bt = 0.f;
+    load_run<BF16, 4>(a.v, (size_t)bh * a.dv + slice * DS + 4 * c4, v4);
+    if constexpr (VAR == SLA_RETNET) ld_scalar = ((const float*)a.ld)[h];
+    if constexpr (VAR == SLA_GDN) {
+        ld_scalar = ((const float*)a.ld)[bh];
+        bt = a.beta[bh];
+    }
     d_f32x4 S[RPT];
 #pragma unroll
-    for (int i = 0; i < RPT; ++i) S[i] = srow[(size_t)(rg + NRG * i) * NC4];
+    for (int i = 0; i < RPT; ++i) S[i] = srow[(size_t)(rg + NRG * i) * row4];
 
-    float gq, gk;
     if (a.wq) {
         // Fused gate projection (Eq. 4 needs the logits of every head of the token): TPH threads per head (16; 8 for
         // dk = 32), each thread DK/TPH >= 4 adjacent elements of q[b,h',:] . W_GQ[:,h'] and k[b,h',:] . W_GK[:,h'],
         // summed over the TPH threads with shuffles -- 2 H dk multiply-adds against the dk dv of the state update, and
         // one launch less in front of every decode step.
         __shared__ float lg[2][64];
-        constexpr int TPH = DK >= 64 ? 16 : 8, EPT = DK / TPH;
-        const int sub = tid % TPH;
-        for (int h2 = tid / TPH; h2 < a.H; h2 += kDecThreads / TPH) {
-            const size_t at = ((size_t)b * a.H + h2) * DK + sub * EPT, wat = (size_t)h2 * DK + sub * EPT;
-            float xq[EPT], xk[EPT], wq[EPT], wk[EPT];
-            load_run<BF16, EPT>(a.q, at, xq);
-            load_run<false, EPT>(a.wq, wat, wq);
-            if (a.wk) {
-                load_run<BF16, EPT>(a.k, at, xk);
-                load_run<false, EPT>(a.wk, wat, wk);
-            }
+        while (h2 < a.H) {
             float sq = 0.f, sk = 0.f;
 #pragma unroll
             for (int e = 0; e < EPT; ++e) {
@@ -140,30 +194,19 @@ __global__ __launch_bounds__(kDecThreads) void sla_decode_kernel(const DArgs a) 
                 lg[0][h2] = sq;
                 lg[1][h2] = sk;
             }
+            h2 += kDecThreads / TPH;
+            if (h2 < a.H) load_projection();
         }
         __syncthreads();
-        gq = decode_gate(lg[0], a.H, h, lane);
-        gk = a.wk ? decode_gate(lg[1], a.H, h, lane) : 1.f;
-    } else {
-        gq = decode_gate(a.ql + (size_t)b * a.H, a.H, h, lane);
-        gk = a.kl ? decode_gate(a.kl + (size_t)b * a.H, a.H, h, lane) : 1.f;
+        if (lane < a.H) {
+            lq = lg[0][lane];
+            lk = lg[1][lane];
+        }
     }
+    const float gq = decode_gate(lq, a.H, h, lane);
+    const float gk = a.wk || a.kl ? decode_gate(lk, a.H, h, lane) : 1.f;
 
-    float qd[RPT], kd[RPT], ad[RPT];
-    float a_scalar = 1.f;
-    if constexpr (VAR == SLA_RETNET) a_scalar = dec_exp(((const float*)a.ld)[h]);
-    if constexpr (VAR == SLA_GDN) a_scalar = dec_exp(((const float*)a.ld)[bh]);
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-        const size_t d = (size_t)bh * DK + rg + NRG * i;
-        qd[i] = load_elem<BF16>(a.q, d);
-        kd[i] = load_elem<BF16>(a.k, d);
-        ad[i] = VAR == SLA_GLA ? dec_exp(load_elem<BF16>(a.ld, d)) : a_scalar;
-    }
-    float v4[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v4[j] = load_elem<BF16>(a.v, (size_t)bh * DV + 4 * c4 + j);
-
+    const float a_scalar = dec_exp(ld_scalar);
     // Sec. 5.1: the write.  RetNet / GLA: S <- a S + (G^K k)^T v.  Delta rule: Sb = a S, u = beta (G^K v - k Sb),
     // S <- Sb + k^T u, which needs k Sb over all rows first.
     float w4[4];  // what is added as k_d * w
@@ -178,15 +221,14 @@ __global__ __launch_bounds__(kDecThreads) void sla_decode_kernel(const DArgs a) 
             }
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) red[rg][4 * c4 + j] = ks[j];
+        for (int j = 0; j < 4; ++j) ks[j] = wave_rows_sum<NC4>(ks[j]);
+        if (lane < NC4) *(d_f32x4*)&red[wave][4 * c4] = d_f32x4{ks[0], ks[1], ks[2], ks[3]};
         __syncthreads();
-        const float bt = a.beta[bh];
+        d_f32x4 t = *(const d_f32x4*)&red[0][4 * c4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            float t = 0.f;
-            for (int g = 0; g < NRG; ++g) t += red[g][4 * c4 + j];
-            w4[j] = bt * (gk * v4[j] - t);
-        }
+        for (int g = 1; g < NW; ++g) t += *(const d_f32x4*)&red[g][4 * c4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w4[j] = bt * (gk * v4[j] - t[j]);
         __syncthreads();
     } else {
 #pragma unroll
@@ -196,62 +238,68 @@ __global__ __launch_bounds__(kDecThreads) void sla_decode_kernel(const DArgs a) 
     float y[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int i = 0; i < RPT; ++i) {
+        const float al = VAR == SLA_GLA ? dec_exp(ad[i]) : a_scalar;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const float decayed = VAR == SLA_GDN ? S[i][j] : ad[i] * S[i][j];
+            const float decayed = VAR == SLA_GDN ? S[i][j] : al * S[i][j];
             S[i][j] = decayed + kd[i] * w4[j];
             y[j] += qd[i] * S[i][j];  // Eq. 6: the read-out uses the updated state
         }
-        srow[(size_t)(rg + NRG * i) * NC4] = S[i];
+        srow[(size_t)(rg + NRG * i) * row4] = S[i];
     }
 
     // out = G^Q (q S): sum the row groups
 #pragma unroll
-    for (int j = 0; j < 4; ++j) red[rg][4 * c4 + j] = y[j];
+    for (int j = 0; j < 4; ++j) y[j] = wave_rows_sum<NC4>(y[j]);
+    if (lane < NC4) *(d_f32x4*)&red[wave][4 * c4] = d_f32x4{y[0], y[1], y[2], y[3]};
     __syncthreads();
-    if (tid < DV / 2) {
+    if (tid < DS / 2) {
         float o0 = 0.f, o1 = 0.f;
-        for (int g = 0; g < NRG; ++g) {
+#pragma unroll
+        for (int g = 0; g < NW; ++g) {
             o0 += red[g][2 * tid];
             o1 += red[g][2 * tid + 1];
         }
         o0 *= gq;
         o1 *= gq;
+        const size_t at = ((size_t)bh * a.dv + slice * DS) / 2 + tid;
         if constexpr (BF16)
-            ((uint32_t*)a.out)[((size_t)bh * DV) / 2 + tid] = dec_pack_bf16(o0, o1);
+            ((uint32_t*)a.out)[at] = dec_pack_bf16(o0, o1);
         else
-            ((float2*)a.out)[((size_t)bh * DV) / 2 + tid] = make_float2(o0, o1);
+            ((float2*)a.out)[at] = make_float2(o0, o1);
     }
 }
 
 template <bool BF16, int VAR, int DK>
-int launch_dv(const DArgs& a, int dv, hipStream_t stream) {
-    const dim3 grid((unsigned)(a.B * a.H)), block(kDecThreads);
-    switch (dv) {
+int launch_dv(const DArgs& a, hipStream_t stream) {
+    // 64-column slices; 32-column ones while 64 give at most one workgroup per compute unit (see the file header)
+    const size_t wide = (size_t)a.B * a.H * (a.dv / 64);
+    const int ds = wide <= 256 ? 32 : 64;
+    const dim3 grid((unsigned)(((size_t)a.B * a.H + 7) / 8 * 8 * (a.dv / ds))), block(kDecThreads);
+    switch (ds) {
+        case 32: hipLaunchKernelGGL((sla_decode_kernel<BF16, VAR, DK, 32>), grid, block, 0, stream, a); break;
         case 64: hipLaunchKernelGGL((sla_decode_kernel<BF16, VAR, DK, 64>), grid, block, 0, stream, a); break;
-        case 128: hipLaunchKernelGGL((sla_decode_kernel<BF16, VAR, DK, 128>), grid, block, 0, stream, a); break;
-        case 256: hipLaunchKernelGGL((sla_decode_kernel<BF16, VAR, DK, 256>), grid, block, 0, stream, a); break;
         default: return SLA_ERR_UNSUPPORTED;
     }
     return hipGetLastError() == hipSuccess ? SLA_OK : SLA_ERR_HIP;
 }
 
 template <bool BF16, int VAR>
-int launch_dk(const DArgs& a, int dk, int dv, hipStream_t stream) {
+int launch_dk(const DArgs& a, int dk, hipStream_t stream) {
     switch (dk) {
-        case 32: return launch_dv<BF16, VAR, 32>(a, dv, stream);
-        case 64: return launch_dv<BF16, VAR, 64>(a, dv, stream);
-        case 128: return launch_dv<BF16, VAR, 128>(a, dv, stream);
+        case 32: return launch_dv<BF16, VAR, 32>(a, stream);
+        case 64: return launch_dv<BF16, VAR, 64>(a, stream);
+        case 128: return launch_dv<BF16, VAR, 128>(a, stream);
         default: return SLA_ERR_UNSUPPORTED;
     }
 }
 
 template <bool BF16>
-int launch_var(const DArgs& a, int variant, int dk, int dv, hipStream_t stream) {
+int launch_var(const DArgs& a, int variant, int dk, hipStream_t stream) {
     switch (variant) {
-        case SLA_RETNET: return launch_dk<BF16, SLA_RETNET>(a, dk, dv, stream);
-        case SLA_GLA: return launch_dk<BF16, SLA_GLA>(a, dk, dv, stream);
-        case SLA_GDN: return launch_dk<BF16, SLA_GDN>(a, dk, dv, stream);
+        case SLA_RETNET: return launch_dk<BF16, SLA_RETNET>(a, dk, stream);
+        case SLA_GLA: return launch_dk<BF16, SLA_GLA>(a, dk, stream);
+        case SLA_GDN: return launch_dk<BF16, SLA_GDN>(a, dk, stream);
         default: return SLA_ERR_UNSUPPORTED;
     }
 }
@@ -264,9 +312,9 @@ int launch_decode(const sla_params& p, const void* q, const void* k, const void*
     DArgs a;
     a.q = q; a.k = k; a.v = v; a.ql = ql; a.kl = kl; a.wq = wq; a.wk = wk; a.ld = ld; a.beta = beta; a.state = state;
     a.out = out;
-    a.B = p.B; a.H = p.H;
-    if (p.dtype == SLA_BF16) return launch_var<true>(a, p.variant, p.dk, p.dv, stream);
-    return launch_var<false>(a, p.variant, p.dk, p.dv, stream);
+    a.B = p.B; a.H = p.H; a.dv = p.dv;
+    if (p.dtype == SLA_BF16) return launch_var<true>(a, p.variant, p.dk, stream);
+    return launch_var<false>(a, p.variant, p.dk, stream);
 }
 
 }  // namespace sla

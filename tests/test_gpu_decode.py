@@ -156,3 +156,14 @@ def test_fused_gate_projection_matches_oracle(variant, dtype, H, dk, dv, both):
     print(f"[parity] fused decode {_name(variant)} {dtype} H={H} dk={dk} dv={dv} out_err={eo:.3e} state_err={ef:.3e}",
           flush=True)
     assert eo <= TOL[dtype] and ef <= 1e-5
+
+
+@pytest.mark.parametrize("variant", VARIANTS)
+@pytest.mark.parametrize("B,H,dk,dv", [(64, 4, 32, 64), (43, 6, 32, 64), (32, 2, 128, 256), (13, 5, 64, 256)])
+def test_slice_widths(variant, B, H, dk, dv):
+    """Both sides of the rule for the slice width: 256 and 258, 256 and 260 workgroups of 64 columns."""
+    d = si.custom(variant, "bf16", B=B, T=2, H=H, dk=dk, dv=dv, seed=2600 + variant + B)
+    s0 = si.initial_state(B, H, dk, dv, seed=26)
+    o, f = decode_chain(variant, d, "bf16", s0)
+    ro, rf = run_oracle(variant, d, s0)
+    assert rel_err(o, ro) <= TOL["bf16"] and rel_err(f, rf) <= 1e-5
