@@ -130,6 +130,13 @@ def _p(x) -> Optional[int]:
     return None if not x else int(x)
 
 
+def _stream(t) -> int:
+    """The current stream of the tensor's device, as the hipStream_t handle (no Stream object is made for it)."""
+    import torch
+
+    return torch._C._cuda_getCurrentRawStream(t.get_device())
+
+
 def sla_status_string(status: int) -> str:
     return load_library().sla_status_string(int(status)).decode()
 
@@ -288,7 +295,7 @@ def forward_varlen(variant: int, q, k, v, q_head_logits, k_head_logits, log_deca
     ptr = lambda t: None if t is None else t.data_ptr()
     rc = sla_forward_varlen(params, ptr(q), ptr(k), ptr(v), ptr(q_head_logits), ptr(k_head_logits), ptr(log_decay),
                             ptr(beta), ptr(cu_seqlens), ptr(initial_state), ptr(out), ptr(fin),
-                            torch.cuda.current_stream(q.device).cuda_stream)
+                            _stream(q))
     if rc != 0:
         raise SlaError(rc, sla_status_string(rc))
     return out, fin
@@ -322,7 +329,7 @@ def backward_varlen(variant: int, q, k, v, q_head_logits, k_head_logits, log_dec
         params, ptr(q), ptr(k), ptr(v), ptr(q_head_logits), ptr(k_head_logits), ptr(log_decay), ptr(cu_seqlens),
         ptr(initial_state), ptr(d_out), ptr(d_final_state), ptr(g["dq"]), ptr(g["dk"]), ptr(g["dv"]),
         ptr(g["dq_head_logits"]), ptr(g["dk_head_logits"]), ptr(g["dlog_decay"]), ptr(g["d_initial_state"]),
-        ptr(workspace), workspace.numel(), torch.cuda.current_stream(dev).cuda_stream,
+        ptr(workspace), workspace.numel(), _stream(q),
     )
     if rc != 0:
         raise SlaError(rc, sla_status_string(rc))
@@ -345,7 +352,7 @@ def short_conv_silu(x, w):
     y = torch.empty_like(x)
     dtype = {torch.float32: F32, torch.bfloat16: BF16}[x.dtype]
     rc = sla_short_conv_silu(dtype, B, T, C, w.shape[1], x.data_ptr(), w.data_ptr(), y.data_ptr(),
-                             torch.cuda.current_stream(x.device).cuda_stream)
+                             _stream(x))
     if rc != 0:
         raise SlaError(rc, sla_status_string(rc))
     return y
@@ -389,7 +396,7 @@ def short_conv_silu_l2(x, w, head_width: int = 0, eps: float = 1e-6):
     y = torch.empty_like(x)
     dtype = {torch.float32: F32, torch.bfloat16: BF16}[x.dtype]
     rc = sla_short_conv_silu_l2(dtype, B, T, C, w.shape[1], head_width, eps, x.data_ptr(), w.data_ptr(), y.data_ptr(),
-                                torch.cuda.current_stream(x.device).cuda_stream)
+                                _stream(x))
     if rc != 0:
         raise SlaError(rc, sla_status_string(rc))
     return y
@@ -408,7 +415,7 @@ def short_conv_silu_l2_backward(x, w, dy, head_width: int = 0, eps: float = 1e-6
     dtype = {torch.float32: F32, torch.bfloat16: BF16}[x.dtype]
     rc = sla_short_conv_silu_l2_backward(dtype, B, T, C, K, head_width, eps, x.data_ptr(), w.data_ptr(), dy.data_ptr(),
                                          dx.data_ptr(), dw.data_ptr(), ws.data_ptr(), ws.numel(),
-                                         torch.cuda.current_stream(x.device).cuda_stream)
+                                         _stream(x))
     if rc != 0:
         raise SlaError(rc, sla_status_string(rc))
     return dx, dw
@@ -425,7 +432,7 @@ def gate_logits_backward(x, w, d_head_logits, dx):
     need = sla_gate_logits_backward_workspace_bytes(params)
     ws = torch.empty(max(need, 16), dtype=torch.uint8, device=x.device)
     rc = sla_gate_logits_backward(params, x.data_ptr(), w.data_ptr(), d_head_logits.data_ptr(), dx.data_ptr(),
-                                  dw.data_ptr(), ws.data_ptr(), ws.numel(), torch.cuda.current_stream(x.device).cuda_stream)
+                                  dw.data_ptr(), ws.data_ptr(), ws.numel(), _stream(x))
     if rc != 0:
         raise SlaError(rc, sla_status_string(rc))
     return dw
@@ -456,7 +463,7 @@ def gate_logits(q, k, w_gq, w_gk, *, dv: int = 0):
     params = SlaParams(GLA, dtype, B, T, H, dk, dv or dk, 0, 0, 1)
     ptr = lambda t: None if t is None else t.data_ptr()
     rc = sla_gate_logits(params, ptr(q), ptr(k), ptr(w_gq), ptr(w_gk), ptr(ql), ptr(kl),
-                         torch.cuda.current_stream(q.device).cuda_stream)
+                         _stream(q))
     if rc != 0:
         raise SlaError(rc, sla_status_string(rc))
     return ql, kl
@@ -528,7 +535,7 @@ def backward(variant: int, q, k, v, q_head_logits, k_head_logits, log_decay, d_o
         params, ptr(q), ptr(k), ptr(v), ptr(q_head_logits), ptr(k_head_logits), ptr(log_decay), ptr(initial_state),
         ptr(d_out), ptr(d_final_state), ptr(g["dq"]), ptr(g["dk"]), ptr(g["dv"]), ptr(g["dq_head_logits"]),
         ptr(g["dk_head_logits"]), ptr(g["dlog_decay"]), ptr(g["d_initial_state"]), ptr(workspace),
-        workspace.numel() * workspace.element_size(), torch.cuda.current_stream(dev).cuda_stream,
+        workspace.numel() * workspace.element_size(), _stream(q),
     )
     if rc != 0:
         raise SlaError(rc, sla_status_string(rc))
@@ -603,7 +610,7 @@ def backward_gdn_varlen(q, k, v, q_head_logits, k_head_logits, log_decay, beta, 
         params, ptr(q), ptr(k), ptr(v), ptr(q_head_logits), ptr(k_head_logits), ptr(log_decay), ptr(beta),
         ptr(cu_seqlens), ptr(initial_state), ptr(d_out), ptr(d_final_state), ptr(g["dq"]), ptr(g["dk"]), ptr(g["dv"]),
         ptr(g["dq_head_logits"]), ptr(g["dk_head_logits"]), ptr(g["dlog_decay"]), ptr(g["dbeta"]),
-        ptr(g["d_initial_state"]), ptr(workspace), workspace.numel(), torch.cuda.current_stream(dev).cuda_stream,
+        ptr(g["d_initial_state"]), ptr(workspace), workspace.numel(), _stream(q),
     )
     if rc != 0:
         raise SlaError(rc, sla_status_string(rc))
@@ -648,7 +655,7 @@ def backward_gdn(q, k, v, q_head_logits, k_head_logits, log_decay, beta, d_out, 
         ptr(initial_state), ptr(d_out), ptr(d_final_state), ptr(g["dq"]), ptr(g["dk"]), ptr(g["dv"]),
         ptr(g["dq_head_logits"]), ptr(g["dk_head_logits"]), ptr(g["dlog_decay"]), ptr(g["dbeta"]),
         ptr(g["d_initial_state"]), ptr(workspace), workspace.numel() * workspace.element_size(),
-        torch.cuda.current_stream(dev).cuda_stream,
+        _stream(q),
     )
     if rc != 0:
         raise SlaError(rc, sla_status_string(rc))
@@ -663,45 +670,33 @@ def decode_step(variant: int, q, k, v, q_head_logits, k_head_logits, log_decay, 
     arguments must be None."""
     import torch
 
-    if w_gq is not None:
-        assert q_head_logits is None and k_head_logits is None
-        B, H, dk = q.shape
-        dv = v.shape[-1]
-        for w in (w_gq, w_gk):
-            assert w is None or (w.dtype == torch.float32 and tuple(w.shape) == (H, dk) and w.is_contiguous())
-        assert state.dtype == torch.float32 and state.shape == (B, H, dk, dv) and state.is_contiguous()
-        dtype = {torch.float32: F32, torch.bfloat16: BF16}[q.dtype]
-        if out is None:
-            out = torch.empty((B, H, dv), dtype=q.dtype, device=q.device)
-        params = SlaParams(variant, dtype, B, 1, H, dk, dv, 0, 0, 1)
-        ptr = lambda t: None if t is None else t.data_ptr()
-        rc = sla_decode_step_fused(params, ptr(q), ptr(k), ptr(v), ptr(w_gq), ptr(w_gk), ptr(log_decay), ptr(beta),
-                                   ptr(state), ptr(out), torch.cuda.current_stream(q.device).cuda_stream)
-        if rc != 0:
-            raise SlaError(rc, sla_status_string(rc))
-        return out
-
-    assert q.is_cuda and q.is_contiguous() and k.is_contiguous() and v.is_contiguous()
     B, H, dk = q.shape
     dv = v.shape[-1]
-    assert k.shape == (B, H, dk) and v.shape == (B, H, dv) and k.dtype == q.dtype and v.dtype == q.dtype
-    dtype = {torch.float32: F32, torch.bfloat16: BF16}[q.dtype]
-    assert q_head_logits.dtype == torch.float32 and q_head_logits.shape == (B, H) and q_head_logits.is_contiguous()
-    if k_head_logits is not None:
-        assert k_head_logits.dtype == torch.float32 and k_head_logits.shape == (B, H) and k_head_logits.is_contiguous()
-    want = {RETNET: ((H,), torch.float32), GLA: ((B, H, dk), q.dtype), GDN: ((B, H), torch.float32)}[variant]
-    assert tuple(log_decay.shape) == want[0] and log_decay.dtype == want[1] and log_decay.is_contiguous()
-    if beta is not None:
-        assert beta.dtype == torch.float32 and beta.shape == (B, H) and beta.is_contiguous()
-    assert state.dtype == torch.float32 and state.shape == (B, H, dk, dv) and state.is_contiguous()
+    dtype = BF16 if q.dtype is torch.bfloat16 else {torch.float32: F32}[q.dtype]
+    f32 = torch.float32
+    assert state.dtype is f32 and state.shape == (B, H, dk, dv) and state.is_contiguous()
+    if w_gq is not None:
+        assert q_head_logits is None and k_head_logits is None
+        for w in (w_gq, w_gk):
+            assert w is None or (w.dtype is f32 and w.shape == (H, dk) and w.is_contiguous())
+        call, gq, gk = load_library().sla_decode_step_fused, w_gq, w_gk
+    else:
+        assert q.is_cuda and q.is_contiguous() and k.is_contiguous() and v.is_contiguous()
+        assert k.shape == (B, H, dk) and v.shape == (B, H, dv) and k.dtype is q.dtype and v.dtype is q.dtype
+        assert q_head_logits.dtype is f32 and q_head_logits.shape == (B, H) and q_head_logits.is_contiguous()
+        if k_head_logits is not None:
+            assert k_head_logits.dtype is f32 and k_head_logits.shape == (B, H) and k_head_logits.is_contiguous()
+        want = {RETNET: ((H,), f32), GLA: ((B, H, dk), q.dtype), GDN: ((B, H), f32)}[variant]
+        assert log_decay.shape == want[0] and log_decay.dtype is want[1] and log_decay.is_contiguous()
+        if beta is not None:
+            assert beta.dtype is f32 and beta.shape == (B, H) and beta.is_contiguous()
+        call, gq, gk = load_library().sla_decode_step, q_head_logits, k_head_logits
     if out is None:
-        out = torch.empty((B, H, dv), dtype=q.dtype, device=q.device)
-    params = SlaParams(variant, dtype, B, 1, H, dk, dv, 0, 0, 1)
-    ptr = lambda t: None if t is None else t.data_ptr()
-    rc = sla_decode_step(
-        params, ptr(q), ptr(k), ptr(v), ptr(q_head_logits), ptr(k_head_logits), ptr(log_decay), ptr(beta), ptr(state),
-        ptr(out), torch.cuda.current_stream(q.device).cuda_stream,
-    )
+        out = q.new_empty((B, H, dv))
+    # a token's host time is part of every step: the arguments go to the C entry point without the raw wrappers between
+    rc = call(ctypes.byref(SlaParams(variant, dtype, B, 1, H, dk, dv, 0, 0, 1)), q.data_ptr(),
+              None if k is None else k.data_ptr(), v.data_ptr(), gq.data_ptr(), None if gk is None else gk.data_ptr(), None if log_decay is None else log_decay.data_ptr(),
+              None if beta is None else beta.data_ptr(), state.data_ptr(), out.data_ptr(), _stream(q))
     if rc != 0:
         raise SlaError(rc, sla_status_string(rc))
     return out
@@ -772,7 +767,7 @@ def forward(
         final_state = torch.empty((B, H, dk, dv), dtype=torch.float32, device=q.device)
     params = SlaParams(variant, dtype, B, T, H, dk, dv, dv_split, FLAG_HEAD_MAJOR if head_major else 0, segments)
     ptr = lambda t: None if t is None else t.data_ptr()
-    stream = torch.cuda.current_stream(q.device).cuda_stream
+    stream = _stream(q)
     if segments == 1:
         rc = sla_forward(
             params, ptr(q), ptr(k), ptr(v), ptr(q_head_logits), ptr(k_head_logits), ptr(log_decay), ptr(beta),
