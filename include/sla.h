@@ -195,8 +195,8 @@ int sla_decode_step_fused(const sla_params* p, const void* q, const void* k, con
  * scalar objective L = sum(out * d_out) + sum(final_state * d_final_state) it writes dL/d(input) for every
  * differentiable input of the forward call made with the same p, q, k, v, logits, log_decay and initial_state.
  * bf16 tensors run in block form on the matrix cores; fp32 tensors (p->dtype == SLA_F32) run token by token in fp32
- * vector arithmetic (gradients to fp32 rounding, any log_decay <= 0, single pass only: p->segments >= 2 is
- * SLA_ERR_UNSUPPORTED).  The delta rule has its own entry point, sla_backward_gdn.
+ * vector arithmetic (gradients to fp32 rounding, any log_decay <= 0; p->segments >= 2 is SLA_ERR_UNSUPPORTED:
+ * rectangular batches with few sequences are cut into segments by the library, and the workspace query counts that).  The delta rule has its own entry point, sla_backward_gdn.
  * p->dv_split is ignored.  p->segments >= 2 asks for the segment-parallel schedule (for batches with few sequences,
  * as in sla_forward_ws): every batch row is cut into that many segments (of a multiple of 64 tokens, at least 256)
  * which run in parallel; the entry state and the end cotangent of every segment come from two pre-passes.  It needs

@@ -695,7 +695,8 @@ def decode_step(variant: int, q, k, v, q_head_logits, k_head_logits, log_decay, 
         out = q.new_empty((B, H, dv))
     # a token's host time is part of every step: the arguments go to the C entry point without the raw wrappers between
     rc = call(ctypes.byref(SlaParams(variant, dtype, B, 1, H, dk, dv, 0, 0, 1)), q.data_ptr(),
-              None if k is None else k.data_ptr(), v.data_ptr(), gq.data_ptr(), None if gk is None else gk.data_ptr(), None if log_decay is None else log_decay.data_ptr(),
+              None if k is None else k.data_ptr(), v.data_ptr(), gq.data_ptr(), None if gk is None else gk.data_ptr(),
+              None if log_decay is None else log_decay.data_ptr(),
               None if beta is None else beta.data_ptr(), state.data_ptr(), out.data_ptr(), _stream(q))
     if rc != 0:
         raise SlaError(rc, sla_status_string(rc))

@@ -57,9 +57,22 @@ struct FArgs {
     size_t plane;          // floats between partial planes (>= rows * H)
     size_t rows;           // tokens in all
     const int* cu;         // packed batch (see Where), else null
-    int B, T, H;
+    int B, T, H;           // B: sequences; with nseg > 1 segments, nseg of them to a batch row of T tokens
+    int nseg, seg_len;
     bool head_major;
 };
+
+// What a workgroup owns: a sequence, or with nseg > 1 one segment of seg_len tokens of a batch row, which then runs as
+// a sequence of its own (me.b and me.bh number the segments, and with them the states).
+__device__ __forceinline__ Where where_segment(const FArgs& a, int nslices) {
+    Where me = where(a, nslices);
+    if (a.nseg > 1 && me.bh >= 0) {
+        const int t0 = (me.b % a.nseg) * a.seg_len;
+        me.T = min(a.seg_len, a.T - t0);
+        me.tok0 = (size_t)(me.b / a.nseg) * a.T + t0;
+    }
+    return me;
+}
 
 constexpr int kSc = 4;  // per-token scalars {G^Q, G^K, alpha of the head (RetNet; 1 for GLA), -}
 
@@ -68,7 +81,8 @@ struct Rows {
     size_t base, step;
 };
 __device__ __forceinline__ Rows rows_of(const FArgs& a, const Where& me, int D) {
-    if (a.head_major) return Rows{((size_t)me.bh * a.T) * D, (size_t)D};
+    if (a.head_major)
+        return Rows{((size_t)((me.b / a.nseg) * a.H + me.h) * a.T + (size_t)(me.b % a.nseg) * a.seg_len) * D, (size_t)D};
     return Rows{(me.tok0 * a.H + me.h) * D, (size_t)a.H * D};
 }
 
@@ -126,7 +140,7 @@ __global__ __launch_bounds__(kThreads) void sla_bwd32_dv_kernel(const FArgs a) {
                   oDO = oV + kChunk * kSlice, oSC = oDO + kChunk * kSlice, kBuf = oSC + kSc * kChunk;
     extern __shared__ __align__(16) unsigned char smem[];
     float* lds = (float*)smem;
-    const Where me = where(a, DV / kSlice);
+    const Where me = where_segment(a, DV / kSlice);
     if (me.bh < 0) return;
     const int T = me.T, nch = (T + kChunk - 1) / kChunk;
     const Rows rk = rows_of(a, me, DK), rv = rows_of(a, me, DV);
@@ -222,7 +236,7 @@ __global__ __launch_bounds__(kThreads) void sla_bwd32_key_kernel(const FArgs a) 
                   oSC = oDQ + (NEED_DQ ? kChunk * kSlice : 0), kBuf = oSC + kSc * kChunk;
     extern __shared__ __align__(16) unsigned char smem[];
     float* lds = (float*)smem;
-    const Where me = where(a, DK / kSlice);
+    const Where me = where_segment(a, DK / kSlice);
     if (me.bh < 0) return;
     const int T = me.T, nch = (T + kChunk - 1) / kChunk;
     const Rows rk = rows_of(a, me, DK), rv = rows_of(a, me, DV);
@@ -343,7 +357,145 @@ __global__ __launch_bounds__(kThreads) void sla_bwd32_key_kernel(const FArgs a) 
     }
 }
 
-size_t round4(size_t n) { return (n + 3) & ~(size_t)3; }
+// ------------------------------------------------------------------------------------------------------------
+// Pre-pass of the segment schedule (see launch_backward_f32): what a segment alone leaves behind.  blockIdx.y = 0,
+// forward in time: the state at its end from a zero state; 1, backward in time: the cotangent of the state at its
+// start when the one at its end is zero.  Both are M[key][value] with the decay per key, so both run on the tile of
+// the key sweeps (rows: value columns, 64 key columns per workgroup); no sums across lanes.  `totals`: the segment's
+// whole decay per key (the product the state itself would be multiplied by, factor by factor).
+// ------------------------------------------------------------------------------------------------------------
+template <bool GLA, int DK, int DV, bool FWD>
+__device__ __forceinline__ void segment_alone(const FArgs& a, const Where& me, float* lds, float* end, float* totals) {
+    constexpr int RT = DV / 16;
+    constexpr int oR = 0, oC = oR + kChunk * DV, oA = oC + kChunk * kSlice, oSC = oA + (GLA ? kChunk * kSlice : 0),
+                  kBuf = oSC + kSc * kChunk;
+    const int T = me.T, nch = (T + kChunk - 1) / kChunk;
+    const Rows rk = rows_of(a, me, DK), rv = rows_of(a, me, DV);
+    if (me.wave >= kWaves) {
+        const int lt = me.tid - 64 * kWaves;
+        const float ha = head_alpha_of(a, me.h);
+        const size_t ks = rk.base + me.slice * kSlice;
+        for (int c = 0; c <= nch; ++c) {
+            if (c < nch) {
+                const int t0 = (FWD ? c : nch - 1 - c) * kChunk;
+                float* buf = lds + (c & 1) * kBuf;
+                RegsF<DV> xr;
+                RegsF<kSlice> xc;
+                RegsA<kSlice> xa;
+                RegsG xs;
+                xr.load((FWD ? a.v : a.dout) + rv.base, rv.step, t0, T, lt);
+                xc.load((FWD ? a.k : a.q) + ks, rk.step, t0, T, lt);
+                if constexpr (GLA) xa.load(a.ld + ks, rk.step, t0, T, lt);
+                xs.load(a, me.tok0, me.h, t0, T, lt);
+                xr.put_rows(buf + oR, t0, T, lt);
+                xc.put(buf + oC, t0, T, lt);
+                if constexpr (GLA) xa.put_exp(buf + oA, t0, T, lt);
+                xs.put(buf + oSC, ha, t0, T, lt);
+            }
+            __syncthreads();
+        }
+        return;
+    }
+    float M[RT][CW] = {};
+    fc total = {1.f, 1.f};
+    __syncthreads();
+    for (int c = 0; c < nch; ++c) {
+        const float* buf = lds + (c & 1) * kBuf;
+#pragma unroll 4
+        for (int ii = 0; ii < kChunk; ++ii) {
+            const int i = FWD ? ii : kChunk - 1 - ii;
+            const f4 sc = *(const f4*)(buf + oSC + kSc * i);
+            const float gate = FWD ? sc[1] : sc[0];
+            float x[RT];
+            get_rows<RT>(x, buf + oR + i * DV + me.rg * 4);
+            const int lc = i * kSlice + me.lcol;
+            const fc y = *(const fc*)(buf + oC + lc);
+            fc al = fc{sc[2], sc[2]};
+            if constexpr (GLA) al = *(const fc*)(buf + oA + lc);
+#pragma unroll
+            for (int r = 0; r < RT; ++r)
+#pragma unroll
+                for (int j = 0; j < CW; ++j) {
+                    if constexpr (FWD) {
+                        M[r][j] = M[r][j] * al[j] + (gate * x[r]) * y[j];
+                    } else {
+                        M[r][j] += (gate * x[r]) * y[j];
+                        M[r][j] *= al[j];
+                    }
+                }
+            total *= al;  // a token past the end has factor 1
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < CW; ++j) {
+        float* d = end + ((size_t)me.bh * DK + me.col + j) * DV + me.rg * RT;
+#pragma unroll
+        for (int r = 0; r < RT; r += 4) *(f4*)(d + r) = f4{M[r][j], M[r + 1][j], M[r + 2][j], M[r + 3][j]};
+    }
+    // the totals of segment 0 come from the forward half, the others from the backward half
+    if (me.rg == 0 && FWD == (me.b % a.nseg == 0)) *(fc*)(totals + (size_t)me.bh * DK + me.col) = total;
+}
+
+template <bool GLA, int DK, int DV>
+__global__ __launch_bounds__(kThreads) void sla_bwd32_segment_kernel(const FArgs a, float* states, float* cotangents,
+                                                                      float* totals, bool want_ds0) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const Where me = where_segment(a, DK / kSlice);
+    if (me.bh < 0) return;
+    const int seg = me.b % a.nseg;
+    if (blockIdx.y == 0) {
+        if (seg == a.nseg - 1) return;  // nothing follows it
+        segment_alone<GLA, DK, DV, true>(a, me, (float*)smem, states, totals);
+    } else {
+        if (seg == 0 && !want_ds0) return;  // nothing comes before it
+        segment_alone<GLA, DK, DV, false>(a, me, (float*)smem, cotangents, totals);
+    }
+}
+
+// Chains the segments: the recurrences are linear, so the state at a segment's end is its own plus its whole decay
+// times the one it is entered with, and the same backward in time for the cotangents.  In place: `states` becomes the
+// entry states, `cotangents` the cotangents at the segments' ends; ds0: the gradient of the initial state, or null.
+// One thread per (batch row, head, key, four value columns) and direction (blockIdx.y).
+__global__ __launch_bounds__(kEw) void sla_bwd32_chain_kernel(float* states, float* cotangents, const float* totals,
+                                                              const float* s0, const float* dsf, float* ds0, int B, int H,
+                                                              int dk, int dv, int nseg) {
+    const size_t per_head = (size_t)dk * (dv / 4), idx = (size_t)blockIdx.x * kEw + threadIdx.x;
+    if (idx >= (size_t)B * H * per_head) return;
+    const size_t bh = idx / per_head, b = bh / H, h = bh % H, in = idx % per_head;
+    const int d = (int)(in / (dv / 4));
+    const size_t user = bh * dk * dv + in * 4;
+    auto seg_head = [&](int s) { return (b * nseg + s) * H + h; };
+    const f4 zero = {0.f, 0.f, 0.f, 0.f};
+    if (blockIdx.y == 0) {
+        f4 e = s0 ? *(const f4*)(s0 + user) : zero;
+        for (int s = 0; s < nseg; ++s) {
+            float* at = states + seg_head(s) * dk * dv + in * 4;
+            const bool last = s == nseg - 1;
+            const f4 x = last ? zero : *(const f4*)at;
+            *(f4*)at = e;
+            if (!last) {
+                const float D = totals[seg_head(s) * dk + d];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) e[i] = x[i] + D * e[i];
+            }
+        }
+    } else {
+        f4 t = dsf ? *(const f4*)(dsf + user) : zero;
+        for (int s = nseg - 1; s >= 0; --s) {
+            float* at = cotangents + seg_head(s) * dk * dv + in * 4;
+            const bool more = s > 0 || ds0;
+            const f4 x = more ? *(const f4*)at : zero;
+            *(f4*)at = t;
+            if (more) {
+                const float D = totals[seg_head(s) * dk + d];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) t[i] = x[i] + D * t[i];
+            }
+        }
+        if (ds0) *(f4*)(ds0 + user) = t;
+    }
+}
 
 template <typename K>
 bool allow_lds(K kernel, int lds) {
@@ -353,8 +505,15 @@ bool allow_lds(K kernel, int lds) {
     return false;
 }
 
+struct Segments {  // buffers of the segment schedule, see launch_backward_f32
+    float* states;
+    float* cotangents;
+    float* totals;
+};
+
 template <bool GLA, int DK, int DV>
-int launch_sweeps(const FArgs& a, bool state_only, hipStream_t stream) {
+int launch_sweeps(FArgs a, const Segments& sg, bool state_only, hipStream_t stream) {
+    constexpr int ldsS = 2 * 4 * (kChunk * DV + (GLA ? 2 : 1) * kChunk * kSlice + kSc * kChunk);
     constexpr int ldsV = 2 * 4 * ((GLA ? 3 : 2) * kChunk * DK + 2 * kChunk * kSlice + kSc * kChunk);
     constexpr int ldsQ = 2 * 4 * (2 * kChunk * DV + (GLA ? 3 : 2) * kChunk * kSlice + kSc * kChunk);
     constexpr int ldsK = 2 * 4 * (2 * kChunk * DV + (GLA ? 4 : 2) * kChunk * kSlice + kSc * kChunk);
@@ -369,13 +528,29 @@ int launch_sweeps(const FArgs& a, bool state_only, hipStream_t stream) {
     if (!((configured.load(std::memory_order_acquire) >> dev) & 1u)) {
         if (!allow_lds(sla_bwd32_dv_kernel<GLA, DK, DV>, ldsV) ||
             !allow_lds(sla_bwd32_key_kernel<GLA, DK, DV, true>, ldsQ) ||
-            !allow_lds(sla_bwd32_key_kernel<GLA, DK, DV, false>, ldsK))
+            !allow_lds(sla_bwd32_key_kernel<GLA, DK, DV, false>, ldsK) ||
+            !allow_lds(sla_bwd32_segment_kernel<GLA, DK, DV>, ldsS))
             return SLA_ERR_HIP;
         configured.fetch_or(uint64_t(1) << dev, std::memory_order_release);
     }
     const unsigned bh = (unsigned)(a.B * a.H);
     const dim3 block(kThreads);
     auto grid = [bh](unsigned slices) { return dim3(((bh + 7u) / 8u) * 8u * slices); };  // see tok::where()
+    if (a.nseg > 1) {
+        dim3 g = grid(DK / kSlice);
+        g.y = 2;
+        hipLaunchKernelGGL((sla_bwd32_segment_kernel<GLA, DK, DV>), g, block, (size_t)ldsS, stream, a, sg.states,
+                           sg.cotangents, sg.totals, a.ds0 != nullptr);
+        const int rows = a.B / a.nseg;
+        const size_t n = (size_t)rows * a.H * DK * (DV / 4);
+        hipLaunchKernelGGL(sla_bwd32_chain_kernel, dim3((unsigned)((n + kEw - 1) / kEw), 2), dim3(kEw), 0, stream,
+                           sg.states, sg.cotangents, (const float*)sg.totals, a.s0, a.dsf, a.ds0, rows, a.H, DK, DV,
+                           a.nseg);
+        if (hipGetLastError() != hipSuccess) return SLA_ERR_HIP;
+        a.s0 = sg.states;
+        a.dsf = sg.cotangents;
+        a.ds0 = nullptr;
+    }
     hipLaunchKernelGGL((sla_bwd32_dv_kernel<GLA, DK, DV>), grid(DV / kSlice), block, (size_t)ldsV, stream, a);
     if (!state_only) {
         hipLaunchKernelGGL((sla_bwd32_key_kernel<GLA, DK, DV, true>), grid(DK / kSlice), block, (size_t)ldsQ, stream, a);
@@ -385,34 +560,70 @@ int launch_sweeps(const FArgs& a, bool state_only, hipStream_t stream) {
 }
 
 template <bool GLA, int DK>
-int launch_dv(const FArgs& a, int dv, bool state_only, hipStream_t stream) {
+int launch_dv(const FArgs& a, const Segments& sg, int dv, bool state_only, hipStream_t stream) {
     switch (dv) {
-        case 64: return launch_sweeps<GLA, DK, 64>(a, state_only, stream);
-        case 128: return launch_sweeps<GLA, DK, 128>(a, state_only, stream);
-        case 256: return launch_sweeps<GLA, DK, 256>(a, state_only, stream);
+        case 64: return launch_sweeps<GLA, DK, 64>(a, sg, state_only, stream);
+        case 128: return launch_sweeps<GLA, DK, 128>(a, sg, state_only, stream);
+        case 256: return launch_sweeps<GLA, DK, 256>(a, sg, state_only, stream);
         default: return SLA_ERR_UNSUPPORTED;
     }
 }
 
 template <bool GLA>
-int launch_dk(const FArgs& a, int dk, int dv, bool state_only, hipStream_t stream) {
+int launch_dk(const FArgs& a, const Segments& sg, int dk, int dv, bool state_only, hipStream_t stream) {
     switch (dk) {
-        case 64: return launch_dv<GLA, 64>(a, dv, state_only, stream);
-        case 128: return launch_dv<GLA, 128>(a, dv, state_only, stream);
+        case 64: return launch_dv<GLA, 64>(a, sg, dv, state_only, stream);
+        case 128: return launch_dv<GLA, 128>(a, sg, dv, state_only, stream);
         default: return SLA_ERR_UNSUPPORTED;
     }
 }
 
+// Segments per batch row.  A sweep is a serial walk of about 0.3 us a token in every workgroup, so few sequences leave
+// most of the chip idle: rows are cut until the narrowest sweep has a workgroup for each of 256 compute units, into
+// segments of at least 32 tokens.  Heads up to 64 x 128 take half the vector work per token, so two workgroups share a
+// compute unit to gain and 512 are wanted, but not with segments under 64 tokens, where the pre-pass and the chain cost
+// more than that gives.  Call in us, one pass -> 256 wanted / 512 wanted:
+//     B=2 T=1021 H=8  64 x 128    917 -> 149 / 161           B=6 T=1500 H=16 64 x 64    1000 -> 602 / 411
+//     B=1 T=300  H=4  64 x 64     215 -> 55 (64 tokens: 76)  B=7 T=1000 H=16 64 x 128    921 -> 697 / 656
+//     B=1 T=4096 H=2  128 x 128  3827 -> 162 / 186           B=4 T=2048 H=5  128 x 256  2548 -> 789 / 829
+//     B=5 T=300  H=12 128 x 256   421 -> 375 / 424           B=8 T=700  H=16 128 x 128   765 (one pass) / 809
+// Packed batches run in one pass (their lengths are known on the device only).
+int segments_of(const sla_params& p, bool packed, int* seg_len) {
+    constexpr int kShortest = 32;
+    *seg_len = p.T;
+    const size_t groups = (size_t)p.B * p.H * ((p.dk < p.dv ? p.dk : p.dv) / kSlice);
+    if (packed || groups == 0 || p.T < 2 * kShortest) return 1;
+    const size_t target = p.dk * p.dv <= 64 * 128 && groups * p.T >= 512 * 64 ? 512 : 256;
+    if (2 * groups > target) return 1;
+    const int want = (int)(target / groups);
+    int len = ((p.T + want - 1) / want + kChunk - 1) / kChunk * kChunk;
+    if (len < kShortest) len = kShortest;
+    *seg_len = len;
+    return (p.T + len - 1) / len;
+}
+
+size_t round4(size_t n) { return (n + 3) & ~(size_t)3; }
+
 }  // namespace
 
 // Workspace, in floats: gates 2 [B,T,H]; dk/8 partial planes of dG^Q and dv/8 of dG^K (one per compute wave and
-// slice); for GLA rowsum(X_T' * S_T) [B,H,dk].
+// slice); for GLA rowsum(X_T' * S_T) [B,H,dk] (per segment); with nseg > 1 segments per batch row also their states and
+// cotangents 2 [B,nseg,H,dk,dv] and their decays [B,nseg,H,dk].
 size_t backward_f32_workspace_floats(const sla_params& p, bool packed) {
     const size_t rows = packed ? (size_t)p.T : (size_t)p.B * p.T, n = round4(rows * p.H);
+    int len = 0;
+    const size_t nseg = segments_of(p, packed, &len), heads = (size_t)p.B * nseg * p.H;
     return n * (2 + (size_t)p.dk / (4 * CW) + (size_t)p.dv / (4 * CW)) +
-           (p.variant == SLA_GLA ? round4((size_t)p.B * p.H * p.dk) : 0);
+           (p.variant == SLA_GLA ? round4(heads * p.dk) : 0) +
+           (nseg > 1 ? 2 * heads * p.dk * p.dv + round4(heads * p.dk) : 0);
 }
 
+// One pass, or -- few sequences, see segments_of() -- every batch row in nseg segments that run side by side:
+//   1. what each segment alone leaves behind, forward (its state) and backward (its cotangent), in one launch;
+//   2. the chain kernel turns those into every segment's entry state and end cotangent;
+//   3. the three sweeps over B * nseg sequences.  The decay gradient's running sum starts, per segment, from
+//      rowsum(cotangent * state) at its end, the same identity as at the end of a whole sequence.
+// All of it in fp32 and with the decay applied token by token, so the domain is that of the single pass.
 int launch_backward_f32(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
                         const float* kl, const void* ld, const float* s0, const void* dout, const float* dsf, void* dq,
                         void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, const int* cu,
@@ -431,15 +642,26 @@ int launch_backward_f32(const sla_params& p, const void* q, const void* k, const
     a.gq = gq; a.gk = gk;
     a.part_q = w; w += n * pq;
     a.part_k = w; w += n * pv;
+    int seg_len = 0;
+    const int nseg = segments_of(p, cu != nullptr, &seg_len);
+    const size_t heads = (size_t)p.B * nseg * p.H;
     a.corr = w;
+    if (p.variant == SLA_GLA) w += round4(heads * p.dk);
+    Segments sg = {nullptr, nullptr, nullptr};
+    if (nseg > 1) {
+        sg.states = w; w += heads * p.dk * p.dv;
+        sg.cotangents = w; w += heads * p.dk * p.dv;
+        sg.totals = w;
+    }
+    a.nseg = nseg; a.seg_len = seg_len;
     a.plane = n; a.rows = rows; a.cu = cu;
-    a.B = p.B; a.T = p.T; a.H = p.H;
+    a.B = p.B * nseg; a.T = p.T; a.H = p.H;
     a.head_major = (p.flags & SLA_FLAG_HEAD_MAJOR) != 0;
     const bool state_only = rows == 0;  // no tokens: the final state's cotangent is the initial state's
     int rc = launch_bwd_gates(ql, kl, gq, gk, rows, p.H, stream);
     if (rc != SLA_OK) return rc;
-    rc = p.variant == SLA_GLA ? launch_dk<true>(a, p.dk, p.dv, state_only, stream)
-                              : launch_dk<false>(a, p.dk, p.dv, state_only, stream);
+    rc = p.variant == SLA_GLA ? launch_dk<true>(a, sg, p.dk, p.dv, state_only, stream)
+                              : launch_dk<false>(a, sg, p.dk, p.dv, state_only, stream);
     if (rc != SLA_OK || state_only) return rc;
     rc = launch_bwd_logits(gq, a.part_q, pq, n, dql, rows, p.H, cu, p.B, stream);
     if (rc == SLA_OK && kl) rc = launch_bwd_logits(gk, a.part_k, pv, n, dkl, rows, p.H, cu, p.B, stream);

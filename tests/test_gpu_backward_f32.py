@@ -98,3 +98,38 @@ def test_full_size(name):
     d = si.generate(w)
     cot = si.cotangents(w.B, w.T, w.H, w.dk, w.dv, seed=w.seed + 50)
     check_backward(w.variant, d, cot, label=f"f32 {name}", c_oracle=True, dtype="f32")
+
+
+@pytest.mark.parametrize("variant", [RETNET, GLA])
+@pytest.mark.parametrize("head_major", [False, True])
+@pytest.mark.parametrize("B,T,H,dk,dv", [(1, 63, 2, 64, 64), (1, 64, 2, 64, 64), (1, 97, 3, 128, 64), (2, 1021, 8, 64, 128),
+                                         (16, 260, 16, 64, 64), (4, 130, 32, 64, 256), (43, 100, 3, 64, 256)])
+@pytest.mark.parametrize("states", [False, True])
+def test_segments_agree_with_the_single_pass(variant, head_major, B, T, H, dk, dv, states):
+    """Rectangular batches with few sequences are cut into segments, packed ones are not: the same sequences through
+    both.  (Sizes: both sides of the shortest row that is cut, a last segment of one token, 16 segments, two segments
+    by the 512-workgroup rule, by the 256 one, and one sequence too many for it.)  fp32 throughout, another order of
+    summation: ten times the 1e-7 .. 1e-6 by which either differs from the fp64 oracle."""
+    import torch
+
+    import paper_2602_01744_amd as sla
+
+    g = torch.Generator(device="cuda").manual_seed(1990 + T)
+    n = lambda *s: torch.randn(s, generator=g, device="cuda")
+    q, k, v, do = n(B, T, H, dk) * dk**-0.5, n(B, T, H, dk) * dk**-0.5, n(B, T, H, dv), n(B, T, H, dv)
+    ql, kl = n(B, T, H), n(B, T, H)
+    ld = -torch.rand(B, T, H, dk, generator=g, device="cuda") * 0.1 if variant == GLA else -torch.rand(H, generator=g, device="cuda") * 0.1
+    s0, dsf = (n(B, H, dk, dv), n(B, H, dk, dv)) if states else (None, None)
+    swap = lambda t: t.transpose(1, 2).contiguous() if head_major and t is not None and t.dim() == 4 else t
+    a = sla.backward(variant, swap(q), swap(k), swap(v), ql, kl, swap(ld), swap(do), s0, dsf,
+                     want_d_initial_state=states, head_major=head_major)
+    flat = lambda t: t.reshape(B * T, *t.shape[2:]) if t.dim() > 1 else t
+    cu = torch.arange(B + 1, dtype=torch.int32, device="cuda") * T
+    b = sla.backward_varlen(variant, *(flat(t) for t in (q, k, v, ql, kl, ld, do)), cu, s0, dsf, want_d_initial_state=states)
+    for name, want in b.items():
+        if want is None:
+            assert a[name] is None
+            continue
+        got = swap(a[name]) if name in ("dq", "dk", "dv", "dlog_decay") else a[name]
+        err = float((got.double() - want.reshape(got.shape).double()).abs().max() / want.double().abs().max())
+        assert err <= 1e-5, (name, err)
