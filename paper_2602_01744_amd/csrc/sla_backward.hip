@@ -33,6 +33,7 @@
 #include <atomic>
 
 #include "sla.h"
+#include "sla_gate_grad.h"
 
 namespace sla {
 
@@ -54,6 +55,9 @@ constexpr int kCols = 64;       // columns of the sliced dimension per workgroup
 constexpr int kTS = 20;         // token stride (elements) of the transposed [column][token] tiles
 constexpr int kFS = 68;         // row stride (elements) of the [token][64 columns] tiles
 constexpr float kLog2e = 1.4426950408889634f;
+
+constexpr int kSweepState = 8;   // the dv sweep's state recurrence alone (pre-pass of the segment schedule)
+constexpr int kGatesReady = 16;  // the workspace already holds the gates (the pre-pass made them)
 
 struct BArgs {
     const uint16_t* q;
@@ -80,8 +84,7 @@ struct BArgs {
     size_t rows;             // tokens in all: B * T, or the packed total
     const int* cu;           // packed variable-length batch: sequence b is tokens cu[b] .. cu[b+1]-1 of T; else null
     bool head_major;         // q, k, v, d_out, the GLA decay and their gradients are [B,H,T,d] instead of [B,T,H,d]
-    int sweeps;              // which of the three sweeps to launch: 1 = dq, 2 = dv, 4 = dk (all: 7)
-    bool dv_state_only;      // the dv sweep writes d_initial_state but not dv (pre-pass of the segment schedule)
+    int sweeps;              // which of the three sweeps to launch: 1 = dq, 2 = dv, 4 = dk (all: 7); kSweepState
     int skip_every;          // > 0: the dv sweep skips every sequence whose index is a multiple of it
     unsigned int* status;    // sticky device status word (SLA_DEVICE_*): a bounded wait that expired is recorded here
 };
@@ -959,12 +962,16 @@ __global__ __launch_bounds__(kBwdThreads) void sla_bwd_dk_kernel(const BArgs a) 
 // ------------------------------------------------------------------------------------------------------------
 // Sweep R1: backward in time, state dS[d][n] (key rows, 16 value columns per wave) -> dv, dG^K, d initial state.
 // ------------------------------------------------------------------------------------------------------------
-template <int DK>
+// SO: the pre-pass of the segment schedule, which wants the state recurrence alone (d_initial_state, no dv).  It needs
+// q, the decay and d_out only, so its producers neither load k nor make the operands of the dv products: it is the
+// producers that bound this sweep.  B=8 T=4096 H=4 128 x 256 in 4 segments, pre-pass 115 -> 76 us (GLA).
+template <int DK, bool SO>
 struct SmemV {
+    static constexpr int row_tile = SO ? 0 : kTok * (DK + 8) * 2;
     static constexpr int oQA = 0;
-    static constexpr int oKD = oQA + kTok * (DK + 8) * 2;
-    static constexpr int oKB = oKD + kTok * (DK + 8) * 2;
-    static constexpr int oQAT = oKB + kTok * (DK + 8) * 2;
+    static constexpr int oKD = oQA + row_tile;
+    static constexpr int oKB = oKD + row_tile;
+    static constexpr int oQAT = oKB + row_tile;
     static constexpr int oDYT = oQAT + DK * kTS * 2;
     static constexpr int oAT = oDYT + kCols * kTS * 2;
     static constexpr int oGK = oAT + DK * 4;
@@ -983,9 +990,9 @@ struct PreVals {  // N groups of eight key columns of one token, and (member 0) 
     float gq[2], gk;
 };
 
-template <int VAR, int DK, int DV>
+template <int VAR, int DK, int DV, bool SO>
 __global__ __launch_bounds__(kBwdThreads) void sla_bwd_dv_kernel(const BArgs a) {
-    typedef SmemV<DK> L;
+    typedef SmemV<DK, SO> L;
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int NSL = DV / kCols;
     constexpr int N = DK / 64;  // each member wave stages half of the key columns: DK / 8 per lane
@@ -1026,10 +1033,10 @@ __global__ __launch_bounds__(kBwdThreads) void sla_bwd_dv_kernel(const BArgs a) 
 #pragma unroll
                 for (int j = 0; j < N; ++j) {
                     if constexpr (VAR == SLA_GLA) p.ld[j] = load16(a.ld + wrow * DK + d0 + 32 * j);
-                    p.kx[j] = load16(a.k + wrow * DK + d0 + 32 * j);
+                    if constexpr (!SO) p.kx[j] = load16(a.k + wrow * DK + d0 + 32 * j);
                     p.qx[j] = load16(a.q + wrow * DK + d0 + 32 * j);
                 }
-                p.gk = a.gk[row];
+                if constexpr (!SO) p.gk = a.gk[row];
                 if (m == 0) {  // uniform over the wave
 #pragma unroll
                     for (int rep = 0; rep < 2; ++rep) {
@@ -1049,7 +1056,9 @@ __global__ __launch_bounds__(kBwdThreads) void sla_bwd_dv_kernel(const BArgs a) 
                     const int c0 = d0 + 32 * j;
                     float c[8], tot[8];
                     block_decay<VAR>(keep(p.ld[j], ok), head_step, ok, c, tot);
-                    const u4 qx = keep(p.qx[j], ok), kx = keep(p.kx[j], ok);
+                    const u4 qx = keep(p.qx[j], ok);
+                    u4 kx = {0u, 0u, 0u, 0u};
+                    if constexpr (!SO) kx = keep(p.kx[j], ok);
                     // kb = k A / p as (k / p) A: the block's decay A is one exponential per column, which the state
                     // update wants anyway, instead of one more per element (the quarter-rate unit is the busiest)
                     float A[8];
@@ -1058,14 +1067,20 @@ __global__ __launch_bounds__(kBwdThreads) void sla_bwd_dv_kernel(const BArgs a) 
                     u4 qa, kd, kb;
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const float kl = bf_lo(kx[i]) * ex2(-c[2 * i]), kh = bf_hi(kx[i]) * ex2(-c[2 * i + 1]);
-                        qa[i] = pack2(bf_lo(qx[i]) * ex2(c[2 * i]), bf_hi(qx[i]) * ex2(c[2 * i + 1]));
-                        kd[i] = pack2(kl, kh);
-                        kb[i] = pack2(kl * A[2 * i], kh * A[2 * i + 1]);
+                        if constexpr (SO) {
+                            qa[i] = pack2(bf_lo(qx[i]) * ex2(c[2 * i]), bf_hi(qx[i]) * ex2(c[2 * i + 1]));
+                        } else {
+                            const float kl = bf_lo(kx[i]) * ex2(-c[2 * i]), kh = bf_hi(kx[i]) * ex2(-c[2 * i + 1]);
+                            qa[i] = pack2(bf_lo(qx[i]) * ex2(c[2 * i]), bf_hi(qx[i]) * ex2(c[2 * i + 1]));
+                            kd[i] = pack2(kl, kh);
+                            kb[i] = pack2(kl * A[2 * i], kh * A[2 * i + 1]);
+                        }
                     }
-                    put_perm<DK>((uint16_t*)(buf + L::oQA), t, c0 >> 3, qa);
-                    put_perm<DK>((uint16_t*)(buf + L::oKD), t, c0 >> 3, kd);
-                    put_perm<DK>((uint16_t*)(buf + L::oKB), t, c0 >> 3, kb);
+                    if constexpr (!SO) {
+                        put_perm<DK>((uint16_t*)(buf + L::oQA), t, c0 >> 3, qa);
+                        put_perm<DK>((uint16_t*)(buf + L::oKD), t, c0 >> 3, kd);
+                        put_perm<DK>((uint16_t*)(buf + L::oKB), t, c0 >> 3, kb);
+                    }
                     put_T((uint16_t*)(buf + L::oQAT), c0, t, qa);
                     if (t == 0) {
                         float* at = (float*)(buf + L::oAT) + c0;
@@ -1073,7 +1088,9 @@ __global__ __launch_bounds__(kBwdThreads) void sla_bwd_dv_kernel(const BArgs a) 
                         *(f4*)(at + 4) = f4{A[4], A[5], A[6], A[7]};
                     }
                 }
-                if (m == 0 && g == 0) ((float*)(buf + L::oGK))[t] = ok ? p.gk : 0.f;
+                if constexpr (!SO) {
+                    if (m == 0 && g == 0) ((float*)(buf + L::oGK))[t] = ok ? p.gk : 0.f;
+                }
                 if (m == 0) {
 #pragma unroll
                     for (int rep = 0; rep < 2; ++rep) {
@@ -1109,7 +1126,7 @@ __global__ __launch_bounds__(kBwdThreads) void sla_bwd_dv_kernel(const BArgs a) 
         const uint16_t* KBp = (const uint16_t*)(buf + L::oKB);
         f4 Ys = {0.f, 0.f, 0.f, 0.f}, Yi = {0.f, 0.f, 0.f, 0.f};
         const s4 fdy = get_T((const uint16_t*)(buf + L::oDYT), cb + r, g);
-        if (!a.dv_state_only) {  // the pre-pass of the segment schedule wants the state recurrence alone
+        if constexpr (!SO) {
             // Pq[t][j] = qa_t . kd_j, kept for j <= t
             f4 Pq = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -1136,7 +1153,7 @@ __global__ __launch_bounds__(kBwdThreads) void sla_bwd_dv_kernel(const BArgs a) 
         }
         consumer_release(ring, blk);  // every operand of the block is in registers
         const int tok = t0 + r;
-        if (tok < T && !a.dv_state_only) {
+        if (!SO && tok < T) {
             *(u2*)(a.dv + (wide0 + (size_t)tok * wstep) * DV + sbase + cb + 4 * g) =
                 u2{pack2(gk * (Ys[0] + Yi[0]), gk * (Ys[1] + Yi[1])), pack2(gk * (Ys[2] + Yi[2]), gk * (Ys[3] + Yi[3]))};
         }
@@ -1194,12 +1211,17 @@ __global__ __launch_bounds__(kEwThreads) void sla_bwd_gates_kernel(const float* 
     }
 }
 
-// dlogits = G * (dG - sum_h G dG), dG summed over its partial planes
+// dlogits = G * (dG - sum_h G dG), dG summed over its partial planes; blockIdx.y picks the gate (one launch for both).
 // Packed batches (cu != null): rows outside [cu[0], cu[B]) belong to no sequence; the sweeps never wrote their
 // partial planes, and their gradients are not written either.
-__global__ __launch_bounds__(kEwThreads) void sla_bwd_logits_kernel(const float* g, const float* part, int planes,
-                                                                     size_t plane, float* dl, size_t rows, int H,
-                                                                     const int* cu, int B) {
+__global__ __launch_bounds__(kEwThreads) void sla_bwd_logits_kernel(const GateGrad read, const GateGrad write, size_t rows,
+                                                                    int H, const int* cu, int B) {
+    const GateGrad& x = blockIdx.y ? write : read;
+    const float* g = x.g;
+    const float* part = x.part;
+    const int planes = x.planes;
+    const size_t plane = x.plane;
+    float* dl = x.dl;
     __shared__ float sx[kEwThreads];
     const int per = kEwThreads / H, tid = threadIdx.x, lr = tid / H, h = tid - lr * H;
     const size_t row = (size_t)blockIdx.x * per + lr;
@@ -1234,7 +1256,7 @@ bool allow_lds(K kernel, int lds) {
 
 template <int VAR, int DK, int DV>
 int launch_sweeps(const BArgs& a, hipStream_t stream) {
-    constexpr int ldsF = SmemF<DV>::total, ldsV = SmemV<DK>::total, ldsK = SmemK<DV>::total;
+    constexpr int ldsF = SmemF<DV>::total, ldsV = SmemV<DK, false>::total, ldsS = SmemV<DK, true>::total, ldsK = SmemK<DV>::total;
     // once per device and instantiation (bit d = done on device d); not a stream operation
     static std::atomic<uint64_t> configured{0};
     int dev = 0;
@@ -1243,7 +1265,8 @@ int launch_sweeps(const BArgs& a, hipStream_t stream) {
         return SLA_ERR_HIP;
     }
     if (!((configured.load(std::memory_order_acquire) >> dev) & 1u)) {
-        if (!allow_lds(sla_bwd_dq_kernel<VAR, DK, DV>, ldsF) || !allow_lds(sla_bwd_dv_kernel<VAR, DK, DV>, ldsV) ||
+        if (!allow_lds(sla_bwd_dq_kernel<VAR, DK, DV>, ldsF) || !allow_lds(sla_bwd_dv_kernel<VAR, DK, DV, false>, ldsV) ||
+            !allow_lds(sla_bwd_dv_kernel<VAR, DK, DV, true>, ldsS) ||
             !allow_lds(sla_bwd_dk_kernel<VAR, DK, DV>, ldsK))
             return SLA_ERR_HIP;
         configured.fetch_or(uint64_t(1) << dev, std::memory_order_release);
@@ -1253,8 +1276,10 @@ int launch_sweeps(const BArgs& a, hipStream_t stream) {
     auto grid = [bh](unsigned slices) { return dim3(((bh + 7u) / 8u) * 8u * slices); };  // see logical_workgroup()
     if (a.sweeps & 1)
         hipLaunchKernelGGL((sla_bwd_dq_kernel<VAR, DK, DV>), grid(DK / kCols), block, (size_t)ldsF, stream, a);
+    if (a.sweeps & kSweepState)
+        hipLaunchKernelGGL((sla_bwd_dv_kernel<VAR, DK, DV, true>), grid(DV / kCols), block, (size_t)ldsS, stream, a);
     if (a.sweeps & 2)
-        hipLaunchKernelGGL((sla_bwd_dv_kernel<VAR, DK, DV>), grid(DV / kCols), block, (size_t)ldsV, stream, a);
+        hipLaunchKernelGGL((sla_bwd_dv_kernel<VAR, DK, DV, false>), grid(DV / kCols), block, (size_t)ldsV, stream, a);
     if (a.sweeps & 4)
         hipLaunchKernelGGL((sla_bwd_dk_kernel<VAR, DK, DV>), grid(DK / kCols), block, (size_t)ldsK, stream, a);
     return hipGetLastError() == hipSuccess ? SLA_OK : SLA_ERR_HIP;
@@ -1289,13 +1314,12 @@ int launch_bwd_gates(const float* ql, const float* kl, float* gq, float* gk, siz
     return hipGetLastError() == hipSuccess ? SLA_OK : SLA_ERR_HIP;
 }
 
-// dlogits = G * (dG - sum_h G dG) with dG the sum of `planes` partial planes, `plane` floats apart (shared with the
-// fp32 path).
-int launch_bwd_logits(const float* g, const float* part, int planes, size_t plane, float* dl, size_t rows, int H,
-                      const int* cu, int B, hipStream_t stream) {
+// Both gates' logit gradients (no write gate: write.dl null), shared with the fp32 path.
+int launch_bwd_logits(const GateGrad& read, const GateGrad& write, size_t rows, int H, const int* cu, int B,
+                      hipStream_t stream) {
     if (rows == 0) return SLA_OK;
     const unsigned per = kEwThreads / (unsigned)H, eg = (unsigned)((rows + per - 1) / per);
-    hipLaunchKernelGGL(sla_bwd_logits_kernel, dim3(eg), dim3(kEwThreads), 0, stream, g, part, planes, plane, dl, rows,
+    hipLaunchKernelGGL(sla_bwd_logits_kernel, dim3(eg, write.dl ? 2 : 1), dim3(kEwThreads), 0, stream, read, write, rows,
                        H, cu, B);
     return hipGetLastError() == hipSuccess ? SLA_OK : SLA_ERR_HIP;
 }
@@ -1323,17 +1347,16 @@ size_t backward_workspace_floats(const sla_params& p, bool packed) {
 namespace {
 
 // Segment schedule of the backward pass (rectangular batch with few sequences): see launch_backward_segments.
-__global__ __launch_bounds__(kEwThreads) void sla_bwd_segment_offsets_kernel(int* cu, int B, int T, int nseg, int len) {
-    const int i = blockIdx.x * kEwThreads + threadIdx.x;
-    if (i > B * nseg) return;
-    const int b = i / nseg, s = i - b * nseg;
-    cu[i] = i == B * nseg ? B * T : b * T + min(s * len, T);
-}
-
-// dsf[b][s] = the caller's final-state cotangent for the last segment of a batch row, zero for the others.
-__global__ __launch_bounds__(kEwThreads) void sla_bwd_segment_seed_kernel(const f4* dsf_user, f4* dsf, int nseg,
-                                                                          size_t per_row, size_t count) {
+// cu: the segments' offsets; dsf[b][s]: the caller's final-state cotangent for the last segment of a batch row, zero for
+// the others.
+__global__ __launch_bounds__(kEwThreads) void sla_bwd_segment_seed_kernel(const f4* dsf_user, f4* dsf, int* cu, int B,
+                                                                          int T, int nseg, int len, size_t per_row,
+                                                                          size_t count) {
     const size_t i = (size_t)blockIdx.x * kEwThreads + threadIdx.x;
+    if (i <= (size_t)B * nseg) {
+        const int b = (int)i / nseg, s = (int)i - b * nseg;
+        cu[i] = b == B ? B * T : b * T + min(s * len, T);
+    }
     if (i >= count) return;
     const size_t bs = i / per_row, b = bs / nseg, s = bs - b * nseg;
     dsf[i] = (dsf_user && s == (size_t)nseg - 1) ? dsf_user[b * per_row + (i - bs * per_row)] : f4{0.f, 0.f, 0.f, 0.f};
@@ -1393,7 +1416,7 @@ sla_params packed_segments(const sla_params& p, int nseg) {
 int launch_backward_some(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
                          const float* kl, const void* ld, const float* s0, const void* dout, const float* dsf, void* dq,
                          void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, const int* cu,
-                         hipStream_t stream, int sweeps, bool dv_state_only, int skip_every = 0);
+                         hipStream_t stream, int sweeps, int skip_every = 0);
 
 // Few sequences (B * H * slices below the number of compute units): every batch row is cut into nseg segments of
 // seg_len tokens, which then run as B * nseg packed sequences, each with its own entry state and end cotangent:
@@ -1414,16 +1437,16 @@ int launch_backward_segments(const sla_params& p, int nseg, int seg_len, int dvw
     float* seg_dsf = w; w += states;
     int* cu = (int*)w;
     const unsigned eb = kEwThreads;
-    hipLaunchKernelGGL(sla_bwd_segment_offsets_kernel, dim3((unsigned)(pk.B + eb) / eb), dim3(eb), 0, stream, cu, p.B,
-                       p.T, nseg, seg_len);
+    // a segment's states are more 16-byte pieces than there are segments, so one grid covers the offsets too
     hipLaunchKernelGGL(sla_bwd_segment_seed_kernel, dim3((unsigned)((states / 4 + eb - 1) / eb)), dim3(eb), 0, stream,
-                       (const f4*)dsf, (f4*)seg_dsf, nseg, (size_t)p.H * p.dk * p.dv / 4, states / 4);
+                       (const f4*)dsf, (f4*)seg_dsf, cu, p.B, p.T, nseg, seg_len, (size_t)p.H * p.dk * p.dv / 4,
+                       states / 4);
     if (hipGetLastError() != hipSuccess) return SLA_ERR_HIP;
     int rc = launch_segment_states(p, dvw, nseg, seg_len, q, k, v, ql, kl, ld, s0, fwd, totals, stream);
     if (rc != SLA_OK) return rc;
     // the start cotangent of a row's first segment is wanted only as the gradient of the initial state
     rc = launch_backward_some(pk, q, k, v, ql, kl, ld, nullptr, dout, seg_dsf, dq, dk, dv, dql, dkl, dld, part, ws, cu,
-                              stream, 2, true, ds0 ? 0 : nseg);
+                              stream, kSweepState, ds0 ? 0 : nseg);
     if (rc != SLA_OK) return rc;
     const size_t n = (size_t)p.B * p.H * p.dk * (p.dv / 4);
     if (p.variant == SLA_GLA)
@@ -1436,7 +1459,7 @@ int launch_backward_segments(const sla_params& p, int nseg, int seg_len, int dvw
                            p.dk, p.dv, nseg, seg_len);
     if (hipGetLastError() != hipSuccess) return SLA_ERR_HIP;
     return launch_backward_some(pk, q, k, v, ql, kl, ld, fwd, dout, seg_dsf, dq, dk, dv, dql, dkl, dld, nullptr, ws, cu,
-                                stream, 7, false);
+                                stream, 7 | kGatesReady);
 }
 
 int launch_backward(const sla_params& p, const void* q, const void* k, const void* v, const float* ql, const float* kl,
@@ -1444,18 +1467,16 @@ int launch_backward(const sla_params& p, const void* q, const void* k, const voi
                     float* dql, float* dkl, void* dld, float* ds0, float* ws, const int* cu, hipStream_t stream) {
     if (p.dtype == SLA_F32)  // fp32 tensors: token by token in fp32 vector arithmetic
         return launch_backward_f32(p, q, k, v, ql, kl, ld, s0, dout, dsf, dq, dk, dv, dql, dkl, dld, ds0, ws, cu, stream);
-    return launch_backward_some(p, q, k, v, ql, kl, ld, s0, dout, dsf, dq, dk, dv, dql, dkl, dld, ds0, ws, cu, stream, 7,
-                                false);
+    return launch_backward_some(p, q, k, v, ql, kl, ld, s0, dout, dsf, dq, dk, dv, dql, dkl, dld, ds0, ws, cu, stream, 7);
 }
 
 int launch_backward_some(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
                          const float* kl, const void* ld, const float* s0, const void* dout, const float* dsf, void* dq,
                          void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, const int* cu,
-                         hipStream_t stream, int sweeps, bool dv_state_only, int skip_every) {
+                         hipStream_t stream, int sweeps, int skip_every) {
     const size_t rows = cu ? (size_t)p.T : (size_t)p.B * p.T, n = round4(rows * p.H);
     BArgs a;
     a.sweeps = sweeps;
-    a.dv_state_only = dv_state_only;
     a.skip_every = skip_every;
     a.status = device_status_word();
     if (!a.status) return SLA_ERR_HIP;
@@ -1480,17 +1501,17 @@ int launch_backward_some(const sla_params& p, const void* q, const void* k, cons
     a.head_major = (p.flags & SLA_FLAG_HEAD_MAJOR) != 0;
 
     const unsigned eb = kEwThreads, per = eb / (unsigned)p.H, eg = (unsigned)((rows + per - 1) / per);
-    if (rows > 0) {
+    if (rows > 0 && !(sweeps & kGatesReady)) {
         hipLaunchKernelGGL(sla_bwd_gates_kernel, dim3(eg), dim3(eb), 0, stream, ql, kl, gq, gk, rows, p.H);
         if (hipGetLastError() != hipSuccess) return SLA_ERR_HIP;
     }
     const int rc = p.variant == SLA_GLA ? launch_dk<SLA_GLA>(a, p.dk, p.dv, stream)
                                         : launch_dk<SLA_RETNET>(a, p.dk, p.dv, stream);
-    if (rc != SLA_OK || rows == 0 || sweeps != 7) return rc;
+    if (rc != SLA_OK || rows == 0 || (sweeps & 7) != 7) return rc;
     // the sweeps write the planes of one gate rows * H floats apart (the space reserved per plane is n >= rows * H)
-    int rl = launch_bwd_logits(gq, a.part_q, p.dk / 16, rows * p.H, dql, rows, p.H, cu, p.B, stream);
-    if (rl == SLA_OK && kl) rl = launch_bwd_logits(gk, a.part_k, p.dk / 16, rows * p.H, dkl, rows, p.H, cu, p.B, stream);
-    return rl;
+    const size_t plane = rows * p.H;
+    return launch_bwd_logits(GateGrad{gq, a.part_q, p.dk / 16, plane, dql},
+                             GateGrad{gk, a.part_k, p.dk / 16, plane, kl ? dkl : nullptr}, rows, p.H, cu, p.B, stream);
 }
 
 }  // namespace sla

@@ -23,14 +23,12 @@
 #include <atomic>
 
 #include "sla.h"
+#include "sla_gate_grad.h"
 #include "sla_token_sweep.h"
 
 namespace sla {
 
 int launch_bwd_gates(const float* ql, const float* kl, float* gq, float* gk, size_t rows, int H, hipStream_t stream);
-int launch_bwd_logits(const float* g, const float* part, int planes, size_t plane, float* dl, size_t rows, int H,
-                      const int* cu, int B, hipStream_t stream);
-
 namespace {
 
 using namespace tok;
@@ -663,9 +661,8 @@ int launch_backward_f32(const sla_params& p, const void* q, const void* k, const
     rc = p.variant == SLA_GLA ? launch_dk<true>(a, sg, p.dk, p.dv, state_only, stream)
                               : launch_dk<false>(a, sg, p.dk, p.dv, state_only, stream);
     if (rc != SLA_OK || state_only) return rc;
-    rc = launch_bwd_logits(gq, a.part_q, pq, n, dql, rows, p.H, cu, p.B, stream);
-    if (rc == SLA_OK && kl) rc = launch_bwd_logits(gk, a.part_k, pv, n, dkl, rows, p.H, cu, p.B, stream);
-    return rc;
+    return launch_bwd_logits(GateGrad{gq, a.part_q, pq, n, dql}, GateGrad{gk, a.part_k, pv, n, kl ? dkl : nullptr}, rows,
+                             p.H, cu, p.B, stream);
 }
 
 }  // namespace sla
