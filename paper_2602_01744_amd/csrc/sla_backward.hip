@@ -1379,13 +1379,24 @@ __global__ __launch_bounds__(kEwThreads) void sla_bwd_segment_combine_kernel(con
     const size_t head_sz = (size_t)dk * dv, off = (size_t)d * dv + n;
     auto at = [&](int s) { return ((size_t)(b * nseg + s) * H + h) * head_sz + off; };
     f4 t = *(const f4*)(part + at(nseg - 1));
-    for (int s = nseg - 2; s >= 0; --s) {
-        *(f4*)(dsf + at(s)) = t;
-        const float D = VAR == SLA_GLA ? totals[((size_t)(b * (nseg - 1) + s) * H + h) * dk + d]
-                                       : ex2(ld_head[h] * kLog2e * (float)len);  // segments before the last are full
-        const f4 x = *(const f4*)(part + at(s));
+    constexpr int kAtOnce = 4;  // loads this many segments ahead of the chain
+    for (int s0 = nseg - 2; s0 >= 0; s0 -= kAtOnce) {
+        f4 x[kAtOnce];
+        float D[kAtOnce];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) t[i] = x[i] + D * t[i];
+        for (int u = 0; u < kAtOnce; ++u) {
+            const int s = max(s0 - u, 0);
+            x[u] = *(const f4*)(part + at(s));
+            D[u] = VAR == SLA_GLA ? totals[((size_t)(b * (nseg - 1) + s) * H + h) * dk + d]
+                                  : ex2(ld_head[h] * kLog2e * (float)len);  // segments before the last are full
+        }
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u) {
+            if (s0 - u < 0) break;
+            *(f4*)(dsf + at(s0 - u)) = t;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) t[i] = x[u][i] + D[u] * t[i];
+        }
     }
     if (ds0_user) *(f4*)(ds0_user + (size_t)bh * head_sz + off) = t;
 }

@@ -1278,21 +1278,39 @@ __global__ void sla_segment_combine_kernel(const KArgs a, int dk) {
     f32x4 E = {0.f, 0.f, 0.f, 0.f};
     if (a.s0) E = *(const f32x4*)(a.s0 + (size_t)bh * head_sz + off);
     *(f32x4*)(a.ws_state + ((size_t)(b * a.nseg) * a.H + h) * head_sz + off) = E;
-    for (int s = 0; s + 1 < a.nseg; ++s) {
-        float D;
-        if constexpr (VAR == SLA_GLA) {
-            const float* dp = a.ws_decay + ((size_t)(b * (a.nseg - 1) + s) * a.H + h) * kMaxSlots * dk + d;
-            D = 1.f;
-            for (int w = 0; w < a.nparts; ++w) D *= dp[w * dk];
-        } else {
-            D = fast_exp2(((const float*)a.ld)[h] * kLog2e * (float)a.Ls);  // segments before the last are full
-        }
-        if (a.ws_total && n == 0) a.ws_total[((size_t)(b * (a.nseg - 1) + s) * a.H + h) * dk + d] = D;
-        f32x4* Lp = (f32x4*)(a.ws_state + ((size_t)(b * a.nseg + s + 1) * a.H + h) * head_sz + off);
-        const f32x4 Lseg = *Lp;
+    // Only E is chained: the segments' end states and decays are loaded kAtOnce segments ahead of it, so that the loop
+    // costs a memory latency per four segments and not two for each (B=4 H=8 d=128, 4 segments: 5.3 -> 4.9 us; B=8
+    // H=4 128 x 256 GLA 9.8 -> 6.8 us; B=1 T=65536 H=32 GLA 12.0 -> 5.9 us).
+    constexpr int kAtOnce = 4;
+    for (int s0 = 0; s0 + 1 < a.nseg; s0 += kAtOnce) {
+        f32x4 Lseg[kAtOnce];
+        float D[kAtOnce];
+        auto slot = [&](int s) { return (f32x4*)(a.ws_state + ((size_t)(b * a.nseg + s + 1) * a.H + h) * head_sz + off); };
 #pragma unroll
-        for (int i = 0; i < 4; ++i) E[i] = D * E[i] + Lseg[i];
-        *Lp = E;
+        for (int u = 0; u < kAtOnce; ++u) {
+            const int s = min(s0 + u, a.nseg - 2);
+            Lseg[u] = *slot(s);
+            if constexpr (VAR == SLA_GLA) {
+                const float* dp = a.ws_decay + ((size_t)(b * (a.nseg - 1) + s) * a.H + h) * kMaxSlots * dk + d;
+                float part[kMaxSlots];
+#pragma unroll
+                for (int w = 0; w < kMaxSlots; ++w) part[w] = dp[min(w, a.nparts - 1) * dk];
+                D[u] = 1.f;
+#pragma unroll
+                for (int w = 0; w < kMaxSlots; ++w) D[u] *= w < a.nparts ? part[w] : 1.f;
+            } else {
+                D[u] = fast_exp2(((const float*)a.ld)[h] * kLog2e * (float)a.Ls);  // segments before the last are full
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kAtOnce; ++u) {
+            const int s = s0 + u;
+            if (s + 1 >= a.nseg) break;
+            if (a.ws_total && n == 0) a.ws_total[((size_t)(b * (a.nseg - 1) + s) * a.H + h) * dk + d] = D[u];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) E[i] = D[u] * E[i] + Lseg[u][i];
+            *slot(s) = E;
+        }
     }
 }
 
