@@ -463,32 +463,47 @@ __global__ __launch_bounds__(kEw) void sla_bwd32_chain_kernel(float* states, flo
     const size_t bh = idx / per_head, b = bh / H, h = bh % H, in = idx % per_head;
     const int d = (int)(in / (dv / 4));
     const size_t user = bh * dk * dv + in * 4;
+    constexpr int kAtOnce = 8;  // only e and t are chained: what the segments left is loaded ahead of them
     auto seg_head = [&](int s) { return (b * nseg + s) * H + h; };
+    auto at = [&](float* p, int s) { return p + seg_head(s) * dk * dv + in * 4; };
     const f4 zero = {0.f, 0.f, 0.f, 0.f};
     if (blockIdx.y == 0) {
         f4 e = s0 ? *(const f4*)(s0 + user) : zero;
-        for (int s = 0; s < nseg; ++s) {
-            float* at = states + seg_head(s) * dk * dv + in * 4;
-            const bool last = s == nseg - 1;
-            const f4 x = last ? zero : *(const f4*)at;
-            *(f4*)at = e;
-            if (!last) {
-                const float D = totals[seg_head(s) * dk + d];
+        for (int s0 = 0; s0 < nseg; s0 += kAtOnce) {
+            f4 x[kAtOnce];
+            float D[kAtOnce];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) e[i] = x[i] + D * e[i];
+            for (int u = 0; u < kAtOnce; ++u) {  // the last segment's own slot and decay are not read (nseg >= 2)
+                const int s = min(s0 + u, nseg - 2);
+                x[u] = *(const f4*)at(states, s);
+                D[u] = totals[seg_head(s) * dk + d];
+            }
+#pragma unroll
+            for (int u = 0; u < kAtOnce; ++u) {
+                if (s0 + u >= nseg) break;
+                *(f4*)at(states, s0 + u) = e;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) e[i] = x[u][i] + D[u] * e[i];
             }
         }
     } else {
         f4 t = dsf ? *(const f4*)(dsf + user) : zero;
-        for (int s = nseg - 1; s >= 0; --s) {
-            float* at = cotangents + seg_head(s) * dk * dv + in * 4;
-            const bool more = s > 0 || ds0;
-            const f4 x = more ? *(const f4*)at : zero;
-            *(f4*)at = t;
-            if (more) {
-                const float D = totals[seg_head(s) * dk + d];
+        const int lowest = ds0 ? 0 : 1;  // the first segment's start cotangent exists only if it is wanted
+        for (int s0 = nseg - 1; s0 >= 0; s0 -= kAtOnce) {
+            f4 x[kAtOnce];
+            float D[kAtOnce];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) t[i] = x[i] + D * t[i];
+            for (int u = 0; u < kAtOnce; ++u) {
+                const int s = max(s0 - u, lowest);
+                x[u] = *(const f4*)at(cotangents, s);
+                D[u] = totals[seg_head(s) * dk + d];
+            }
+#pragma unroll
+            for (int u = 0; u < kAtOnce; ++u) {
+                if (s0 - u < 0) break;
+                *(f4*)at(cotangents, s0 - u) = t;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) t[i] = x[u][i] + D[u] * t[i];
             }
         }
         if (ds0) *(f4*)(ds0 + user) = t;
@@ -581,16 +596,17 @@ int launch_dk(const FArgs& a, const Segments& sg, int dk, int dv, bool state_onl
 // segments of at least 32 tokens.  Heads up to 64 x 128 take half the vector work per token, so two workgroups share a
 // compute unit to gain and 512 are wanted, but not with segments under 64 tokens, where the pre-pass and the chain cost
 // more than that gives.  Call in us, one pass -> 256 wanted / 512 wanted:
-//     B=2 T=1021 H=8  64 x 128    917 -> 149 / 161           B=6 T=1500 H=16 64 x 64    1000 -> 602 / 411
-//     B=1 T=300  H=4  64 x 64     215 -> 55 (64 tokens: 76)  B=7 T=1000 H=16 64 x 128    921 -> 697 / 656
-//     B=1 T=4096 H=2  128 x 128  3827 -> 162 / 186           B=4 T=2048 H=5  128 x 256  2548 -> 789 / 829
-//     B=5 T=300  H=12 128 x 256   421 -> 375 / 424           B=8 T=700  H=16 128 x 128   765 (one pass) / 809
+//     B=2 T=1021 H=8  64 x 128    917 -> 141 / 150           B=6 T=1500 H=16 64 x 64    1000 -> 602 / 397
+//     B=1 T=300  H=4  64 x 64     215 -> 52 (64 tokens: 76)  B=7 T=1000 H=16 64 x 128    921 -> 697 / 641
+//     B=1 T=4096 H=2  128 x 128  3827 -> 139 / 149           B=4 T=2048 H=5  128 x 256  2548 -> 758 / 802
+//     B=5 T=300  H=12 128 x 256   421 -> 368 / 410           B=8 T=700  H=16 128 x 128   708 (one pass) / 790
+// Rows of up to 128 tokens stay in one pass and in the workspace it takes: such a call is 0.15 ms at most.
 // Packed batches run in one pass (their lengths are known on the device only).
 int segments_of(const sla_params& p, bool packed, int* seg_len) {
-    constexpr int kShortest = 32;
+    constexpr int kShortest = 32, kOnePass = 128;
     *seg_len = p.T;
     const size_t groups = (size_t)p.B * p.H * ((p.dk < p.dv ? p.dk : p.dv) / kSlice);
-    if (packed || groups == 0 || p.T < 2 * kShortest) return 1;
+    if (packed || groups == 0 || p.T <= kOnePass) return 1;
     const size_t target = p.dk * p.dv <= 64 * 128 && groups * p.T >= 512 * 64 ? 512 : 256;
     if (2 * groups > target) return 1;
     const int want = (int)(target / groups);

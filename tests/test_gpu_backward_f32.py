@@ -102,12 +102,13 @@ def test_full_size(name):
 
 @pytest.mark.parametrize("variant", [RETNET, GLA])
 @pytest.mark.parametrize("head_major", [False, True])
-@pytest.mark.parametrize("B,T,H,dk,dv", [(1, 63, 2, 64, 64), (1, 64, 2, 64, 64), (1, 97, 3, 128, 64), (2, 1021, 8, 64, 128),
-                                         (16, 260, 16, 64, 64), (4, 130, 32, 64, 256), (43, 100, 3, 64, 256)])
+@pytest.mark.parametrize("B,T,H,dk,dv", [(1, 128, 2, 64, 64), (1, 129, 2, 64, 64), (1, 161, 3, 128, 64),
+                                         (2, 1021, 8, 64, 128), (16, 260, 16, 64, 64), (4, 130, 32, 64, 256),
+                                         (43, 200, 3, 64, 256)])
 @pytest.mark.parametrize("states", [False, True])
 def test_segments_agree_with_the_single_pass(variant, head_major, B, T, H, dk, dv, states):
     """Rectangular batches with few sequences are cut into segments, packed ones are not: the same sequences through
-    both.  (Sizes: both sides of the shortest row that is cut, a last segment of one token, 16 segments, two segments
+    both.  (Sizes: both sides of the shortest row that is cut, last segments of one token, 16 segments, two segments
     by the 512-workgroup rule, by the 256 one, and one sequence too many for it.)  fp32 throughout, another order of
     summation: ten times the 1e-7 .. 1e-6 by which either differs from the fp64 oracle."""
     import torch
