@@ -209,25 +209,41 @@ template <bool BF16, int K, int LPH>
 __global__ __launch_bounds__(kGThreads) void sla_feature_map_bwd_kernel(const void* x, const float* w, const void* dy,
                                                                          void* dx, float* part, int B, int T, int C,
                                                                          int seg_len, float eps) {
-    const int groups = C / 8, segs = (T + seg_len - 1) / seg_len;
-    const size_t idx = (size_t)blockIdx.x * kGThreads + threadIdx.x;
-    const size_t total = (size_t)B * segs * groups;
-    const bool live = idx < total;
-    const size_t id = live ? idx : total - 1;
-    const int cg = (int)(id % groups), seg = (int)((id / groups) % segs), b = (int)(id / ((size_t)groups * segs));
+    // With seg_len = 64 the threads run over (batch row, segment, eight channels); with shorter ones `sub` waves walk
+    // seg_len of a segment's tokens each for the same 64 x 8 channels, and their shares of dw meet in LDS, so that the
+    // partial sums are those of 64-token segments whatever the walk.
+    __shared__ float red[8 * K][kGThreads];
+    const int groups = C / 8, segs = (T + kSegMax - 1) / kSegMax, sub = kSegMax / seg_len, tid = threadIdx.x;
+    const int part_no = sub == 1 ? 0 : (tid >> 6) % sub;
+    int cg, seg, b;
+    bool live;
+    if (sub == 1) {
+        const size_t idx = (size_t)blockIdx.x * kGThreads + tid, total = (size_t)B * segs * groups;
+        live = idx < total;
+        const size_t id = live ? idx : total - 1;
+        cg = (int)(id % groups); seg = (int)((id / groups) % segs); b = (int)(id / ((size_t)groups * segs));
+    } else {
+        const int cols = (groups + 63) / 64, per = kGThreads / 64 / sub, runs = (segs + per - 1) / per;
+        cg = (int)(blockIdx.x % cols) * 64 + (tid & 63);
+        seg = (int)((blockIdx.x / cols) % runs) * per + (tid >> 6) / sub;
+        b = (int)(blockIdx.x / ((size_t)cols * runs));
+        live = cg < groups && seg < segs;
+        cg = min(cg, groups - 1);
+        seg = min(seg, segs - 1);
+    }
     float wt[K][8];
 #pragma unroll
     for (int c = 0; c < 8; ++c)
 #pragma unroll
         for (int i = 0; i < K; ++i) wt[i][c] = w[(size_t)(8 * cg + c) * K + i];
-    const int t0 = seg * seg_len, t1 = min(T, t0 + seg_len);
+    const int t0 = seg * kSegMax + part_no * seg_len, t1 = min(T, t0 + seg_len);  // t0 >= T: nothing to do
     const size_t row0 = (size_t)b * T;
     float hist[K][8];  // hist[i] = x[t - (K-1) + i]
 #pragma unroll
     for (int i = 0; i < K - 1; ++i) {
         const int t = t0 - (K - 1) + i;
         if (t >= 0) {
-            ld8<BF16>(x, (row0 + t) * C + 8 * cg, hist[i + 1]);
+            ld8<BF16>(x, (row0 + min(t, T - 1)) * C + 8 * cg, hist[i + 1]);
         } else {
 #pragma unroll
             for (int c = 0; c < 8; ++c) hist[i + 1][c] = 0.f;
@@ -324,7 +340,24 @@ __global__ __launch_bounds__(kGThreads) void sla_feature_map_bwd_kernel(const vo
         if (n >= U) fetch(n % U, t0 + seg_len + n);
         token(t0 + seg_len + n, std::false_type{}, xr[n % U], gr[n % U]);
     }
-    if (live) {
+    if (sub > 1) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+#pragma unroll
+            for (int i = 0; i < K; ++i) red[c * K + i][tid] = t0 < T ? dwacc[i][c] : 0.f;
+        __syncthreads();
+        if (part_no == 0) {
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+#pragma unroll
+                for (int i = 0; i < K; ++i) {
+                    float sum = red[c * K + i][tid];
+                    for (int n = 1; n < sub; ++n) sum += red[c * K + i][tid + n * 64];
+                    dwacc[i][c] = sum;
+                }
+        }
+    }
+    if (live && part_no == 0) {
         float* p = part + ((size_t)(b * segs + seg) * C + 8 * cg) * K;
 #pragma unroll
         for (int c = 0; c < 8; ++c)
@@ -454,31 +487,21 @@ int sum_partials(const float* part, float* out, size_t stride, int nparts, hipSt
 // Tokens per thread.  64 while that leaves two wavefronts per SIMD (131072 threads): a segment re-reads the K-1 tokens
 // before it, and the backward also recomputes the K-1 tokens after it.  With fewer, a thread's walk is a serial chain
 // of about 0.3 us (backward 0.65 us) a token whatever else the chip does, so it is cut: B=4 T=777 640 channels, forward
-// 24.9 -> 9.6 us, backward 46.6 -> 20.0 us, 64 against 16.  `least`: the shortest the caller allows.
-int segment_length(int B, int T, int C, int least) {
+// 24.9 -> 9.6 us, backward 46.6 -> 22.4 us, 64 against 16.
+int segment_length(int B, int T, int C) {
     int seg = kSegMax;
-    while (seg > least && (size_t)B * ((T + seg - 1) / seg) * (C / 8) < 131072) seg /= 2;
+    while (seg > kSegMin && (size_t)B * ((T + seg - 1) / seg) * (C / 8) < 131072) seg /= 2;
     return seg;
-}
-
-// The backward's shortest segment: a bound on the partial sums of dw (which the workspace holds) that does not depend
-// on the channels: long batches have wavefronts enough with segments of 64 at any usual width.
-int backward_least(int B, int T) {
-    const size_t rows = (size_t)B * T;
-    return rows >= 131072 ? kSegMax : rows >= 32768 ? 32 : kSegMin;
 }
 
 }  // namespace
 
-// Partial sums of dw the workspace has room for: one per batch row and segment of the shortest length.
-size_t feature_map_partials(int B, int T) {
-    const int least = backward_least(B, T);
-    return (size_t)B * ((T + least - 1) / least);
-}
+// Partial sums of dw: one per batch row and 64 tokens.
+size_t feature_map_partials(int B, int T) { return (size_t)B * ((T + kSegMax - 1) / kSegMax); }
 
 int launch_feature_map(int dtype, int B, int T, int C, int taps, int head_width, float eps, const void* x, const float* w,
                        void* y, hipStream_t stream) {
-    const int seg = segment_length(B, T, C, kSegMin);
+    const int seg = segment_length(B, T, C);
     const size_t threads = (size_t)B * ((T + seg - 1) / seg) * (C / 8);
     const dim3 grid((unsigned)((threads + kGThreads - 1) / kGThreads));
     if (dtype == SLA_BF16)
@@ -497,9 +520,12 @@ int launch_short_conv_silu(int dtype, int B, int T, int C, int taps, const void*
 int launch_feature_map_backward(int dtype, int B, int T, int C, int taps, int head_width, float eps, const void* x,
                                 const float* w, const void* dy, void* dx, float* dw, float* workspace,
                                 hipStream_t stream) {
-    const int seg = segment_length(B, T, C, backward_least(B, T));
-    const size_t nparts = (size_t)B * ((T + seg - 1) / seg), threads = nparts * (C / 8);
-    const dim3 grid((unsigned)((threads + kGThreads - 1) / kGThreads));
+    const int seg = segment_length(B, T, C), sub = kSegMax / seg, per = kGThreads / 64 / sub;
+    const size_t segs = (T + kSegMax - 1) / kSegMax, nparts = feature_map_partials(B, T), groups = (size_t)C / 8;
+    // see the kernel: threads over (row, segment, channels), or waves over parts of segments and 64 x 8 channels
+    const size_t blocks = sub == 1 ? (nparts * groups + kGThreads - 1) / kGThreads
+                                   : B * ((segs + per - 1) / per) * ((groups + 63) / 64);
+    const dim3 grid((unsigned)blocks);
     const int rc = dtype == SLA_BF16 ? feature_map_taps<true>(taps, head_width / 8, true, grid, stream, x, w, dy, dx,
                                                               workspace, B, T, C, seg, eps)
                                      : feature_map_taps<false>(taps, head_width / 8, true, grid, stream, x, w, dy, dx,

@@ -117,7 +117,7 @@ def test_feature_map_segment_lengths_agree(C):
 
     import paper_2602_01744_amd as sla
 
-    B, T = 40, 1090
+    B, T = 40, 1160  # 19 segments of 64 tokens, the last of 8
     gen = torch.Generator(device="cuda").manual_seed(3300 + C)
     x, dy = (torch.randn(B, T, C, generator=gen, device="cuda").bfloat16() for _ in range(2))
     w = torch.randn(C, 4, generator=gen, device="cuda") * 0.5
