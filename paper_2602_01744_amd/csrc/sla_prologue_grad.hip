@@ -8,9 +8,10 @@
 //
 // All of it streams, but the feature map is bound by the vector pipes as much as by memory: about 130 (backward 265)
 // instructions per eight channels and token.  Hence U tokens' loads in flight, whose registers are reloaded where they
-// are read, shifts of the window by unrolling instead of moves, and the reciprocal in sigmoidf().  bf16, B=8 T=4096
-// 2048 channels: forward with L2 65 -> 58 us (268 MB, 4.6 TB/s), without 55 -> 44 us, backward 125 -> 102 us (402 MB,
-// 3.9 TB/s; 227 registers: two wavefronts per SIMD).  The device's own copy of the same tensor takes 37 us.
+// are read, shifts of the window by unrolling instead of moves, and the short division of sigmoid8().  bf16, B=8 T=4096
+// 2048 channels, one call after another on the same tensors, without these -> with them (with, but IEEE divisions):
+// forward with L2 65 -> 49 us (61; 268 MB), without 58 -> 50 us (56), backward 122 -> 90 us (103; 402 MB, 231 registers:
+// two wavefronts per SIMD).
 //
 // A thread owns eight adjacent channels (16 bytes of a token row), a wave covers 1 KB of every
 // row it touches.  Sums over tokens (dW, dw) are taken in two deterministic stages: every thread leaves the sum
@@ -96,12 +97,26 @@ __device__ __forceinline__ float head_allsum(float s) {
     return s;
 }
 
-// 1 / (1 + e^-s): the hardware reciprocal with one Newton step, 7 instructions where the IEEE division alone takes 10.
-// An infinite e^-s makes the step 0 * inf; fmaxf drops that NaN, and the result is the 0 it should be.  (A NaN s gives
-// 0 here; every use multiplies by s.)
-__device__ __forceinline__ float sigmoidf(float s) {
-    const float d = 1.f + __builtin_amdgcn_exp2f(-s * kLog2e), r = __builtin_amdgcn_rcpf(d);
-    return fmaxf(__builtin_fmaf(__builtin_fmaf(-d, r, 1.f), r, r), 0.f);
+// o = 1 / d, or with QUOTIENT s / d, d = 1 + e^-s: the IEEE divisions, bit for bit, at half their instructions.  The
+// hardware reciprocal with one Newton step is 1 / d correctly rounded for every s > -87, and one more residual makes
+// s times it s / d correctly rounded for every finite one of those, -0 included (all 2^32 values of s compared).  Left
+// out are s below, where 1 / d comes near the subnormals, and s = inf, whose residual is NaN: a group that holds one
+// takes the divisions themselves.
+template <bool QUOTIENT>
+__device__ __forceinline__ void sigmoid8(const float (&s)[8], float (&o)[8]) {
+    float lo = s[0], hi = s[0];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        const float d = 1.f + __builtin_amdgcn_exp2f(-s[c] * kLog2e), x = __builtin_amdgcn_rcpf(d);
+        const float r = __builtin_fmaf(__builtin_fmaf(-d, x, 1.f), x, x), q = s[c] * r;
+        o[c] = QUOTIENT ? __builtin_fmaf(-__builtin_fmaf(d, q, -s[c]), r, q) : r;
+        lo = fminf(lo, s[c]);
+        hi = fmaxf(hi, s[c]);
+    }
+    if (__builtin_expect(!(lo > -87.f) || (QUOTIENT && !(hi < INFINITY)), 0)) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c) o[c] = (QUOTIENT ? s[c] : 1.f) / (1.f + __builtin_amdgcn_exp2f(-s[c] * kLog2e));
+    }
 }
 
 // Eight adjacent elements as loaded: a load in flight keeps four registers (bf16; fp32: eight) until it is used.
@@ -178,13 +193,17 @@ __global__ __launch_bounds__(kGThreads) void sla_feature_map_kernel(const void* 
                 for (int c = 0; c < 8; ++c) hist[i][c] = hist[i + 1][c];
             in[u].get(hist[K - 1]);
             in[u].load(x, (row0 + min(tb + U + u, T - 1)) * C + 8 * cg);
-            float out[8], ss = 0.f;
+            float s[8], out[8], ss = 0.f;
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
-                float s = 0.f;
+                s[c] = 0.f;
 #pragma unroll
-                for (int i = 0; i < K; ++i) s += wt[i][c] * hist[i][c];
-                out[c] = s * sigmoidf(s);
+                for (int i = 0; i < K; ++i) s[c] += wt[i][c] * hist[i][c];
+            }
+            sigmoid8<LPH == 0>(s, out);
+#pragma unroll
+            for (int c = 0; c < 8; ++c) {
+                if constexpr (LPH > 0) out[c] *= s[c];
                 ss += out[c] * out[c];
             }
             if constexpr (LPH > 0) {
@@ -276,8 +295,11 @@ __global__ __launch_bounds__(kGThreads) void sla_feature_map_bwd_kernel(const vo
 #pragma unroll
             for (int i = 0; i < K; ++i) acc += wt[i][c] * hist[i][c];
             s[c] = acc;
-            sg[c] = sigmoidf(acc);
-            a[c] = acc * sg[c];
+        }
+        sigmoid8<false>(s, sg);
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            a[c] = s[c] * sg[c];
             ss += a[c] * a[c];
             ag += a[c] * g[c];
         }

@@ -145,3 +145,49 @@ def test_feature_map_saturates():
     dx, _ = sla.short_conv_silu_l2_backward(x, w, dy)
     assert torch.equal(dx[..., :6], torch.where(x > 0, dy, torch.zeros_like(x))[..., :6])
     assert torch.equal(dx[..., 6:], torch.ones_like(dx[..., 6:]))
+
+
+def test_silu_is_a_correctly_rounded_division():
+    """silu(s) = s / (1 + e^-s) with one rounding of the quotient.  Where s * log2(e) rounds to a whole number n the
+    hardware's power of two is exact and so is 1 + 2^-n for |n| <= 23, which leaves the division as the only rounding:
+    equality with numpy's.  Where 1 / (1 + e^-s) is subnormal the quotient is not: 88 units of fp32 rounding in the
+    exponent, e^-s off by 88 * 2^-23 at most."""
+    import torch
+
+    import paper_2602_01744_amd as sla
+
+    log2e, s, want = np.float32(1.4426950408889634), [], []
+    for n in range(-23, 24):
+        near = np.float32(n / 1.4426950408889634)
+        for x in {near, np.nextafter(near, np.float32(-99)), np.nextafter(near, np.float32(99))}:
+            if np.float32(x * log2e) == n:
+                s.append(x)
+                want.append(np.float32(x) / np.float32(1.0 + 2.0**-n))
+    s, want = np.array(s, np.float32), np.array(want, np.float32)
+    assert len(s) >= 47
+    one = lambda a: torch.from_numpy(np.resize(a, -(-len(a) // 8) * 8)).cuda().view(1, -1, 8)
+    w = torch.ones(8, 1, device="cuda")
+    assert torch.equal(sla.short_conv_silu(one(s), w), one(want))
+    s = np.linspace(-88.6, -87.4, 64).astype(np.float32)
+    got = sla.short_conv_silu(one(s), w).cpu().double().numpy().ravel()
+    exact = s.astype(np.float64) / (1.0 + np.exp(-s.astype(np.float64)))
+    assert np.abs(got / exact - 1.0).max() <= 88 * 2.0**-23 + 2.0**-22
+
+
+def test_short_division_equals_the_division():
+    """A group of eight values with one below -87 takes the compiler's divisions, any other the short form: the same
+    values with and without such a neighbour, bit for bit (every 509th bit pattern, infinities and both zeros)."""
+    import torch
+
+    import paper_2602_01744_amd as sla
+
+    bits = torch.arange(-(1 << 31), 1 << 31, 509, dtype=torch.int64, device="cuda")
+    bits = torch.cat([bits, torch.tensor([0, -(1 << 31), 0x7F800000], device="cuda")]).to(torch.int32)
+    x = bits[len(bits) % 7 :].view(torch.float32).view(-1, 7)
+    w = torch.ones(8, 1, device="cuda")
+    run = lambda first: torch.cat([torch.full_like(x[:, :1], first), x], 1).view(1, -1, 8).contiguous()
+    for f in (lambda z: sla.short_conv_silu(z, w),
+              lambda z: sla.short_conv_silu_l2_backward(z, w, torch.ones_like(z))[0]):
+        a, b = (f(run(first))[0, :, 1:] for first in (1.0, -90.0))
+        differ = a.contiguous().view(torch.int32) != b.contiguous().view(torch.int32)
+        assert int((differ & ~(torch.isnan(a) & torch.isnan(b))).sum()) == 0
