@@ -131,10 +131,14 @@ def _p(x) -> Optional[int]:
 
 
 def _stream(t) -> int:
-    """The current stream of the tensor's device, as the hipStream_t handle (no Stream object is made for it)."""
+    """The current stream of the tensor's device, as the hipStream_t handle (no Stream object is made for it).  Refuses a
+    tensor in host memory, whose device index -1 would otherwise mean the current GPU."""
     import torch
 
-    return torch._C._cuda_getCurrentRawStream(t.get_device())
+    device = t.get_device()
+    if device < 0:
+        raise ValueError(f"expected a tensor on a GPU, but got one on: {t.device}")
+    return torch._C._cuda_getCurrentRawStream(device)
 
 
 def sla_status_string(status: int) -> str:

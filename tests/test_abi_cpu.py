@@ -417,3 +417,29 @@ def test_prologue_gradient_entry_points_validate(lib):
     assert gl(p, A, A, 0, A, A, A, n, 0) == -1
     assert gl(_ok_params(dk=48), A, A, A, A, A, A, n, 0) == -3
     assert gl(_ok_params(B=0), 0, 0, 0, 0, 0, 0, 0, 0) == 0
+
+
+@pytest.mark.parametrize("call", ["decode_step", "decode_step_fused", "short_conv_silu_l2_backward", "gate_logits_backward"])
+def test_host_tensors_are_refused_before_the_library_is_called(lib, monkeypatch, call):
+    """Entry points without a check of their own rely on the stream's: a host tensor's device index, -1, must not pass as
+    "the current device", or a kernel would be handed host addresses.  The library's calls are stubs here."""
+    import torch
+
+    from paper_2602_01744_amd import binding
+
+    class Stub:
+        def __getattr__(self, name):
+            return lambda *a: 64 if name.endswith("_bytes") else pytest.fail(f"{name} was called")
+
+    monkeypatch.setattr(binding, "load_library", lambda: Stub())
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda index: 0, raising=False)
+    x, w, state = torch.zeros(1, 2, 64), torch.zeros(2, 64), torch.zeros(1, 2, 64, 64)
+    with pytest.raises((ValueError, AssertionError)):
+        if call == "decode_step":
+            binding.decode_step(sla.RETNET, x, x, x, x[..., 0].contiguous(), None, w[:, 0].contiguous(), None, state)
+        elif call == "decode_step_fused":
+            binding.decode_step(sla.RETNET, x, x, x, None, None, w[:, 0].contiguous(), None, state, w_gq=w)
+        elif call == "short_conv_silu_l2_backward":
+            binding.short_conv_silu_l2_backward(x, torch.zeros(64, 4), x)
+        else:
+            binding.gate_logits_backward(state, w, x[..., 0], state)
