@@ -9,20 +9,28 @@
 // state stays in registers between the read and the write -- also for the delta rule, whose write depends on a
 // reduction (k S) over the whole slice.  Sums over rows meet by shuffles inside a wave and through LDS between the four
 // waves.  The slices of a head run on one XCD.
-// Slice width: 64 columns (8 state rows per thread at dk = 128).  32 while 64 give at most 256 workgroups: the call is
-// then one round of loads and stores whose length is the rows per thread (64 / 32 columns, us: B=1 H=4 128 x 256 fused
-// 3.8 / 3.7, B=4 H=16 128 x 128 5.0 / 4.9); from there on 32 pays for twice the q, k, decay and gate loads (B=32 H=32
-// 64 x 64 fused 9.2 / 11.2), and 128 and more have fewer wavefronts per compute unit (B=64 H=16 128 x 256 49.9 / 52.4).
+// Slice width: 64 columns (8 state rows per thread at dk = 128).  32 while 64 give at most 2 dk workgroups: the call is
+// then one round of loads and stores whose length is the rows per thread (64 / 32 columns, us: B=2 H=64 128 x 64
+// 3.8 / 3.5, B=2 H=32 64 x 64 3.1 / 3.0, but B=8 H=32 64 x 64 3.5 / 3.6); from there on 32 pays for twice the q, k, decay
+// and gate loads, and 128 and more have fewer wavefronts per compute unit (B=64 H=16 128 x 256 49.9 / 52.4).
+// With the projection fused every slice forms all H logits again, so 32 end at dk workgroups (B=8 H=16 128 x 128
+// 5.1 / 5.3; B=16 H=16 32 x 64 3.6 / 3.9), and past 256 slices are eight state rows per thread wide (against 64 columns,
+// GLA: B=64 H=64 32 x 256 48 -> 42, B=8 H=64 64 x 128 8.4 -> 8.1, B=8 H=64 32 x 256 9.3 -> 7.2), for GLA sixteen
+// beyond 32 heads and 512 workgroups (B=16 H=48 128 x 128 20.1 -> 17.2, B=4 H=64 128 x 256 12.8 -> 11.8; B=4 H=64 128 x 128
+// 8.3 -> 8.8; the delta rule, whose k S waits for the whole slice, B=16 H=64 128 x 128 26.9 -> 28.7).
 // Kernel time in us against one workgroup per (batch, head) and the gates' loads behind the state's, the earlier form
 // (bf16, graph of 48 steps; "far": over several states, so that they come from HBM, "near": one state, which the
 // memory-side cache holds):
-//     B  H  dk x dv                      near           far
-//     1  4  128 x 256 GLA, fused      6.2 ->  3.7
-//     1  16 128 x 128 delta rule      4.8 ->  3.8
-//     64 16 128 x 128 delta rule     23.0 -> 21.6   30.9 -> 28.1 (4.8 TB/s)
-//     64 16 128 x 128 GLA, fused     21.8 -> 22.4   29.8 -> 29.2
-//     64 16 128 x 256 delta rule     50.2 -> 41.0   64.0 -> 51.7 (5.2 TB/s)
-//     256 32 32 x 64  GLA            23.2 -> 22.4   28.4 -> 26.2
+//     B   H  dk x dv                      near           far
+//     1   4  128 x 256 GLA, fused      6.2 ->  3.6
+//     8   16 128 x 128 GLA             5.4 ->  4.5    6.4 ->  4.8
+//     32  16 128 x 128 GLA             9.5 ->  8.9   16.2 -> 15.8
+//     64  16 128 x 128 delta rule     23.0 -> 21.7   30.9 -> 28.2 (4.8 TB/s)
+//     64  16 128 x 128 GLA, fused     21.7 -> 22.4   29.7 -> 29.3
+//     64  16 128 x 256 GLA            48.9 -> 40.7   61.8 -> 50.3 (5.3 TB/s)
+//     16  64 128 x 256 GLA, fused     57.4 -> 48.1   68.8 -> 63.1
+//     64  64 32 x 256  GLA, fused     41.1 -> 41.5   53.0 -> 51.4
+//     256 32 32 x 64   GLA            23.2 -> 22.4   28.3 -> 26.1
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -113,8 +121,15 @@ __device__ __forceinline__ float wave_rows_sum(float x) {
     return x;
 }
 
+// Which form of the gates an instantiation holds.  kLogits is the plain step alone, five workgroups of dk = 128 to a
+// compute unit (B=32 H=16 128 x 128 GLA 10.3 / 17.2 -> 9.1 / 15.9 us, near / far; B=32 H=64 64 x 64 10.9 / 15.8 -> 9.3 / 15.2).
+// kEither decides at run time, and the projection's registers leave three workgroups: the better where the state
+// overflows the caches anyway, and the plain step's choice from 60 MB on (B=64 H=16 128 x 128 GLA 21.4 / 28.1 us,
+// 22.1 / 27.7 by kLogits; 128 x 256 40.6 / 50.3 and 41.7 / 51.8).
+enum Gates { kLogits, kProjected, kEither };
+
 // One workgroup: `DS` adjacent value columns (slice blockIdx.x % slices) of one (batch, head).
-template <bool BF16, int VAR, int DK, int DS>
+template <bool BF16, int VAR, int DK, int DS, Gates GATES>
 __global__ __launch_bounds__(kDecThreads) void sla_decode_kernel(const DArgs a) {
     constexpr int NC4 = DS / 4;             // threads along a row of the slice
     constexpr int NRG = kDecThreads / NC4;  // row groups
@@ -131,8 +146,37 @@ __global__ __launch_bounds__(kDecThreads) void sla_decode_kernel(const DArgs a) 
     if (bh >= a.B * a.H) return;
     const int c4 = tid % NC4, rg = tid / NC4, row4 = a.dv / 4;
 
+    const bool fused = GATES == kProjected || (GATES == kEither && a.wq);
+    d_f32x4* srow = (d_f32x4*)(a.state + (size_t)bh * DK * a.dv + slice * DS) + c4;
+    float qd[RPT], kd[RPT], ad[RPT], v4[4], ld_scalar = 0.f, bt = 0.f;
+    d_f32x4 S[RPT];
+    auto load_vectors = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) {
+            const size_t d = (size_t)bh * DK + rg + NRG * i;
+            qd[i] = load_elem<BF16>(a.q, d);
+            kd[i] = load_elem<BF16>(a.k, d);
+            if constexpr (VAR == SLA_GLA) ad[i] = load_elem<BF16>(a.ld, d);
+        }
+        load_run<BF16, 4>(a.v, (size_t)bh * a.dv + slice * DS + 4 * c4, v4);
+        if constexpr (VAR == SLA_RETNET) ld_scalar = ((const float*)a.ld)[h];
+        if constexpr (VAR == SLA_GDN) {
+            ld_scalar = ((const float*)a.ld)[bh];
+            bt = a.beta[bh];
+        }
+    };
+    auto load_state = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < RPT; ++i) S[i] = srow[(size_t)(rg + NRG * i) * row4];
+    };
+
     // Loads come back in the order they were issued, so what the gates are made of goes first: they are then formed
-    // while the state tile and the token's vectors, all issued before anything waits, are still on their way.
+    // while the state tile and the token's vectors, all issued before anything waits, are still on their way.  kProjected
+    // asks for the state first and for the vectors behind the projection, whose registers they then take: four workgroups
+    // to a compute unit instead of three.  It is chosen where the state fits the caches (GLA, near: B=32 H=64 64 x 64
+    // 16.8 -> 15.4 us, B=100 H=8 128 x 64 10.1 -> 8.3; delta rule, far: B=24 H=16 128 x 256 24.5 -> 22.7), and for GLA
+    // where the projection takes more than the one round of loads that goes out ahead of the state, beyond 16 heads
+    // (B=16 H=64 128 x 256 53.4 -> 48.1, B=256 H=4 128 x 128 22.6 -> 22.0 near, 28.9 -> 29.7 far).
     constexpr int TPH = DK >= 64 ? 16 : 8, EPT = DK / TPH;  // fused projection: threads per head, elements per thread
     const int sub = tid % TPH;
     int h2 = tid / TPH;
@@ -146,33 +190,19 @@ __global__ __launch_bounds__(kDecThreads) void sla_decode_kernel(const DArgs a) 
             load_run<false, EPT>(a.wk, wat, wk);
         }
     };
-    if (a.wq) {
+    if constexpr (GATES == kProjected) load_state();
+    if (fused) {
         if (h2 < a.H) load_projection();
     } else if (lane < a.H) {
         lq = a.ql[(size_t)b * a.H + lane];
         if (a.kl) lk = a.kl[(size_t)b * a.H + lane];
     }
-    d_f32x4* srow = (d_f32x4*)(a.state + (size_t)bh * DK * a.dv + slice * DS) + c4;
-    float qd[RPT], kd[RPT], ad[RPT];
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) {
-        const size_t d = (size_t)bh * DK + rg + NRG * i;
-        qd[i] = load_elem<BF16>(a.q, d);
-        kd[i] = load_elem<BF16>(a.k, d);
-        if constexpr (VAR == SLA_GLA) ad[i] = load_elem<BF16>(a.ld, d);
+    if constexpr (GATES != kProjected) {
+        load_vectors();
+        load_state();
     }
-    float v4[4], ld_scalar = 0.f, bt = 0.f;
-    load_run<BF16, 4>(a.v, (size_t)bh * a.dv + slice * DS + 4 * c4, v4);
-    if constexpr (VAR == SLA_RETNET) ld_scalar = ((const float*)a.ld)[h];
-    if constexpr (VAR == SLA_GDN) {
-        ld_scalar = ((const float*)a.ld)[bh];
-        bt = a.beta[bh];
-    }
-    d_f32x4 S[RPT];
-#pragma unroll
-    for (int i = 0; i < RPT; ++i) S[i] = srow[(size_t)(rg + NRG * i) * row4];
 
-    if (a.wq) {
+    if (fused) {
         // Fused gate projection (Eq. 4 needs the logits of every head of the token): TPH threads per head (16; 8 for
         // dk = 32), each thread DK/TPH >= 4 adjacent elements of q[b,h',:] . W_GQ[:,h'] and k[b,h',:] . W_GK[:,h'],
         // summed over the TPH threads with shuffles -- 2 H dk multiply-adds against the dk dv of the state update, and
@@ -203,8 +233,9 @@ __global__ __launch_bounds__(kDecThreads) void sla_decode_kernel(const DArgs a) 
             lk = lg[1][lane];
         }
     }
+    if constexpr (GATES == kProjected) load_vectors();
     const float gq = decode_gate(lq, a.H, h, lane);
-    const float gk = a.wk || a.kl ? decode_gate(lk, a.H, h, lane) : 1.f;
+    const float gk = (fused ? (const void*)a.wk : (const void*)a.kl) ? decode_gate(lk, a.H, h, lane) : 1.f;
 
     const float a_scalar = dec_exp(ld_scalar);
     // Sec. 5.1: the write.  RetNet / GLA: S <- a S + (G^K k)^T v.  Delta rule: Sb = a S, u = beta (G^K v - k Sb),
@@ -270,15 +301,52 @@ __global__ __launch_bounds__(kDecThreads) void sla_decode_kernel(const DArgs a) 
     }
 }
 
+// The whole state below 60 MB, well inside the caches' capacity: see Gates.
+template <int DK>
+bool small_state(const DArgs& a) {
+    return (size_t)a.B * a.H * DK * a.dv * 4 < (size_t)60 << 20;
+}
+
+// Value columns per workgroup (the figures are in the file header).
+template <int VAR, int DK>
+int slice_width(const DArgs& a) {
+    const size_t heads = (size_t)a.B * a.H, narrow = heads * (a.dv / 64);  // workgroups at 64 columns
+    int ds = 64;
+    if (narrow <= (a.wq ? 1 : 2) * (size_t)DK) {
+        ds = 32;
+    } else if (a.wq && narrow > 256) {  // every slice repeats the projection: eight state rows per thread, or sixteen
+        ds = 8192 / DK;
+        if (narrow > 512 && ds < 128 && (small_state<DK>(a) || (VAR == SLA_GLA && a.H > 32))) ds = 128;
+    }
+    if (ds > a.dv) ds = a.dv;
+    if ((heads + 7) / 8 * 8 * (a.dv / ds) * kDecThreads > 0xffffffffu) ds = a.dv;  // a launch holds fewer than 2^32 threads
+    return ds;
+}
+
+template <bool BF16, int VAR, int DK, int DS>
+void launch_width(const DArgs& a, hipStream_t stream) {
+    const dim3 grid((unsigned)(((size_t)a.B * a.H + 7) / 8 * 8 * (a.dv / DS))), block(kDecThreads);
+    const bool small = small_state<DK>(a);
+    if (a.wq && (small || (VAR == SLA_GLA && a.H > 16))) {
+        hipLaunchKernelGGL((sla_decode_kernel<BF16, VAR, DK, DS, kProjected>), grid, block, 0, stream, a);
+        return;
+    }
+    if constexpr (DS <= 64) {
+        if (!a.wq && small) {
+            hipLaunchKernelGGL((sla_decode_kernel<BF16, VAR, DK, DS, kLogits>), grid, block, 0, stream, a);
+            return;
+        }
+    }
+    hipLaunchKernelGGL((sla_decode_kernel<BF16, VAR, DK, DS, kEither>), grid, block, 0, stream, a);
+}
+
 template <bool BF16, int VAR, int DK>
 int launch_dv(const DArgs& a, hipStream_t stream) {
-    // 64-column slices; 32-column ones while 64 give at most one workgroup per compute unit (see the file header)
-    const size_t wide = (size_t)a.B * a.H * (a.dv / 64);
-    const int ds = wide <= 256 ? 32 : 64;
-    const dim3 grid((unsigned)(((size_t)a.B * a.H + 7) / 8 * 8 * (a.dv / ds))), block(kDecThreads);
-    switch (ds) {
-        case 32: hipLaunchKernelGGL((sla_decode_kernel<BF16, VAR, DK, 32>), grid, block, 0, stream, a); break;
-        case 64: hipLaunchKernelGGL((sla_decode_kernel<BF16, VAR, DK, 64>), grid, block, 0, stream, a); break;
+    switch (slice_width<VAR, DK>(a)) {
+        case 32: launch_width<BF16, VAR, DK, 32>(a, stream); break;
+        case 64: launch_width<BF16, VAR, DK, 64>(a, stream); break;
+        case 128: launch_width<BF16, VAR, DK, 128>(a, stream); break;
+        case 256: launch_width<BF16, VAR, DK, 256>(a, stream); break;
         default: return SLA_ERR_UNSUPPORTED;
     }
     return hipGetLastError() == hipSuccess ? SLA_OK : SLA_ERR_HIP;

@@ -167,3 +167,37 @@ def test_slice_widths(variant, B, H, dk, dv):
     o, f = decode_chain(variant, d, "bf16", s0)
     ro, rf = run_oracle(variant, d, s0)
     assert rel_err(o, ro) <= TOL["bf16"] and rel_err(f, rf) <= 1e-5
+
+
+@pytest.mark.parametrize("variant", VARIANTS)
+@pytest.mark.parametrize("B,H,dk,dv", [(32, 4, 128, 64), (43, 3, 128, 64), (16, 4, 64, 64), (13, 5, 64, 64), (5, 26, 32, 128),
+                                       (13, 5, 32, 256), (33, 4, 64, 128), (5, 33, 128, 128), (9, 33, 128, 128),
+                                       (60, 17, 128, 128), (21, 48, 128, 128)])
+def test_fused_slice_widths(variant, B, H, dk, dv):
+    """Both sides of the fused step's rules: dk and dk + 1 workgroups of 64 columns; past 256, slices of 128 and 256 for
+    narrow keys; past 512, 128 columns for a small state or (GLA) many heads; states past 60 MB."""
+    import torch
+    import paper_2602_01744_amd as sla
+    from oracle import sla_numpy
+
+    d = si.custom(variant, "bf16", B=B, T=1, H=H, dk=dk, dv=dv, seed=2800 + variant + B)
+    w = si.gate_weights(H, dk, seed=2801)
+    d["q_logits"], d["k_logits"] = sla_numpy.gate_logits(d["q"], w["w_gq"]), sla_numpy.gate_logits(d["k"], w["w_gk"])
+    s0 = si.initial_state(B, H, dk, dv, seed=28)
+    ro, rf = run_oracle(variant, d, s0)
+    state = torch.from_numpy(np.ascontiguousarray(s0, dtype=np.float32)).cuda()
+    q, k, v = (_dev(d[n][:, 0], "bf16", True) for n in ("q", "k", "v"))
+    ld = _dev(d["log_decay"] if variant == RETNET else d["log_decay"][:, 0], "bf16", variant == GLA)
+    beta = None if d["beta"] is None else _dev(d["beta"][:, 0], "bf16", False)
+    o = sla.decode_step(variant, q, k, v, None, None, ld, beta, state, w_gq=torch.from_numpy(w["w_gq"]).cuda(),
+                        w_gk=torch.from_numpy(w["w_gk"]).cuda())
+    eo = rel_err(o.float().cpu().numpy().astype(np.float64), ro[:, 0])
+    ef = rel_err(state.cpu().numpy().astype(np.float64), rf)
+    assert eo <= TOL["bf16"] and ef <= 1e-5
+
+
+@pytest.mark.parametrize("variant", VARIANTS)
+@pytest.mark.parametrize("B,H,dk,dv", [(16, 4, 32, 64), (13, 5, 32, 64), (32, 4, 64, 64), (43, 3, 64, 64)])
+def test_slice_widths_of_narrow_keys(variant, B, H, dk, dv):
+    """2 dk workgroups of 64 columns and one more."""
+    test_slice_widths(variant, B, H, dk, dv)
