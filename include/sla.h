@@ -167,7 +167,8 @@ int sla_forward_static(const sla_params* p, const void* q, const void* k, const 
  *   log_decay       RetNet: fp32 [H];  GLA: dtype [B,H,dk];  GDN: fp32 [B,H]
  *   beta            GDN: fp32 [B,H]; NULL otherwise
  *   state           [B,H,dk,dv] fp32    read and overwritten with the state after the token; required
- *   out             [B,H,dv]    dtype   written
+ *   out             [B,H,dv]    dtype   written.  May lie on v, or with dv == dk on q, k or the GLA log_decay (the same
+ *                               address: a head's row is written after all of that head has been read); on nothing else.
  */
 int sla_decode_step(const sla_params* p, const void* q, const void* k, const void* v,
                     const float* q_head_logits, const float* k_head_logits,
@@ -183,7 +184,8 @@ int sla_decode_step(const sla_params* p, const void* q, const void* k, const voi
  *
  *   w_gq   [H,dk] fp32   device, read only: row h is column h of the paper's matrix; required
  *   w_gk   [H,dk] fp32   or NULL (G^K = 1)
- * Everything else as sla_decode_step.
+ * Everything else as sla_decode_step, but that every head's q and k are read for every head: out may lie on v or the GLA
+ * log_decay only.
  */
 int sla_decode_step_fused(const sla_params* p, const void* q, const void* k, const void* v,
                           const float* w_gq, const float* w_gk,

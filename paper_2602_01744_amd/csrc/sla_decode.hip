@@ -309,7 +309,7 @@ bool small_state(const DArgs& a) {
 
 // Value columns per workgroup (the figures are in the file header).
 template <int VAR, int DK>
-int slice_width(const DArgs& a) {
+int slice_width(const DArgs& a, bool overlap) {
     const size_t heads = (size_t)a.B * a.H, narrow = heads * (a.dv / 64);  // workgroups at 64 columns
     int ds = 64;
     if (narrow <= (a.wq ? 1 : 2) * (size_t)DK) {
@@ -319,7 +319,9 @@ int slice_width(const DArgs& a) {
         if (narrow > 512 && ds < 128 && (small_state<DK>(a) || (VAR == SLA_GLA && a.H > 32))) ds = 128;
     }
     if (ds > a.dv) ds = a.dv;
-    if ((heads + 7) / 8 * 8 * (a.dv / ds) * kDecThreads > 0xffffffffu) ds = a.dv;  // a launch holds fewer than 2^32 threads
+    // One workgroup per head reads all of the head's inputs before it writes any of its out, so that out may lie on them;
+    // and a launch holds fewer than 2^32 threads.
+    if (overlap || (heads + 7) / 8 * 8 * (a.dv / ds) * kDecThreads > 0xffffffffu) ds = a.dv;
     return ds;
 }
 
@@ -342,7 +344,15 @@ void launch_width(const DArgs& a, hipStream_t stream) {
 
 template <bool BF16, int VAR, int DK>
 int launch_dv(const DArgs& a, hipStream_t stream) {
-    switch (slice_width<VAR, DK>(a)) {
+    const size_t es = BF16 ? 2 : 4, heads = (size_t)a.B * a.H;
+    auto on_out = [&](const void* x, size_t bytes) {
+        const uintptr_t o = (uintptr_t)a.out, i = (uintptr_t)x;
+        return x && o < i + bytes && i < o + heads * a.dv * es;
+    };
+    const bool overlap = on_out(a.q, heads * DK * es) || on_out(a.k, heads * DK * es) || on_out(a.v, heads * a.dv * es) ||
+                         (VAR == SLA_GLA && on_out(a.ld, heads * DK * es)) ||
+                         (VAR == SLA_GDN && (on_out(a.ld, heads * 4) || on_out(a.beta, heads * 4)));
+    switch (slice_width<VAR, DK>(a, overlap)) {
         case 32: launch_width<BF16, VAR, DK, 32>(a, stream); break;
         case 64: launch_width<BF16, VAR, DK, 64>(a, stream); break;
         case 128: launch_width<BF16, VAR, DK, 128>(a, stream); break;

@@ -201,3 +201,34 @@ def test_fused_slice_widths(variant, B, H, dk, dv):
 def test_slice_widths_of_narrow_keys(variant, B, H, dk, dv):
     """2 dk workgroups of 64 columns and one more."""
     test_slice_widths(variant, B, H, dk, dv)
+
+
+@pytest.mark.parametrize("variant", VARIANTS)
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("B,H,d", [(2, 3, 64), (40, 16, 128)])
+def test_out_may_be_an_input(variant, fused, B, H, d):
+    """out in the memory of an input: one workgroup then owns a whole head, and reads all of it before it writes.  The
+    outputs agree with those in a tensor of their own up to the order of fp32 sums (a last bit of bf16, 2^-8)."""
+    import torch
+    import paper_2602_01744_amd as sla
+
+    x = si.custom(variant, "bf16", B=B, T=1, H=H, dk=d, dv=d, seed=2900 + variant)
+    s0 = torch.from_numpy(si.initial_state(B, H, d, d, seed=29).astype(np.float32)).cuda()
+    ql, kl = (_dev(x[n][:, 0], "bf16", False) for n in ("q_logits", "k_logits"))
+    w = torch.from_numpy(si.gate_weights(H, d, seed=29)["w_gq"]).cuda()
+
+    def step(alias):
+        t = {n: _dev(x[n][:, 0], "bf16", True) for n in ("q", "k", "v")}
+        t["log_decay"] = _dev(x["log_decay"] if variant == RETNET else x["log_decay"][:, 0], "bf16", variant == GLA)
+        beta = None if x["beta"] is None else _dev(x["beta"][:, 0], "bf16", False)
+        state = s0.clone()
+        gates = dict(w_gq=w, w_gk=w) if fused else {}
+        o = sla.decode_step(variant, t["q"], t["k"], t["v"], None if fused else ql, None if fused else kl, t["log_decay"], beta,
+                            state, out=t.get(alias), **gates)
+        return o.float(), state
+
+    want, ws = step(None)
+    for alias in ["v"] if fused else ["q", "k", "v"] + ["log_decay"] * (variant == GLA):
+        got, gs = step(alias)
+        assert float((got - want).norm() / want.norm()) <= 2.0**-8, alias
+        assert float((gs - ws).norm() / ws.norm()) <= 1e-6, alias
