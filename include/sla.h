@@ -74,8 +74,8 @@ typedef struct {
     int32_t B;       /* batch size            >= 0 */
     int32_t T;       /* tokens per sequence   >= 0 */
     int32_t H;       /* heads                 1..64 */
-    int32_t dk;      /* key/query head width  32, 64 or 128 (32: the backward passes run it zero-padded to 64, single
-                        pass only, with the padded copies in their workspace) */
+    int32_t dk;      /* key/query head width  32, 64 or 128 (32: the backward passes run it zero-padded to 64, with
+                        the padded copies in their workspace and no segments on request) */
     int32_t dv;      /* value head width      64, 128 or 256 */
     int32_t dv_split; /* 0 = let the library choose; else value columns per workgroup: 16, 32 or 64 (<= dv).
                         A scheduling knob only: results are bit-identical for every width
@@ -87,8 +87,8 @@ typedef struct {
                          from a zero entry state, a small kernel chains them through the segments' decays, the
                          main pass starts every segment from its entry state).  0 = the library chooses when a
                          workspace is given (1 when there are enough rows to fill the device); 1 = one fused
-                         pass.  The result is the same up to fp32 rounding of the chained states.  sla_backward
-                         cuts only on request (>= 2), see there. */
+                         pass.  The result is the same up to fp32 rounding of the chained states.  For
+                         sla_backward see there. */
 } sla_params;
 
 /*
@@ -197,13 +197,17 @@ int sla_decode_step_fused(const sla_params* p, const void* q, const void* k, con
  * scalar objective L = sum(out * d_out) + sum(final_state * d_final_state) it writes dL/d(input) for every
  * differentiable input of the forward call made with the same p, q, k, v, logits, log_decay and initial_state.
  * bf16 tensors run in block form on the matrix cores; fp32 tensors (p->dtype == SLA_F32) run token by token in fp32
- * vector arithmetic (gradients to fp32 rounding, any log_decay <= 0; p->segments >= 2 is SLA_ERR_UNSUPPORTED:
- * rectangular batches with few sequences are cut into segments by the library, and the workspace query counts that).  The delta rule has its own entry point, sla_backward_gdn.
- * p->dv_split is ignored.  p->segments >= 2 asks for the segment-parallel schedule (for batches with few sequences,
+ * vector arithmetic (gradients to fp32 rounding, any log_decay <= 0).  The delta rule has its own entry point,
+ * sla_backward_gdn.  p->dv_split is ignored.
+ * bf16 tensors: p->segments >= 2 asks for the segment-parallel schedule (for batches with few sequences,
  * as in sla_forward_ws): every batch row is cut into that many segments (of a multiple of 64 tokens, at least 256)
  * which run in parallel; the entry state and the end cotangent of every segment come from two pre-passes.  It needs
  * the [B,T,H,d] layout (p->flags == 0) and a larger workspace (sla_backward_workspace_bytes accounts for it); 0 and 1
- * run the single pass.
+ * run the single pass.  fp32 tensors: >= 2 is SLA_ERR_UNSUPPORTED; with 0 and 1 the library itself cuts rectangular
+ * batches with few sequences of more than 128 tokens into segments, if the workspace has the room that
+ * sla_backward_workspace_bytes asks for, and runs the single pass otherwise.  That room may be larger for a smaller B or T;
+ * the single pass takes what sla_backward_varlen_workspace_bytes says for the same B and p->T = B * T, which never grows as
+ * they shrink, so a workspace made for a larger call serves a smaller one, whichever of the two sizes it has.
  *
  *   q, k, v, q_head_logits, k_head_logits, log_decay, initial_state   as for sla_forward (device, read only)
  *   d_out            [B,T,H,dv]  dtype   cotangent of out; required
@@ -214,7 +218,8 @@ int sla_decode_step_fused(const sla_params* p, const void* q, const void* k, con
  *   dk_head_logits   [B,T,H]     fp32    written; required when k_head_logits is given, NULL otherwise
  *   dlog_decay       GLA: [B,T,H,dk] dtype, written, required;  RetNet: must be NULL (the decay is a constant)
  *   d_initial_state  [B,H,dk,dv] fp32    written, or NULL (not wanted)
- *   workspace        device memory of at least sla_backward_workspace_bytes(p) bytes, 16-byte aligned; holds
+ *   workspace        device memory of at least sla_backward_workspace_bytes(p) bytes (fp32 tensors: or the single
+ *                    pass's, see above), 16-byte aligned; holds
  *                    the gates, partial gate gradients and (GLA, bf16) block sums of q * dq and the state entering
  *                    every 512th token of a sequence (dlog_decay is re-derived from rowsum(dS * S) there, so its
  *                    error does not grow with the sequence length).  Contents on entry are ignored; calls that
@@ -229,7 +234,7 @@ int sla_backward(const sla_params* p, const void* q, const void* k, const void* 
                  void* dlog_decay, float* d_initial_state,
                  void* workspace, size_t workspace_bytes, void* stream);
 
-/* Bytes of workspace sla_backward needs for *p (0 when *p is not a shape it supports). */
+/* Bytes of workspace sla_backward wants for *p (0 when *p is not a shape it supports). */
 size_t sla_backward_workspace_bytes(const sla_params* p);
 
 /*
@@ -385,8 +390,8 @@ int sla_segments(const sla_params* p, int compute_units);
 /*
  * Number of segments to put into p->segments for sla_backward on a device with that many compute units (>= 1; 1 when
  * the single pass already gives every compute unit a workgroup, or for the delta rule); <0 on error.  The narrowest
- * of the three sweeps runs B * H * min(dk, dv) / 64 workgroups per segment.  sla_backward itself never chooses:
- * its workspace size must not depend on the device.
+ * of the three sweeps runs B * H * min(dk, dv) / 64 workgroups per segment.  sla_backward itself does not
+ * choose for bf16 tensors; 1 for fp32 tensors, where it does.
  */
 int sla_backward_segments(const sla_params* p, int compute_units);
 

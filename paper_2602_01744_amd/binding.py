@@ -493,12 +493,12 @@ def sla_backward(params, q, k, v, q_head_logits, k_head_logits, log_decay, initi
 def backward(variant: int, q, k, v, q_head_logits, k_head_logits, log_decay, d_out, initial_state=None,
              d_final_state=None, *, want_d_initial_state: bool = False, workspace=None, head_major: bool = False,
              segments: int = 1):
-    """Gradients of ``forward`` (RetNet, GLA; bfloat16, or float32 in the single pass) on the current CUDA(HIP) device
-    and stream.  Returns a dict
-    of new tensors: dq, dk, dv, dq_head_logits, dk_head_logits (None without k_head_logits), dlog_decay (GLA only,
-    else None) and d_initial_state (None unless asked for).  ``segments`` >= 2 cuts every batch row into that many
-    segments that run in parallel (for batches with few sequences); 0 asks ``sla_backward_segments`` for the count
-    that fills this device."""
+    """Gradients of ``forward`` (RetNet, GLA; bfloat16 or float32) on the current CUDA(HIP) device and stream.  Returns a
+    dict of new tensors: dq, dk, dv, dq_head_logits, dk_head_logits (None without k_head_logits), dlog_decay (GLA only,
+    else None) and d_initial_state (None unless asked for).  bfloat16: ``segments`` >= 2 cuts every batch row into that
+    many segments that run in parallel (for batches with few sequences); 0 asks ``sla_backward_segments`` for the count
+    that fills this device.  float32: ``segments`` must be 0 or 1; the library cuts rows over 128 tokens of batches with few
+    sequences by itself, unless a ``workspace`` is given that only has the room of the single pass."""
     import torch
 
     assert q.is_cuda and q.dtype in (torch.bfloat16, torch.float32)

@@ -13,10 +13,7 @@ int launch_forward(const sla_params& p, int dvw, int nseg, int seg_len, const vo
                    const float* ql, const float* kl, const void* ld, const float* beta, const float* s0, void* out,
                    float* sT, float* workspace, const int* cu, hipStream_t stream);
 size_t segment_workspace_floats(const sla_params& p, int nseg);
-size_t backward_workspace_floats(const sla_params& p, bool packed);
-int launch_backward(const sla_params& p, const void* q, const void* k, const void* v, const float* ql, const float* kl,
-                    const void* ld, const float* s0, const void* dout, const float* dsf, void* dq, void* dk, void* dv,
-                    float* dql, float* dkl, void* dld, float* ds0, float* ws, const int* cu, hipStream_t stream);
+size_t backward_workspace_floats(const sla_params& p, bool packed, bool least);
 size_t backward_segment_extra_floats(const sla_params& p, int nseg);
 sla_params packed_segments(const sla_params& p, int nseg);
 int launch_backward_segments(const sla_params& p, int nseg, int seg_len, int dvw, const void* q, const void* k,
@@ -25,11 +22,11 @@ int launch_backward_segments(const sla_params& p, int nseg, int seg_len, int dvw
                              void* dld, float* ds0, float* ws, hipStream_t stream);
 size_t backward_gdn_workspace_floats(const sla_params& p, bool packed);
 // any supported key width: heads of width 32 run zero-padded to 64 (sla_backward_narrow.hip)
-size_t backward_any_workspace_floats(const sla_params& p, bool packed);
+size_t backward_any_workspace_floats(const sla_params& p, bool packed, bool least);
 int launch_backward_any(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
                         const float* kl, const void* ld, const float* s0, const void* dout, const float* dsf, void* dq,
-                        void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, const int* cu,
-                        bool packed, hipStream_t stream);
+                        void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, size_t ws_floats,
+                        const int* cu, bool packed, hipStream_t stream);
 size_t backward_gdn_any_workspace_floats(const sla_params& p, bool packed);
 int launch_backward_gdn_any(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
                             const float* kl, const float* ld, const float* beta, const float* s0, const void* dout,
@@ -349,19 +346,21 @@ int sla_decode_step_fused(const sla_params* p, const void* q, const void* k, con
                               (hipStream_t)stream);
 }
 
-// The backward pass cuts batch rows into segments only on request (p->segments >= 2), so that its workspace size
-// does not depend on the device; the cut itself is the forward's.
+// bf16 tensors: the backward pass cuts batch rows into segments only on request (p->segments >= 2); the cut itself is the
+// forward's.  fp32 tensors: sla_backward_f32.hip cuts them by itself where the workspace allows it.  Neither rule looks at
+// the device, so the workspace's size does not depend on it.
 static int backward_segments(const sla_params& p, bool packed, int* seg_len) {
     *seg_len = p.T;
     if (packed || p.segments < 2 || p.T == 0) return 1;
     return choose_segments(p, 1, seg_len);
 }
 
-static size_t backward_floats(const sla_params& p, bool packed) {
+// least: what the call runs with at all (fp32 tensors: one pass), not what it wants.
+static size_t backward_floats(const sla_params& p, bool packed, bool least) {
     int len = 0;
     const int nseg = backward_segments(p, packed, &len);
-    if (nseg <= 1) return sla::backward_any_workspace_floats(p, packed);
-    return sla::backward_workspace_floats(sla::packed_segments(p, nseg), true) +
+    if (nseg <= 1) return sla::backward_any_workspace_floats(p, packed, least);
+    return sla::backward_workspace_floats(sla::packed_segments(p, nseg), true, least) +
            sla::backward_segment_extra_floats(p, nseg);
 }
 
@@ -373,7 +372,7 @@ static int backward_impl(const sla_params* p, const void* q, const void* k, cons
     int rc = check_params(p);
     if (rc != SLA_OK) return rc;
     if (p->variant == SLA_GDN || (packed && p->flags != 0)) return SLA_ERR_UNSUPPORTED;
-    // fp32 tensors and key heads of width 32: the single pass only
+    // fp32 tensors and key heads of width 32: no segments on request
     if ((p->dtype == SLA_F32 || p->dk < 64) && p->segments >= 2) return SLA_ERR_UNSUPPORTED;
     if (p->B > 0 && p->T > 0) {
         if (!q || !k || !v || !q_head_logits || !log_decay || !d_out || !dq || !dk || !dv || !dq_head_logits)
@@ -390,7 +389,7 @@ static int backward_impl(const sla_params* p, const void* q, const void* k, cons
     if (cu && (reinterpret_cast<uintptr_t>(cu) & 3u)) return SLA_ERR_ALIGN;
     if (p->B == 0) return SLA_OK;
     if (p->T == 0 && !d_initial_state) return SLA_OK;
-    if (!workspace || backward_floats(*p, packed) * sizeof(float) > workspace_bytes) return SLA_ERR_WORKSPACE;
+    if (!workspace || backward_floats(*p, packed, true) * sizeof(float) > workspace_bytes) return SLA_ERR_WORKSPACE;
     int seg_len = 0;
     const int nseg = backward_segments(*p, packed, &seg_len);
     if (nseg > 1) {
@@ -402,8 +401,8 @@ static int backward_impl(const sla_params* p, const void* q, const void* k, cons
     }
     return sla::launch_backward_any(*p, q, k, v, q_head_logits, k_head_logits, log_decay, initial_state, d_out,
                                     d_final_state, dq, dk, dv, dq_head_logits, dk_head_logits, dlog_decay,
-                                    d_initial_state, (float*)workspace, packed && p->T > 0 ? cu : nullptr, packed,
-                                    (hipStream_t)stream);
+                                    d_initial_state, (float*)workspace, workspace_bytes / sizeof(float),
+                                    packed && p->T > 0 ? cu : nullptr, packed, (hipStream_t)stream);
 }
 
 int sla_backward(const sla_params* p, const void* q, const void* k, const void* v, const float* q_head_logits,
@@ -587,12 +586,12 @@ int sla_gate_logits_backward(const sla_params* p, const void* x, const float* w,
 size_t sla_backward_workspace_bytes(const sla_params* p) {
     if (check_params(p) != SLA_OK || p->variant == SLA_GDN) return 0;
     if ((p->dtype == SLA_F32 || p->dk < 64) && p->segments >= 2) return 0;
-    return backward_floats(*p, false) * sizeof(float);
+    return backward_floats(*p, false, false) * sizeof(float);
 }
 
 size_t sla_backward_varlen_workspace_bytes(const sla_params* p) {
     if (check_params(p) != SLA_OK || p->variant == SLA_GDN) return 0;
-    return sla::backward_any_workspace_floats(*p, true) * sizeof(float);
+    return sla::backward_any_workspace_floats(*p, true, false) * sizeof(float);
 }
 
 size_t sla_workspace_bytes(const sla_params* p, int compute_units) {

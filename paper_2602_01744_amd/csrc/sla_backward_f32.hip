@@ -623,13 +623,17 @@ size_t round4(size_t n) { return (n + 3) & ~(size_t)3; }
 // Workspace, in floats: gates 2 [B,T,H]; dk/8 partial planes of dG^Q and dv/8 of dG^K (one per compute wave and
 // slice); for GLA rowsum(X_T' * S_T) [B,H,dk] (per segment); with nseg > 1 segments per batch row also their states and
 // cotangents 2 [B,nseg,H,dk,dv] and their decays [B,nseg,H,dk].
-size_t backward_f32_workspace_floats(const sla_params& p, bool packed) {
-    const size_t rows = packed ? (size_t)p.T : (size_t)p.B * p.T, n = round4(rows * p.H);
-    int len = 0;
-    const size_t nseg = segments_of(p, packed, &len), heads = (size_t)p.B * nseg * p.H;
+static size_t f32_workspace_floats(const sla_params& p, bool packed, size_t nseg) {
+    const size_t rows = packed ? (size_t)p.T : (size_t)p.B * p.T, n = round4(rows * p.H), heads = (size_t)p.B * nseg * p.H;
     return n * (2 + (size_t)p.dk / (4 * CW) + (size_t)p.dv / (4 * CW)) +
            (p.variant == SLA_GLA ? round4(heads * p.dk) : 0) +
            (nseg > 1 ? 2 * heads * p.dk * p.dv + round4(heads * p.dk) : 0);
+}
+
+// What the schedule segments_of() picks wants; `least`: what one pass takes, which every call runs with.
+size_t backward_f32_workspace_floats(const sla_params& p, bool packed, bool least) {
+    int len = 0;
+    return f32_workspace_floats(p, packed, least ? 1 : segments_of(p, packed, &len));
 }
 
 // One pass, or -- few sequences, see segments_of() -- every batch row in nseg segments that run side by side:
@@ -637,11 +641,12 @@ size_t backward_f32_workspace_floats(const sla_params& p, bool packed) {
 //   2. the chain kernel turns those into every segment's entry state and end cotangent;
 //   3. the three sweeps over B * nseg sequences.  The decay gradient's running sum starts, per segment, from
 //      rowsum(cotangent * state) at its end, the same identity as at the end of a whole sequence.
-// All of it in fp32 and with the decay applied token by token, so the domain is that of the single pass.
+// All of it in fp32 and with the decay applied token by token, so the domain is that of the single pass.  ws_floats: the
+// workspace's size; one pass if the segments do not fit in it.
 int launch_backward_f32(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
                         const float* kl, const void* ld, const float* s0, const void* dout, const float* dsf, void* dq,
-                        void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, const int* cu,
-                        hipStream_t stream) {
+                        void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, size_t ws_floats,
+                        const int* cu, hipStream_t stream) {
     const size_t rows = cu ? (size_t)p.T : (size_t)p.B * p.T, n = round4(rows * p.H);
     const int pq = p.dk / (4 * CW), pv = p.dv / (4 * CW);
     FArgs a;
@@ -657,7 +662,11 @@ int launch_backward_f32(const sla_params& p, const void* q, const void* k, const
     a.part_q = w; w += n * pq;
     a.part_k = w; w += n * pv;
     int seg_len = 0;
-    const int nseg = segments_of(p, cu != nullptr, &seg_len);
+    int nseg = segments_of(p, cu != nullptr, &seg_len);
+    if (f32_workspace_floats(p, cu != nullptr, nseg) > ws_floats) {
+        nseg = 1;
+        seg_len = p.T;
+    }
     const size_t heads = (size_t)p.B * nseg * p.H;
     a.corr = w;
     if (p.variant == SLA_GLA) w += round4(heads * p.dk);

@@ -221,6 +221,21 @@ def test_backward_workspace_size(lib):
     assert sla.sla_backward_workspace_bytes(_ok_params(dtype=sla.F32, B=B, T=1024, H=H, dk=dk, dv=dv, segments=2)) == 0
 
 
+@pytest.mark.parametrize("variant", [sla.RETNET, sla.GLA])
+@pytest.mark.parametrize("B,T,H,dk,dv,nseg", [(1, 128, 2, 64, 64, 1), (1, 129, 2, 64, 64, 5), (2, 1021, 8, 64, 128, 16),
+                                              (64, 256, 1, 128, 256, 2), (65, 256, 1, 128, 256, 1), (1, 4096, 2, 128, 128, 64)])
+def test_backward_workspace_of_fp32_segments(lib, variant, B, T, H, dk, dv, nseg):
+    """Around the cuts of the fp32 schedule: the query asks for the segments' states, cotangents and decays, and the single
+    pass's size, which the call also accepts, is the packed call's and does not grow as B or T shrink."""
+    size = lambda B, T: sla.sla_backward_workspace_bytes(_ok_params(variant=variant, dtype=sla.F32, B=B, T=T, H=H, dk=dk, dv=dv))
+    one = lambda B, T: sla.sla_backward_varlen_workspace_bytes(_ok_params(variant=variant, dtype=sla.F32, B=B, T=B * T, H=H, dk=dk, dv=dv))
+    heads = B * nseg * H
+    seg = 4 * (2 * heads * dk * dv + heads * dk + (heads - B * H) * dk * (variant == sla.GLA)) if nseg > 1 else 0
+    assert size(B, T) == one(B, T) + seg
+    for b, t in ((B, T - 1), (B, T // 2), (max(B - 1, 1), T), (max(B // 2, 1), T)):
+        assert one(b, t) <= one(B, T) <= size(B, T)
+
+
 def test_gate_logits_rejects_bad_calls(lib):
     ok = _ok_params()
     call = lambda p, q=A, k=A, wq=A, wk=A, ql=A, kl=A: sla.sla_gate_logits(p, q, k, wq, wk, ql, kl, 0)

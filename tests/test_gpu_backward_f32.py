@@ -134,3 +134,35 @@ def test_segments_agree_with_the_single_pass(variant, head_major, B, T, H, dk, d
         got = swap(a[name]) if name in ("dq", "dk", "dv", "dlog_decay") else a[name]
         err = float((got.double() - want.reshape(got.shape).double()).abs().max() / want.double().abs().max())
         assert err <= 1e-5, (name, err)
+
+
+@pytest.mark.parametrize("variant", [RETNET, GLA])
+@pytest.mark.parametrize("dk", [32, 128])
+def test_a_workspace_of_the_single_pass_is_enough(variant, dk):
+    """A batch that would be cut, with the workspace a larger one asks for (which is not cut and asks for less): it runs in
+    one pass, as its rows do in a packed batch, bit for bit."""
+    import torch
+
+    import paper_2602_01744_amd as sla
+
+    B, T, H, dv = 1, 300, 16, 64
+    size = lambda B: sla.sla_backward_workspace_bytes(sla.SlaParams(variant, sla.F32, B, T, H, dk, dv, 0, 0, 1))
+    if dk == 128:
+        assert size(20) < size(5)
+    need = sla.sla_backward_varlen_workspace_bytes(sla.SlaParams(variant, sla.F32, B, B * T, H, dk, dv, 0, 0, 1))
+    assert need < size(B)
+    g = torch.Generator(device="cuda").manual_seed(1995)
+    n = lambda *s: torch.randn(s, generator=g, device="cuda")
+    q, k, v, do = n(B, T, H, dk) * dk**-0.5, n(B, T, H, dk) * dk**-0.5, n(B, T, H, dv), n(B, T, H, dv)
+    ql, kl, s0, dsf = n(B, T, H), n(B, T, H), n(B, H, dk, dv), n(B, H, dk, dv)
+    ld = -torch.rand(B, T, H, dk, generator=g, device="cuda") * 0.1 if variant == GLA else -torch.rand(H, generator=g, device="cuda") * 0.1
+    ws = torch.full((need + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    a = sla.backward(variant, q, k, v, ql, kl, ld, do, s0, dsf, want_d_initial_state=True, workspace=ws[:need])
+    assert bool((ws[need:] == 0xA5).all())
+    with pytest.raises(sla.SlaError):
+        sla.backward(variant, q, k, v, ql, kl, ld, do, s0, dsf, want_d_initial_state=True, workspace=ws[: need - 16])
+    flat = lambda t: t.reshape(B * T, *t.shape[2:]) if t.dim() > 1 else t
+    cu = torch.arange(B + 1, dtype=torch.int32, device="cuda") * T
+    b = sla.backward_varlen(variant, *(flat(t) for t in (q, k, v, ql, kl, ld, do)), cu, s0, dsf, want_d_initial_state=True)
+    for name, want in b.items():
+        assert (want is None and a[name] is None) or torch.equal(a[name].reshape(want.shape), want), name
