@@ -228,28 +228,16 @@ template <bool BF16, int K, int LPH>
 __global__ __launch_bounds__(kGThreads) void sla_feature_map_bwd_kernel(const void* x, const float* w, const void* dy,
                                                                          void* dx, float* part, int B, int T, int C,
                                                                          int seg_len, float eps) {
-    // With seg_len = 64 the threads run over (batch row, segment, eight channels); with shorter ones `sub` waves walk
-    // seg_len of a segment's tokens each for the same 64 x 8 channels, and their shares of dw meet in LDS, so that the
-    // partial sums are those of 64-token segments whatever the walk.
+    // Threads run over (batch row, 64-token segment, eight channels).  With a shorter seg_len, `sub` waves or pairs of waves
+    // of a workgroup walk seg_len of the segment's tokens each for the same of these, and their shares of dw meet in LDS,
+    // so that the partial sums are those of 64-token segments whatever the walk.
     __shared__ float red[8 * K][kGThreads];
     const int groups = C / 8, segs = (T + kSegMax - 1) / kSegMax, sub = kSegMax / seg_len, tid = threadIdx.x;
-    const int part_no = sub == 1 ? 0 : (tid >> 6) % sub;
-    int cg, seg, b;
-    bool live;
-    if (sub == 1) {
-        const size_t idx = (size_t)blockIdx.x * kGThreads + tid, total = (size_t)B * segs * groups;
-        live = idx < total;
-        const size_t id = live ? idx : total - 1;
-        cg = (int)(id % groups); seg = (int)((id / groups) % segs); b = (int)(id / ((size_t)groups * segs));
-    } else {
-        const int cols = (groups + 63) / 64, per = kGThreads / 64 / sub, runs = (segs + per - 1) / per;
-        cg = (int)(blockIdx.x % cols) * 64 + (tid & 63);
-        seg = (int)((blockIdx.x / cols) % runs) * per + (tid >> 6) / sub;
-        b = (int)(blockIdx.x / ((size_t)cols * runs));
-        live = cg < groups && seg < segs;
-        cg = min(cg, groups - 1);
-        seg = min(seg, segs - 1);
-    }
+    const int width = kGThreads / sub, part_no = tid / width;
+    const size_t idx = (size_t)blockIdx.x * width + tid % width, total = (size_t)B * segs * groups;
+    const bool live = idx < total;
+    const size_t id = live ? idx : total - 1;
+    const int cg = (int)(id % groups), seg = (int)((id / groups) % segs), b = (int)(id / ((size_t)groups * segs));
     float wt[K][8];
 #pragma unroll
     for (int c = 0; c < 8; ++c)
@@ -374,7 +362,7 @@ __global__ __launch_bounds__(kGThreads) void sla_feature_map_bwd_kernel(const vo
 #pragma unroll
                 for (int i = 0; i < K; ++i) {
                     float sum = red[c * K + i][tid];
-                    for (int n = 1; n < sub; ++n) sum += red[c * K + i][tid + n * 64];
+                    for (int n = 1; n < sub; ++n) sum += red[c * K + i][tid + n * width];
                     dwacc[i][c] = sum;
                 }
         }
@@ -542,12 +530,9 @@ int launch_short_conv_silu(int dtype, int B, int T, int C, int taps, const void*
 int launch_feature_map_backward(int dtype, int B, int T, int C, int taps, int head_width, float eps, const void* x,
                                 const float* w, const void* dy, void* dx, float* dw, float* workspace,
                                 hipStream_t stream) {
-    const int seg = segment_length(B, T, C), sub = kSegMax / seg, per = kGThreads / 64 / sub;
-    const size_t segs = (T + kSegMax - 1) / kSegMax, nparts = feature_map_partials(B, T), groups = (size_t)C / 8;
-    // see the kernel: threads over (row, segment, channels), or waves over parts of segments and 64 x 8 channels
-    const size_t blocks = sub == 1 ? (nparts * groups + kGThreads - 1) / kGThreads
-                                   : B * ((segs + per - 1) / per) * ((groups + 63) / 64);
-    const dim3 grid((unsigned)blocks);
+    const int seg = segment_length(B, T, C), width = kGThreads * seg / kSegMax;  // see the kernel
+    const size_t nparts = feature_map_partials(B, T), threads = nparts * (C / 8);
+    const dim3 grid((unsigned)((threads + width - 1) / width));
     const int rc = dtype == SLA_BF16 ? feature_map_taps<true>(taps, head_width / 8, true, grid, stream, x, w, dy, dx,
                                                               workspace, B, T, C, seg, eps)
                                      : feature_map_taps<false>(taps, head_width / 8, true, grid, stream, x, w, dy, dx,

@@ -191,3 +191,22 @@ def test_short_division_equals_the_division():
         a, b = (f(run(first))[0, :, 1:] for first in (1.0, -90.0))
         differ = a.contiguous().view(torch.int32) != b.contiguous().view(torch.int32)
         assert int((differ & ~(torch.isnan(a) & torch.isnan(b))).sum()) == 0
+
+
+@pytest.mark.parametrize("B,T,C,head", [(3, 1000, 128, 128), (70, 4000, 128, 128), (140, 4000, 72, 0), (300, 4000, 64, 0)])
+def test_feature_map_backward_with_few_channels(B, T, C, head):
+    """Waves that hold several segments of few channels each, walked by four, two and one threads: dx of sampled rows
+    equals those rows run alone, bit for bit, and dw the sum over parts of the batch."""
+    import torch
+
+    import paper_2602_01744_amd as sla
+
+    gen = torch.Generator(device="cuda").manual_seed(3400 + C)
+    x, dy = (torch.randn(B, T, C, generator=gen, device="cuda").bfloat16() for _ in range(2))
+    w = torch.randn(C, 4, generator=gen, device="cuda") * 0.5
+    dx, dw = sla.short_conv_silu_l2_backward(x, w, dy, head)
+    for b in {0, B // 2, B - 1}:
+        assert torch.equal(sla.short_conv_silu_l2_backward(x[b : b + 1], w, dy[b : b + 1], head)[0][0], dx[b])
+    total = sum(sla.short_conv_silu_l2_backward(x[b : b + 2].contiguous(), w, dy[b : b + 2].contiguous(), head)[1].double()
+                for b in range(0, B, 2))
+    assert float((dw.double() - total).abs().max() / total.abs().max()) <= 1e-5
