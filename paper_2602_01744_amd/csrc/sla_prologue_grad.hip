@@ -494,13 +494,14 @@ int sum_partials(const float* part, float* out, size_t stride, int nparts, hipSt
     return hipGetLastError() == hipSuccess ? SLA_OK : SLA_ERR_HIP;
 }
 
-// Tokens per thread.  64 while that leaves two wavefronts per SIMD (131072 threads): a segment re-reads the K-1 tokens
-// before it, and the backward also recomputes the K-1 tokens after it.  With fewer, a thread's walk is a serial chain
-// of about 0.3 us (backward 0.65 us) a token whatever else the chip does, so it is cut: B=4 T=777 640 channels, forward
-// 24.9 -> 9.6 us, backward 46.6 -> 22.4 us, 64 against 16.
+// Tokens per thread.  64 while that leaves about two wavefronts per SIMD (114688 threads of 131072): a segment re-reads the
+// K-1 tokens before it, and the backward also recomputes the K-1 tokens after it.  With fewer, a thread's walk is a serial
+// chain of about 0.3 us (backward 0.65 us) a token whatever else the chip does, so it is cut: B=4 T=777 640 channels,
+// forward 24.9 -> 9.6 us, backward 46.6 -> 22.4 us, 64 against 16.  Not for the last eighth: B=64 T=4000 128 channels,
+// forward 33.7 us by 16 tokens and 28.5 by 32 (128000 threads), backward 73 and 62; B=128 52 us by 32 and 46 by 64.
 int segment_length(int B, int T, int C) {
     int seg = kSegMax;
-    while (seg > kSegMin && (size_t)B * ((T + seg - 1) / seg) * (C / 8) < 131072) seg /= 2;
+    while (seg > kSegMin && (size_t)B * ((T + seg - 1) / seg) * (C / 8) < 114688) seg /= 2;
     return seg;
 }
 
