@@ -13,7 +13,10 @@ int launch_forward(const sla_params& p, int dvw, int nseg, int seg_len, const vo
                    const float* ql, const float* kl, const void* ld, const float* beta, const float* s0, void* out,
                    float* sT, float* workspace, const int* cu, hipStream_t stream);
 size_t segment_workspace_floats(const sla_params& p, int nseg);
-size_t backward_workspace_floats(const sla_params& p, bool packed, bool least);
+size_t backward_workspace_floats(const sla_params& p, bool packed);
+int launch_backward(const sla_params& p, const void* q, const void* k, const void* v, const float* ql, const float* kl,
+                    const void* ld, const float* s0, const void* dout, const float* dsf, void* dq, void* dk, void* dv,
+                    float* dql, float* dkl, void* dld, float* ds0, float* ws, const int* cu, hipStream_t stream);
 size_t backward_segment_extra_floats(const sla_params& p, int nseg);
 sla_params packed_segments(const sla_params& p, int nseg);
 int launch_backward_segments(const sla_params& p, int nseg, int seg_len, int dvw, const void* q, const void* k,
@@ -22,11 +25,11 @@ int launch_backward_segments(const sla_params& p, int nseg, int seg_len, int dvw
                              void* dld, float* ds0, float* ws, hipStream_t stream);
 size_t backward_gdn_workspace_floats(const sla_params& p, bool packed);
 // any supported key width: heads of width 32 run zero-padded to 64 (sla_backward_narrow.hip)
-size_t backward_any_workspace_floats(const sla_params& p, bool packed, bool least);
+size_t backward_any_workspace_floats(const sla_params& p, bool packed);
 int launch_backward_any(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
                         const float* kl, const void* ld, const float* s0, const void* dout, const float* dsf, void* dq,
-                        void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, size_t ws_floats,
-                        const int* cu, bool packed, hipStream_t stream);
+                        void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, const int* cu,
+                        bool packed, hipStream_t stream);
 size_t backward_gdn_any_workspace_floats(const sla_params& p, bool packed);
 int launch_backward_gdn_any(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
                             const float* kl, const float* ld, const float* beta, const float* s0, const void* dout,
@@ -355,12 +358,18 @@ static int backward_segments(const sla_params& p, bool packed, int* seg_len) {
     return choose_segments(p, 1, seg_len);
 }
 
-// least: what the call runs with at all (fp32 tensors: one pass), not what it wants.
-static size_t backward_floats(const sla_params& p, bool packed, bool least) {
+// fp32 tensors: what the library's own schedule wants, which p.segments == 0 stands for from here on; 1 is the single pass.
+static sla_params with_own_segments(const sla_params& p, bool own) {
+    sla_params r = p;
+    if (p.dtype == SLA_F32) r.segments = own ? 0 : 1;
+    return r;
+}
+
+static size_t backward_floats(const sla_params& p, bool packed) {
     int len = 0;
     const int nseg = backward_segments(p, packed, &len);
-    if (nseg <= 1) return sla::backward_any_workspace_floats(p, packed, least);
-    return sla::backward_workspace_floats(sla::packed_segments(p, nseg), true, least) +
+    if (nseg <= 1) return sla::backward_any_workspace_floats(p, packed);
+    return sla::backward_workspace_floats(sla::packed_segments(p, nseg), true) +
            sla::backward_segment_extra_floats(p, nseg);
 }
 
@@ -389,7 +398,10 @@ static int backward_impl(const sla_params* p, const void* q, const void* k, cons
     if (cu && (reinterpret_cast<uintptr_t>(cu) & 3u)) return SLA_ERR_ALIGN;
     if (p->B == 0) return SLA_OK;
     if (p->T == 0 && !d_initial_state) return SLA_OK;
-    if (!workspace || backward_floats(*p, packed, true) * sizeof(float) > workspace_bytes) return SLA_ERR_WORKSPACE;
+    // fp32 tensors: one pass where the library's own segments do not fit, and an error only where that does not either
+    sla_params run = with_own_segments(*p, true);
+    if (backward_floats(run, packed) * sizeof(float) > workspace_bytes) run = with_own_segments(*p, false);
+    if (!workspace || backward_floats(run, packed) * sizeof(float) > workspace_bytes) return SLA_ERR_WORKSPACE;
     int seg_len = 0;
     const int nseg = backward_segments(*p, packed, &seg_len);
     if (nseg > 1) {
@@ -399,10 +411,10 @@ static int backward_impl(const sla_params* p, const void* q, const void* k, cons
                                              dk_head_logits, dlog_decay, d_initial_state, (float*)workspace,
                                              (hipStream_t)stream);
     }
-    return sla::launch_backward_any(*p, q, k, v, q_head_logits, k_head_logits, log_decay, initial_state, d_out,
+    return sla::launch_backward_any(run, q, k, v, q_head_logits, k_head_logits, log_decay, initial_state, d_out,
                                     d_final_state, dq, dk, dv, dq_head_logits, dk_head_logits, dlog_decay,
-                                    d_initial_state, (float*)workspace, workspace_bytes / sizeof(float),
-                                    packed && p->T > 0 ? cu : nullptr, packed, (hipStream_t)stream);
+                                    d_initial_state, (float*)workspace, packed && p->T > 0 ? cu : nullptr, packed,
+                                    (hipStream_t)stream);
 }
 
 int sla_backward(const sla_params* p, const void* q, const void* k, const void* v, const float* q_head_logits,
@@ -586,12 +598,12 @@ int sla_gate_logits_backward(const sla_params* p, const void* x, const float* w,
 size_t sla_backward_workspace_bytes(const sla_params* p) {
     if (check_params(p) != SLA_OK || p->variant == SLA_GDN) return 0;
     if ((p->dtype == SLA_F32 || p->dk < 64) && p->segments >= 2) return 0;
-    return backward_floats(*p, false, false) * sizeof(float);
+    return backward_floats(with_own_segments(*p, true), false) * sizeof(float);
 }
 
 size_t sla_backward_varlen_workspace_bytes(const sla_params* p) {
     if (check_params(p) != SLA_OK || p->variant == SLA_GDN) return 0;
-    return sla::backward_any_workspace_floats(*p, true, false) * sizeof(float);
+    return sla::backward_any_workspace_floats(*p, true) * sizeof(float);
 }
 
 size_t sla_workspace_bytes(const sla_params* p, int compute_units) {

@@ -1324,17 +1324,17 @@ int launch_bwd_logits(const GateGrad& read, const GateGrad& write, size_t rows, 
     return hipGetLastError() == hipSuccess ? SLA_OK : SLA_ERR_HIP;
 }
 
-size_t backward_f32_workspace_floats(const sla_params& p, bool packed, bool least);  // sla_backward_f32.hip
+size_t backward_f32_workspace_floats(const sla_params& p, bool packed);  // sla_backward_f32.hip
 int launch_backward_f32(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
                         const float* kl, const void* ld, const float* s0, const void* dout, const float* dsf, void* dq,
-                        void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, size_t ws_floats,
-                        const int* cu, hipStream_t stream);
+                        void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, const int* cu,
+                        hipStream_t stream);
 
 // Workspace, in floats: gates G^Q, G^K [B,T,H]; partial dG^Q and dG^K (dk/16 planes each); for GLA the sums of
 // q * dq over every 16-token block [rows/16 + B + 1][H,dk], the final-state term of dlog_decay [B,H,dk] and the
-// states kept every 512 tokens [rows/512 + 1][H,dk,dv] in bf16.  `least` matters to fp32 tensors only.
-size_t backward_workspace_floats(const sla_params& p, bool packed, bool least) {
-    if (p.dtype == SLA_F32) return backward_f32_workspace_floats(p, packed, least);
+// states kept every 512 tokens [rows/512 + 1][H,dk,dv] in bf16.
+size_t backward_workspace_floats(const sla_params& p, bool packed) {
+    if (p.dtype == SLA_F32) return backward_f32_workspace_floats(p, packed);
     const size_t rows = packed ? (size_t)p.T : (size_t)p.B * p.T;
     const size_t n = round4(rows * p.H);
     size_t total = n * (2 + 2 * (p.dk / 16));
@@ -1441,7 +1441,7 @@ int launch_backward_segments(const sla_params& p, int nseg, int seg_len, int dvw
                              void* dld, float* ds0, float* ws, hipStream_t stream) {
     const sla_params pk = packed_segments(p, nseg);
     const size_t states = (size_t)pk.B * p.H * p.dk * p.dv;
-    float* w = ws + backward_workspace_floats(pk, true, false);
+    float* w = ws + backward_workspace_floats(pk, true);
     float* fwd = w; w += round4(segment_workspace_floats(p, nseg));  // entry states first
     float* totals = w; w += round4((size_t)p.B * (nseg - 1) * p.H * p.dk);
     float* part = w; w += states;
@@ -1475,11 +1475,9 @@ int launch_backward_segments(const sla_params& p, int nseg, int seg_len, int dvw
 
 int launch_backward(const sla_params& p, const void* q, const void* k, const void* v, const float* ql, const float* kl,
                     const void* ld, const float* s0, const void* dout, const float* dsf, void* dq, void* dk, void* dv,
-                    float* dql, float* dkl, void* dld, float* ds0, float* ws, size_t ws_floats, const int* cu,
-                    hipStream_t stream) {
+                    float* dql, float* dkl, void* dld, float* ds0, float* ws, const int* cu, hipStream_t stream) {
     if (p.dtype == SLA_F32)  // fp32 tensors: token by token in fp32 vector arithmetic
-        return launch_backward_f32(p, q, k, v, ql, kl, ld, s0, dout, dsf, dq, dk, dv, dql, dkl, dld, ds0, ws, ws_floats, cu,
-                                   stream);
+        return launch_backward_f32(p, q, k, v, ql, kl, ld, s0, dout, dsf, dq, dk, dv, dql, dkl, dld, ds0, ws, cu, stream);
     return launch_backward_some(p, q, k, v, ql, kl, ld, s0, dout, dsf, dq, dk, dv, dql, dkl, dld, ds0, ws, cu, stream, 7);
 }
 

@@ -10,12 +10,16 @@
 //     dk_t = G^K_t v_t X_t^T       dq_t = G^Q_t dout_t S_t^T       dG^Q_t = q_t . (dout_t S_t^T)
 //     dlog_decay_t = rowsum(X_T' * S_T) + sum_{s >= t} (q_s * dq_s - k_s * dk_s)     (GLA; X_T' the caller's cotangent
 //     of the final state; a writer j and a reader s contribute the same amount to q_s dq_s and to k_j dk_j and cross
-//     token t's decay exactly when j < t <= s)
+//     token t's decay exactly when j < t <= s).  Where a row runs in segments, each is a sequence of its own: S_T and X_T'
+//     are its exit state and the cotangent of that, so the sum restarts at every segment's end from an fp32 row sum.  It
+//     is the shorter sum that decides: against 64 bits dlog_decay is off by 0.25 to 0.95 of what one pass leaves (T=130
+//     64 x 64 4.7e-7 -> 2.6e-7, T=300 128 x 256 8.7e-7 -> 3.4e-7, T=4136 128 x 128 3.0e-6 -> 4.0e-7, 2-norms).
 // Every output contracts a state over one of its two dimensions, so the pass is three sweeps that each carry one
 // state tile in registers, sliced over the dimension that is not contracted:
 //   dv sweep, backward in time, X[dk rows, 64 value columns]:  dv, partial dG^K, d_initial_state;
 //   dq sweep, forward in time, S^T[dv rows, 64 key columns]:   dq, partial dG^Q, rowsum(X_T' * S_T);
-//   dk sweep, backward in time, X^T[dv rows, 64 key columns]:  dk, dlog_decay (a running sum in fp64 per key column).
+//   dk sweep, backward in time, X^T[dv rows, 64 key columns]:  dk, dlog_decay (a running sum in fp64 per key column,
+//                                                              over the sequence or the segment).
 // The gate gradients then go through the head softmax in sla_bwd_logits_kernel (sla_backward.hip).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -601,12 +605,13 @@ int launch_dk(const FArgs& a, const Segments& sg, int dk, int dv, bool state_onl
 //     B=1 T=4096 H=2  128 x 128  3827 -> 139 / 149           B=4 T=2048 H=5  128 x 256  2548 -> 758 / 802
 //     B=5 T=300  H=12 128 x 256   421 -> 368 / 410           B=8 T=700  H=16 128 x 128   708 (one pass) / 790
 // Rows of up to 128 tokens stay in one pass and in the workspace it takes: such a call is 0.15 ms at most.
-// Packed batches run in one pass (their lengths are known on the device only).
+// Packed batches run in one pass (their lengths are known on the device only), and so does p.segments == 1: the caller's
+// workspace has no room for more.
 int segments_of(const sla_params& p, bool packed, int* seg_len) {
     constexpr int kShortest = 32, kOnePass = 128;
     *seg_len = p.T;
     const size_t groups = (size_t)p.B * p.H * ((p.dk < p.dv ? p.dk : p.dv) / kSlice);
-    if (packed || groups == 0 || p.T <= kOnePass) return 1;
+    if (packed || p.segments == 1 || groups == 0 || p.T <= kOnePass) return 1;
     const size_t target = p.dk * p.dv <= 64 * 128 && groups * p.T >= 512 * 64 ? 512 : 256;
     if (2 * groups > target) return 1;
     const int want = (int)(target / groups);
@@ -623,17 +628,13 @@ size_t round4(size_t n) { return (n + 3) & ~(size_t)3; }
 // Workspace, in floats: gates 2 [B,T,H]; dk/8 partial planes of dG^Q and dv/8 of dG^K (one per compute wave and
 // slice); for GLA rowsum(X_T' * S_T) [B,H,dk] (per segment); with nseg > 1 segments per batch row also their states and
 // cotangents 2 [B,nseg,H,dk,dv] and their decays [B,nseg,H,dk].
-static size_t f32_workspace_floats(const sla_params& p, bool packed, size_t nseg) {
-    const size_t rows = packed ? (size_t)p.T : (size_t)p.B * p.T, n = round4(rows * p.H), heads = (size_t)p.B * nseg * p.H;
+size_t backward_f32_workspace_floats(const sla_params& p, bool packed) {
+    const size_t rows = packed ? (size_t)p.T : (size_t)p.B * p.T, n = round4(rows * p.H);
+    int len = 0;
+    const size_t nseg = segments_of(p, packed, &len), heads = (size_t)p.B * nseg * p.H;
     return n * (2 + (size_t)p.dk / (4 * CW) + (size_t)p.dv / (4 * CW)) +
            (p.variant == SLA_GLA ? round4(heads * p.dk) : 0) +
            (nseg > 1 ? 2 * heads * p.dk * p.dv + round4(heads * p.dk) : 0);
-}
-
-// What the schedule segments_of() picks wants; `least`: what one pass takes, which every call runs with.
-size_t backward_f32_workspace_floats(const sla_params& p, bool packed, bool least) {
-    int len = 0;
-    return f32_workspace_floats(p, packed, least ? 1 : segments_of(p, packed, &len));
 }
 
 // One pass, or -- few sequences, see segments_of() -- every batch row in nseg segments that run side by side:
@@ -641,12 +642,11 @@ size_t backward_f32_workspace_floats(const sla_params& p, bool packed, bool leas
 //   2. the chain kernel turns those into every segment's entry state and end cotangent;
 //   3. the three sweeps over B * nseg sequences.  The decay gradient's running sum starts, per segment, from
 //      rowsum(cotangent * state) at its end, the same identity as at the end of a whole sequence.
-// All of it in fp32 and with the decay applied token by token, so the domain is that of the single pass.  ws_floats: the
-// workspace's size; one pass if the segments do not fit in it.
+// All of it in fp32 and with the decay applied token by token, so the domain is that of the single pass.
 int launch_backward_f32(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
                         const float* kl, const void* ld, const float* s0, const void* dout, const float* dsf, void* dq,
-                        void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, size_t ws_floats,
-                        const int* cu, hipStream_t stream) {
+                        void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, const int* cu,
+                        hipStream_t stream) {
     const size_t rows = cu ? (size_t)p.T : (size_t)p.B * p.T, n = round4(rows * p.H);
     const int pq = p.dk / (4 * CW), pv = p.dv / (4 * CW);
     FArgs a;
@@ -662,11 +662,7 @@ int launch_backward_f32(const sla_params& p, const void* q, const void* k, const
     a.part_q = w; w += n * pq;
     a.part_k = w; w += n * pv;
     int seg_len = 0;
-    int nseg = segments_of(p, cu != nullptr, &seg_len);
-    if (f32_workspace_floats(p, cu != nullptr, nseg) > ws_floats) {
-        nseg = 1;
-        seg_len = p.T;
-    }
+    const int nseg = segments_of(p, cu != nullptr, &seg_len);
     const size_t heads = (size_t)p.B * nseg * p.H;
     a.corr = w;
     if (p.variant == SLA_GLA) w += round4(heads * p.dk);

@@ -12,11 +12,10 @@
 
 namespace sla {
 
-size_t backward_workspace_floats(const sla_params& p, bool packed, bool least);
+size_t backward_workspace_floats(const sla_params& p, bool packed);
 int launch_backward(const sla_params& p, const void* q, const void* k, const void* v, const float* ql, const float* kl,
                     const void* ld, const float* s0, const void* dout, const float* dsf, void* dq, void* dk, void* dv,
-                    float* dql, float* dkl, void* dld, float* ds0, float* ws, size_t ws_floats, const int* cu,
-                    hipStream_t stream);
+                    float* dql, float* dkl, void* dld, float* ds0, float* ws, const int* cu, hipStream_t stream);
 size_t backward_gdn_workspace_floats(const sla_params& p, bool packed);
 int launch_backward_gdn(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
                         const float* kl, const float* ld, const float* beta, const float* s0, const void* dout,
@@ -84,26 +83,23 @@ sla_params widened(const sla_params& p) {
 }  // namespace
 
 // Workspace of sla_backward / sla_backward_varlen in floats, any supported key width, without the segments that the caller
-// asks for.  fp32 tensors: with those the library picks, or (`least`) without, which is enough to run.
-size_t backward_any_workspace_floats(const sla_params& p, bool packed, bool least) {
-    if (p.dk != kNarrow) return backward_workspace_floats(p, packed, least);
+// asks for (with those that fp32 tensors are cut into by themselves).
+size_t backward_any_workspace_floats(const sla_params& p, bool packed) {
+    if (p.dk != kNarrow) return backward_workspace_floats(p, packed);
     const Padded s = padded_sizes(p, packed);
-    return backward_workspace_floats(widened(p), packed, least) + 6 * s.wide + 3 * s.state;
+    return backward_workspace_floats(widened(p), packed) + 6 * s.wide + 3 * s.state;
 }
 
 int launch_backward_any(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
                         const float* kl, const void* ld, const float* s0, const void* dout, const float* dsf, void* dq,
-                        void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, size_t ws_floats,
-                        const int* cu, bool packed, hipStream_t stream) {
+                        void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, const int* cu,
+                        bool packed, hipStream_t stream) {
     if (p.dk != kNarrow)
-        return launch_backward(p, q, k, v, ql, kl, ld, s0, dout, dsf, dq, dk, dv, dql, dkl, dld, ds0, ws, ws_floats, cu,
-                               stream);
+        return launch_backward(p, q, k, v, ql, kl, ld, s0, dout, dsf, dq, dk, dv, dql, dkl, dld, ds0, ws, cu, stream);
     const sla_params w = widened(p);
     const Padded s = padded_sizes(p, packed);
     const bool gla = p.variant == SLA_GLA;
-    // the wide pass's part, as much as it wants if there is room
-    const size_t inner = backward_workspace_floats(w, packed, ws_floats < backward_any_workspace_floats(p, packed, false));
-    float* x = ws + inner;
+    float* x = ws + backward_workspace_floats(w, packed);
     float* qp = x; x += s.wide;
     float* kp = x; x += s.wide;
     float* lp = x; x += s.wide;
@@ -122,7 +118,7 @@ int launch_backward_any(const sla_params& p, const void* q, const void* k, const
     if (rc != SLA_OK) return rc;
     rc = launch_backward(w, qp, kp, v, ql, kl, gla ? (const void*)lp : ld, s0 ? s0p : nullptr, dout,
                          dsf ? dsfp : nullptr, dqp, dkp, dv, dql, dkl, gla ? (void*)dlp : nullptr, ds0 ? ds0p : nullptr,
-                         ws, inner, cu, stream);
+                         ws, cu, stream);
     if (rc != SLA_OK) return rc;
     rc = unpad(dqp, dq, s.rows_h, s.per_row, stream);
     if (rc == SLA_OK) rc = unpad(dkp, dk, s.rows_h, s.per_row, stream);
