@@ -10,7 +10,7 @@
 // instructions per eight channels and token.  Hence U tokens' loads in flight, whose registers are reloaded where they
 // are read, shifts of the window by unrolling instead of moves, and the short division of sigmoid8().  bf16, B=8 T=4096
 // 2048 channels, one call after another on the same tensors, without these -> with them (with, but IEEE divisions):
-// forward with L2 65 -> 49 us (61; 268 MB), without 58 -> 50 us (56), backward 122 -> 90 us (103; 402 MB, 231 registers:
+// forward with L2 65 -> 49 us (61; 268 MB), without 58 -> 50 us (56), backward 122 -> 90 us (103; 402 MB, 229 registers:
 // two wavefronts per SIMD).
 //
 // A thread owns eight adjacent channels (16 bytes of a token row), a wave covers 1 KB of every

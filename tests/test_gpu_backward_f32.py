@@ -67,9 +67,25 @@ def test_any_decay_is_in_range():
     check_backward(GLA, d, cot, dtype="f32", label="f32 decay in [-40, 0]")
 
 
+@pytest.mark.parametrize("variant", [RETNET, GLA])
+@pytest.mark.parametrize("states", [False, True])
+def test_any_decay_is_in_range_of_the_segments(variant, states):
+    """Log-decays down to -40 a token, exact zeros among them, on a row that runs in segments: their whole decays underflow."""
+    B, T, H, dk, dv = 1, 300, 2, 64, 128
+    d = si.custom(variant, "f32", B=B, T=T, H=H, dk=dk, dv=dv, seed=1973)
+    r = np.random.default_rng(1974)
+    ld = -40.0 * r.random(size=d["log_decay"].shape) ** 4
+    ld[r.random(size=ld.shape) < 0.2] = 0.0
+    d["log_decay"] = ld.astype(np.float32)
+    cot = si.cotangents(B, T, H, dk, dv, seed=1975, final_state=states)
+    s0 = si.initial_state(B, H, dk, dv, seed=1976) if states else None
+    check_backward(variant, d, cot, s0, want_ds0=states, dtype="f32", label=f"f32 segments, decay in [-40, 0] states={states}")
+
+
 def test_long_sequence_decay_gradient():
-    """dlog_decay sums q dq - k dk over every later token, two sums that nearly cancel: the running sum is kept in
-    fp64, so the error of the earliest tokens stays at the fp32 bar."""
+    """dlog_decay sums q dq - k dk over every later token, two sums that nearly cancel.  The library cuts this row into 52
+    segments of 80 tokens; the running sum, in fp64, restarts at each one's end from rowsum(cotangent * state) there, so
+    the error of the earliest tokens stays at the fp32 bar."""
     B, T, H, dk, dv = 1, 4096 + 40, 2, 128, 128
     d = si.custom(GLA, "f32", B=B, T=T, H=H, dk=dk, dv=dv, seed=1977)
     cot = si.cotangents(B, T, H, dk, dv, seed=1978, final_state=True)
