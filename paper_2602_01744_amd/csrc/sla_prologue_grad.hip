@@ -6,12 +6,13 @@
 //   * the Gated DeltaNet blocks' feature map (Sec. 5.1, Model Configuration: short convolution, then SiLU), with
 //     an optional division of every head's vector by sqrt(sum of squares + eps), forward and backward.
 //
-// All of it streams, but the feature map is bound by the vector pipes as much as by memory: about 130 (backward 265)
-// instructions per eight channels and token.  Hence U tokens' loads in flight, whose registers are reloaded where they
-// are read, shifts of the window by unrolling instead of moves, and the short division of sigmoid8().  bf16, B=8 T=4096
-// 2048 channels, one call after another on the same tensors, without these -> with them (with, but IEEE divisions):
-// forward with L2 65 -> 49 us (61; 268 MB), without 58 -> 50 us (56), backward 122 -> 90 us (103; 402 MB, 229 registers:
-// two wavefronts per SIMD).
+// All of it streams, but the feature map is bound by the vector pipes as much as by memory: about 150 (backward 245, with L2
+// 295) instructions per eight channels and token, which keep the pipes 70 % (77, 81 %) busy.  Hence U tokens' loads in
+// flight, whose registers are reloaded where they are read, shifts of the window by unrolling instead of moves, and the
+// short division of sigmoid8().  bf16, B=8 T=4096 2048 channels, one call after another on the same tensors, without these
+// -> with them (with, but IEEE divisions): forward with L2 65 -> 49 us (61; 268 MB), without 58 -> 50 us (56), backward
+// 122 -> 90 us (103; 402 MB, 229 registers: two wavefronts per SIMD).  Inside a training step, whose other tensors displace
+// these from the caches, 60, 60 and 104 us.
 //
 // A thread owns eight adjacent channels (16 bytes of a token row), a wave covers 1 KB of every
 // row it touches.  Sums over tokens (dW, dw) are taken in two deterministic stages: every thread leaves the sum
