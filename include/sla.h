@@ -203,7 +203,8 @@ int sla_decode_step_fused(const sla_params* p, const void* q, const void* k, con
  * as in sla_forward_ws): every batch row is cut into that many segments (of a multiple of 64 tokens, at least 256)
  * which run in parallel; the entry state and the end cotangent of every segment come from two pre-passes.  It needs
  * the [B,T,H,d] layout (p->flags == 0) and a larger workspace (sla_backward_workspace_bytes accounts for it); 0 and 1
- * run the single pass.  fp32 tensors: >= 2 is SLA_ERR_UNSUPPORTED; with 0 and 1 the library itself cuts rectangular
+ * run the single pass.  In a workspace of sla_backward_chunks_workspace_bytes both give way to the chunk-parallel
+ * schedule described there, which is the faster one.  fp32 tensors: >= 2 is SLA_ERR_UNSUPPORTED; with 0 and 1 the library itself cuts rectangular
  * batches with few sequences of more than 128 tokens into segments, if the workspace has the room that
  * sla_backward_workspace_bytes asks for, and runs the single pass otherwise.  That room may be larger for a smaller B or T;
  * the single pass takes what sla_backward_varlen_workspace_bytes says for the same B and p->T = B * T, which never grows as
@@ -236,6 +237,16 @@ int sla_backward(const sla_params* p, const void* q, const void* k, const void* 
 
 /* Bytes of workspace sla_backward wants for *p (0 when *p is not a shape it supports). */
 size_t sla_backward_workspace_bytes(const sla_params* p);
+
+/*
+ * Bytes of workspace with which sla_backward (packed == 0) or sla_backward_varlen (packed != 0) runs bf16 tensors
+ * chunk-parallel as fast as it can; never less than their own queries.  Every 64-token chunk of a head is then worked on
+ * independently, from the states at the chunk boundaries that a first kernel leaves in the workspace (p->segments makes
+ * no difference).  A smaller workspace holds the states of a part of the batch at a time (same results); one with less
+ * than 64 MiB for them, where that is not all of them, runs the sweeps described at sla_backward.  The gradients of the
+ * two agree to the rounding of bf16 operands.  fp32 tensors: the same as the other queries.
+ */
+size_t sla_backward_chunks_workspace_bytes(const sla_params* p, int packed);
 
 /*
  * Backward pass of sla_forward for the gated delta rule (Softmax-GatedDeltaNet, Sec. 5.1, with the gates of

@@ -107,6 +107,8 @@ def load_library():
     lib.sla_backward_gdn_varlen_workspace_bytes.argtypes = [pp]
     lib.sla_backward_workspace_bytes.restype = ctypes.c_size_t
     lib.sla_backward_workspace_bytes.argtypes = [pp]
+    lib.sla_backward_chunks_workspace_bytes.restype = ctypes.c_size_t
+    lib.sla_backward_chunks_workspace_bytes.argtypes = [pp, ctypes.c_int]
     lib.sla_workspace_bytes.restype = ctypes.c_size_t
     lib.sla_workspace_bytes.argtypes = [pp, ctypes.c_int]
     lib.sla_segments.restype = ctypes.c_int
@@ -325,7 +327,7 @@ def backward_varlen(variant: int, q, k, v, q_head_logits, k_head_logits, log_dec
         "d_initial_state": torch.empty((B, H, dk, dv), dtype=torch.float32, device=dev) if want_d_initial_state else None,
     }
     params = SlaParams(variant, BF16 if q.dtype == torch.bfloat16 else F32, B, T, H, dk, dv, 0, 0, 1)
-    need = sla_backward_varlen_workspace_bytes(params)
+    need = sla_backward_chunks_workspace_bytes(params, packed=True)
     workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
     ptr = lambda t: None if t is None else t.data_ptr()
     rc = sla_backward_varlen(
@@ -472,6 +474,10 @@ def gate_logits(q, k, w_gq, w_gk, *, dv: int = 0):
     return ql, kl
 
 
+def sla_backward_chunks_workspace_bytes(params: SlaParams, packed: bool = False) -> int:
+    return int(load_library().sla_backward_chunks_workspace_bytes(ctypes.byref(params), int(bool(packed))))
+
+
 def sla_backward_workspace_bytes(params: SlaParams) -> int:
     return int(load_library().sla_backward_workspace_bytes(ctypes.byref(params)))
 
@@ -530,7 +536,7 @@ def backward(variant: int, q, k, v, q_head_logits, k_head_logits, log_decay, d_o
     if int(segments) == 0:
         cus = torch.cuda.get_device_properties(q.device).multi_processor_count
         params.segments = max(sla_backward_segments(params, cus), 1)
-    need = sla_backward_workspace_bytes(params)
+    need = sla_backward_chunks_workspace_bytes(params)
     if workspace is None:
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
     ptr = lambda t: None if t is None else t.data_ptr()

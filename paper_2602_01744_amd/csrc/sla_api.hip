@@ -17,6 +17,14 @@ size_t backward_workspace_floats(const sla_params& p, bool packed);
 int launch_backward(const sla_params& p, const void* q, const void* k, const void* v, const float* ql, const float* kl,
                     const void* ld, const float* s0, const void* dout, const float* dsf, void* dq, void* dk, void* dv,
                     float* dql, float* dkl, void* dld, float* ds0, float* ws, const int* cu, hipStream_t stream);
+// The chunk-parallel schedule (sla_chunk_backward.hip).  Weak: the host-side checks also link without the kernels that
+// schedules were added with, and run the ones they know then.
+__attribute__((weak)) bool backward_chunks_fit(const sla_params& p, bool packed, size_t workspace_floats);
+__attribute__((weak)) int launch_backward_chunks(const sla_params& p, const void* q, const void* k, const void* v,
+                                                 const float* ql, const float* kl, const void* ld, const float* s0,
+                                                 const void* dout, const float* dsf, void* dq, void* dk, void* dv,
+                                                 float* dql, float* dkl, void* dld, float* ds0, float* ws, size_t floats,
+                                                 const int* cu, bool packed, hipStream_t stream);
 size_t backward_segment_extra_floats(const sla_params& p, int nseg);
 sla_params packed_segments(const sla_params& p, int nseg);
 int launch_backward_segments(const sla_params& p, int nseg, int seg_len, int dvw, const void* q, const void* k,
@@ -404,8 +412,14 @@ static int backward_impl(const sla_params* p, const void* q, const void* k, cons
     if (!workspace || backward_floats(run, packed) * sizeof(float) > workspace_bytes) return SLA_ERR_WORKSPACE;
     int seg_len = 0;
     const int nseg = backward_segments(*p, packed, &seg_len);
+    if (nseg > 1 && p->flags != 0) return SLA_ERR_UNSUPPORTED;  // the segments run as a packed batch: [B,T,H,d] only
+    // bf16 tensors: chunk-parallel where the workspace allows it
+    if (sla::backward_chunks_fit && sla::backward_chunks_fit(*p, packed, workspace_bytes / sizeof(float)))
+        return sla::launch_backward_chunks(*p, q, k, v, q_head_logits, k_head_logits, log_decay, initial_state, d_out,
+                                           d_final_state, dq, dk, dv, dq_head_logits, dk_head_logits, dlog_decay,
+                                           d_initial_state, (float*)workspace, workspace_bytes / sizeof(float),
+                                           packed ? cu : nullptr, packed, (hipStream_t)stream);
     if (nseg > 1) {
-        if (p->flags != 0) return SLA_ERR_UNSUPPORTED;  // the segments run as a packed batch: [B,T,H,d] only
         return sla::launch_backward_segments(*p, nseg, seg_len, 64, q, k, v, q_head_logits, k_head_logits, log_decay,
                                              initial_state, d_out, d_final_state, dq, dk, dv, dq_head_logits,
                                              dk_head_logits, dlog_decay, d_initial_state, (float*)workspace,

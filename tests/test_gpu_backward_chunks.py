@@ -1,0 +1,80 @@
+"""GPU parity of the chunk-parallel backward of RetNet and GLA on bf16 tensors (sla_backward with the workspace that
+sla_backward_chunks_workspace_bytes asks for), at the edges of its 64-token chunks and 16-token blocks, for every key
+width's split over the waves, against the gradient oracle; and the schedules it can run in against each other.
+Tolerance: the bf16 bar of test_gpu_backward.py."""
+import numpy as np
+import pytest
+
+import sla_inputs as si
+from gpu_util import GLA, RETNET
+from test_gpu_backward import check_backward
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("variant", [RETNET, GLA])
+@pytest.mark.parametrize("T,dk,dv", [(1, 128, 128), (15, 64, 64), (16, 32, 64), (17, 128, 64), (33, 64, 128), (48, 32, 256),
+                                     (63, 128, 256), (64, 64, 64), (65, 128, 128), (80, 32, 128), (129, 64, 256), (191, 128, 128)])
+def test_edges_of_chunks_and_blocks(variant, T, dk, dv):
+    d = si.custom(variant, "bf16", B=2, T=T, H=3, dk=dk, dv=dv, seed=3000 + T)
+    cot = si.cotangents(2, T, 3, dk, dv, seed=3001 + T, final_state=True)
+    check_backward(variant, d, cot, si.initial_state(2, 3, dk, dv, seed=3002 + T), want_ds0=True, label=f"chunks T={T} {dk}x{dv}")
+
+
+def _tensors(variant, B, T, H, dk, dv, seed):
+    import torch
+
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    n = lambda *s: torch.randn(s, generator=g, device="cuda")
+    q, k = ((n(B, T, H, dk) * dk ** -0.5).bfloat16() for _ in range(2))
+    v, do = n(B, T, H, dv).bfloat16(), n(B, T, H, dv).bfloat16()
+    ld = (torch.nn.functional.logsigmoid(n(B, T, H, dk)) / 16).bfloat16() if variant == GLA else -0.02 * torch.arange(1, H + 1, device="cuda")
+    return q, k, v, n(B, T, H), n(B, T, H), ld.contiguous(), do
+
+
+@pytest.mark.parametrize("variant,B,T,H,dk,dv", [(GLA, 3, 1500, 24, 128, 128), (RETNET, 40, 130, 24, 64, 128), (GLA, 1, 2048, 20, 128, 256)])
+def test_parts_give_the_same_bits(variant, B, T, H, dk, dv):
+    """A workspace too small for the states of the whole batch: the call works it off in parts (whole rows, or heads of one
+    row), each result exactly as in one part.  The smallest workspace of all runs the sweeps, to the bf16 bar."""
+    import torch
+    import paper_2602_01744_amd as sla
+
+    x = _tensors(variant, B, T, H, dk, dv, seed=3100)
+    p = sla.SlaParams(variant, sla.BF16, B, T, H, dk, dv, 0, 0, 1)
+    want, least = sla.sla_backward_chunks_workspace_bytes(p), 4 * 4 * B * T * H + (64 << 20)
+    assert least < want  # the shape has more states than the smallest part's 64 MiB
+    whole = sla.backward(variant, *x)
+    parts = sla.backward(variant, *x, workspace=torch.empty(least, dtype=torch.uint8, device="cuda"))
+    sweeps = sla.backward(variant, *x, workspace=torch.empty(min(sla.sla_backward_workspace_bytes(p), least - 16), dtype=torch.uint8, device="cuda"))
+    for n, t in whole.items():
+        if t is not None:
+            assert torch.equal(t, parts[n]), n
+            rel = ((t.double() - sweeps[n].double()).norm() / sweeps[n].double().norm()).item()
+            assert rel <= (4e-2 if n == "dlog_decay" else 2e-2), (n, rel)  # the bar of each side
+
+
+@pytest.mark.parametrize("variant", [RETNET, GLA])
+def test_layouts_and_packing_give_the_same_bits(variant):
+    """[B,H,T,d] tensors, and the rows as a packed batch with empty sequences in between, against the rectangular call."""
+    import torch
+    import paper_2602_01744_amd as sla
+
+    B, T, H, dk, dv = 3, 201, 5, 128, 128
+    q, k, v, ql, kl, ld, do = _tensors(variant, B, T, H, dk, dv, seed=3200)
+    ref = sla.backward(variant, q, k, v, ql, kl, ld, do, want_d_initial_state=True)
+    hm = lambda t: t.transpose(1, 2).contiguous()
+    got = sla.backward(variant, hm(q), hm(k), hm(v), ql, kl, hm(ld) if variant == GLA else ld, hm(do), head_major=True,
+                       want_d_initial_state=True)
+    for n, t in ref.items():
+        if t is not None:
+            assert torch.equal(t, got[n] if t.dim() == 3 or n == "d_initial_state" else got[n].transpose(1, 2)), n
+    flat = lambda t: t.reshape(B * T, *t.shape[2:])
+    cu = torch.tensor([0, 0, T, 2 * T, 2 * T, 2 * T, 3 * T], dtype=torch.int32, device="cuda")
+    got = sla.backward_varlen(variant, flat(q), flat(k), flat(v), flat(ql), flat(kl), flat(ld) if variant == GLA else ld,
+                              flat(do), cu, want_d_initial_state=True)
+    for n, t in ref.items():
+        if n == "d_initial_state":
+            assert torch.equal(t, got[n][[1, 2, 5]]) and not got[n][[0, 3, 4]].any()
+        elif t is not None:
+            assert torch.equal(flat(t), got[n]), n
