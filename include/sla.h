@@ -395,6 +395,10 @@ size_t sla_gate_logits_backward_workspace_bytes(const sla_params* p);
 /* Bytes of workspace sla_forward_ws wants for *p on a device with that many compute units (0: none needed). */
 size_t sla_workspace_bytes(const sla_params* p, int compute_units);
 
+/* Bytes with which sla_forward_ws runs fastest (>= sla_workspace_bytes, 0 where that is 0): its pre-pass may then cut the
+ * segments into shorter pieces, so that it too has a workgroup for every compute unit. */
+size_t sla_forward_workspace_bytes(const sla_params* p, int compute_units);
+
 /* Number of segments the library would choose for *p given a workspace (>= 1); <0 on error. */
 int sla_segments(const sla_params* p, int compute_units);
 

@@ -109,6 +109,8 @@ def load_library():
     lib.sla_backward_workspace_bytes.argtypes = [pp]
     lib.sla_backward_chunks_workspace_bytes.restype = ctypes.c_size_t
     lib.sla_backward_chunks_workspace_bytes.argtypes = [pp, ctypes.c_int]
+    lib.sla_forward_workspace_bytes.restype = ctypes.c_size_t
+    lib.sla_forward_workspace_bytes.argtypes = [pp, ctypes.c_int]
     lib.sla_workspace_bytes.restype = ctypes.c_size_t
     lib.sla_workspace_bytes.argtypes = [pp, ctypes.c_int]
     lib.sla_segments.restype = ctypes.c_int
@@ -156,6 +158,10 @@ def sla_default_dv_split(params: SlaParams, compute_units: int) -> int:
 
 def sla_workspace_bytes(params: SlaParams, compute_units: int) -> int:
     return int(load_library().sla_workspace_bytes(ctypes.byref(params), int(compute_units)))
+
+
+def sla_forward_workspace_bytes(params: SlaParams, compute_units: int) -> int:
+    return int(load_library().sla_forward_workspace_bytes(ctypes.byref(params), int(compute_units)))
 
 
 def sla_segments(params: SlaParams, compute_units: int) -> int:
@@ -749,7 +755,8 @@ def forward(
 
     segments = 1 runs one fused pass (sla_forward).  segments = 0 lets the library choose the
     segment-parallel schedule, segments > 1 asks for that many segments (sla_forward_ws); the workspace
-    is then taken from ``workspace`` (a CUDA tensor of at least sla_workspace_bytes bytes) or allocated here.
+    is then taken from ``workspace`` (a CUDA tensor of at least sla_workspace_bytes bytes; sla_forward_workspace_bytes of them run
+    fastest) or allocated here.
 
     head_major = True: q, k, v (and the GLA log_decay, and the returned out) are [B,H,T,d] (SLA_FLAG_HEAD_MAJOR)."""
     import torch
@@ -784,7 +791,7 @@ def forward(
             ptr(initial_state), ptr(out), ptr(final_state), stream,
         )
     else:
-        need = sla_workspace_bytes(params, _compute_units(q.device))
+        need = sla_forward_workspace_bytes(params, _compute_units(q.device))
         if workspace is None and need > 0:
             workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
         ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()

@@ -9,10 +9,11 @@
 #include "sla.h"
 
 namespace sla {
-int launch_forward(const sla_params& p, int dvw, int nseg, int seg_len, const void* q, const void* k, const void* v,
+int launch_forward(const sla_params& p, int dvw, int nseg, int seg_len, int pieces, const void* q, const void* k, const void* v,
                    const float* ql, const float* kl, const void* ld, const float* beta, const float* s0, void* out,
                    float* sT, float* workspace, const int* cu, hipStream_t stream);
 size_t segment_workspace_floats(const sla_params& p, int nseg);
+size_t piece_workspace_floats(const sla_params& p, int npiece);
 size_t backward_workspace_floats(const sla_params& p, bool packed);
 int launch_backward(const sla_params& p, const void* q, const void* k, const void* v, const float* ql, const float* kl,
                     const void* ld, const float* s0, const void* dout, const float* dsf, void* dq, void* dk, void* dv,
@@ -200,6 +201,28 @@ int choose_segments(const sla_params& p, int cus, int* seg_len) {
     return nseg;
 }
 
+// Pieces per segment of the pre-pass.  It covers nseg - 1 of nseg segments: with one workgroup for each, 1 / nseg of the
+// compute units have nothing to do.  More pieces than compute units run in rounds; a round costs about kRound tokens besides
+// its own.  Pieces are whole blocks and as long as segments have to be.  The pre-pass of B=1 T=65536 H=32 128 x 128 GLA (4
+// segments) takes 346 us in 4 pieces each against 419 (memory has 4.7 of the 5.3 TB/s then), of B=8 T=4096 H=4 128 x 256 (2)
+// in 2 pieces 29 against 45; cutting B=4 T=2048 H=8 (4 segments of 512), whose 2 pieces would run in 2 rounds, gains nothing.
+int choose_pieces(const sla_params& p, int cus, int nseg, int seg_len, int dvw) {
+    constexpr int64_t kRound = 128, kMostPieces = 8;
+    if (nseg <= 1) return 1;
+    const int64_t rows = (int64_t)p.B * p.H * (p.dv / dvw) * (nseg - 1);
+    int best = 1;
+    int64_t least = 0;
+    for (int m = 1; m <= kMostPieces; ++m) {
+        if (m > 1 && (seg_len % (16 * m) != 0 || seg_len / m < kMinSegment)) continue;
+        const int64_t cost = (rows * m + cus - 1) / cus * (seg_len / m + kRound);
+        if (m == 1 || cost < least) {
+            least = cost;
+            best = m;
+        }
+    }
+    return best;
+}
+
 int choose_dv_split(const sla_params& p, int cus, int nseg = 1) {
     if (p.dv_split != 0) return p.dv_split;
     // The widest slice that still gives every compute unit a workgroup; narrower slices repeat the
@@ -211,6 +234,11 @@ int choose_dv_split(const sla_params& p, int cus, int nseg = 1) {
         if (seqs * (p.dv / w) >= cus) return w;
     }
     return 16;
+}
+
+bool pieces_fit(const sla_params& p, int nseg, int pieces, size_t bytes) {
+    if (pieces == 1) return true;
+    return (sla::segment_workspace_floats(p, nseg) + sla::piece_workspace_floats(p, (nseg - 1) * pieces)) * sizeof(float) <= bytes;
 }
 
 }  // namespace
@@ -249,7 +277,9 @@ int sla_forward_ws(const sla_params* p, const void* q, const void* k, const void
         seg_len = p->T;
     }
     const int dvw = choose_dv_split(*p, cus, nseg);
-    return sla::launch_forward(*p, dvw, nseg, seg_len, q, k, v, q_head_logits, k_head_logits, log_decay, beta,
+    int pieces = choose_pieces(*p, cus, nseg, seg_len, dvw);
+    if (!pieces_fit(*p, nseg, pieces, workspace_bytes)) pieces = 1;
+    return sla::launch_forward(*p, dvw, nseg, seg_len, pieces, q, k, v, q_head_logits, k_head_logits, log_decay, beta,
                                initial_state, out, final_state, (float*)workspace, nullptr, (hipStream_t)stream);
 }
 
@@ -302,7 +332,9 @@ int sla_forward_static(const sla_params* p, const void* q, const void* k, const 
         if (!ws) return SLA_ERR_HIP;
     }
     const int dvw = choose_dv_split(*p, cus, nseg);
-    return sla::launch_forward(*p, dvw, nseg, seg_len, q, k, v, q_head_logits, k_head_logits, log_decay, beta,
+    int pieces = choose_pieces(*p, cus, nseg, seg_len, dvw);
+    if (!pieces_fit(*p, nseg, pieces, SLA_STATIC_SCRATCH_BYTES)) pieces = 1;
+    return sla::launch_forward(*p, dvw, nseg, seg_len, pieces, q, k, v, q_head_logits, k_head_logits, log_decay, beta,
                                initial_state, out, final_state, ws, nullptr, (hipStream_t)stream);
 }
 
@@ -320,7 +352,7 @@ int sla_forward_varlen(const sla_params* p, const void* q, const void* k, const 
     const int cus = device_compute_units();
     if (cus <= 0) return SLA_ERR_HIP;
     const int dvw = choose_dv_split(*p, cus, 1);
-    return sla::launch_forward(*p, dvw, 1, p->T, q, k, v, q_head_logits, k_head_logits, log_decay, beta, initial_state,
+    return sla::launch_forward(*p, dvw, 1, p->T, 1, q, k, v, q_head_logits, k_head_logits, log_decay, beta, initial_state,
                                out, final_state, nullptr, p->T == 0 ? nullptr : cu_seqlens, (hipStream_t)stream);
 }
 
@@ -625,6 +657,15 @@ size_t sla_workspace_bytes(const sla_params* p, int compute_units) {
     int seg_len = 0;
     const int nseg = choose_segments(*p, compute_units, &seg_len);
     return sla::segment_workspace_floats(*p, nseg) * sizeof(float);
+}
+
+size_t sla_forward_workspace_bytes(const sla_params* p, int compute_units) {
+    const size_t least = sla_workspace_bytes(p, compute_units);
+    if (least == 0) return 0;
+    int seg_len = 0;
+    const int nseg = choose_segments(*p, compute_units, &seg_len);
+    const int pieces = choose_pieces(*p, compute_units, nseg, seg_len, choose_dv_split(*p, compute_units, nseg));
+    return least + (pieces > 1 ? sla::piece_workspace_floats(*p, (nseg - 1) * pieces) * sizeof(float) : 0);
 }
 
 int sla_backward_segments(const sla_params* p, int compute_units) {

@@ -30,6 +30,12 @@ struct KArgs {
     int nparts;  // producer waves of the pre-pass: partial decay products per segment in ws_decay
     float* ws_state;
     float* ws_decay;
+    // The pre-pass covers one segment less than the main pass and would leave compute units idle: it may cut each segment
+    // into `pieces` of equal length, whose end states and decays lie in areas of their own, laid out as those of npiece + 1
+    // segments.  pieces == 1: the segments themselves, in ws_state and ws_decay.
+    int pieces;
+    float* piece_state;
+    float* piece_decay;
     // Used by the backward pass's segment schedule, which wants only what the pre-pass and the combine kernel
     // produce: the entry state of every segment (ws_state) and, in ws_total[b][s][h][dk], the total decay of each
     // segment but the last.  states_only stops the call after the combine kernel.

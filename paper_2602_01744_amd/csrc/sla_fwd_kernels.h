@@ -1264,9 +1264,10 @@ static int launch_one(const KArgs& a, hipStream_t stream) {
 
 // Segment combine (between the pre-pass and the main pass of the segment-parallel schedule):
 //   E_0 = initial state,  E_{s+1} = diag(D_s) E_s + L_s,
-// with L_s the end state of segment s from a zero entry state (the pre-pass left it in slot s + 1) and
-// D_s its total decay.  Slot s ends up holding E_s.  One thread per (batch, head, d, 4 value columns).
-template <int VAR>
+// with L_s the end state of piece s of the pre-pass from a zero entry state (left in the pieces' slot s + 1) and
+// D_s its total decay.  Slot s of the segments ends up holding the state entering segment s; where every piece is a segment
+// the two areas are one (CUT: they are not).  One thread per (batch, head, d, 4 value columns).
+template <int VAR, bool CUT>
 __global__ void sla_segment_combine_kernel(const KArgs a, int dk) {
     const int dv4 = a.dv / 4;
     const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -1282,16 +1283,19 @@ __global__ void sla_segment_combine_kernel(const KArgs a, int dk) {
     // costs a memory latency per four segments and not two for each (B=4 H=8 d=128, 4 segments: 5.3 -> 4.9 us; B=8
     // H=4 128 x 256 GLA 9.8 -> 6.8 us; B=1 T=65536 H=32 GLA 12.0 -> 5.9 us).
     constexpr int kAtOnce = 4;
-    for (int s0 = 0; s0 + 1 < a.nseg; s0 += kAtOnce) {
+    const int pieces = CUT ? a.pieces : 1, np = (a.nseg - 1) * pieces;
+    const float len = (float)(CUT ? a.Ls / pieces : a.Ls);
+    [[maybe_unused]] int in_seg = 0, seg = 0;
+    for (int s0 = 0; s0 < np; s0 += kAtOnce) {
         f32x4 Lseg[kAtOnce];
         float D[kAtOnce];
-        auto slot = [&](int s) { return (f32x4*)(a.ws_state + ((size_t)(b * a.nseg + s + 1) * a.H + h) * head_sz + off); };
+        auto slot = [&](int s) { return (f32x4*)(a.piece_state + ((size_t)(b * (np + 1) + s + 1) * a.H + h) * head_sz + off); };
 #pragma unroll
         for (int u = 0; u < kAtOnce; ++u) {
-            const int s = min(s0 + u, a.nseg - 2);
+            const int s = min(s0 + u, np - 1);
             Lseg[u] = *slot(s);
             if constexpr (VAR == SLA_GLA) {
-                const float* dp = a.ws_decay + ((size_t)(b * (a.nseg - 1) + s) * a.H + h) * kMaxSlots * dk + d;
+                const float* dp = a.piece_decay + ((size_t)(b * np + s) * a.H + h) * kMaxSlots * dk + d;
                 float part[kMaxSlots];
 #pragma unroll
                 for (int w = 0; w < kMaxSlots; ++w) part[w] = dp[min(w, a.nparts - 1) * dk];
@@ -1299,17 +1303,23 @@ __global__ void sla_segment_combine_kernel(const KArgs a, int dk) {
 #pragma unroll
                 for (int w = 0; w < kMaxSlots; ++w) D[u] *= w < a.nparts ? part[w] : 1.f;
             } else {
-                D[u] = fast_exp2(((const float*)a.ld)[h] * kLog2e * (float)a.Ls);  // segments before the last are full
+                D[u] = fast_exp2(((const float*)a.ld)[h] * kLog2e * len);  // segments before the last are full
             }
         }
 #pragma unroll
         for (int u = 0; u < kAtOnce; ++u) {
             const int s = s0 + u;
-            if (s + 1 >= a.nseg) break;
+            if (s >= np) break;
             if (a.ws_total && n == 0) a.ws_total[((size_t)(b * (a.nseg - 1) + s) * a.H + h) * dk + d] = D[u];
 #pragma unroll
             for (int i = 0; i < 4; ++i) E[i] = D[u] * E[i] + Lseg[u][i];
-            *slot(s) = E;
+            if constexpr (CUT) {
+                if (++in_seg < pieces) continue;
+                in_seg = 0;
+                *(f32x4*)(a.ws_state + ((size_t)(b * a.nseg + ++seg) * a.H + h) * head_sz + off) = E;
+            } else {
+                *slot(s) = E;
+            }
         }
     }
 }
@@ -1321,14 +1331,26 @@ static int launch(const KArgs& a, hipStream_t stream) {
     if constexpr (VAR == SLA_GDN) {
         return SLA_ERR_UNSUPPORTED;  // the delta rule's segment transition is a dense matrix; not built
     } else {
-        KArgs pre = a;
-        pre.nseg_grid = a.nseg - 1;
         KArgs mid = a;
+        if (a.pieces == 1) {
+            mid.piece_state = a.ws_state;
+            mid.piece_decay = a.ws_decay;
+        }
+        KArgs pre = mid;  // the pieces take the place of the segments
+        pre.nseg_grid = (a.nseg - 1) * a.pieces;
+        pre.nseg = pre.nseg_grid + 1;
+        pre.Ls = a.Ls / a.pieces;
+        pre.ws_state = mid.piece_state;
+        pre.ws_decay = mid.piece_decay;
         mid.nparts = Smem<P, VAR, DK, DVW>::slots;
         int rc = launch_one<P, VAR, DK, DVW, HG, true>(pre, stream);
         if (rc != SLA_OK) return rc;
         const size_t n = (size_t)a.B * a.H * DK * (a.dv / 4);
-        hipLaunchKernelGGL(sla_segment_combine_kernel<VAR>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, mid, DK);
+        const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+        if (a.pieces > 1)
+            hipLaunchKernelGGL((sla_segment_combine_kernel<VAR, true>), grid, block, 0, stream, mid, DK);
+        else
+            hipLaunchKernelGGL((sla_segment_combine_kernel<VAR, false>), grid, block, 0, stream, mid, DK);
         if (hipGetLastError() != hipSuccess) return SLA_ERR_HIP;
         if (a.states_only) return SLA_OK;
         return launch_one<P, VAR, DK, DVW, HG, false>(a, stream);

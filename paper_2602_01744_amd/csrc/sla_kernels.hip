@@ -25,7 +25,13 @@ size_t segment_workspace_floats(const sla_params& p, int nseg) {
     return heads * nseg * p.dk * p.dv + heads * (nseg - 1) * kMaxSlots * p.dk;  // entry states, decay products
 }
 
-int launch_forward(const sla_params& p, int dvw, int nseg, int seg_len, const void* q, const void* k, const void* v,
+// Further floats for a pre-pass that works on npiece pieces instead.
+size_t piece_workspace_floats(const sla_params& p, int npiece) {
+    const size_t heads = (size_t)p.B * p.H;
+    return heads * (npiece + 1) * p.dk * p.dv + heads * npiece * kMaxSlots * p.dk;
+}
+
+int launch_forward(const sla_params& p, int dvw, int nseg, int seg_len, int pieces, const void* q, const void* k, const void* v,
                    const float* ql, const float* kl, const void* ld, const float* beta, const float* s0, void* out,
                    float* sT, float* workspace, const int* cu, hipStream_t stream) {
     KArgs a;
@@ -35,6 +41,12 @@ int launch_forward(const sla_params& p, int dvw, int nseg, int seg_len, const vo
     a.nseg = nseg; a.nseg_grid = nseg; a.nparts = 0; a.Ls = nseg > 1 ? seg_len : p.T;
     a.ws_state = workspace;
     a.ws_decay = workspace ? workspace + (size_t)p.B * nseg * p.H * p.dk * p.dv : nullptr;
+    a.pieces = pieces;
+    a.piece_state = a.piece_decay = nullptr;
+    if (pieces > 1) {
+        a.piece_state = workspace + segment_workspace_floats(p, nseg);
+        a.piece_decay = a.piece_state + (size_t)p.B * ((nseg - 1) * pieces + 1) * p.H * p.dk * p.dv;
+    }
     a.ws_total = nullptr;
     a.states_only = false;
     a.cu = cu;
@@ -66,6 +78,8 @@ int launch_segment_states(const sla_params& p, int dvw, int nseg, int seg_len, c
     a.nseg = nseg; a.nseg_grid = nseg; a.nparts = 0; a.Ls = seg_len;
     a.ws_state = workspace;
     a.ws_decay = workspace + (size_t)p.B * nseg * p.H * p.dk * p.dv;
+    a.pieces = 1;
+    a.piece_state = a.piece_decay = nullptr;
     a.ws_total = totals;
     a.states_only = true;
     a.cu = nullptr;
