@@ -7,13 +7,18 @@
 #include <mutex>
 
 #include "sla.h"
+#include "sla_fwd_args.h"
 
 namespace sla {
-int launch_forward(const sla_params& p, int dvw, int nseg, int seg_len, int pieces, const void* q, const void* k, const void* v,
+int launch_forward(const sla_params& p, int dvw, int nseg, int seg_len, const void* q, const void* k, const void* v,
                    const float* ql, const float* kl, const void* ld, const float* beta, const float* s0, void* out,
                    float* sT, float* workspace, const int* cu, hipStream_t stream);
+// Weak, as launch_backward_chunks below.
+__attribute__((weak)) int launch_forward_pieces(const sla_params& p, int dvw, int nseg, int seg_len, int pieces,
+                                                const void* q, const void* k, const void* v, const float* ql,
+                                                const float* kl, const void* ld, const float* beta, const float* s0,
+                                                void* out, float* sT, float* workspace, const int* cu, hipStream_t stream);
 size_t segment_workspace_floats(const sla_params& p, int nseg);
-size_t piece_workspace_floats(const sla_params& p, int npiece);
 size_t backward_workspace_floats(const sla_params& p, bool packed);
 int launch_backward(const sla_params& p, const void* q, const void* k, const void* v, const float* ql, const float* kl,
                     const void* ld, const float* s0, const void* dout, const float* dsf, void* dq, void* dk, void* dv,
@@ -236,9 +241,11 @@ int choose_dv_split(const sla_params& p, int cus, int nseg = 1) {
     return 16;
 }
 
+size_t piece_floats(const sla_params& p, int nseg, int pieces) {
+    return pieces > 1 ? sla::piece_workspace_floats((size_t)p.B * p.H, (nseg - 1) * pieces, p.dk, p.dv) : 0;
+}
 bool pieces_fit(const sla_params& p, int nseg, int pieces, size_t bytes) {
-    if (pieces == 1) return true;
-    return (sla::segment_workspace_floats(p, nseg) + sla::piece_workspace_floats(p, (nseg - 1) * pieces)) * sizeof(float) <= bytes;
+    return (sla::segment_workspace_floats(p, nseg) + piece_floats(p, nseg, pieces)) * sizeof(float) <= bytes;
 }
 
 }  // namespace
@@ -277,9 +284,11 @@ int sla_forward_ws(const sla_params* p, const void* q, const void* k, const void
         seg_len = p->T;
     }
     const int dvw = choose_dv_split(*p, cus, nseg);
-    int pieces = choose_pieces(*p, cus, nseg, seg_len, dvw);
-    if (!pieces_fit(*p, nseg, pieces, workspace_bytes)) pieces = 1;
-    return sla::launch_forward(*p, dvw, nseg, seg_len, pieces, q, k, v, q_head_logits, k_head_logits, log_decay, beta,
+    const int pieces = choose_pieces(*p, cus, nseg, seg_len, dvw);
+    if (pieces > 1 && sla::launch_forward_pieces && pieces_fit(*p, nseg, pieces, workspace_bytes))
+        return sla::launch_forward_pieces(*p, dvw, nseg, seg_len, pieces, q, k, v, q_head_logits, k_head_logits, log_decay,
+                                          beta, initial_state, out, final_state, (float*)workspace, nullptr, (hipStream_t)stream);
+    return sla::launch_forward(*p, dvw, nseg, seg_len, q, k, v, q_head_logits, k_head_logits, log_decay, beta,
                                initial_state, out, final_state, (float*)workspace, nullptr, (hipStream_t)stream);
 }
 
@@ -332,9 +341,11 @@ int sla_forward_static(const sla_params* p, const void* q, const void* k, const 
         if (!ws) return SLA_ERR_HIP;
     }
     const int dvw = choose_dv_split(*p, cus, nseg);
-    int pieces = choose_pieces(*p, cus, nseg, seg_len, dvw);
-    if (!pieces_fit(*p, nseg, pieces, SLA_STATIC_SCRATCH_BYTES)) pieces = 1;
-    return sla::launch_forward(*p, dvw, nseg, seg_len, pieces, q, k, v, q_head_logits, k_head_logits, log_decay, beta,
+    const int pieces = choose_pieces(*p, cus, nseg, seg_len, dvw);
+    if (pieces > 1 && sla::launch_forward_pieces && pieces_fit(*p, nseg, pieces, SLA_STATIC_SCRATCH_BYTES))
+        return sla::launch_forward_pieces(*p, dvw, nseg, seg_len, pieces, q, k, v, q_head_logits, k_head_logits, log_decay,
+                                          beta, initial_state, out, final_state, ws, nullptr, (hipStream_t)stream);
+    return sla::launch_forward(*p, dvw, nseg, seg_len, q, k, v, q_head_logits, k_head_logits, log_decay, beta,
                                initial_state, out, final_state, ws, nullptr, (hipStream_t)stream);
 }
 
@@ -352,7 +363,7 @@ int sla_forward_varlen(const sla_params* p, const void* q, const void* k, const 
     const int cus = device_compute_units();
     if (cus <= 0) return SLA_ERR_HIP;
     const int dvw = choose_dv_split(*p, cus, 1);
-    return sla::launch_forward(*p, dvw, 1, p->T, 1, q, k, v, q_head_logits, k_head_logits, log_decay, beta, initial_state,
+    return sla::launch_forward(*p, dvw, 1, p->T, q, k, v, q_head_logits, k_head_logits, log_decay, beta, initial_state,
                                out, final_state, nullptr, p->T == 0 ? nullptr : cu_seqlens, (hipStream_t)stream);
 }
 
@@ -665,7 +676,7 @@ size_t sla_forward_workspace_bytes(const sla_params* p, int compute_units) {
     int seg_len = 0;
     const int nseg = choose_segments(*p, compute_units, &seg_len);
     const int pieces = choose_pieces(*p, compute_units, nseg, seg_len, choose_dv_split(*p, compute_units, nseg));
-    return least + (pieces > 1 ? sla::piece_workspace_floats(*p, (nseg - 1) * pieces) * sizeof(float) : 0);
+    return least + piece_floats(*p, nseg, pieces) * sizeof(float);
 }
 
 int sla_backward_segments(const sla_params* p, int compute_units) {

@@ -52,4 +52,9 @@ struct KArgs {
     unsigned int* status;
 };
 
+// Floats that a pre-pass on npiece pieces wants besides the segments' own: end states and decay products.
+inline size_t piece_workspace_floats(size_t heads, int npiece, int dk, int dv) {
+    return heads * (npiece + 1) * dk * dv + heads * npiece * kMaxSlots * dk;
+}
+
 }  // namespace sla

@@ -25,13 +25,8 @@ size_t segment_workspace_floats(const sla_params& p, int nseg) {
     return heads * nseg * p.dk * p.dv + heads * (nseg - 1) * kMaxSlots * p.dk;  // entry states, decay products
 }
 
-// Further floats for a pre-pass that works on npiece pieces instead.
-size_t piece_workspace_floats(const sla_params& p, int npiece) {
-    const size_t heads = (size_t)p.B * p.H;
-    return heads * (npiece + 1) * p.dk * p.dv + heads * npiece * kMaxSlots * p.dk;
-}
-
-int launch_forward(const sla_params& p, int dvw, int nseg, int seg_len, int pieces, const void* q, const void* k, const void* v,
+// pieces > 1: the workspace also has piece_workspace_floats().
+int launch_forward_pieces(const sla_params& p, int dvw, int nseg, int seg_len, int pieces, const void* q, const void* k, const void* v,
                    const float* ql, const float* kl, const void* ld, const float* beta, const float* s0, void* out,
                    float* sT, float* workspace, const int* cu, hipStream_t stream) {
     KArgs a;
@@ -60,6 +55,12 @@ int launch_forward(const sla_params& p, int dvw, int nseg, int seg_len, int piec
     }
     if (p.dtype == SLA_BF16) return dispatch_forward_bf16(a, p.variant, p.dk, dvw, stream);
     return dispatch_forward_f32(a, p.variant, p.dk, dvw, stream);
+}
+
+int launch_forward(const sla_params& p, int dvw, int nseg, int seg_len, const void* q, const void* k, const void* v,
+                   const float* ql, const float* kl, const void* ld, const float* beta, const float* s0, void* out,
+                   float* sT, float* workspace, const int* cu, hipStream_t stream) {
+    return launch_forward_pieces(p, dvw, nseg, seg_len, 1, q, k, v, ql, kl, ld, beta, s0, out, sT, workspace, cu, stream);
 }
 
 // The first two steps of the segment-parallel schedule alone (RetNet, GLA; nseg >= 2; rectangular batch): on return
