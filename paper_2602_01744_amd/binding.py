@@ -109,6 +109,8 @@ def load_library():
     lib.sla_backward_workspace_bytes.argtypes = [pp]
     lib.sla_backward_chunks_workspace_bytes.restype = ctypes.c_size_t
     lib.sla_backward_chunks_workspace_bytes.argtypes = [pp, ctypes.c_int]
+    lib.sla_backward_gdn_chunks_workspace_bytes.restype = ctypes.c_size_t
+    lib.sla_backward_gdn_chunks_workspace_bytes.argtypes = [pp, ctypes.c_int]
     lib.sla_forward_workspace_bytes.restype = ctypes.c_size_t
     lib.sla_forward_workspace_bytes.argtypes = [pp, ctypes.c_int]
     lib.sla_workspace_bytes.restype = ctypes.c_size_t
@@ -561,6 +563,10 @@ def sla_backward_gdn_workspace_bytes(params: SlaParams) -> int:
     return int(load_library().sla_backward_gdn_workspace_bytes(ctypes.byref(params)))
 
 
+def sla_backward_gdn_chunks_workspace_bytes(params: SlaParams, packed: bool = False) -> int:
+    return int(load_library().sla_backward_gdn_chunks_workspace_bytes(ctypes.byref(params), int(bool(packed))))
+
+
 def sla_backward_gdn(params, q, k, v, q_head_logits, k_head_logits, log_decay, beta, initial_state, d_out,
                      d_final_state, dq, dk, dv, dq_head_logits, dk_head_logits, dlog_decay, dbeta, d_initial_state,
                      workspace, workspace_bytes, stream) -> int:
@@ -618,7 +624,7 @@ def backward_gdn_varlen(q, k, v, q_head_logits, k_head_logits, log_decay, beta, 
         "d_initial_state": torch.empty((B, H, dk, dv), dtype=torch.float32, device=dev) if want_d_initial_state else None,
     }
     params = SlaParams(GDN, BF16 if q.dtype == torch.bfloat16 else F32, B, T, H, dk, dv, 0, 0, 1)
-    need = sla_backward_gdn_varlen_workspace_bytes(params)
+    need = sla_backward_gdn_chunks_workspace_bytes(params, packed=True)
     workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
     ptr = lambda t: None if t is None else t.data_ptr()
     rc = sla_backward_gdn_varlen(
@@ -661,7 +667,7 @@ def backward_gdn(q, k, v, q_head_logits, k_head_logits, log_decay, beta, d_out, 
         "d_initial_state": torch.empty((B, H, dk, dv), dtype=torch.float32, device=dev) if want_d_initial_state else None,
     }
     params = SlaParams(GDN, BF16 if q.dtype == torch.bfloat16 else F32, B, T, H, dk, dv, 0, 0, 1)
-    need = sla_backward_gdn_workspace_bytes(params)
+    need = sla_backward_gdn_chunks_workspace_bytes(params)
     if workspace is None:
         workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
     ptr = lambda t: None if t is None else t.data_ptr()

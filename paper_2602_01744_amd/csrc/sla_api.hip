@@ -31,6 +31,12 @@ __attribute__((weak)) int launch_backward_chunks(const sla_params& p, const void
                                                  const void* dout, const float* dsf, void* dq, void* dk, void* dv,
                                                  float* dql, float* dkl, void* dld, float* ds0, float* ws, size_t floats,
                                                  const int* cu, bool packed, hipStream_t stream);
+__attribute__((weak)) size_t backward_gdn_chunks_workspace_floats(const sla_params& p, bool packed);
+__attribute__((weak)) int launch_backward_gdn_chunks(const sla_params& p, const void* q, const void* k, const void* v,
+                                                     const float* ql, const float* kl, const float* ld, const float* beta,
+                                                     const float* s0, const void* dout, const float* dsf, void* dq, void* dk,
+                                                     void* dv, float* dql, float* dkl, float* dld, float* dbeta, float* ds0,
+                                                     float* ws, const int* cu, bool packed, hipStream_t stream);
 size_t backward_segment_extra_floats(const sla_params& p, int nseg);
 sla_params packed_segments(const sla_params& p, int nseg);
 int launch_backward_segments(const sla_params& p, int nseg, int seg_len, int dvw, const void* q, const void* k,
@@ -520,6 +526,13 @@ static int backward_gdn_impl(const sla_params* p, const void* q, const void* k, 
     if (p->T == 0 && !d_initial_state) return SLA_OK;
     if (p->T > 0 && (!workspace || sla::backward_gdn_any_workspace_floats(*p, packed) * sizeof(float) > workspace_bytes))
         return SLA_ERR_WORKSPACE;
+    // bf16 tensors: chunk-parallel where the workspace allows it
+    const size_t chunks = sla::backward_gdn_chunks_workspace_floats ? sla::backward_gdn_chunks_workspace_floats(*p, packed) : 0;
+    if (chunks > 0 && chunks * sizeof(float) <= workspace_bytes)
+        return sla::launch_backward_gdn_chunks(*p, q, k, v, q_head_logits, k_head_logits, log_decay, beta, initial_state,
+                                               d_out, d_final_state, dq, dk, dv, dq_head_logits, dk_head_logits, dlog_decay,
+                                               dbeta, d_initial_state, (float*)workspace, packed ? cu : nullptr, packed,
+                                               (hipStream_t)stream);
     return sla::launch_backward_gdn_any(*p, q, k, v, q_head_logits, k_head_logits, log_decay, beta, initial_state,
                                         d_out, d_final_state, dq, dk, dv, dq_head_logits, dk_head_logits, dlog_decay,
                                         dbeta, d_initial_state, (float*)workspace, packed && p->T > 0 ? cu : nullptr,

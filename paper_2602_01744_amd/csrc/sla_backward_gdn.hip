@@ -629,6 +629,14 @@ size_t backward_gdn_workspace_floats(const sla_params& p, bool packed) {
     return n * (3 + 2 * pv + pk) + round4(pk * p.B * p.H) + 2 * round4(rows * p.H * p.dv) + round4(rows * p.H * p.dk);
 }
 
+int launch_gdn_decay_scan(const float* e, const float* corr, int planes, int B, int T, int H, const int* cu,
+                          const float* phi, float* dld, hipStream_t stream) {
+    const unsigned spans = phi ? (unsigned)((T + kSpan - 1) / kSpan) : 1u;
+    hipLaunchKernelGGL(gdn_bwd_decay_scan_kernel, dim3((unsigned)(B * H), spans), dim3(kEw), 0, stream, e, corr, planes, B, T,
+                       H, cu, phi, dld);
+    return hipGetLastError() == hipSuccess ? SLA_OK : SLA_ERR_HIP;
+}
+
 int launch_backward_gdn(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
                         const float* kl, const float* ld, const float* beta, const float* s0, const void* dout,
                         const float* dsf, void* dq, void* dk, void* dv, float* dql, float* dkl, float* dld,
@@ -695,10 +703,8 @@ int launch_backward_gdn(const sla_params& p, const void* q, const void* k, const
     const unsigned per = kEw / (unsigned)p.H, eg = (unsigned)((rows + per - 1) / per);
     hipLaunchKernelGGL(gdn_bwd_finish_kernel, dim3(eg), dim3(kEw), 0, stream, a, pk, pv, dql, kl ? dkl : nullptr,
                        dbeta, e);
-    const unsigned spans = anchor_phi ? (unsigned)((p.T + kSpan - 1) / kSpan) : 1u;
-    hipLaunchKernelGGL(gdn_bwd_decay_scan_kernel, dim3((unsigned)(p.B * p.H), spans), dim3(kEw), 0, stream, (const float*)e,
-                       dsf ? (const float*)a.corr : nullptr, pk, p.B, p.T, p.H, cu, (const float*)anchor_phi, dld);
-    return hipGetLastError() == hipSuccess ? SLA_OK : SLA_ERR_HIP;
+    if (hipGetLastError() != hipSuccess) return SLA_ERR_HIP;
+    return launch_gdn_decay_scan(e, dsf ? a.corr : nullptr, pk, p.B, p.T, p.H, cu, anchor_phi, dld, stream);
 }
 
 }  // namespace sla

@@ -421,6 +421,16 @@ __device__ __forceinline__ void run_sweep(const Frame& f, unsigned char* smem, i
     }
 }
 
+// Chunk-parallel schedule: the state (or cotangent) at the boundary in hand, rows of DK elements per value column n.  The
+// wave's operand is kept as it is: lane (r, g) holds key dimensions 16 t + 4 g .. +3 and 16 (t + 1) + 4 g .. +3 of column n,
+// which go next to each other: group of four G of 32 dimensions sits at place 2 (G % 4) + G / 4.
+template <int DK, int DV>
+__device__ __forceinline__ void keep_state(bf* states, const Frame& f, int I, int n, int t, int g, s8 x) {
+    const size_t slot = (f.a.cu ? f.s.tok0 / kGdnChunk + f.s.b : (size_t)f.s.b * ((f.s.T + kGdnChunk - 1) / kGdnChunk)) + I / 2;
+    static_assert(kGdnChunk == 2 * C, "two blocks per chunk");
+    *(s8*)(states + ((slot * f.a.H + f.s.h) * DV + n) * DK + 16 * t + 8 * g) = x;
+}
+
 // ---- sweep 1: forward, S[dk, 16 value columns per wave] -> res ------------------------------------------------
 template <int DK>
 struct Stage1 {
@@ -451,13 +461,11 @@ struct Load1 {
     }
 };
 
-template <int DK, int DV>
-__global__ __launch_bounds__(kThreads) void gdn_blk_state_kernel(const GdnBlockArgs a, const Areas ar) {
+// KEEP: res leaves as rows, and the state entering every chunk is kept (see GdnBlockArgs).
+template <int DK, int DV, bool KEEP>
+__device__ __forceinline__ void state_sweep(const GdnBlockArgs& a, const Areas& ar, const Seq& s, unsigned char* smem) {
     typedef Stage1<DK> L;
     constexpr int NT = DK / 16, RKr = L::RKr, RKc = L::RKc;
-    extern __shared__ __align__(16) unsigned char smem[];
-    const Seq s = where(a, DV / kCols);
-    if (s.bh < 0) return;
     const Frame f{a, ar, s};
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3), r = lane & 15,
               g = lane >> 4;
@@ -482,6 +490,7 @@ __global__ __launch_bounds__(kThreads) void gdn_blk_state_kernel(const GdnBlockA
 #pragma unroll
             for (int t = 0; t < NT; t += 2) {
                 const s8 bS = pack8(S[t], S[t + 1]);
+                if (KEEP && (I & 1) == 0) keep_state<DK, DV>(a.keep_s, f, I, n, t, g, bS);
                 mma(X[0], op_rows(Kr, RKr, r, 16 * t, g), bS);
                 mma(X[1], op_rows(Kr, RKr, 16 + r, 16 * t, g), bS);
             }
@@ -491,14 +500,22 @@ __global__ __launch_bounds__(kThreads) void gdn_blk_state_kernel(const GdnBlockA
                 Rp[ta] = sc4(sc, kGk, 16 * ta + 4 * g) * tile_cols(Vs, kSlC, 16 * ta, 16 * w, r, g) -
                          sc4(sc, kP, 16 * ta + 4 * g) * X[ta];
             const s8 bR = pack8(Rp[0], Rp[1]);
-            bf* dst = ar.res + (f.bhi(I) * (size_t)DV + n) * C + 4 * g;
+            [[maybe_unused]] bf* dst = KEEP ? nullptr : ar.res + (f.bhi(I) * (size_t)DV + n) * C + 4 * g;
             f4 Up[2];
 #pragma unroll
             for (int ta = 0; ta < 2; ++ta) {
                 f4 rs = {0.f, 0.f, 0.f, 0.f};
-                mma(rs, op_rows(T1, kSmR, 16 * ta + r, 0, g), bR);
+                const s8 aT = op_rows(T1, kSmR, 16 * ta + r, 0, g);
+                mma(rs, aT, bR);
                 const u2 pk = pack4(rs);
-                *(u2*)(dst + 16 * ta) = pk;
+                if constexpr (KEEP) {  // the same product transposed: four adjacent columns of token 16 ta + r
+                    f4 rt = {0.f, 0.f, 0.f, 0.f};
+                    mma(rt, bR, aT);
+                    if (16 * ta + r < f.valid(I))
+                        *(u2*)(a.res_rows + ((f.row0(I) + 16 * ta + r) * a.H + s.h) * DV + s.slice * kCols + 16 * w + 4 * g) = pack4(rt);
+                } else {
+                    *(u2*)(dst + 16 * ta) = pk;
+                }
                 Up[ta] = sc4(sc, kBeta, 16 * ta + 4 * g) * sc4(sc, kAP, 16 * ta + 4 * g) * unpack4(pk);
             }
             const s8 bU = pack8(Up[0], Up[1]);
@@ -512,16 +529,26 @@ __global__ __launch_bounds__(kThreads) void gdn_blk_state_kernel(const GdnBlockA
         [&]() {});
 }
 
+template <int DK, int DV>
+__global__ __launch_bounds__(kThreads) void gdn_blk_state_kernel(const GdnBlockArgs a, const Areas ar) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const Seq s = where(a, DV / kCols);
+    if (s.bh < 0) return;
+    state_sweep<DK, DV, false>(a, ar, s, smem);
+}
+
 // ---- sweep 2: backward, X[dk, 16 value columns per wave] -> w, dv, dG^K, dbeta, d_initial_state -----------------
-template <int DK>
+// KEEP (chunk-parallel schedule): neither v nor res is needed.
+template <int DK, bool KEEP>
 struct Stage2 {
     static constexpr int RKr = rows_stride(DK), RKc = cols_stride(DK);
     static constexpr int oK = 0, oKc = oK + C * RKr * 2, oQ = oKc + C * RKc * 2, oO = oQ + C * RKc * 2,
-                         oV = oO + C * kSlC * 2, oR = oV + C * kSlR * 2, oT = oR + kCols * kSmC * 2,  // T' (by columns)
+                         oV = oO + C * kSlC * 2, oR = oV + (KEEP ? 0 : C * kSlR * 2),
+                         oT = oR + (KEEP ? 0 : kCols * kSmC * 2),                                     // T' (by columns)
                          oL = oT + C * kSmC * 2,                                             // Lq, -Lk: made by the sweep
                          oS = oL + 2 * C * kSmR * 2, bytes = oS + kScal * 4;
 };
-template <int DK, int DV>
+template <int DK, int DV, bool KEEP>
 struct Load2 {
     Rows<C, DK * 2> k, q;
     Rows<C, kCols * 2> o, v;
@@ -534,19 +561,23 @@ struct Load2 {
         k.load(f.a.k + row * DK, (size_t)f.a.H * DK * 2, valid, lt);
         q.load(f.a.q + row * DK, (size_t)f.a.H * DK * 2, valid, lt);
         o.load(f.a.dout + row * DV + n0, (size_t)f.a.H * DV * 2, valid, lt);
-        v.load(f.a.v + row * DV + n0, (size_t)f.a.H * DV * 2, valid, lt);
-        rs.load(f.ar.res + (bhi * (size_t)DV + n0) * C, C * 2, kCols, lt);
+        if constexpr (!KEEP) {
+            v.load(f.a.v + row * DV + n0, (size_t)f.a.H * DV * 2, valid, lt);
+            rs.load(f.ar.res + (bhi * (size_t)DV + n0) * C, C * 2, kCols, lt);
+        }
         t.load(f.ar.pre + bhi * (size_t)(kPreMats * kMat) + mT1 * kMat, C * 2, C, lt);
         sc.load(f.ar.scal + bhi * (size_t)kScal, C * 4, kKinds, lt);
     }
     __device__ __forceinline__ void put(unsigned char* st, int lt) const {
-        typedef Stage2<DK> L;
+        typedef Stage2<DK, KEEP> L;
         k.put(st + L::oK, L::RKr * 2, lt);
         k.put(st + L::oKc, L::RKc * 2, lt);
         q.put(st + L::oQ, L::RKc * 2, lt);
         o.put(st + L::oO, kSlC * 2, lt);
-        v.put(st + L::oV, kSlR * 2, lt);
-        rs.put(st + L::oR, kSmC * 2, lt);
+        if constexpr (!KEEP) {
+            v.put(st + L::oV, kSlR * 2, lt);
+            rs.put(st + L::oR, kSmC * 2, lt);
+        }
         t.put(st + L::oT, kSmC * 2, lt);
         sc.put(st + L::oS, C * 4, lt);
     }
@@ -554,9 +585,9 @@ struct Load2 {
 
 // Sweep 2's block-local matrices, diag(G^Q) Lq = diag(G^Q) tril(D * Q K^T) and -Lk = -strict_tril(D * K K^T), from
 // the staged rows of q and k; one 16 x 16 tile per wave as in local_matrices().
-template <int DK>
+template <int DK, bool KEEP>
 __device__ __forceinline__ void gram_matrices(unsigned char* st, int w, int r, int g) {
-    typedef Stage2<DK> L;
+    typedef Stage2<DK, KEEP> L;
     const bf* Kr = (const bf*)(st + L::oK);
     const bf* Qr = (const bf*)(st + L::oQ);
     const float* sc = (const float*)(st + L::oS);
@@ -586,20 +617,18 @@ __device__ __forceinline__ void gram_matrices(unsigned char* st, int w, int r, i
     *(u2*)(Lkn + tt * kSmR + 16 * tb + 4 * g) = pack4(lk);
 }
 
-template <int DK, int DV>
-__global__ __launch_bounds__(kThreads) void gdn_blk_cotangent_kernel(const GdnBlockArgs a, const Areas ar) {
-    typedef Stage2<DK> L;
+// KEEP: only du leaves, as rows, and the cotangent behind every chunk is kept (see GdnBlockArgs).
+template <int DK, int DV, bool KEEP>
+__device__ __forceinline__ void cotangent_sweep(const GdnBlockArgs& a, const Areas& ar, const Seq& s, unsigned char* smem) {
+    typedef Stage2<DK, KEEP> L;
     constexpr int NT = DK / 16, RKr = L::RKr, RKc = L::RKc;
-    extern __shared__ __align__(16) unsigned char smem[];
-    const Seq s = where(a, DV / kCols);
-    if (s.bh < 0) return;
     const Frame f{a, ar, s};
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3), r = lane & 15,
               g = lane >> 4;
     const int n0 = s.slice * kCols, n = n0 + 16 * w + r;
     const int plane = (n0 >> 4) + w;
     f4 X[NT];
-    run_sweep<false, 4, Load2<DK, DV>, kAhead>(
+    run_sweep<false, 4, Load2<DK, DV, KEEP>, kAhead>(
         f, smem, L::bytes,
         [&]() {
 #pragma unroll
@@ -626,6 +655,7 @@ __global__ __launch_bounds__(kThreads) void gdn_blk_cotangent_kernel(const GdnBl
 #pragma unroll
             for (int t = 0; t < NT; t += 2) {
                 const s8 bX = pack8(X[t], X[t + 1]);
+                if (KEEP && ((I & 1) || I == s.nblk - 1)) keep_state<DK, DV>(a.keep_x, f, I, n, t, g, bX);
                 mma(dU[0], op_rows(Kr, RKr, r, 16 * t, g), bX);
                 mma(dU[1], op_rows(Kr, RKr, 16 + r, 16 * t, g), bX);
             }
@@ -662,12 +692,12 @@ __global__ __launch_bounds__(kThreads) void gdn_blk_cotangent_kernel(const GdnBl
                 wT[ta] = f4{0.f, 0.f, 0.f, 0.f};
                 duT[ta] = f4{0.f, 0.f, 0.f, 0.f};
                 mma(wv[ta], aT2[ta], pdU);   // w[t = 16 ta + 4g + i][column r]
-                mma(wT[ta], pdU, aT2[ta]);   // w[t = 16 ta + r][column 4g + i]
+                if constexpr (!KEEP) mma(wT[ta], pdU, aT2[ta]);   // w[t = 16 ta + r][column 4g + i]
                 mma(duT[ta], pdU, id[ta]);   // dU, transposed the same way
             }
             const u2 pw0 = pack4(wv[0]), pw1 = pack4(wv[1]);
             const s8 pw = __builtin_bit_cast(s8, u4{pw0.x, pw0.y, pw1.x, pw1.y});
-            {
+            if constexpr (!KEEP) {
                 bf* dst = ar.w + (f.bhi(I) * (size_t)DV + n) * C + 4 * g;
                 *(u2*)dst = pw0;
                 *(u2*)(dst + 16) = pw1;
@@ -678,6 +708,10 @@ __global__ __launch_bounds__(kThreads) void gdn_blk_cotangent_kernel(const GdnBl
             for (int ta = 0; ta < 2; ++ta) {
                 mma(duT[ta], pw, op_cols(Lkn, kSmR, 0, 16 * ta, r, g));  // du = dU - Lk^T w, token 16 ta + r
                 const int tt = 16 * ta + r;
+                if constexpr (KEEP) {
+                    if (tt < valid) *(f4*)(a.du_rows + ((row0 + tt) * a.H + s.h) * DV + n0 + 16 * w + 4 * g) = duT[ta];
+                    continue;
+                }
                 const f4 rs4 = tile_cols(Rs, kSmC, 16 * w, 16 * ta, r, g);            // res[token tt][column 16w + 4g + i]
                 const f4 v4 = unpack4(*(const s4*)(Vs + tt * kSlR + 16 * w + 4 * g));  // v[token tt][the same columns]
                 float pb = 0.f, pk = 0.f;
@@ -709,7 +743,27 @@ __global__ __launch_bounds__(kThreads) void gdn_blk_cotangent_kernel(const GdnBl
                     for (int i = 0; i < 4; ++i) a.ds0[((size_t)s.bh * DK + 16 * t + 4 * g + i) * DV + n] = X[t][i];
             }
         },
-        NoFirst(), [&](unsigned char* st, int lw, int ll) { gram_matrices<DK>(st, lw, ll & 15, ll >> 4); });
+        NoFirst(), [&](unsigned char* st, int lw, int ll) { gram_matrices<DK, KEEP>(st, lw, ll & 15, ll >> 4); });
+}
+
+template <int DK, int DV>
+__global__ __launch_bounds__(kThreads) void gdn_blk_cotangent_kernel(const GdnBlockArgs a, const Areas ar) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const Seq s = where(a, DV / kCols);
+    if (s.bh < 0) return;
+    cotangent_sweep<DK, DV, false>(a, ar, s, smem);
+}
+
+// Chunk-parallel schedule: both sweeps in one launch (blockIdx.y), as neither needs anything of the other.
+template <int DK, int DV>
+__global__ __launch_bounds__(kThreads) void gdn_blk_pair_kernel(const GdnBlockArgs a, const Areas ar) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const Seq s = where(a, DV / kCols);
+    if (s.bh < 0) return;
+    if (blockIdx.y == 0)
+        cotangent_sweep<DK, DV, true>(a, ar, s, smem);
+    else
+        state_sweep<DK, DV, true>(a, ar, s, smem);
 }
 
 // ---- sweeps 3 and 4: X^T / S^T [dv, 16 key columns per wave] ---------------------------------------------------
@@ -1032,7 +1086,7 @@ bool allow_lds(K kernel, int lds) {
 template <int DK, int DV>
 int launch_all(const GdnBlockArgs& a, const Areas& ar, size_t blocks, hipStream_t stream) {
     constexpr int ns3 = DV > 128 ? 2 : 3;  // stages of sweep 3 (see run_sweep); sweep 2 has three, sweep 4 two
-    constexpr int lds1 = 2 * Stage1<DK>::bytes, lds2 = 3 * Stage2<DK>::bytes, lds3 = ns3 * Stage3<DV, false>::bytes,
+    constexpr int lds1 = 2 * Stage1<DK>::bytes, lds2 = 3 * Stage2<DK, false>::bytes, lds3 = ns3 * Stage3<DV, false>::bytes,
                   lds4 = 2 * Stage3<DV, true>::bytes;
     static_assert(lds1 <= 160 * 1024 && lds2 <= 160 * 1024 && lds3 <= 160 * 1024 && lds4 <= 160 * 1024, "LDS");
     static std::atomic<uint64_t> configured{0};  // bit d: attributes set on device d
@@ -1057,6 +1111,37 @@ int launch_all(const GdnBlockArgs& a, const Areas& ar, size_t blocks, hipStream_
     return hipGetLastError() == hipSuccess ? SLA_OK : SLA_ERR_HIP;
 }
 
+template <int DK, int DV>
+int launch_pair(const GdnBlockArgs& a, const Areas& ar, size_t blocks, hipStream_t stream) {
+    constexpr int lds1 = 2 * Stage1<DK>::bytes, lds2 = 3 * Stage2<DK, true>::bytes, lds = lds1 > lds2 ? lds1 : lds2;
+    static_assert(lds <= 160 * 1024, "LDS");
+    static std::atomic<uint64_t> configured{0};  // bit d: attributes set on device d
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) {
+        (void)hipGetLastError();
+        return SLA_ERR_HIP;
+    }
+    if (!((configured.load(std::memory_order_acquire) >> dev) & 1u)) {
+        if (!allow_lds(gdn_blk_pair_kernel<DK, DV>, lds)) return SLA_ERR_HIP;
+        configured.fetch_or(uint64_t(1) << dev, std::memory_order_release);
+    }
+    const unsigned bh = (unsigned)(a.B * a.H), local = (unsigned)(blocks * (size_t)a.H);
+    hipLaunchKernelGGL((gdn_blk_pre_kernel<DK>), dim3(local), dim3(64), 0, stream, a, ar);
+    hipLaunchKernelGGL((gdn_blk_pair_kernel<DK, DV>), dim3(((bh + 7u) / 8u) * 8u * (DV / kCols), 2), dim3(kThreads),
+                       (size_t)lds, stream, a, ar);
+    return hipGetLastError() == hipSuccess ? SLA_OK : SLA_ERR_HIP;
+}
+
+template <int DK>
+int launch_pair_dv(const GdnBlockArgs& a, const Areas& ar, size_t blocks, hipStream_t stream) {
+    switch (a.dim_v) {
+        case 64: return launch_pair<DK, 64>(a, ar, blocks, stream);
+        case 128: return launch_pair<DK, 128>(a, ar, blocks, stream);
+        case 256: return launch_pair<DK, 256>(a, ar, blocks, stream);
+        default: return SLA_ERR_UNSUPPORTED;
+    }
+}
+
 template <int DK>
 int launch_dv(const GdnBlockArgs& a, const Areas& ar, size_t blocks, hipStream_t stream) {
     switch (a.dim_v) {
@@ -1073,6 +1158,18 @@ size_t gdn_block_workspace_floats(int B, int T, int H, int dk, int dv, bool pack
     const size_t blocks = ws_blocks(B, T, packed), rows = packed ? (size_t)T : (size_t)B * T, bh = blocks * (size_t)H;
     (void)rows;
     return bh * kScal + bh * kPreMats * kMat / 2 + 2 * (bh * (size_t)dv * C / 2) + bh * (size_t)dk * C / 2;
+}
+
+size_t gdn_pair_workspace_floats(int B, int T, int H, bool packed) {
+    return ws_blocks(B, T, packed) * (size_t)H * (kScal + kPreMats * kMat / 2);
+}
+
+int launch_gdn_block_pair(const GdnBlockArgs& a, hipStream_t stream) {
+    const size_t blocks = ws_blocks(a.B, a.T, a.cu != nullptr);
+    const Areas ar = areas(a.block_ws, blocks, a.rows, a.H, a.dim_k, a.dim_v);  // scal and pre, its first two, are all it needs
+    if (a.dim_k == 64) return launch_pair_dv<64>(a, ar, blocks, stream);
+    if (a.dim_k == 128) return launch_pair_dv<128>(a, ar, blocks, stream);
+    return SLA_ERR_UNSUPPORTED;
 }
 
 int launch_gdn_block_sweeps(const GdnBlockArgs& a, hipStream_t stream) {

@@ -167,6 +167,10 @@ template <int DV>
 __device__ __forceinline__ int piece(int tile, int c) { return (tile * (DV / 32) + c) * 1024; }  // bytes
 __device__ __forceinline__ int key_of(int i, int r) { return 8 * (r >> 2) + 4 * i + (r & 3); }
 
+// the lower triangle's ten 16 x 16 tiles (t block, j block), dealt to the waves in turn
+constexpr uint64_t kTileT = 0x3323213210ull, kTileJ = 0x0102103210ull;
+static_assert(((kTileT >> 36) & 15) == 3 && ((kTileJ >> 36) & 15) == 0, "ten tiles");
+
 // 16-byte unit u of row `row` of an LDS array with U units per row: rows that a group of 16 lanes reads together lie on
 // different banks.
 template <int U>

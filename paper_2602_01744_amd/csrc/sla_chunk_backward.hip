@@ -64,10 +64,6 @@ struct Lds {
     static_assert(total <= 80 * 1024, "two workgroups per compute unit");
 };
 
-// the lower triangle's ten 16 x 16 tiles (t block, j block), dealt to the waves in turn
-constexpr uint64_t kTileT = 0x3323213210ull, kTileJ = 0x0102103210ull;
-static_assert(((kTileT >> 36) & 15) == 3 && ((kTileJ >> 36) & 15) == 0, "ten tiles");
-
 template <int VAR, int DK, int DV>
 __global__ __launch_bounds__(kThreads, 2) void sla_chunk_backward_kernel(const Args a) {
     typedef Lds<VAR, DK> L;
@@ -735,11 +731,11 @@ int launch_backward_chunks(const sla_params& p, const void* q, const void* k, co
     a.ld_head = p.variant == SLA_RETNET ? (const float*)ld : nullptr;
     a.s0 = s0; a.dsf = dsf; a.ds0 = ds0;
     a.dq = (uint16_t*)dq; a.dk = (uint16_t*)dk; a.dv = (uint16_t*)dv; a.dld = (uint16_t*)dld;
-    float *gq = ws, *gk = ws + n;
-    a.gq = gq; a.gk = gk; a.dgq = ws + 2 * n; a.dgk = ws + 3 * n;
     const chk::Parts parts = chk::parts_of(p, packed, std::min(kMostStates, floats - 4 * n));
-    a.S = (chk::u4*)(ws + 4 * n);
-    a.X = (chk::u4*)(ws + 4 * n + parts.floats / 2);
+    a.S = (chk::u4*)ws;  // the states first: on the cache lines that the allocation begins on
+    a.X = (chk::u4*)(ws + parts.floats / 2);
+    float *gq = ws + parts.floats, *gk = gq + n;
+    a.gq = gq; a.gk = gk; a.dgq = gk + n; a.dgk = gk + 2 * n;
     a.B = p.B; a.T = p.T; a.H = p.H; a.cu = cu;
     a.head_major = (p.flags & SLA_FLAG_HEAD_MAJOR) != 0;
     a.nchunk = (p.T + chk::kChunk - 1) / chk::kChunk;

@@ -35,6 +35,13 @@ struct GdnBlockArgs {
     size_t rows;            // tokens in all: B * T, or the packed total T
     const int* cu;          // packed batch: sequence b is tokens cu[b] .. cu[b+1]-1 of the T in all; else null
     int B, T, H, dim_k, dim_v;
+    // Chunk-parallel schedule (sla_chunk_gdn.hip): where the two state sweeps leave, for every 64-token chunk, the state
+    // entering it and the cotangent of the state behind it, bf16 [chunk slot][H][dv][dk], see keep_state() for the order
+    // inside a row; and res (bf16) and du (fp32) as rows [rows,H,dv].
+    uint16_t* keep_s;
+    uint16_t* keep_x;
+    uint16_t* res_rows;
+    float* du_rows;
 };
 
 // The decay gradient is a suffix sum of per-token scalars built from bf16-operand products, whose rounding adds up
@@ -47,5 +54,15 @@ inline size_t gdn_anchor_count(size_t rows) { return rows / kGdnAnchor + 1; }
 size_t gdn_block_workspace_floats(int B, int T, int H, int dk, int dv, bool packed);
 // Runs the block-local pre-pass and the four state sweeps on `stream`.
 int launch_gdn_block_sweeps(const GdnBlockArgs& a, hipStream_t stream);
+
+// dlog_decay from the per-token scalars e, see gdn_bwd_decay_scan_kernel (sla_backward_gdn.hip).
+int launch_gdn_decay_scan(const float* e, const float* corr, int planes, int B, int T, int H, const int* cu,
+                          const float* phi, float* dld, hipStream_t stream);
+
+// The chunk-parallel schedule's part of it: the pre-pass and, in one launch, the two sweeps that find res and du.  block_ws
+// then holds gdn_pair_workspace_floats() floats.
+constexpr int kGdnChunk = 64;
+size_t gdn_pair_workspace_floats(int B, int T, int H, bool packed);
+int launch_gdn_block_pair(const GdnBlockArgs& a, hipStream_t stream);
 
 }  // namespace sla
