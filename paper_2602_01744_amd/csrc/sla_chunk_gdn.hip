@@ -15,8 +15,8 @@
 // Against the four sweeps of sla_backward_gdn_block.hip, a training step with its convolutions and projections: few sequences 1.6 to
 // 3 times (B=2 T=4096 H=4 128 x 256 1142 -> 381 us, B=2 T=1000 H=8 128 x 128 256 -> 120, B=1 T=300 H=4 113 -> 65, 4096 packed
 // tokens H=8 303 -> 162), where the sweeps leave some compute units idle 1.1 to 1.25 times (B=8 T=4096 H=12 1110 -> 1012, 64 x 128
-// heads H=16 959 -> 774), as fast where they fill the chip (B=8 T=4096 H=16 128 x 128: 1767 and 1769; two sweeps 420 us and this
-// kernel 430 for 3.6 GB).  No output is further from fp32 tensors than theirs (dk 5.2e-3 -> 4.8e-3, dv 4.7e-3 -> 4.4e-3,
+// heads H=16 959 -> 774); where they fill the chip see sweeps_fill_the_chip().  Two sweeps 420 us and this kernel 430 for 3.6 GB
+// in all at B=8 T=4096 H=16 128 x 128.  No output is further from fp32 tensors than theirs (dk 5.2e-3 -> 4.8e-3, dv 4.7e-3 -> 4.4e-3,
 // dlog_decay 3.7e-2 -> 3.3e-2, dbeta the same): du stays in fp32, so that dbeta and w are what they were.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -434,10 +434,18 @@ static GdnChunkSizes gdn_chunk_sizes(const sla_params& p, bool packed) {
     return z;
 }
 
+// Long rows whose sweeps have a workgroup for each of 256 compute units, or nearly, in every round gain nothing: B=8 H=16
+// 128 x 128 T=4096 1761 -> 1771 us a training step, T=2048 561 -> 564, T=512 171 -> 155; three quarters of the chip (H=12 T=4096)
+// 1110 -> 1012.  Packed sequences end at different times and leave it idle whatever their number.
+static bool sweeps_fill_the_chip(const sla_params& p, bool packed) {
+    const size_t cus = 256, wgs = (size_t)p.B * p.H * (p.dk < p.dv ? p.dk : p.dv) / 64, rounds = (wgs + cus - 1) / cus;
+    return !packed && p.T >= 1024 && wgs >= cus && 16 * wgs >= 15 * cus * rounds;
+}
+
 // 0: this call does not run chunk-parallel (heads of width 32 are padded by sla_backward_narrow.hip, which runs the sweeps).
 // Its states may take a GiB, as in sla_chunk_backward.hip.
 size_t backward_gdn_chunks_workspace_floats(const sla_params& p, bool packed) {
-    if (p.dtype != SLA_BF16 || p.dk < 64 || p.T == 0 || p.B == 0) return 0;
+    if (p.dtype != SLA_BF16 || p.dk < 64 || p.T == 0 || p.B == 0 || sweeps_fill_the_chip(p, packed)) return 0;
     const GdnChunkSizes z = gdn_chunk_sizes(p, packed);
     return 2 * z.state <= (size_t)1 << 28 ? z.floats : 0;
 }

@@ -26,6 +26,9 @@ def test_size(packed):
     for p in (_params(dtype=sla.F32), _params(dk=32), _params(T=0), _params(B=0), _params(B=8, T=65536, H=16)):
         assert sla.sla_backward_gdn_chunks_workspace_bytes(p, packed) == least(p)
     assert sla.sla_backward_gdn_chunks_workspace_bytes(_params(variant=sla.GLA), packed) == 0
+    # 256 workgroups of long rows in the sweeps: they keep a rectangular batch
+    full = _params(B=8, T=4096, H=16)
+    assert (sla.sla_backward_gdn_chunks_workspace_bytes(full, packed) == least(full)) == (not packed)
 
 
 @pytest.mark.gpu
