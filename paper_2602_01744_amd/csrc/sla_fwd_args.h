@@ -30,12 +30,6 @@ struct KArgs {
     int nparts;  // producer waves of the pre-pass: partial decay products per segment in ws_decay
     float* ws_state;
     float* ws_decay;
-    // The pre-pass covers one segment less than the main pass and would leave compute units idle: it may cut each segment
-    // into `pieces` of equal length, whose end states and decays lie in areas of their own, laid out as those of npiece + 1
-    // segments.  pieces == 1: the segments themselves, in ws_state and ws_decay.
-    int pieces;
-    float* piece_state;
-    float* piece_decay;
     // Used by the backward pass's segment schedule, which wants only what the pre-pass and the combine kernel
     // produce: the entry state of every segment (ws_state) and, in ws_total[b][s][h][dk], the total decay of each
     // segment but the last.  states_only stops the call after the combine kernel.
@@ -50,6 +44,16 @@ struct KArgs {
     // Sticky device status word (bits of SLA_DEVICE_*): a bounded wait that expired, a GLA block decay outside the
     // documented range.  Never null.
     unsigned int* status;
+};
+
+// The host side's view of a call: what the kernels take and, for the segment schedule, how the pre-pass is cut.
+struct KCall : KArgs {
+    // The pre-pass covers one segment less than the main pass and would leave compute units idle: it may cut each segment
+    // into `pieces` of equal length, whose end states and decays lie in areas of their own, laid out as those of npiece + 1
+    // segments.  pieces == 1: the segments themselves, in ws_state and ws_decay.
+    int pieces;
+    float* piece_state;
+    float* piece_decay;
 };
 
 // Floats that a pre-pass on npiece pieces wants besides the segments' own: end states and decay products.

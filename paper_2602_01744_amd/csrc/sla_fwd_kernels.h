@@ -1268,7 +1268,7 @@ static int launch_one(const KArgs& a, hipStream_t stream) {
 // D_s its total decay.  Slot s of the segments ends up holding the state entering segment s; where every piece is a segment
 // the two areas are one (CUT: they are not).  One thread per (batch, head, d, 4 value columns).
 template <int VAR, bool CUT>
-__global__ void sla_segment_combine_kernel(const KArgs a, int dk) {
+__global__ void sla_segment_combine_kernel(const KArgs a, int dk, int cut, float* piece_state, const float* piece_decay) {
     const int dv4 = a.dv / 4;
     const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t per_head = (size_t)dk * dv4;
@@ -1283,19 +1283,19 @@ __global__ void sla_segment_combine_kernel(const KArgs a, int dk) {
     // costs a memory latency per four segments and not two for each (B=4 H=8 d=128, 4 segments: 5.3 -> 4.9 us; B=8
     // H=4 128 x 256 GLA 9.8 -> 6.8 us; B=1 T=65536 H=32 GLA 12.0 -> 5.9 us).
     constexpr int kAtOnce = 4;
-    const int pieces = CUT ? a.pieces : 1, np = (a.nseg - 1) * pieces;
+    const int pieces = CUT ? cut : 1, np = (a.nseg - 1) * pieces;
     const float len = (float)(CUT ? a.Ls / pieces : a.Ls);
     [[maybe_unused]] int in_seg = 0, seg = 0;
     for (int s0 = 0; s0 < np; s0 += kAtOnce) {
         f32x4 Lseg[kAtOnce];
         float D[kAtOnce];
-        auto slot = [&](int s) { return (f32x4*)(a.piece_state + ((size_t)(b * (np + 1) + s + 1) * a.H + h) * head_sz + off); };
+        auto slot = [&](int s) { return (f32x4*)((CUT ? piece_state : a.ws_state) + ((size_t)(b * (np + 1) + s + 1) * a.H + h) * head_sz + off); };
 #pragma unroll
         for (int u = 0; u < kAtOnce; ++u) {
             const int s = min(s0 + u, np - 1);
             Lseg[u] = *slot(s);
             if constexpr (VAR == SLA_GLA) {
-                const float* dp = a.piece_decay + ((size_t)(b * np + s) * a.H + h) * kMaxSlots * dk + d;
+                const float* dp = (CUT ? piece_decay : a.ws_decay) + ((size_t)(b * np + s) * a.H + h) * kMaxSlots * dk + d;
                 float part[kMaxSlots];
 #pragma unroll
                 for (int w = 0; w < kMaxSlots; ++w) part[w] = dp[min(w, a.nparts - 1) * dk];
@@ -1326,31 +1326,31 @@ __global__ void sla_segment_combine_kernel(const KArgs a, int dk) {
 
 // One call = one fused launch, or (segment-parallel schedule, RetNet and GLA) pre-pass + combine + main pass.
 template <class P, int VAR, int DK, int DVW, int HG>
-static int launch(const KArgs& a, hipStream_t stream) {
+static int launch(const KCall& a, hipStream_t stream) {
     if (a.nseg <= 1) return launch_one<P, VAR, DK, DVW, HG, false>(a, stream);
     if constexpr (VAR == SLA_GDN) {
         return SLA_ERR_UNSUPPORTED;  // the delta rule's segment transition is a dense matrix; not built
     } else {
-        KArgs mid = a;
-        if (a.pieces == 1) {
-            mid.piece_state = a.ws_state;
-            mid.piece_decay = a.ws_decay;
+        KArgs pre = a, mid = a;
+        pre.nseg_grid = a.nseg - 1;
+        if (a.pieces > 1) {  // the pieces take the place of the segments
+            pre.nseg_grid = (a.nseg - 1) * a.pieces;
+            pre.nseg = pre.nseg_grid + 1;
+            pre.Ls = a.Ls / a.pieces;
+            pre.ws_state = a.piece_state;
+            pre.ws_decay = a.piece_decay;
         }
-        KArgs pre = mid;  // the pieces take the place of the segments
-        pre.nseg_grid = (a.nseg - 1) * a.pieces;
-        pre.nseg = pre.nseg_grid + 1;
-        pre.Ls = a.Ls / a.pieces;
-        pre.ws_state = mid.piece_state;
-        pre.ws_decay = mid.piece_decay;
         mid.nparts = Smem<P, VAR, DK, DVW>::slots;
         int rc = launch_one<P, VAR, DK, DVW, HG, true>(pre, stream);
         if (rc != SLA_OK) return rc;
         const size_t n = (size_t)a.B * a.H * DK * (a.dv / 4);
         const dim3 grid((unsigned)((n + 255) / 256)), block(256);
         if (a.pieces > 1)
-            hipLaunchKernelGGL((sla_segment_combine_kernel<VAR, true>), grid, block, 0, stream, mid, DK);
+            hipLaunchKernelGGL((sla_segment_combine_kernel<VAR, true>), grid, block, 0, stream, mid, DK, a.pieces, a.piece_state,
+                               (const float*)a.piece_decay);
         else
-            hipLaunchKernelGGL((sla_segment_combine_kernel<VAR, false>), grid, block, 0, stream, mid, DK);
+            hipLaunchKernelGGL((sla_segment_combine_kernel<VAR, false>), grid, block, 0, stream, mid, DK, a.pieces, a.piece_state,
+                               (const float*)a.piece_decay);
         if (hipGetLastError() != hipSuccess) return SLA_ERR_HIP;
         if (a.states_only) return SLA_OK;
         return launch_one<P, VAR, DK, DVW, HG, false>(a, stream);
@@ -1358,14 +1358,14 @@ static int launch(const KArgs& a, hipStream_t stream) {
 }
 
 template <class P, int VAR, int DK, int DVW>
-static int dispatch_heads(const KArgs& a, hipStream_t stream) {
+static int dispatch_heads(const KCall& a, hipStream_t stream) {
     if (a.H <= 16) return launch<P, VAR, DK, DVW, 4>(a, stream);
     if (a.H <= 32) return launch<P, VAR, DK, DVW, 8>(a, stream);
     return launch<P, VAR, DK, DVW, 16>(a, stream);
 }
 
 template <class P, int VAR, int DK>
-static int dispatch_dvw(const KArgs& a, int dvw, hipStream_t stream) {
+static int dispatch_dvw(const KCall& a, int dvw, hipStream_t stream) {
     switch (dvw) {
         case 16: return dispatch_heads<P, VAR, DK, 16>(a, stream);
         case 32: return dispatch_heads<P, VAR, DK, 32>(a, stream);
@@ -1375,7 +1375,7 @@ static int dispatch_dvw(const KArgs& a, int dvw, hipStream_t stream) {
 }
 
 template <class P, int VAR>
-static int dispatch_dk(const KArgs& a, int dk, int dvw, hipStream_t stream) {
+static int dispatch_dk(const KCall& a, int dk, int dvw, hipStream_t stream) {
     switch (dk) {
         case 32: return dispatch_dvw<P, VAR, 32>(a, dvw, stream);
         case 64: return dispatch_dvw<P, VAR, 64>(a, dvw, stream);
@@ -1385,7 +1385,7 @@ static int dispatch_dk(const KArgs& a, int dk, int dvw, hipStream_t stream) {
 }
 
 template <class P>
-static int dispatch_variant(const KArgs& a, int variant, int dk, int dvw, hipStream_t stream) {
+static int dispatch_variant(const KCall& a, int variant, int dk, int dvw, hipStream_t stream) {
     switch (variant) {
         case SLA_RETNET: return dispatch_dk<P, SLA_RETNET>(a, dk, dvw, stream);
         case SLA_GLA: return dispatch_dk<P, SLA_GLA>(a, dk, dvw, stream);

@@ -8,8 +8,8 @@
 
 namespace sla {
 
-int dispatch_forward_bf16(const KArgs& a, int variant, int dk, int dvw, hipStream_t stream);
-int dispatch_forward_f32(const KArgs& a, int variant, int dk, int dvw, hipStream_t stream);
+int dispatch_forward_bf16(const KCall& a, int variant, int dk, int dvw, hipStream_t stream);
+int dispatch_forward_f32(const KCall& a, int variant, int dk, int dvw, hipStream_t stream);
 unsigned int* device_status_word();  // sla_api.hip
 
 // T == 0: the state passes through unchanged.
@@ -29,7 +29,7 @@ size_t segment_workspace_floats(const sla_params& p, int nseg) {
 int launch_forward_pieces(const sla_params& p, int dvw, int nseg, int seg_len, int pieces, const void* q, const void* k, const void* v,
                    const float* ql, const float* kl, const void* ld, const float* beta, const float* s0, void* out,
                    float* sT, float* workspace, const int* cu, hipStream_t stream) {
-    KArgs a;
+    KCall a;
     a.head_major = (p.flags & SLA_FLAG_HEAD_MAJOR) != 0;
     a.q = q; a.k = k; a.v = v; a.ql = ql; a.kl = kl; a.ld = ld; a.beta = beta; a.s0 = s0; a.out = out; a.sT = sT;
     a.B = p.B; a.T = p.T; a.H = p.H; a.dv = p.dv; a.nslice = p.dv / dvw;
@@ -71,7 +71,7 @@ int launch_segment_states(const sla_params& p, int dvw, int nseg, int seg_len, c
                           const void* v, const float* ql, const float* kl, const void* ld, const float* s0,
                           float* workspace, float* totals, hipStream_t stream) {
     if (nseg < 2 || p.variant == SLA_GDN || p.T == 0) return SLA_ERR_UNSUPPORTED;
-    KArgs a;
+    KCall a;
     a.head_major = false;
     a.q = q; a.k = k; a.v = v; a.ql = ql; a.kl = kl; a.ld = ld; a.beta = nullptr; a.s0 = s0; a.out = nullptr;
     a.sT = nullptr;

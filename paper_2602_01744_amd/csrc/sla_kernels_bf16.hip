@@ -3,7 +3,7 @@
 
 namespace sla {
 
-int dispatch_forward_bf16(const KArgs& a, int variant, int dk, int dvw, hipStream_t stream) {
+int dispatch_forward_bf16(const KCall& a, int variant, int dk, int dvw, hipStream_t stream) {
     return dispatch_variant<PrecBF16>(a, variant, dk, dvw, stream);
 }
 

@@ -3,7 +3,7 @@
 
 namespace sla {
 
-int dispatch_forward_f32(const KArgs& a, int variant, int dk, int dvw, hipStream_t stream) {
+int dispatch_forward_f32(const KCall& a, int variant, int dk, int dvw, hipStream_t stream) {
     return dispatch_variant<PrecF32>(a, variant, dk, dvw, stream);
 }
 
