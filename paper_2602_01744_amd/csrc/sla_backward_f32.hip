@@ -66,8 +66,8 @@ struct FArgs {
 
 // What a workgroup owns: a sequence, or with nseg > 1 one segment of seg_len tokens of a batch row, which then runs as
 // a sequence of its own (me.b and me.bh number the segments, and with them the states).
-__device__ __forceinline__ Where where_segment(const FArgs& a, int nslices) {
-    Where me = where(a, nslices);
+__device__ __forceinline__ Where where_segment(const FArgs& a, int nslices, int block, int grid) {
+    Where me = where(a, nslices, block, grid);
     if (a.nseg > 1 && me.bh >= 0) {
         const int t0 = (me.b % a.nseg) * a.seg_len;
         me.T = min(a.seg_len, a.T - t0);
@@ -136,13 +136,12 @@ __device__ __forceinline__ float head_alpha_of(const FArgs& a, int h) {
 // dv sweep: backward in time, X[dk rows, value columns].
 // ------------------------------------------------------------------------------------------------------------
 template <bool GLA, int DK, int DV>
-__global__ __launch_bounds__(kThreads) void sla_bwd32_dv_kernel(const FArgs a) {
+__device__ __forceinline__ void dv_sweep(const FArgs& a, unsigned char* smem, int block, int grid) {
     constexpr int RT = DK / 16;
     constexpr int oK = 0, oQ = oK + kChunk * DK, oA = oQ + kChunk * DK, oV = oA + (GLA ? kChunk * DK : 0),
                   oDO = oV + kChunk * kSlice, oSC = oDO + kChunk * kSlice, kBuf = oSC + kSc * kChunk;
-    extern __shared__ __align__(16) unsigned char smem[];
     float* lds = (float*)smem;
-    const Where me = where_segment(a, DV / kSlice);
+    const Where me = where_segment(a, DV / kSlice, block, grid);
     if (me.bh < 0) return;
     const int T = me.T, nch = (T + kChunk - 1) / kChunk;
     const Rows rk = rows_of(a, me, DK), rv = rows_of(a, me, DV);
@@ -230,15 +229,14 @@ __global__ __launch_bounds__(kThreads) void sla_bwd32_dv_kernel(const FArgs a) {
 //   else:  X^T += (G^Q dout)^T q;   dk = G^K v X^T;   run += q dq - k dk;   X^T = X^T diag(alpha)
 // ------------------------------------------------------------------------------------------------------------
 template <bool GLA, int DK, int DV, bool FWD>
-__global__ __launch_bounds__(kThreads) void sla_bwd32_key_kernel(const FArgs a) {
+__device__ __forceinline__ void key_sweep(const FArgs& a, unsigned char* smem, int block, int grid) {
     constexpr int RT = DV / 16;
     constexpr bool NEED_DQ = GLA && !FWD;
     constexpr int oDO = 0, oV = oDO + kChunk * DV, oK = oV + kChunk * DV, oQ = oK + kChunk * kSlice,
                   oA = oQ + kChunk * kSlice, oDQ = oA + (GLA ? kChunk * kSlice : 0),
                   oSC = oDQ + (NEED_DQ ? kChunk * kSlice : 0), kBuf = oSC + kSc * kChunk;
-    extern __shared__ __align__(16) unsigned char smem[];
     float* lds = (float*)smem;
-    const Where me = where_segment(a, DK / kSlice);
+    const Where me = where_segment(a, DK / kSlice, block, grid);
     if (me.bh < 0) return;
     const int T = me.T, nch = (T + kChunk - 1) / kChunk;
     const Rows rk = rows_of(a, me, DK), rv = rows_of(a, me, DV);
@@ -359,6 +357,35 @@ __global__ __launch_bounds__(kThreads) void sla_bwd32_key_kernel(const FArgs a) 
     }
 }
 
+template <bool GLA, int DK, int DV>
+__global__ __launch_bounds__(kThreads) void sla_bwd32_dv_kernel(const FArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    dv_sweep<GLA, DK, DV>(a, smem, (int)blockIdx.x, (int)gridDim.x);
+}
+template <bool GLA, int DK, int DV, bool FWD>
+__global__ __launch_bounds__(kThreads) void sla_bwd32_key_kernel(const FArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    key_sweep<GLA, DK, DV, FWD>(a, smem, (int)blockIdx.x, (int)gridDim.x);
+}
+// The dq, the dv and, RetNet, the dk sweep side by side, DK / kSlice, DV / kSlice and DK / kSlice workgroups a sequence and
+// head: none needs anything of the others (GLA's dk sweep makes the decay gradient from dq).  A sweep is bound by its serial
+// walk over the tokens, so the chip has room for another one's workgroups: B=2 T=1021 H=8 64 x 128 GLA 122 -> 116 us for the
+// backward pass, a training step of B=8 T=700 H=16 128 x 128 GLA 786 -> 707 us, of B=4 T=300 H=4 64 x 64 82 -> 73 us.
+template <bool GLA, int DK, int DV>
+constexpr int kSideBySide = (GLA ? 1 : 2) * (DK / kSlice) + DV / kSlice;
+template <bool GLA, int DK, int DV>
+__global__ __launch_bounds__(kThreads) void sla_bwd32_sweeps_kernel(const FArgs a) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int each = (int)gridDim.x / kSideBySide<GLA, DK, DV>, nk = each * (DK / kSlice), nv = each * (DV / kSlice);
+    const int block = (int)blockIdx.x;
+    if (block < nk)
+        key_sweep<GLA, DK, DV, true>(a, smem, block, nk);
+    else if (GLA || block < nk + nv)
+        dv_sweep<GLA, DK, DV>(a, smem, block - nk, nv);
+    else
+        key_sweep<GLA, DK, DV, GLA>(a, smem, block - nk - nv, nk);
+}
+
 // ------------------------------------------------------------------------------------------------------------
 // Pre-pass of the segment schedule (see launch_backward_f32): what a segment alone leaves behind.  blockIdx.y = 0,
 // forward in time: the state at its end from a zero state; 1, backward in time: the cotangent of the state at its
@@ -443,7 +470,7 @@ template <bool GLA, int DK, int DV>
 __global__ __launch_bounds__(kThreads) void sla_bwd32_segment_kernel(const FArgs a, float* states, float* cotangents,
                                                                       float* totals, bool want_ds0) {
     extern __shared__ __align__(16) unsigned char smem[];
-    const Where me = where_segment(a, DK / kSlice);
+    const Where me = where_segment(a, DK / kSlice, (int)blockIdx.x, (int)gridDim.x);
     if (me.bh < 0) return;
     const int seg = me.b % a.nseg;
     if (blockIdx.y == 0) {
@@ -534,6 +561,10 @@ int launch_sweeps(FArgs a, const Segments& sg, bool state_only, hipStream_t stre
     constexpr int ldsV = 2 * 4 * ((GLA ? 3 : 2) * kChunk * DK + 2 * kChunk * kSlice + kSc * kChunk);
     constexpr int ldsQ = 2 * 4 * (2 * kChunk * DV + (GLA ? 3 : 2) * kChunk * kSlice + kSc * kChunk);
     constexpr int ldsK = 2 * 4 * (2 * kChunk * DV + (GLA ? 4 : 2) * kChunk * kSlice + kSc * kChunk);
+    // One launch for several sweeps where its workgroups' larger LDS still lets two share a compute unit (ldsK is ldsQ for
+    // RetNet, whose dk sweep is among them).
+    constexpr int ldsVQ = ldsV > ldsQ ? ldsV : ldsQ;
+    constexpr bool kTogether = ldsVQ <= 80 * 1024;
     static_assert(ldsV <= 160 * 1024 && ldsQ <= 160 * 1024 && ldsK <= 160 * 1024, "fits the LDS of a compute unit");
     // once per device and instantiation (bit d = done on device d); not a stream operation
     static std::atomic<uint64_t> configured{0};
@@ -546,7 +577,7 @@ int launch_sweeps(FArgs a, const Segments& sg, bool state_only, hipStream_t stre
         if (!allow_lds(sla_bwd32_dv_kernel<GLA, DK, DV>, ldsV) ||
             !allow_lds(sla_bwd32_key_kernel<GLA, DK, DV, true>, ldsQ) ||
             !allow_lds(sla_bwd32_key_kernel<GLA, DK, DV, false>, ldsK) ||
-            !allow_lds(sla_bwd32_segment_kernel<GLA, DK, DV>, ldsS))
+            !allow_lds(sla_bwd32_segment_kernel<GLA, DK, DV>, ldsS) || !allow_lds(sla_bwd32_sweeps_kernel<GLA, DK, DV>, ldsVQ))
             return SLA_ERR_HIP;
         configured.fetch_or(uint64_t(1) << dev, std::memory_order_release);
     }
@@ -568,9 +599,15 @@ int launch_sweeps(FArgs a, const Segments& sg, bool state_only, hipStream_t stre
         a.dsf = sg.cotangents;
         a.ds0 = nullptr;
     }
-    hipLaunchKernelGGL((sla_bwd32_dv_kernel<GLA, DK, DV>), grid(DV / kSlice), block, (size_t)ldsV, stream, a);
-    if (!state_only) {
-        hipLaunchKernelGGL((sla_bwd32_key_kernel<GLA, DK, DV, true>), grid(DK / kSlice), block, (size_t)ldsQ, stream, a);
+    if (kTogether && !state_only) {
+        hipLaunchKernelGGL((sla_bwd32_sweeps_kernel<GLA, DK, DV>), grid(kSideBySide<GLA, DK, DV>), block, (size_t)ldsVQ, stream,
+                           a);
+    } else {
+        hipLaunchKernelGGL((sla_bwd32_dv_kernel<GLA, DK, DV>), grid(DV / kSlice), block, (size_t)ldsV, stream, a);
+        if (!state_only)
+            hipLaunchKernelGGL((sla_bwd32_key_kernel<GLA, DK, DV, true>), grid(DK / kSlice), block, (size_t)ldsQ, stream, a);
+    }
+    if (!state_only && (GLA || !kTogether)) {
         hipLaunchKernelGGL((sla_bwd32_key_kernel<GLA, DK, DV, false>), grid(DK / kSlice), block, (size_t)ldsK, stream, a);
     }
     return hipGetLastError() == hipSuccess ? SLA_OK : SLA_ERR_HIP;

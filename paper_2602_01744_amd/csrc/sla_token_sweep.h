@@ -159,25 +159,25 @@ struct Where {  // what a workgroup and its lanes own (Args: B, T, H, cu as in t
     size_t tok0;                                         // index of its first token
 };
 template <class Args>
-__device__ __forceinline__ Where where(const Args& a, int nslices) {
+__device__ __forceinline__ Where where(const Args& a, int nslices, int block, int grid) {
     Where w;
     w.tid = threadIdx.x;
     w.wave = __builtin_amdgcn_readfirstlane(w.tid >> 6);
     w.lane = w.tid & 63;
     w.rg = w.lane & 15;
     w.cg = w.lane >> 4;
-    // blockIdx.x % 8 is the XCD a workgroup lands on; the slices of a (sequence, head) pair go to one XCD so that
+    // block % 8 is the XCD a workgroup lands on; the slices of a (sequence, head) pair go to one XCD so that
     // the L2 they share fetches k, q, d_out and the intermediates once.  Rectangular batches: every XCD a contiguous
     // range of pairs; packed ones: pairs dealt round-robin, which spreads the heads of one long sequence over all
     // XCDs.  The grid is 8 * nslices * ceil(pairs / 8); the padding gets bh = -1 and leaves at once.
     {
-        const int pairs = a.B * a.H, xcd = blockIdx.x & 7, place = blockIdx.x >> 3;
+        const int pairs = a.B * a.H, xcd = block & 7, place = block >> 3;
         int wg;
         if (a.cu) {
             const int pair = (place / nslices) * 8 + xcd;
             wg = pair < pairs ? pair * nslices + place % nslices : -1;
         } else {
-            wg = xcd * (int)(gridDim.x >> 3) + place;
+            wg = xcd * (grid >> 3) + place;
             if (wg >= pairs * nslices) wg = -1;
         }
         w.slice = wg < 0 ? 0 : wg % nslices;
@@ -200,6 +200,10 @@ __device__ __forceinline__ Where where(const Args& a, int nslices) {
         w.tok0 = (size_t)start;
     }
     return w;
+}
+template <class Args>
+__device__ __forceinline__ Where where(const Args& a, int nslices) {
+    return where(a, nslices, (int)blockIdx.x, (int)gridDim.x);
 }
 
 }  // namespace tok
