@@ -302,7 +302,7 @@ __device__ __forceinline__ void key_sweep(const FArgs& a, unsigned char* smem, i
                 for (int r = 0; r < RT; ++r)
 #pragma unroll
                     for (int j = 0; j < CW; ++j) {
-                        M[r][j] = M[r][j] * al[j] + (gk * vv[r]) * kf[j];
+                        M[r][j] = __builtin_fmaf(M[r][j], al[j], (gk * vv[r]) * kf[j]);  // the state rounded once, not twice
                         y[j] += dd[r] * M[r][j];
                     }
                 float pq = 0.f;
