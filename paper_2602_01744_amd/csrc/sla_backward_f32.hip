@@ -636,7 +636,7 @@ int launch_dk(const FArgs& a, const Segments& sg, int dk, int dv, bool state_onl
 // most of the chip idle: rows are cut until the narrowest sweep has a workgroup for each of 256 compute units, into
 // segments of at least 32 tokens.  Heads up to 64 x 128 take half the vector work per token, so two workgroups share a
 // compute unit to gain and 512 are wanted, but not with segments under 64 tokens, where the pre-pass and the chain cost
-// more than that gives.  Call in us, one pass -> 256 wanted / 512 wanted:
+// more than that gives.  Call in us (a launch for every sweep), one pass -> 256 wanted / 512 wanted:
 //     B=2 T=1021 H=8  64 x 128    917 -> 141 / 150           B=6 T=1500 H=16 64 x 64    1000 -> 602 / 397
 //     B=1 T=300  H=4  64 x 64     215 -> 52 (64 tokens: 76)  B=7 T=1000 H=16 64 x 128    921 -> 697 / 641
 //     B=1 T=4096 H=2  128 x 128  3827 -> 139 / 149           B=4 T=2048 H=5  128 x 256  2548 -> 758 / 802
