@@ -36,6 +36,7 @@ struct Args {
     const float* dsf;        // cotangent of the final state or null
     float* sT;               // final state or null
     float* ds0;              // gradient of the initial state or null
+    float* end;              // GLA with dsf: [B,H][dv/32][dk] rowsum(dsf * S) over 32 value columns each, S entering the last chunk
     u4* S;                   // operand pieces of the state entering a chunk, see piece()
     u4* X;                   // ... of the gradient with respect to the state behind it
     uint16_t* dq;

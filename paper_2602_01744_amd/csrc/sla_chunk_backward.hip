@@ -9,7 +9,9 @@
 // token: it multiplies the 64 x 64 matrices after the products, whatever its size.
 //     dq = G^Q dq'  dk = G^K dk'  dv = G^K dv'  dG^Q = q . dq'  dG^K = k . dk'
 //     dlog_decay_t = A rowsum(X * S) + sum_j k_j dk_state_j + sum_{s >= t in the chunk} (q_s dq_s - k_s dk_s)
-// The first two terms are rowsum(X * S_end) exactly, so the decay gradient's error is that of 64 tokens.
+// The first two terms are rowsum(X * S_end), from bf16 operands with fp32 sums, so the decay gradient's error is that of 64
+// tokens (T = 2085 128 x 128: 5.3e-3 of its norm against the oracle, the sweeps' 1.6e-2; for the tokens next to the sweeps'
+// fp32 anchors 2.8e-3 against 3.8e-3).  In a row's last chunk S and X are taken in fp32 for the first term, see end.
 // Against the sweeps of sla_backward.hip, which carry the states through all tokens of a sequence (a call, all launches):
 // few sequences 2 to 4 times (B=4 T=500 H=8 128 x 128 GLA 109 -> 45 us; B=8 T=4096 H=4 128 x 256 GLA 522, in four segments,
 // -> 330 us), B=8 T=2048 H=16 128 x 128 GLA 398 -> 390 us, RetNet 306 -> 290 us: there the memory system bounds it, 0.84 GB in
@@ -163,6 +165,13 @@ __global__ __launch_bounds__(kThreads, 2) void sla_chunk_backward_kernel(const A
     if (tid < kChunk) {
         sgq[tid] = load_scalar(scalars_of(a, a.gq, s, h), t0 + tid);
         sgk[tid] = load_scalar(scalars_of(a, a.gk, s, h), t0 + tid);
+    }
+    if (GLA && a.end && t0 + kChunk >= s.T && tid < DK) {  // the row's end: rowsum(X * S) from the state kernel, in fp32
+        const float* src = a.end + ((size_t)b * a.H + h) * (DV / 32) * DK + tid;
+        float sum = 0.f;
+#pragma unroll
+        for (int n = 0; n < DV / 32; ++n) sum += src[n * DK];
+        scorr[tid] = sum;
     }
     load_rows(0);
     load_states(0);
@@ -417,7 +426,7 @@ __global__ __launch_bounds__(kThreads, 2) void sla_chunk_backward_kernel(const A
             *(u2*)n_at(sn2, 32 * blk + 16 + row, 32 * blk + col) = u2{0u, 0u};
         }
     }
-    if constexpr (GLA) {
+    if (GLA && !(a.end && t0 + kChunk >= s.T)) {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const float lo = (r & 1) ? corr[i][1] : corr[i][0], hi2 = (r & 1) ? corr[i][3] : corr[i][2];
@@ -709,15 +718,24 @@ static size_t round4(size_t n) { return (n + 3) & ~(size_t)3; }
 // stay in the memory-side cache gains less than that); below kLeastStates launches are too small to fill the chip at all.
 constexpr size_t kMostStates = (size_t)1 << 28, kLeastStates = (size_t)1 << 24;
 
-static size_t backward_chunks_fixed_floats(const sla_params& p, bool packed) {  // gates and their gradients [B,T,H]
+// Gates and their gradients [B,T,H], and behind the states Args::end.
+static size_t backward_chunks_fixed_floats(const sla_params& p, bool packed) {
     return 4 * round4((packed ? (size_t)p.T : (size_t)p.B * p.T) * p.H);
 }
-size_t backward_chunks_workspace_floats(const sla_params& p, bool packed) {
-    return backward_chunks_fixed_floats(p, packed) + chk::parts_of(p, packed, kMostStates).floats;
+static size_t backward_chunks_end_floats(const sla_params& p) {
+    return p.variant == SLA_GLA ? (size_t)p.B * p.H * p.dk * (p.dv / 32) : 0;
 }
+static chk::Parts backward_chunks_parts(const sla_params& p, bool packed, size_t budget) {  // of states and Args::end
+    const size_t end = backward_chunks_end_floats(p);
+    return chk::parts_of(p, packed, budget > end ? budget - end : 0);
+}
+static size_t backward_chunks_floats(const sla_params& p, bool packed, size_t budget) {
+    return backward_chunks_fixed_floats(p, packed) + backward_chunks_parts(p, packed, budget).floats + backward_chunks_end_floats(p);
+}
+size_t backward_chunks_workspace_floats(const sla_params& p, bool packed) { return backward_chunks_floats(p, packed, kMostStates); }
 // Whether a workspace of that many floats is enough for the chunk-parallel pass.
 bool backward_chunks_fit(const sla_params& p, bool packed, size_t floats) {
-    return p.dtype == SLA_BF16 && p.T > 0 && backward_chunks_fixed_floats(p, packed) + chk::parts_of(p, packed, kLeastStates).floats <= floats;
+    return p.dtype == SLA_BF16 && p.T > 0 && backward_chunks_floats(p, packed, kLeastStates) <= floats;
 }
 
 int launch_backward_chunks(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
@@ -731,11 +749,12 @@ int launch_backward_chunks(const sla_params& p, const void* q, const void* k, co
     a.ld_head = p.variant == SLA_RETNET ? (const float*)ld : nullptr;
     a.s0 = s0; a.dsf = dsf; a.ds0 = ds0;
     a.dq = (uint16_t*)dq; a.dk = (uint16_t*)dk; a.dv = (uint16_t*)dv; a.dld = (uint16_t*)dld;
-    const chk::Parts parts = chk::parts_of(p, packed, std::min(kMostStates, floats - 4 * n));
+    const chk::Parts parts = backward_chunks_parts(p, packed, std::min(kMostStates, floats - backward_chunks_fixed_floats(p, packed)));
     a.S = (chk::u4*)ws;  // the states first: on the cache lines that the allocation begins on
     a.X = (chk::u4*)(ws + parts.floats / 2);
     float *gq = ws + parts.floats, *gk = gq + n;
     a.gq = gq; a.gk = gk; a.dgq = gk + n; a.dgk = gk + 2 * n;
+    a.end = p.variant == SLA_GLA && dsf ? gk + 3 * n : nullptr;  // n floats each: q's and k's gates and their gradients
     a.B = p.B; a.T = p.T; a.H = p.H; a.cu = cu;
     a.head_major = (p.flags & SLA_FLAG_HEAD_MAJOR) != 0;
     a.nchunk = (p.T + chk::kChunk - 1) / chk::kChunk;

@@ -156,6 +156,30 @@ __global__ __launch_bounds__(kStateThreads, 3) void sla_chunk_state_kernel(const
     auto update = [&](int it, const float (&A)[NI]) {
         const int chunk = rev ? nc - 1 - it : it;
         const __amdgpu_buffer_rsrc_t dst = pieces_of<DK, DV>(rev ? a.X : a.S, (size_t)(s.slot0 + chunk) * a.nh + hi);
+        // Behind the last token the decay gradient is rowsum(dsf * S_T), with few sums to average a rounding over: the part of
+        // it that the state entering the last chunk makes is taken from the states as they are here, in fp32, not from the
+        // pieces (T = 8, states in and out: error 2.8e-3 of its norm from those, 1.7e-3 so).
+        if (VAR == SLA_GLA && a.end && !rev && it == nc - 1) {
+            const size_t bh = (size_t)b * a.H + h;
+            const __amdgpu_buffer_rsrc_t x = __builtin_amdgcn_make_buffer_rsrc((void*)(a.dsf + bh * (DK * DV)), 0, DK * DV * 4, kRsrcWord3);
+            const __amdgpu_buffer_rsrc_t y = __builtin_amdgcn_make_buffer_rsrc((void*)(a.end + bh * (DK * DV / 32)), 0, DK * DV / 8, kRsrcWord3);
+            const int at = 4 * (key_of(0, r) * DV + 8 * g);  // bytes; the second tile of a pair is four rows on
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                float sum = 0.f;
+#pragma unroll
+                for (int n = 0; n < 2; ++n) {
+                    const f4 v = __builtin_bit_cast(f4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                            x, at, 4 * ((kt0 + 32 * wp + 4 * ti(i)) * DV + vt0 + 32 * cg + 4 * n), 0));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sum = fmaf(v[e], acc[i][n][e], sum);
+                }
+                sum = all_groups(sum);
+                if (g == 0)
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(sum), y, 4 * key_of(0, r),
+                                                          4 * (((vt0 >> 5) + cg) * DK + kt0 + 32 * wp + 4 * ti(i)), 0);
+            }
+        }
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
             __builtin_amdgcn_raw_buffer_store_b128(pack8(acc[i][0], acc[i][1]), dst,

@@ -15,8 +15,9 @@ def test_size(variant, packed):
     for B, T, H, dk, dv in ((2, 100, 4, 128, 128), (1, 1, 1, 64, 64), (8, 4096, 4, 128, 256), (3, 64, 64, 32, 64)):
         rows = T if packed else B * T
         slots = T // 64 + B + 1 if packed else B * ((T + 63) // 64)
-        # gates and their gradients, rounded to 16 bytes; two bf16 states per chunk and head
-        want = 4 * 4 * ((rows * H + 3) // 4 * 4) + 4 * slots * H * dk * dv
+        # gates and their gradients, rounded to 16 bytes; two bf16 states per chunk and head; GLA: rowsum(d_final * S) in
+        # fp32, a sum for each 32 value columns
+        want = 4 * 4 * ((rows * H + 3) // 4 * 4) + 4 * slots * H * dk * dv + (4 * B * H * dk * dv // 32 if variant == sla.GLA else 0)
         p = _params(variant, B=B, T=T, H=H, dk=dk, dv=dv)
         assert sla.sla_backward_chunks_workspace_bytes(p, packed) == max(want, least(p))
     # no more than 1 GiB of states at a time, however long the batch

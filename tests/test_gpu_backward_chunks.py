@@ -78,3 +78,20 @@ def test_layouts_and_packing_give_the_same_bits(variant):
             assert torch.equal(t, got[n][[1, 2, 5]]) and not got[n][[0, 3, 4]].any()
         elif t is not None:
             assert torch.equal(flat(t), got[n]), n
+
+
+@pytest.mark.parametrize("T,dk,dv", [(1, 128, 128), (16, 32, 64), (63, 64, 256), (64, 128, 64), (65, 64, 128), (130, 128, 256), (200, 32, 128)])
+def test_decay_gradient_behind_the_last_token(T, dk, dv):
+    """dlog_decay of the last token is rowsum(d_final_state * S_T), here with states so large that nothing else counts, plus
+    one token's q dq - k dk.  Formed in fp32 and rounded once, to bf16 (ulp / sqrt(12), 1.6e-3 of the norm for mantissas spread
+    over their logarithm); every state rounded to bf16 on the way adds as much: sqrt(2) of it with one, 2.8e-3 with both."""
+    d = si.custom(GLA, "bf16", B=2, T=T, H=4, dk=dk, dv=dv, seed=3600 + T)
+    d["log_decay"] = si.round_to_bf16((d["log_decay"] * 0.02).astype(np.float32))
+    cot = si.cotangents(2, T, 4, dk, dv, seed=3601 + T, final_state=True)
+    cot["d_final_state"] = cot["d_final_state"] * np.float32(8)
+    s0 = si.initial_state(2, 4, dk, dv, seed=3602 + T) * np.float32(32)
+    got, ref = check_backward(GLA, d, cot, s0, want_ds0=True, label=f"last token T={T} {dk}x{dv}")
+    e = got["dlog_decay"][:, -1] - ref["dlog_decay"][:, -1]
+    err = np.linalg.norm(e) / np.linalg.norm(ref["dlog_decay"][:, -1])
+    print(f"[last token] {err:.2e}", flush=True)
+    assert err <= 2.0e-3  # between none and one
