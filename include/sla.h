@@ -267,7 +267,7 @@ size_t sla_backward_chunks_workspace_bytes(const sla_params* p, int packed);
  *                    sequence, for bf16 tensors).  Contents on entry are ignored; calls that share a workspace must
  *                    not overlap.
  * bf16 tensors run in block form on the matrix cores (32-token blocks, fp32 accumulation, every decay factor <= 1;
- * dlog_decay is re-derived exactly every 512 tokens, so its error does not grow with the sequence length); fp32
+ * dlog_decay is re-derived every 512 tokens from the two states there, unrounded, so its error does not grow with the length); fp32
  * tensors run token by token in fp32 vector arithmetic.
  * Everything is enqueued on `stream`; nothing is allocated, freed or synchronised.  Returns a status code; on error
  * nothing is launched.

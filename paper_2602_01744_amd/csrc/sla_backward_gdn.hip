@@ -502,14 +502,14 @@ __global__ __launch_bounds__(kEw) void gdn_bwd_finish_kernel(const GArgs a, int 
 }
 
 // dlog_decay[b,t,h] = <d_final, S_T>[b,h] + sum_{s >= t} e[b,s,h], in spans of 2 * kEw tokens.  With anchors
-// (phi != null) the sum restarts at every span boundary from the exact value there, the sum over `planes` partials
+// (phi != null) the sum restarts at every span boundary from the exact value there, the sum over phi_planes partials
 // of <X, S> entering that token, so the spans are independent: grid (B * H, spans).  Without, one workgroup per
 // (b, h) takes the spans from the last to the first: grid (B * H, 1).
 constexpr int kSpan = 2 * kEw;
 static_assert(kSpan == kGdnAnchor, "one span of the scan per anchor interval");
 __global__ __launch_bounds__(kEw) void gdn_bwd_decay_scan_kernel(const float* e, const float* corr, int planes, int B,
                                                                  int Ttot, int H, const int* cu, const float* phi,
-                                                                 float* dld) {
+                                                                 int phi_planes, float* dld) {
     __shared__ __align__(16) float sx[kEw];
     const int bh = blockIdx.x, b = bh / H, h = bh % H, tid = threadIdx.x;
     int T = Ttot;
@@ -533,7 +533,7 @@ __global__ __launch_bounds__(kEw) void gdn_bwd_decay_scan_kernel(const float* e,
         if (phi && m < nspan - 1) {
             const size_t aid = (tok0 + (size_t)(m + 1) * kSpan) / kGdnAnchor;
             carry = 0.f;
-            for (int p = 0; p < planes; ++p) carry += phi[(aid * H + h) * (size_t)planes + p];
+            for (int p = 0; p < phi_planes; ++p) carry += phi[(aid * H + h) * (size_t)phi_planes + p];
         }
         // The sum over the later threads, one after another, as a span's carry runs too: the order is part of the result.
         // A wave starts at its own threads, 64 values are in flight, and the whole span's sum is left out where the next one
@@ -630,10 +630,10 @@ size_t backward_gdn_workspace_floats(const sla_params& p, bool packed) {
 }
 
 int launch_gdn_decay_scan(const float* e, const float* corr, int planes, int B, int T, int H, const int* cu,
-                          const float* phi, float* dld, hipStream_t stream) {
+                          const float* phi, int phi_planes, float* dld, hipStream_t stream) {
     const unsigned spans = phi ? (unsigned)((T + kSpan - 1) / kSpan) : 1u;
     hipLaunchKernelGGL(gdn_bwd_decay_scan_kernel, dim3((unsigned)(B * H), spans), dim3(kEw), 0, stream, e, corr, planes, B, T,
-                       H, cu, phi, dld);
+                       H, cu, phi, phi_planes, dld);
     return hipGetLastError() == hipSuccess ? SLA_OK : SLA_ERR_HIP;
 }
 
@@ -704,7 +704,7 @@ int launch_backward_gdn(const sla_params& p, const void* q, const void* k, const
     hipLaunchKernelGGL(gdn_bwd_finish_kernel, dim3(eg), dim3(kEw), 0, stream, a, pk, pv, dql, kl ? dkl : nullptr,
                        dbeta, e);
     if (hipGetLastError() != hipSuccess) return SLA_ERR_HIP;
-    return launch_gdn_decay_scan(e, dsf ? a.corr : nullptr, pk, p.B, p.T, p.H, cu, anchor_phi, dld, stream);
+    return launch_gdn_decay_scan(e, dsf ? a.corr : nullptr, pk, p.B, p.T, p.H, cu, anchor_phi, pk, dld, stream);
 }
 
 }  // namespace sla

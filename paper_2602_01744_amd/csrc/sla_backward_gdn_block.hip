@@ -425,10 +425,19 @@ __device__ __forceinline__ void run_sweep(const Frame& f, unsigned char* smem, i
 // wave's operand is kept as it is: lane (r, g) holds key dimensions 16 t + 4 g .. +3 and 16 (t + 1) + 4 g .. +3 of column n,
 // which go next to each other: group of four G of 32 dimensions sits at place 2 (G % 4) + G / 4.
 template <int DK, int DV>
-__device__ __forceinline__ void keep_state(bf* states, const Frame& f, int I, int n, int t, int g, s8 x) {
-    const size_t slot = (f.a.cu ? f.s.tok0 / kGdnChunk + f.s.b : (size_t)f.s.b * ((f.s.T + kGdnChunk - 1) / kGdnChunk)) + I / 2;
-    static_assert(kGdnChunk == 2 * C, "two blocks per chunk");
+__device__ __forceinline__ void keep_state(bf* states, const Frame& f, size_t slot, int n, int t, int g, s8 x) {
     *(s8*)(states + ((slot * f.a.H + f.s.h) * DV + n) * DK + 16 * t + 8 * g) = x;
+}
+__device__ __forceinline__ size_t chunk_slot(const Frame& f, int I) {
+    static_assert(kGdnChunk == 2 * C, "two blocks per chunk");
+    return (f.a.cu ? f.s.tok0 / kGdnChunk + f.s.b : (size_t)f.s.b * ((f.s.T + kGdnChunk - 1) / kGdnChunk)) + I / 2;
+}
+// What that rounding left of a state: with it the state is known to 2^-17.
+template <int DK, int DV>
+__device__ __forceinline__ void keep_rest(bf* states, const Frame& f, size_t slot, int n, int g, const f4 (&S)[DK / 16]) {
+#pragma unroll
+    for (int t = 0; t < DK / 16; t += 2)
+        keep_state<DK, DV>(states, f, slot, n, t, g, pack8(S[t] - unpack4(pack4(S[t])), S[t + 1] - unpack4(pack4(S[t + 1]))));
 }
 
 // ---- sweep 1: forward, S[dk, 16 value columns per wave] -> res ------------------------------------------------
@@ -487,10 +496,11 @@ __device__ __forceinline__ void state_sweep(const GdnBlockArgs& a, const Areas& 
             const bf* T1 = (const bf*)(st + L::oT);
             const float* sc = (const float*)(st + L::oS);
             f4 X[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+            if (KEEP && I > 0 && (I & (kAnchorBlocks - 1)) == 0) keep_rest<DK, DV>(a.rest_s, f, anchor_id(s, I), n, g, S);
 #pragma unroll
             for (int t = 0; t < NT; t += 2) {
                 const s8 bS = pack8(S[t], S[t + 1]);
-                if (KEEP && (I & 1) == 0) keep_state<DK, DV>(a.keep_s, f, I, n, t, g, bS);
+                if (KEEP && (I & 1) == 0) keep_state<DK, DV>(a.keep_s, f, chunk_slot(f, I), n, t, g, bS);
                 mma(X[0], op_rows(Kr, RKr, r, 16 * t, g), bS);
                 mma(X[1], op_rows(Kr, RKr, 16 + r, 16 * t, g), bS);
             }
@@ -526,7 +536,18 @@ __device__ __forceinline__ void state_sweep(const GdnBlockArgs& a, const Areas& 
                 mma(S[t], op_cols(Kc, RKc, 0, 16 * t, r, g), bU);
             }
         },
-        [&]() {});
+        [&]() {
+            if (KEEP && a.dsf) {  // <d_final, S_T> over this wave's 16 value columns
+                float acc = 0.f;
+#pragma unroll
+                for (int t = 0; t < NT; ++t)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        acc = fmaf(a.dsf[((size_t)s.bh * DK + 16 * t + 4 * g + i) * DV + n], S[t][i], acc);
+                acc = all_groups(row_all(acc));
+                if (lane == 0) a.corr[(size_t)(s.slice * (kCols / 16) + w) * a.B * a.H + s.bh] = acc;
+            }
+        });
 }
 
 template <int DK, int DV>
@@ -652,10 +673,12 @@ __device__ __forceinline__ void cotangent_sweep(const GdnBlockArgs& a, const Are
             const f4 p0 = sc4(sc, kP, 4 * g), p1 = sc4(sc, kP, 16 + 4 * g);
             const f4 gq0 = sc4(sc, kGq, 4 * g), gq1 = sc4(sc, kGq, 16 + 4 * g);
             f4 dU[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};  // K X1, this wave's columns
+            if (KEEP && I + 1 < s.nblk && ((I + 1) & (kAnchorBlocks - 1)) == 0)
+                keep_rest<DK, DV>(a.rest_x, f, anchor_id(s, I + 1), n, g, X);
 #pragma unroll
             for (int t = 0; t < NT; t += 2) {
                 const s8 bX = pack8(X[t], X[t + 1]);
-                if (KEEP && ((I & 1) || I == s.nblk - 1)) keep_state<DK, DV>(a.keep_x, f, I, n, t, g, bX);
+                if (KEEP && ((I & 1) || I == s.nblk - 1)) keep_state<DK, DV>(a.keep_x, f, chunk_slot(f, I), n, t, g, bX);
                 mma(dU[0], op_rows(Kr, RKr, r, 16 * t, g), bX);
                 mma(dU[1], op_rows(Kr, RKr, 16 + r, 16 * t, g), bX);
             }

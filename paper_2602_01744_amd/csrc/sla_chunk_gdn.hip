@@ -8,10 +8,12 @@
 //     dq'_t = p_t dout_t S^T + sum_j N'[t][j] k_j                                   dq = G^Q dq'    dG^Q = q . dq'
 //     dk_t  = (A / p_t) u_t X^T - p_t w_t S^T + sum_j (M + M^T)[t][j] k_j + sum_s N'[s][t] G^Q_s q_s
 //     dv = G^K w    dG^K = w . v    dbeta = du . res
-//     dlog_decay_t = <X, S_end> + sum_{s >= t} (G^Q dG^Q - G^K dG^K)_s      <X, S_end> = A <X, S> + sum_j k_j . ((A / p_j) u_j X^T)
+//     dlog_decay_t = <X, S_end> + sum_{s >= t} (G^Q dG^Q - G^K dG^K)_s
 // (the block form's lines, see sla_backward_gdn_block.hip, which hold for any length of block once u and w are known).
 // Every factor is <= 1.  The suffix sums of the decay gradient run afterwards over spans of 512 tokens, each from <X, S_end>
-// of the chunk that ends it (kGdnAnchor in sla_gdn_block.h).
+// at their ends (kGdnAnchor in sla_gdn_block.h), which has nothing to average a rounding over: both states are
+// taken there as two bf16 parts, 2^-17 off fp32, and at the sequence's end in fp32 by the state sweep.  (From the bf16 states
+// alone the last token's gradient was 2.0e-3 off at T = 8 with states in and out, 2.3e-4 from the sweeps.)
 // Against the four sweeps of sla_backward_gdn_block.hip, a training step with its convolutions and projections: few sequences 1.6 to
 // 3 times (B=2 T=4096 H=4 128 x 256 1142 -> 381 us, B=2 T=1000 H=8 128 x 128 256 -> 120, B=1 T=300 H=4 113 -> 65, 4096 packed
 // tokens H=8 303 -> 162), where the sweeps leave some compute units idle 1.1 to 1.25 times (B=8 T=4096 H=12 1110 -> 1012, 64 x 128
@@ -38,18 +40,20 @@ namespace chk {
 static_assert(kChunk == kGdnChunk, "the sweeps keep a state per chunk");
 
 constexpr int kThreads = 256;
+constexpr int kSpanChunks = kGdnAnchor / kChunk;
 
 struct GdnArgs {
     Args a;  // gq, gk: the gates; dgq, dgk: their gradients; S, X and the decays are below
     const uint16_t* S;    // [slot][H][dv][dk], see keep_state()
     const uint16_t* X;
+    const uint16_t* Srest;  // [rows / 512 + 1][H][dv][dk] what rounding left of S and X at every 512th token of a sequence
+    const uint16_t* Xrest;
     const uint16_t* res;  // [rows,H,dv]
     const float* du;
     const float* ld;      // [rows,H]
     const float* beta;
     float* e;             // [rows,H] the scalars whose suffix sums dlog_decay is
-    float* anchor;        // [rows / 512 + 1][H] <X, S_end> at every 512th token of a sequence
-    float* corr;          // [B,H] and at its end
+    float* anchor;        // [rows / 512 + 1][H][8] <X, S> at every 512th token of a sequence, an eighth of the value columns each
     float* dbeta;
 };
 
@@ -193,7 +197,6 @@ __global__ __launch_bounds__(kThreads, 2) void sla_chunk_gdn_kernel(const GdnArg
         for (int i = 0; i < 2; ++i) aq[m][i] = ak[m][i] = aw[m][i] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int x = 0; x < NM; ++x) N[x] = M[x] = f4{0.f, 0.f, 0.f, 0.f};
-    f4 corr[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};  // S X^T of a key tile; its diagonal is wanted
     float pb = 0.f, pk = 0.f;                                       // this thread's share of du . res, w . v of its token
     for (int c2 = 0; c2 < NS; c2 += 2)
 #pragma unroll
@@ -231,7 +234,6 @@ __global__ __launch_bounds__(kThreads, 2) void sla_chunk_gdn_kernel(const GdnArg
             const int G = 2 * (r & 3) + i, from = (8 * g + (r >> 2)) * L::SS + 32 * wd + 4 * (2 * (G & 3) + (G >> 2));
             fS[i] = join(lds_tr(sS + from), lds_tr(sS + from + 4 * L::SS));
             fX[i] = join(lds_tr(sX + from), lds_tr(sX + from + 4 * L::SS));
-            mma(corr[i], fS[i], fX[i]);
         }
         auto slab = [&](const uint16_t* x, int row) { return op(*(const u4*)(x + 8 * unit_at<4>(row, g))); };
 #pragma unroll
@@ -314,20 +316,16 @@ __global__ __launch_bounds__(kThreads, 2) void sla_chunk_gdn_kernel(const GdnArg
             fk[pp][i] = col_op(sk, 32 * pp + 8 * g, i);
             fq[pp][i] = col_op(sq, 32 * pp + 8 * g, i);
         }
-    float phi = 0.f;
 #pragma unroll
     for (int mm = 0; mm < TB; ++mm) {
         const int m = m0 + mm, t = 16 * m + r;
-        const u4 qx = *(const u4*)(sq + 8 * unit_at<U>(t, 4 * wd + g)), kx = *(const u4*)(sk + 8 * unit_at<U>(t, 4 * wd + g));
+        const u4 qx = *(const u4*)(sq + 8 * unit_at<U>(t, 4 * wd + g));
         const float gq = sgq[t], ct = sc[t], p = ex2(ct), fx = sbeta[t] * ex2(fminf(c_end - ct, 0.f));
         f4 q2[2], k2[2];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             q2[i] = aq[mm][i] * p;
-            k2[i] = ak[mm][i] * fx;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) phi = fmaf(bf_at(kx, 4 * i + e), k2[i][e], phi);
-            k2[i] = k2[i] - aw[mm][i] * p;
+            k2[i] = ak[mm][i] * fx - aw[mm][i] * p;
         }
 #pragma unroll
         for (int pp = 0; pp < 2; ++pp) {
@@ -353,16 +351,27 @@ __global__ __launch_bounds__(kThreads, 2) void sla_chunk_gdn_kernel(const GdnArg
         put_row(a.dk, t, k2[0], k2[1]);
         put_row(a.dq, t, q2[0] * gq, q2[1] * gq);
     }
-    if (wt == 0) {  // A <X, S> over the wave's key dimensions: the diagonals of the two tiles
-        const float A = ex2(c_end);
+    // <X, S> at the end of the 512-token span: the span's eight chunks make an eighth each (in the last one alone it was a
+    // tail of 8 us, 128 x 256).  The states of both sides are in the same order.
+    const int last = chunk | (kSpanChunks - 1), part = chunk & (kSpanChunks - 1);
+    const bool anchored = (last + 1) * kChunk < s.T;
+    const size_t aid = (s.tok0 + (size_t)(last + 1) * kChunk) / kGdnAnchor;
+    if (anchored) {
+        constexpr int kUnits = DK * DV / 8 / kSpanChunks;
+        const u4* X = (const u4*)(ga.X + state + (size_t)(last - chunk) * a.H * (DK * DV)) + part * kUnits;
+        const u4* S = (const u4*)(ga.S + state + (size_t)(last - chunk + 1) * a.H * (DK * DV)) + part * kUnits;
+        const u4* Xr = (const u4*)(ga.Xrest + (aid * a.H + h) * (size_t)(DK * DV)) + part * kUnits;
+        const u4* Sr = (const u4*)(ga.Srest + (aid * a.H + h) * (size_t)(DK * DV)) + part * kUnits;
+        float phi = 0.f;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const float lo = (r & 1) ? corr[i][1] : corr[i][0], hi = (r & 1) ? corr[i][3] : corr[i][2];
-            if (g == (r >> 2)) phi = fmaf(A, (r & 2) ? hi : lo, phi);
+        for (int i = tid; i < kUnits; i += kThreads) {
+            const u4 s0 = S[i], s1 = Sr[i], x0 = X[i], x1 = Xr[i];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) phi = fmaf(bf_at(s0, e) + bf_at(s1, e), bf_at(x0, e) + bf_at(x1, e), phi);
         }
+        phi = all_groups(row_all(phi));
+        if (lane == 0) sphi[w] = phi;
     }
-    phi = all_groups(row_all(phi));
-    if (lane == 0) sphi[w] = phi;
     __syncthreads();
     if (w == 0) {
         float dgq = 0.f;
@@ -376,10 +385,8 @@ __global__ __launch_bounds__(kThreads, 2) void sla_chunk_gdn_kernel(const GdnArg
             ga.dbeta[at] = spb[lane];
             ga.e[at] = sgq[lane] * dgq - sgk[lane] * dgk;
         }
-        const int end = t0 + kChunk;
-        float* at_end = end >= s.T ? ga.corr + (size_t)b * a.H + h
-                        : end % kGdnAnchor == 0 ? ga.anchor + ((s.tok0 + end) / kGdnAnchor) * a.H + h : nullptr;
-        if (lane == 0 && at_end) *at_end = (sphi[0] + sphi[1]) + (sphi[2] + sphi[3]);
+        if (lane == 0 && anchored)
+            ga.anchor[(aid * a.H + h) * kSpanChunks + part] = (sphi[0] + sphi[1]) + (sphi[2] + sphi[3]);
     }
 }
 
@@ -419,7 +426,7 @@ static int launch_gdn_chunks_dv(const GdnArgs& ga, int dv, hipStream_t stream) {
 static size_t round4(size_t n) { return (n + 3) & ~(size_t)3; }
 
 struct GdnChunkSizes {
-    size_t rows, n, slots, state, wide, ends;  // n: floats of a [rows,H] array; state: of S or X; wide: of res, half of du
+    size_t rows, n, slots, state, rest, wide, ends;  // n: floats of a [rows,H] array; state: of S or X; wide: of res, half of du
     size_t floats;
 };
 static GdnChunkSizes gdn_chunk_sizes(const sla_params& p, bool packed) {
@@ -429,8 +436,9 @@ static GdnChunkSizes gdn_chunk_sizes(const sla_params& p, bool packed) {
     z.slots = packed ? (size_t)p.T / kGdnChunk + p.B + 1 : (size_t)p.B * ((p.T + kGdnChunk - 1) / kGdnChunk);
     z.state = z.slots * p.H * p.dk * p.dv / 2;
     z.wide = z.rows * p.H * p.dv / 2;
-    z.ends = round4(gdn_anchor_count(z.rows) * p.H) + round4((size_t)p.B * p.H);
-    z.floats = 5 * z.n + z.ends + 2 * z.state + 3 * z.wide + gdn_pair_workspace_floats(p.B, p.T, p.H, packed);
+    z.rest = gdn_anchor_count(z.rows) * p.H * p.dk * p.dv / 2;
+    z.ends = gdn_anchor_count(z.rows) * p.H * chk::kSpanChunks + (size_t)p.B * p.H * (p.dv / 16);
+    z.floats = 5 * z.n + z.ends + 2 * (z.state + z.rest) + 3 * z.wide + gdn_pair_workspace_floats(p.B, p.T, p.H, packed);
     return z;
 }
 
@@ -459,7 +467,9 @@ int launch_backward_gdn_chunks(const sla_params& p, const void* q, const void* k
     // were 6 % slower)
     uint16_t* S = (uint16_t*)ws;
     uint16_t* X = S + 2 * z.state;
-    uint16_t* res = X + 2 * z.state;
+    uint16_t* Srest = X + 2 * z.state;
+    uint16_t* Xrest = Srest + 2 * z.rest;
+    uint16_t* res = Xrest + 2 * z.rest;
     float* du = (float*)(res + 2 * z.wide);
     float* block_ws = du + 2 * z.wide;
     float* gq = block_ws + gdn_pair_workspace_floats(p.B, p.T, p.H, packed);
@@ -468,11 +478,11 @@ int launch_backward_gdn_chunks(const sla_params& p, const void* q, const void* k
     float* dgk = dgq + z.n;
     float* e = dgk + z.n;
     float* anchor = e + z.n;
-    float* corr = anchor + round4(gdn_anchor_count(z.rows) * p.H);
+    float* ends = anchor + gdn_anchor_count(z.rows) * p.H * chk::kSpanChunks;
     GdnBlockArgs g = {};
     g.q = (const uint16_t*)q; g.k = (const uint16_t*)k; g.v = (const uint16_t*)v; g.dout = (const uint16_t*)dout;
     g.ld = ld; g.beta = beta; g.gq = gq; g.gk = gk; g.s0 = s0; g.dsf = dsf; g.ds0 = ds0;
-    g.keep_s = S; g.keep_x = X; g.res_rows = res; g.du_rows = du;
+    g.keep_s = S; g.keep_x = X; g.rest_s = Srest; g.rest_x = Xrest; g.res_rows = res; g.du_rows = du; g.corr = ends;
     g.block_ws = block_ws;
     g.rows = z.rows; g.cu = cu;
     g.B = p.B; g.T = p.T; g.H = p.H; g.dim_k = p.dk; g.dim_v = p.dv;
@@ -483,11 +493,11 @@ int launch_backward_gdn_chunks(const sla_params& p, const void* q, const void* k
     c.a.B = p.B; c.a.T = p.T; c.a.H = p.H; c.a.cu = cu;
     c.a.nb = p.B; c.a.nh = p.H; c.a.slots = (int)z.slots;
     c.a.nchunk = (p.T + kGdnChunk - 1) / kGdnChunk;
-    c.S = S; c.X = X; c.res = res; c.du = du; c.ld = ld; c.beta = beta; c.e = e; c.anchor = anchor; c.corr = corr; c.dbeta = dbeta;
+    c.S = S; c.X = X; c.Srest = Srest; c.Xrest = Xrest; c.res = res; c.du = du; c.ld = ld; c.beta = beta; c.e = e; c.anchor = anchor; c.dbeta = dbeta;
     int rc = launch_bwd_gates(ql, kl, gq, gk, z.rows, p.H, stream);
     if (rc == SLA_OK) rc = launch_gdn_block_pair(g, stream);
     if (rc == SLA_OK) rc = p.dk == 64 ? chk::launch_gdn_chunks_dv<64>(c, p.dv, stream) : chk::launch_gdn_chunks_dv<128>(c, p.dv, stream);
-    if (rc == SLA_OK) rc = launch_gdn_decay_scan(e, corr, 1, p.B, p.T, p.H, cu, anchor, dld, stream);
+    if (rc == SLA_OK) rc = launch_gdn_decay_scan(e, dsf ? ends : nullptr, p.dv / 16, p.B, p.T, p.H, cu, anchor, chk::kSpanChunks, dld, stream);
     if (rc != SLA_OK) return rc;
     return launch_bwd_logits(GateGrad{gq, dgq, 1, 0, dql}, GateGrad{gk, dgk, 1, 0, kl ? dkl : nullptr}, z.rows, p.H, cu, p.B,
                              stream);

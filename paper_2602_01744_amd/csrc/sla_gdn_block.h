@@ -37,16 +37,20 @@ struct GdnBlockArgs {
     int B, T, H, dim_k, dim_v;
     // Chunk-parallel schedule (sla_chunk_gdn.hip): where the two state sweeps leave, for every 64-token chunk, the state
     // entering it and the cotangent of the state behind it, bf16 [chunk slot][H][dv][dk], see keep_state() for the order
-    // inside a row; and res (bf16) and du (fp32) as rows [rows,H,dv].
+    // inside a row; at every 512th token of a sequence also what that rounding left of the two states, [rows/512 + 1][H][dv][dk]
+    // in the same order; and res (bf16) and du (fp32) as rows [rows,H,dv].  corr: [dv/16][B*H], over the value columns.
     uint16_t* keep_s;
     uint16_t* keep_x;
+    uint16_t* rest_s;
+    uint16_t* rest_x;
     uint16_t* res_rows;
     float* du_rows;
 };
 
 // The decay gradient is a suffix sum of per-token scalars built from bf16-operand products, whose rounding adds up
-// like a random walk over the tokens behind; every kGdnAnchor tokens of a sequence it is re-derived exactly as
-// <X, S> at that boundary (sweep 3 leaves X there, sweep 4 forms the product).  Anchors are numbered by absolute
+// like a random walk over the tokens behind; every kGdnAnchor tokens of a sequence it is re-derived as
+// <X, S> at that boundary in fp32 (sweep 3 leaves X there, sweep 4 forms the product; chunk-parallel: from both states kept as
+// two bf16 parts, 2^-17).  Anchors are numbered by absolute
 // token position / kGdnAnchor: sequences do not overlap, so neither do their anchors (fewer than rows / 512 + 1).
 constexpr int kGdnAnchor = 512;
 inline size_t gdn_anchor_count(size_t rows) { return rows / kGdnAnchor + 1; }
@@ -57,7 +61,7 @@ int launch_gdn_block_sweeps(const GdnBlockArgs& a, hipStream_t stream);
 
 // dlog_decay from the per-token scalars e, see gdn_bwd_decay_scan_kernel (sla_backward_gdn.hip).
 int launch_gdn_decay_scan(const float* e, const float* corr, int planes, int B, int T, int H, const int* cu,
-                          const float* phi, float* dld, hipStream_t stream);
+                          const float* phi, int phi_planes, float* dld, hipStream_t stream);
 
 // The chunk-parallel schedule's part of it: the pre-pass and, in one launch, the two sweeps that find res and du.  block_ws
 // then holds gdn_pair_workspace_floats() floats.

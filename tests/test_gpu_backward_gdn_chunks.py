@@ -18,9 +18,12 @@ def test_size(packed):
         rows = T if packed else B * T
         slots, blocks = ((T // n + B + 1) if packed else B * ((T + n - 1) // n) for n in (64, 32))
         four = lambda n: (n + 3) // 4 * 4
-        # gates, their gradients and the decay's scalar; the ends of 512-token spans and of sequences; two bf16 states per
-        # chunk; res and du; 8 x 32 floats and a bf16 matrix per block
-        want = 5 * four(rows * H) + four((rows // 512 + 1) * H) + four(B * H) + slots * H * dk * dv + 3 * rows * H * dv // 2 + blocks * H * (256 + 512)
+        # gates, their gradients and the decay's scalar; the ends of 512-token spans as eight sums, of sequences as one for each
+        # 16 value columns; two bf16 states per chunk, and the rest of two per span; res and du; 8 x 32 floats and a bf16
+        # matrix per block
+        spans = rows // 512 + 1
+        want = (5 * four(rows * H) + 8 * spans * H + B * H * dv // 16 + (slots + spans) * H * dk * dv + 3 * rows * H * dv // 2
+                + blocks * H * (256 + 512))
         p = _params(B=B, T=T, H=H, dk=dk, dv=dv)
         assert sla.sla_backward_gdn_chunks_workspace_bytes(p, packed) == max(4 * want, least(p))
     for p in (_params(dtype=sla.F32), _params(dk=32), _params(T=0), _params(B=0), _params(B=8, T=65536, H=16)):
@@ -92,3 +95,30 @@ def test_packing_gives_the_same_bits():
             assert torch.equal(t, got[n][[1, 2, 5]]) and not got[n][[0, 3, 4]].any()
         elif t is not None:
             assert torch.equal(flat(t), got[n]), n
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("B,T,dk,dv", [(2, 1, 128, 128), (1, 8, 64, 64), (2, 64, 128, 256), (1, 200, 64, 128), (2, 512, 64, 256), (1, 1025, 128, 128), (2, 1600, 128, 64)])
+def test_decay_gradient_at_anchors(B, T, dk, dv):
+    """dlog_decay of a row's last token, and of every 512th, is <X, S> behind it plus one token's scalar, here with states so
+    large that <X, S> is nearly all of it.  It is formed from the states as the sweeps carry them: 2^-17 of a product's
+    terms, and the rounding of the tokens' own operands, 2^-9 of what they add to states that are 64 times as large: 1e-4.
+    States in bf16 would give 2e-3."""
+    import numpy as np
+    from test_gpu_backward_gdn import check_backward_gdn
+
+    H = 3
+    d = si.custom(sla.GDN, "bf16", B=B, T=T, H=H, dk=dk, dv=dv, seed=3700 + T)
+    d["log_decay"] = (d["log_decay"] * 1e-3).astype(np.float32)
+    d["beta"] = (d["beta"] * 1e-3).astype(np.float32)  # the rule erases what it reads: keep the states for 1600 tokens
+    cot = si.cotangents(B, T, H, dk, dv, seed=3701 + T, final_state=True)
+    cot["d_final_state"] = cot["d_final_state"] * np.float32(64)
+    s0 = si.initial_state(B, H, dk, dv, seed=3702 + T) * np.float32(64)
+    got, ref = check_backward_gdn(d, cot, s0, want_ds0=True, label=f"anchors T={T} {dk}x{dv}")
+    for t in [T - 1] + list(range(511, T - 1, 512)):
+        e = got["dlog_decay"][:, t] - ref["dlog_decay"][:, t]
+        # on the scale of the products' root sum of squares, which <X, S> itself may be small against
+        scale = np.linalg.norm(s0, axis=(2, 3)) * np.linalg.norm(cot["d_final_state"], axis=(2, 3)) / np.sqrt(dk * dv)
+        err = np.abs(e / scale).max()
+        print(f"[anchor] t={t} {err:.2e}", flush=True)
+        assert err <= 5e-4
