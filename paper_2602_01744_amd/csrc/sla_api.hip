@@ -212,15 +212,32 @@ int choose_segments(const sla_params& p, int cus, int* seg_len) {
     return nseg;
 }
 
+int default_dv_split(const sla_params& p, int cus, int nseg) {
+    // The widest slice that still gives every compute unit a workgroup; narrower slices repeat the
+    // per-token decay work of a head in more workgroups, so never go narrower than needed.
+    const int64_t seqs = (int64_t)p.B * p.H * nseg;
+    const int widths[] = {64, 32, 16};
+    for (int w : widths) {
+        if (w > p.dv) continue;
+        if (seqs * (p.dv / w) >= cus) return w;
+    }
+    return 16;
+}
+int choose_dv_split(const sla_params& p, int cus, int nseg = 1) {
+    return p.dv_split != 0 ? p.dv_split : default_dv_split(p, cus, nseg);
+}
+
 // Pieces per segment of the pre-pass.  It covers nseg - 1 of nseg segments: with one workgroup for each, 1 / nseg of the
 // compute units have nothing to do.  More pieces than compute units run in rounds; a round costs about kRound tokens besides
 // its own.  Pieces are whole blocks and as long as segments have to be.  The pre-pass of B=1 T=65536 H=32 128 x 128 GLA (4
 // segments) takes 346 us in 4 pieces each against 419 (memory has 4.7 of the 5.3 TB/s then), of B=8 T=4096 H=4 128 x 256 (2)
 // in 2 pieces 29 against 45; cutting B=4 T=2048 H=8 (4 segments of 512), whose 2 pieces would run in 2 rounds, gains nothing.
-int choose_pieces(const sla_params& p, int cus, int nseg, int seg_len, int dvw) {
+// Counted with the slices the library would choose, whatever dv_split asks for: the pieces decide the order of the sums, and
+// dv_split is to change no result.
+int choose_pieces(const sla_params& p, int cus, int nseg, int seg_len) {
     constexpr int64_t kRound = 128, kMostPieces = 8;
     if (nseg <= 1) return 1;
-    const int64_t rows = (int64_t)p.B * p.H * (p.dv / dvw) * (nseg - 1);
+    const int64_t rows = (int64_t)p.B * p.H * (p.dv / default_dv_split(p, cus, nseg)) * (nseg - 1);
     int best = 1;
     int64_t least = 0;
     for (int m = 1; m <= kMostPieces; ++m) {
@@ -232,19 +249,6 @@ int choose_pieces(const sla_params& p, int cus, int nseg, int seg_len, int dvw) 
         }
     }
     return best;
-}
-
-int choose_dv_split(const sla_params& p, int cus, int nseg = 1) {
-    if (p.dv_split != 0) return p.dv_split;
-    // The widest slice that still gives every compute unit a workgroup; narrower slices repeat the
-    // per-token decay work of a head in more workgroups, so never go narrower than needed.
-    const int64_t seqs = (int64_t)p.B * p.H * nseg;
-    const int widths[] = {64, 32, 16};
-    for (int w : widths) {
-        if (w > p.dv) continue;
-        if (seqs * (p.dv / w) >= cus) return w;
-    }
-    return 16;
 }
 
 size_t piece_floats(const sla_params& p, int nseg, int pieces) {
@@ -290,7 +294,7 @@ int sla_forward_ws(const sla_params* p, const void* q, const void* k, const void
         seg_len = p->T;
     }
     const int dvw = choose_dv_split(*p, cus, nseg);
-    const int pieces = choose_pieces(*p, cus, nseg, seg_len, dvw);
+    const int pieces = choose_pieces(*p, cus, nseg, seg_len);
     if (pieces > 1 && sla::launch_forward_pieces && pieces_fit(*p, nseg, pieces, workspace_bytes))
         return sla::launch_forward_pieces(*p, dvw, nseg, seg_len, pieces, q, k, v, q_head_logits, k_head_logits, log_decay,
                                           beta, initial_state, out, final_state, (float*)workspace, nullptr, (hipStream_t)stream);
@@ -347,7 +351,7 @@ int sla_forward_static(const sla_params* p, const void* q, const void* k, const 
         if (!ws) return SLA_ERR_HIP;
     }
     const int dvw = choose_dv_split(*p, cus, nseg);
-    const int pieces = choose_pieces(*p, cus, nseg, seg_len, dvw);
+    const int pieces = choose_pieces(*p, cus, nseg, seg_len);
     if (pieces > 1 && sla::launch_forward_pieces && pieces_fit(*p, nseg, pieces, SLA_STATIC_SCRATCH_BYTES))
         return sla::launch_forward_pieces(*p, dvw, nseg, seg_len, pieces, q, k, v, q_head_logits, k_head_logits, log_decay,
                                           beta, initial_state, out, final_state, ws, nullptr, (hipStream_t)stream);
@@ -688,7 +692,7 @@ size_t sla_forward_workspace_bytes(const sla_params* p, int compute_units) {
     if (least == 0) return 0;
     int seg_len = 0;
     const int nseg = choose_segments(*p, compute_units, &seg_len);
-    const int pieces = choose_pieces(*p, compute_units, nseg, seg_len, choose_dv_split(*p, compute_units, nseg));
+    const int pieces = choose_pieces(*p, compute_units, nseg, seg_len);
     return least + piece_floats(*p, nseg, pieces) * sizeof(float);
 }
 

@@ -28,6 +28,34 @@ def test_workspace_holds_the_pieces(T, segments):
     assert sla.sla_forward_workspace_bytes(_params(sla.GDN, "bf16", T, 0), 256) == 0
 
 
+WIDTHS = [(2, 4096, 8, 128, 128, 2), (1, 65536, 32, 128, 128, 0), (1, 1100, 2, 64, 64, 2), (4, 8192, 4, 128, 256, 0), (3, 2065, 5, 32, 128, 2)]
+
+
+@pytest.mark.parametrize("B,T,H,dk,dv,segments", WIDTHS)
+def test_slice_width_does_not_choose_the_pieces(B, T, H, dk, dv, segments):
+    """dv_split is a schedule, not a result: the pieces, whose chaining orders the sums, are the same for every width."""
+    sizes = set()
+    for width in (0, 16, 32, 64):
+        p = _params(GLA, "bf16", T, segments, B, H, dk, dv)
+        p.dv_split = width
+        sizes.add(sla.sla_forward_workspace_bytes(p, 256))
+    assert len(sizes) == 1 and sizes.pop() > 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("variant", [RETNET, GLA])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("B,T,H,dk,dv,segments", [(2, 1152, 8, 128, 128, 2), (1, 1100, 2, 64, 64, 2), (1, 3100, 3, 32, 256, 3)])
+def test_slice_width_keeps_the_bits(variant, dtype, B, T, H, dk, dv, segments):
+    d = si.custom(variant, dtype, B=B, T=T, H=H, dk=dk, dv=dv, seed=1800 + T)
+    g, _ = si.to_device(d, dtype, variant)
+    args = [g[n] for n in ("q", "k", "v", "q_logits", "k_logits", "log_decay", "beta")]
+    ref, fin = sla.forward(variant, *args, segments=segments)
+    for width in (16, 32, 64):
+        o, f = sla.forward(variant, *args, segments=segments, dv_split=width)
+        assert torch.equal(o, ref) and torch.equal(f, fin), width
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("variant", [RETNET, GLA])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
