@@ -122,6 +122,8 @@ int sla_forward(const sla_params* p, const void* q, const void* k, const void* v
  * sequential state carry between chunks of Sec. 3.2 (Chunkwise Parallel Training) becomes a two-level scan.
  * workspace may be NULL (then this is sla_forward).  With p->segments == 0 a workspace that is too small makes
  * the call fall back to one fused pass; with p->segments > 1 it is SLA_ERR_WORKSPACE.
+ * In a workspace of sla_forward_workspace_bytes the pre-pass may work on pieces of segments: faster, with the states' fp32
+ * sums in another order than in a workspace of less than that, down to sla_workspace_bytes, where it takes whole segments.
  */
 int sla_forward_ws(const sla_params* p, const void* q, const void* k, const void* v,
                    const float* q_head_logits, const float* k_head_logits,
@@ -131,8 +133,8 @@ int sla_forward_ws(const sla_params* p, const void* q, const void* k, const void
 /*
  * sla_forward_ws for callers that cannot allocate device memory and have no workspace to hand in: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments and results as sla_forward;
- * the schedule is the one sla_forward_ws would choose with a large enough workspace (p->segments as there), and the
- * workspace is a buffer of SLA_STATIC_SCRATCH_BYTES that is part of the library's device image (every GPU the
+ * the schedule is the one sla_forward_ws would choose in a workspace of sla_workspace_bytes (p->segments as there), to the
+ * same bits, and the workspace is a buffer of SLA_STATIC_SCRATCH_BYTES that is part of the library's device image (every GPU the
  * library runs on holds one copy until the process ends).  The call allocates and frees nothing.
  *
  * Limit: a shape whose segment schedule needs more than SLA_STATIC_SCRATCH_BYTES is rejected with SLA_ERR_SCRATCH
@@ -406,7 +408,8 @@ size_t sla_gate_logits_backward_workspace_bytes(const sla_params* p);
 size_t sla_workspace_bytes(const sla_params* p, int compute_units);
 
 /* Bytes with which sla_forward_ws runs fastest (>= sla_workspace_bytes, 0 where that is 0): its pre-pass may then cut the
- * segments into shorter pieces, so that it too has a workgroup for every compute unit. */
+ * segments into shorter pieces, so that it too has a workgroup for every compute unit.  Results agree with those in a
+ * smaller workspace to the rounding of the chained states, not to the bit. */
 size_t sla_forward_workspace_bytes(const sla_params* p, int compute_units);
 
 /* Number of segments the library would choose for *p given a workspace (>= 1); <0 on error. */

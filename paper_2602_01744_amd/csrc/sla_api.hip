@@ -351,10 +351,6 @@ int sla_forward_static(const sla_params* p, const void* q, const void* k, const 
         if (!ws) return SLA_ERR_HIP;
     }
     const int dvw = choose_dv_split(*p, cus, nseg);
-    const int pieces = choose_pieces(*p, cus, nseg, seg_len);
-    if (pieces > 1 && sla::launch_forward_pieces && pieces_fit(*p, nseg, pieces, SLA_STATIC_SCRATCH_BYTES))
-        return sla::launch_forward_pieces(*p, dvw, nseg, seg_len, pieces, q, k, v, q_head_logits, k_head_logits, log_decay,
-                                          beta, initial_state, out, final_state, ws, nullptr, (hipStream_t)stream);
     return sla::launch_forward(*p, dvw, nseg, seg_len, q, k, v, q_head_logits, k_head_logits, log_decay, beta,
                                initial_state, out, final_state, ws, nullptr, (hipStream_t)stream);
 }

@@ -105,3 +105,14 @@ def test_static_scratch_one_pass_shapes_and_limit():
     assert rc == -7, rc
     torch.cuda.synchronize()
     assert bool((canary == 7.0).all())
+
+
+@pytest.mark.parametrize("variant,dtype,T,segments", [(GLA, "bf16", 1100, 2), (GLA, "f32", 2065, 2), (RETNET, "bf16", 3100, 3)])
+def test_static_scratch_matches_workspace_on_long_segments(variant, dtype, T, segments):
+    """Segments long enough that a larger workspace would have the pre-pass work on pieces of them."""
+    import paper_2602_01744_amd as sla
+
+    d = si.custom(variant, dtype, B=1, T=T, H=2, dk=64, dv=64, seed=4400 + T)
+    p = sla.SlaParams(variant, sla.BF16 if dtype == "bf16" else sla.F32, 1, T, 2, 64, 64, 0, 0, segments)
+    assert sla.sla_forward_workspace_bytes(p, 256) > sla.sla_workspace_bytes(p, 256)
+    _check(variant, d, dtype, segments, si.initial_state(1, 2, 64, 64, seed=42), f"{si.VARIANT_NAMES[variant]} T={T}, {segments} segments")
