@@ -107,23 +107,7 @@ __global__ __launch_bounds__(kThreads, 2) void sla_chunk_gdn_kernel(const GdnArg
     if (id >= a.slots * a.H) return;
     const int h = id % a.H, slot = id / a.H;
     int b, chunk;
-    if (a.cu) {
-        int* found = (int*)smem;
-        if (tid == 0) *found = -1;
-        __syncthreads();
-        for (int i = tid; i < a.B; i += kThreads) {
-            const Sequence s = sequence(a, i);
-            if (slot >= s.slot0 && slot < s.slot0 + (s.T + kChunk - 1) / kChunk) *found = i;
-        }
-        __syncthreads();
-        b = __builtin_amdgcn_readfirstlane(*found);
-        __syncthreads();
-        if (b < 0) return;
-        chunk = slot - sequence(a, b).slot0;
-    } else {
-        b = slot / a.nchunk;
-        chunk = slot % a.nchunk;
-    }
+    if (!chunk_of(a, slot, b, chunk)) return;
     const Sequence s = sequence(a, b);
     const int t0 = chunk * kChunk, len = min(kChunk, s.T - t0);
     const Rows rq = rows_of<DK>(a, a.q, s, b, h), rk = rows_of<DK>(a, a.k, s, b, h);

@@ -6,7 +6,7 @@ import numpy as np
 import pytest
 
 import sla_inputs as si
-from gpu_util import GLA, RETNET
+from gpu_util import GDN, GLA, RETNET
 from test_gpu_backward import check_backward
 
 pytestmark = pytest.mark.gpu
@@ -95,3 +95,39 @@ def test_decay_gradient_behind_the_last_token(T, dk, dv):
     err = np.linalg.norm(e) / np.linalg.norm(ref["dlog_decay"][:, -1])
     print(f"[last token] {err:.2e}", flush=True)
     assert err <= 2.0e-3  # between none and one
+
+
+@pytest.mark.parametrize("variant", [RETNET, GLA, GDN])
+@pytest.mark.parametrize("B", [63, 65, 4097])
+def test_many_packed_sequences(monkeypatch, variant, B):
+    """More sequences than one, and than two, steps of the search for a chunk's sequence look at, empty ones among them, the
+    first and last tokens in none: against the sweeps, to the bar of both sides."""
+    import torch
+    import paper_2602_01744_amd as sla
+    from paper_2602_01744_amd import binding
+
+    r = np.random.default_rng(3800 + B)
+    lens = r.integers(0, 4, B) * r.integers(0, 3, B)
+    lens[r.integers(0, B, 3)] = [64, 65, 200]
+    cu = np.concatenate([[5], 5 + np.cumsum(lens)])
+    T, H, dk, dv = int(cu[-1]) + 9, 2, 64, 64
+    q, k, v, ql, kl, ld, do = (t[0].contiguous() if t.dim() > 1 else t for t in _tensors(min(variant, GLA), 1, T, H, dk, dv, 3801))
+    cu = torch.tensor(cu, dtype=torch.int32, device="cuda")
+    if variant == GDN:
+        k = torch.nn.functional.normalize(k.float(), dim=-1).bfloat16()
+        call = lambda: sla.backward_gdn_varlen(q, k, v, ql, kl, ld.float().mean(-1), torch.sigmoid(ql + kl), do, cu, want_d_initial_state=True)
+        names, least = ("sla_backward_gdn_chunks_workspace_bytes", sla.sla_backward_gdn_varlen_workspace_bytes)
+    else:
+        call = lambda: sla.backward_varlen(variant, q, k, v, ql, kl, ld, do, cu, want_d_initial_state=True)
+        names, least = ("sla_backward_chunks_workspace_bytes", sla.sla_backward_varlen_workspace_bytes)
+    got = call()
+    p = sla.SlaParams(variant, sla.BF16, B, T, H, dk, dv, 0, 0, 1)
+    assert getattr(sla, names)(p, True) > least(p)
+    monkeypatch.setattr(binding, names, lambda p, packed=False: least(p))
+    ref = call()
+    inside = slice(int(cu[0]), int(cu[-1]))
+    for n, t in got.items():
+        if t is not None:
+            x, y = (t, ref[n]) if n == "d_initial_state" else (t[inside], ref[n][inside])
+            rel = ((x.double() - y.double()).norm() / y.double().norm()).item()
+            assert rel <= (4e-2 if n == "dlog_decay" else 2e-2), (n, rel)
