@@ -709,17 +709,22 @@ static size_t backward_chunks_fixed_floats(const sla_params& p, bool packed) {
 static size_t backward_chunks_end_floats(const sla_params& p) {
     return p.variant == SLA_GLA ? (size_t)p.B * p.H * p.dk * (p.dv / 32) : 0;
 }
-static chk::Parts backward_chunks_parts(const sla_params& p, bool packed, size_t budget) {  // of states and Args::end
-    const size_t end = backward_chunks_end_floats(p);
-    return chk::parts_of(p, packed, budget > end ? budget - end : 0);
+// How a workspace of that many floats is used: Args::end and as many states as there is room for, kMostStates of them at most.
+static chk::Parts backward_chunks_parts(const sla_params& p, bool packed, size_t floats) {
+    const size_t taken = backward_chunks_fixed_floats(p, packed) + backward_chunks_end_floats(p);
+    return chk::parts_of(p, packed, floats > taken ? std::min(kMostStates, floats - taken) : 0);
 }
-static size_t backward_chunks_floats(const sla_params& p, bool packed, size_t budget) {
-    return backward_chunks_fixed_floats(p, packed) + backward_chunks_parts(p, packed, budget).floats + backward_chunks_end_floats(p);
+static size_t backward_chunks_floats(const sla_params& p, bool packed, const chk::Parts& parts) {
+    return backward_chunks_fixed_floats(p, packed) + backward_chunks_end_floats(p) + parts.floats;
 }
-size_t backward_chunks_workspace_floats(const sla_params& p, bool packed) { return backward_chunks_floats(p, packed, kMostStates); }
+size_t backward_chunks_workspace_floats(const sla_params& p, bool packed) {
+    return backward_chunks_floats(p, packed, chk::parts_of(p, packed, kMostStates));
+}
 // Whether a workspace of that many floats is enough for the chunk-parallel pass.
 bool backward_chunks_fit(const sla_params& p, bool packed, size_t floats) {
-    return p.dtype == SLA_BF16 && p.T > 0 && backward_chunks_floats(p, packed, kLeastStates) <= floats;
+    if (p.dtype != SLA_BF16 || p.T == 0) return false;
+    const size_t least = backward_chunks_fixed_floats(p, packed) + kLeastStates;
+    return backward_chunks_floats(p, packed, backward_chunks_parts(p, packed, least)) <= floats;
 }
 
 int launch_backward_chunks(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
@@ -733,7 +738,7 @@ int launch_backward_chunks(const sla_params& p, const void* q, const void* k, co
     a.ld_head = p.variant == SLA_RETNET ? (const float*)ld : nullptr;
     a.s0 = s0; a.dsf = dsf; a.ds0 = ds0;
     a.dq = (uint16_t*)dq; a.dk = (uint16_t*)dk; a.dv = (uint16_t*)dv; a.dld = (uint16_t*)dld;
-    const chk::Parts parts = backward_chunks_parts(p, packed, std::min(kMostStates, floats - backward_chunks_fixed_floats(p, packed)));
+    const chk::Parts parts = backward_chunks_parts(p, packed, floats);
     a.S = (chk::u4*)ws;  // the states first: on the cache lines that the allocation begins on
     a.X = (chk::u4*)(ws + parts.floats / 2);
     float *gq = ws + parts.floats, *gk = gq + n;

@@ -22,8 +22,13 @@ def test_size(variant, packed):
         assert sla.sla_backward_chunks_workspace_bytes(p, packed) == max(want, least(p))
     # no more than 1 GiB of states at a time, however long the batch
     p = _params(variant, B=8, T=65536, H=16)
-    n = 65536 * (1 if packed else 8) * 16 * 16
+    n = 65536 * (1 if packed else 8) * 16 * 16 + 8 * 16 * 128 * 4 * 4
     assert sla.sla_backward_chunks_workspace_bytes(p, packed) <= max(n + (1 << 30), least(p))
+
+    # batches whose states are a GiB to the byte are worked off at once
+    for B, T, H, dk, dv in ((4, 32768, 8, 128, 128), (1, 32768, 64, 64, 128)):
+        p = _params(variant, B=B, T=T, H=H, dk=dk, dv=dv)
+        assert sla.sla_backward_chunks_workspace_bytes(p) >= 4 * 4 * B * T * H + (1 << 30)
 
 
 def test_where_the_other_queries_hold():
