@@ -7,36 +7,29 @@
 #include <mutex>
 
 #include "sla.h"
+#include "sla_chunk_plan.h"
 #include "sla_fwd_args.h"
 
 namespace sla {
 int launch_forward(const sla_params& p, int dvw, int nseg, int seg_len, const void* q, const void* k, const void* v,
                    const float* ql, const float* kl, const void* ld, const float* beta, const float* s0, void* out,
                    float* sT, float* workspace, const int* cu, hipStream_t stream);
-// Weak, as launch_backward_chunks below.
-__attribute__((weak)) int launch_forward_pieces(const sla_params& p, int dvw, int nseg, int seg_len, int pieces,
-                                                const void* q, const void* k, const void* v, const float* ql,
-                                                const float* kl, const void* ld, const float* beta, const float* s0,
-                                                void* out, float* sT, float* workspace, const int* cu, hipStream_t stream);
+int launch_forward_pieces(const sla_params& p, int dvw, int nseg, int seg_len, int pieces, const void* q, const void* k,
+                          const void* v, const float* ql, const float* kl, const void* ld, const float* beta, const float* s0,
+                          void* out, float* sT, float* workspace, const int* cu, hipStream_t stream);
 size_t segment_workspace_floats(const sla_params& p, int nseg);
 size_t backward_workspace_floats(const sla_params& p, bool packed);
 int launch_backward(const sla_params& p, const void* q, const void* k, const void* v, const float* ql, const float* kl,
                     const void* ld, const float* s0, const void* dout, const float* dsf, void* dq, void* dk, void* dv,
                     float* dql, float* dkl, void* dld, float* ds0, float* ws, const int* cu, hipStream_t stream);
-// The chunk-parallel schedule (sla_chunk_backward.hip).  Weak: the host-side checks also link without the kernels that
-// schedules were added with, and run the ones they know then.
-__attribute__((weak)) bool backward_chunks_fit(const sla_params& p, bool packed, size_t workspace_floats);
-__attribute__((weak)) int launch_backward_chunks(const sla_params& p, const void* q, const void* k, const void* v,
-                                                 const float* ql, const float* kl, const void* ld, const float* s0,
-                                                 const void* dout, const float* dsf, void* dq, void* dk, void* dv,
-                                                 float* dql, float* dkl, void* dld, float* ds0, float* ws, size_t floats,
-                                                 const int* cu, bool packed, hipStream_t stream);
-__attribute__((weak)) size_t backward_gdn_chunks_workspace_floats(const sla_params& p, bool packed);
-__attribute__((weak)) int launch_backward_gdn_chunks(const sla_params& p, const void* q, const void* k, const void* v,
-                                                     const float* ql, const float* kl, const float* ld, const float* beta,
-                                                     const float* s0, const void* dout, const float* dsf, void* dq, void* dk,
-                                                     void* dv, float* dql, float* dkl, float* dld, float* dbeta, float* ds0,
-                                                     float* ws, const int* cu, bool packed, hipStream_t stream);
+int launch_backward_chunks(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
+                           const float* kl, const void* ld, const float* s0, const void* dout, const float* dsf, void* dq,
+                           void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, size_t floats,
+                           const int* cu, bool packed, hipStream_t stream);
+int launch_backward_gdn_chunks(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
+                               const float* kl, const float* ld, const float* beta, const float* s0, const void* dout,
+                               const float* dsf, void* dq, void* dk, void* dv, float* dql, float* dkl, float* dld,
+                               float* dbeta, float* ds0, float* ws, const int* cu, bool packed, hipStream_t stream);
 size_t backward_segment_extra_floats(const sla_params& p, int nseg);
 sla_params packed_segments(const sla_params& p, int nseg);
 int launch_backward_segments(const sla_params& p, int nseg, int seg_len, int dvw, const void* q, const void* k,
@@ -295,7 +288,7 @@ int sla_forward_ws(const sla_params* p, const void* q, const void* k, const void
     }
     const int dvw = choose_dv_split(*p, cus, nseg);
     const int pieces = choose_pieces(*p, cus, nseg, seg_len);
-    if (pieces > 1 && sla::launch_forward_pieces && pieces_fit(*p, nseg, pieces, workspace_bytes))
+    if (pieces > 1 && pieces_fit(*p, nseg, pieces, workspace_bytes))
         return sla::launch_forward_pieces(*p, dvw, nseg, seg_len, pieces, q, k, v, q_head_logits, k_head_logits, log_decay,
                                           beta, initial_state, out, final_state, (float*)workspace, nullptr, (hipStream_t)stream);
     return sla::launch_forward(*p, dvw, nseg, seg_len, q, k, v, q_head_logits, k_head_logits, log_decay, beta,
@@ -463,7 +456,7 @@ static int backward_impl(const sla_params* p, const void* q, const void* k, cons
     const int nseg = backward_segments(*p, packed, &seg_len);
     if (nseg > 1 && p->flags != 0) return SLA_ERR_UNSUPPORTED;  // the segments run as a packed batch: [B,T,H,d] only
     // bf16 tensors: chunk-parallel where the workspace allows it
-    if (sla::backward_chunks_fit && sla::backward_chunks_fit(*p, packed, workspace_bytes / sizeof(float)))
+    if (sla::backward_chunks_fit(*p, packed, workspace_bytes / sizeof(float)))
         return sla::launch_backward_chunks(*p, q, k, v, q_head_logits, k_head_logits, log_decay, initial_state, d_out,
                                            d_final_state, dq, dk, dv, dq_head_logits, dk_head_logits, dlog_decay,
                                            d_initial_state, (float*)workspace, workspace_bytes / sizeof(float),
@@ -527,7 +520,7 @@ static int backward_gdn_impl(const sla_params* p, const void* q, const void* k, 
     if (p->T > 0 && (!workspace || sla::backward_gdn_any_workspace_floats(*p, packed) * sizeof(float) > workspace_bytes))
         return SLA_ERR_WORKSPACE;
     // bf16 tensors: chunk-parallel where the workspace allows it
-    const size_t chunks = sla::backward_gdn_chunks_workspace_floats ? sla::backward_gdn_chunks_workspace_floats(*p, packed) : 0;
+    const size_t chunks = sla::backward_gdn_chunks_workspace_floats(*p, packed);
     if (chunks > 0 && chunks * sizeof(float) <= workspace_bytes)
         return sla::launch_backward_gdn_chunks(*p, q, k, v, q_head_logits, k_head_logits, log_decay, beta, initial_state,
                                                d_out, d_final_state, dq, dk, dv, dq_head_logits, dk_head_logits, dlog_decay,
@@ -674,6 +667,18 @@ size_t sla_backward_workspace_bytes(const sla_params* p) {
 size_t sla_backward_varlen_workspace_bytes(const sla_params* p) {
     if (check_params(p) != SLA_OK || p->variant == SLA_GDN) return 0;
     return sla::backward_any_workspace_floats(*p, true) * sizeof(float);
+}
+
+size_t sla_backward_chunks_workspace_bytes(const sla_params* p, int packed) {
+    const size_t least = packed ? sla_backward_varlen_workspace_bytes(p) : sla_backward_workspace_bytes(p);
+    if (least == 0 || p->dtype != SLA_BF16 || p->T == 0 || p->B == 0) return least;
+    return std::max(least, sla::backward_chunks_workspace_floats(*p, packed != 0) * sizeof(float));
+}
+
+size_t sla_backward_gdn_chunks_workspace_bytes(const sla_params* p, int packed) {
+    const size_t least = packed ? sla_backward_gdn_varlen_workspace_bytes(p) : sla_backward_gdn_workspace_bytes(p);
+    if (least == 0) return 0;
+    return std::max(least, sla::backward_gdn_chunks_workspace_floats(*p, packed != 0) * sizeof(float));
 }
 
 size_t sla_workspace_bytes(const sla_params* p, int compute_units) {

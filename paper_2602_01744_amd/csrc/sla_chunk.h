@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "sla.h"
+#include "sla_chunk_plan.h"
 
 namespace sla {
 namespace chk {
@@ -20,7 +21,7 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf2;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf8;
 typedef __attribute__((address_space(3))) s4 lds_s4;
 
-constexpr int kChunk = 64;  // tokens per chunk: four 16-token blocks, the unit within which GLA's decay products are formed
+constexpr int kChunk = kChunkTokens;  // tokens per chunk: four 16-token blocks, the unit within which GLA's decay products are formed
 constexpr float kLog2e = 1.4426950408889634f;
 
 struct Args {

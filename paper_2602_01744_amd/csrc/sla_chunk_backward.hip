@@ -24,6 +24,7 @@
 
 #include "sla.h"
 #include "sla_chunk.h"
+#include "sla_chunk_plan.h"
 #include "sla_gate_grad.h"
 
 namespace sla {
@@ -668,77 +669,20 @@ static int launch_chunks_dk(const Args& a, int dk, int dv, hipStream_t stream) {
     }
 }
 
-// The parts a call is worked off in, one after the other: whole heads of nb sequences or nh heads of one.  Packed batches:
-// nh heads of all sequences.
-struct Parts {
-    int nb, nh, slots;  // of a part; slots: chunks per head
-    size_t floats;      // of its states, both directions
-};
-static Parts parts_of(const sla_params& p, bool packed, size_t budget) {
-    const int nchunk = (p.T + kChunk - 1) / kChunk, all = p.T / kChunk + p.B + 1;
-    const size_t per = (size_t)p.dk * p.dv;  // two bf16 states
-    Parts r;
-    if (packed) {
-        r.nb = p.B;
-        r.slots = all;
-        r.nh = (int)std::min<size_t>(p.H, std::max<size_t>(1, budget / (per * all)));
-    } else {
-        const size_t heads = std::max<size_t>(1, budget / (per * nchunk));
-        r.nh = (int)std::min<size_t>(p.H, heads);
-        r.nb = r.nh == p.H ? (int)std::min<size_t>(p.B, heads / p.H) : 1;
-        r.slots = r.nb * nchunk;
-    }
-    r.floats = (size_t)r.slots * r.nh * per;
-    return r;
-}
-
 }  // namespace chk
-
-static size_t round4(size_t n) { return (n + 3) & ~(size_t)3; }
-
-// Floats of states a part may hold: as many as the workspace has room for, of which the query asks for no more than
-// kMostStates and the call is content with kLeastStates.  Large parts are better: B=6 T=5690 H=8 128 x 256 RetNet takes
-// 498 us in parts of 1 GiB, 746 in parts of 128 MiB (a launch ends with a partly filled chip, and the intermediate states'
-// stay in the memory-side cache gains less than that); below kLeastStates launches are too small to fill the chip at all.
-constexpr size_t kMostStates = (size_t)1 << 28, kLeastStates = (size_t)1 << 24;
-
-// Gates and their gradients [B,T,H], and behind the states Args::end.
-static size_t backward_chunks_fixed_floats(const sla_params& p, bool packed) {
-    return 4 * round4((packed ? (size_t)p.T : (size_t)p.B * p.T) * p.H);
-}
-static size_t backward_chunks_end_floats(const sla_params& p) {
-    return p.variant == SLA_GLA ? (size_t)p.B * p.H * p.dk * (p.dv / 32) : 0;
-}
-// How a workspace of that many floats is used: Args::end and as many states as there is room for, kMostStates of them at most.
-static chk::Parts backward_chunks_parts(const sla_params& p, bool packed, size_t floats) {
-    const size_t taken = backward_chunks_fixed_floats(p, packed) + backward_chunks_end_floats(p);
-    return chk::parts_of(p, packed, floats > taken ? std::min(kMostStates, floats - taken) : 0);
-}
-static size_t backward_chunks_floats(const sla_params& p, bool packed, const chk::Parts& parts) {
-    return backward_chunks_fixed_floats(p, packed) + backward_chunks_end_floats(p) + parts.floats;
-}
-size_t backward_chunks_workspace_floats(const sla_params& p, bool packed) {
-    return backward_chunks_floats(p, packed, chk::parts_of(p, packed, kMostStates));
-}
-// Whether a workspace of that many floats is enough for the chunk-parallel pass.
-bool backward_chunks_fit(const sla_params& p, bool packed, size_t floats) {
-    if (p.dtype != SLA_BF16 || p.T == 0) return false;
-    const size_t least = backward_chunks_fixed_floats(p, packed) + kLeastStates;
-    return backward_chunks_floats(p, packed, backward_chunks_parts(p, packed, least)) <= floats;
-}
 
 int launch_backward_chunks(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
                            const float* kl, const void* ld, const float* s0, const void* dout, const float* dsf, void* dq,
                            void* dk, void* dv, float* dql, float* dkl, void* dld, float* ds0, float* ws, size_t floats,
                            const int* cu, bool packed, hipStream_t stream) {
-    const size_t rows = packed ? (size_t)p.T : (size_t)p.B * p.T, n = round4(rows * p.H);
+    const size_t rows = packed ? (size_t)p.T : (size_t)p.B * p.T, n = chunk_round4(rows * p.H);
     chk::Args a = {};
     a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v; a.dout = (const uint16_t*)dout;
     a.ld = p.variant == SLA_GLA ? (const uint16_t*)ld : nullptr;
     a.ld_head = p.variant == SLA_RETNET ? (const float*)ld : nullptr;
     a.s0 = s0; a.dsf = dsf; a.ds0 = ds0;
     a.dq = (uint16_t*)dq; a.dk = (uint16_t*)dk; a.dv = (uint16_t*)dv; a.dld = (uint16_t*)dld;
-    const chk::Parts parts = backward_chunks_parts(p, packed, floats);
+    const ChunkParts parts = backward_chunks_parts(p, packed, floats);
     a.S = (chk::u4*)ws;  // the states first: on the cache lines that the allocation begins on
     a.X = (chk::u4*)(ws + parts.floats / 2);
     float *gq = ws + parts.floats, *gk = gq + n;
@@ -764,9 +708,3 @@ int launch_backward_chunks(const sla_params& p, const void* q, const void* k, co
 }
 
 }  // namespace sla
-
-extern "C" size_t sla_backward_chunks_workspace_bytes(const sla_params* p, int packed) {
-    const size_t least = packed ? sla_backward_varlen_workspace_bytes(p) : sla_backward_workspace_bytes(p);
-    if (least == 0 || p->dtype != SLA_BF16 || p->T == 0 || p->B == 0) return least;
-    return std::max(least, sla::backward_chunks_workspace_floats(*p, packed != 0) * sizeof(float));
-}

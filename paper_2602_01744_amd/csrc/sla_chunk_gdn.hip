@@ -28,6 +28,7 @@
 
 #include "sla.h"
 #include "sla_chunk.h"
+#include "sla_chunk_plan.h"
 #include "sla_gate_grad.h"
 #include "sla_gdn_block.h"
 
@@ -407,41 +408,6 @@ static int launch_gdn_chunks_dv(const GdnArgs& ga, int dv, hipStream_t stream) {
 
 }  // namespace chk
 
-static size_t round4(size_t n) { return (n + 3) & ~(size_t)3; }
-
-struct GdnChunkSizes {
-    size_t rows, n, slots, state, rest, wide, ends;  // n: floats of a [rows,H] array; state: of S or X; wide: of res, half of du
-    size_t floats;
-};
-static GdnChunkSizes gdn_chunk_sizes(const sla_params& p, bool packed) {
-    GdnChunkSizes z;
-    z.rows = packed ? (size_t)p.T : (size_t)p.B * p.T;
-    z.n = round4(z.rows * p.H);
-    z.slots = packed ? (size_t)p.T / kGdnChunk + p.B + 1 : (size_t)p.B * ((p.T + kGdnChunk - 1) / kGdnChunk);
-    z.state = z.slots * p.H * p.dk * p.dv / 2;
-    z.wide = z.rows * p.H * p.dv / 2;
-    z.rest = gdn_anchor_count(z.rows) * p.H * p.dk * p.dv / 2;
-    z.ends = gdn_anchor_count(z.rows) * p.H * chk::kSpanChunks + (size_t)p.B * p.H * (p.dv / 16);
-    z.floats = 5 * z.n + z.ends + 2 * (z.state + z.rest) + 3 * z.wide + gdn_pair_workspace_floats(p.B, p.T, p.H, packed);
-    return z;
-}
-
-// Long rows whose sweeps have a workgroup for each of 256 compute units, or nearly, in every round gain nothing: B=8 H=16
-// 128 x 128 T=4096 1761 -> 1771 us a training step, T=2048 561 -> 564, T=512 171 -> 155; three quarters of the chip (H=12 T=4096)
-// 1110 -> 1012.  Packed sequences end at different times and leave it idle whatever their number.
-static bool sweeps_fill_the_chip(const sla_params& p, bool packed) {
-    const size_t cus = 256, wgs = (size_t)p.B * p.H * (p.dk < p.dv ? p.dk : p.dv) / 64, rounds = (wgs + cus - 1) / cus;
-    return !packed && p.T >= 1024 && wgs >= cus && 16 * wgs >= 15 * cus * rounds;
-}
-
-// 0: this call does not run chunk-parallel (heads of width 32 are padded by sla_backward_narrow.hip, which runs the sweeps).
-// Its states may take a GiB, as in sla_chunk_backward.hip.
-size_t backward_gdn_chunks_workspace_floats(const sla_params& p, bool packed) {
-    if (p.dtype != SLA_BF16 || p.dk < 64 || p.T == 0 || p.B == 0 || sweeps_fill_the_chip(p, packed)) return 0;
-    const GdnChunkSizes z = gdn_chunk_sizes(p, packed);
-    return 2 * z.state <= (size_t)1 << 28 ? z.floats : 0;
-}
-
 int launch_backward_gdn_chunks(const sla_params& p, const void* q, const void* k, const void* v, const float* ql,
                                const float* kl, const float* ld, const float* beta, const float* s0, const void* dout,
                                const float* dsf, void* dq, void* dk, void* dv, float* dql, float* dkl, float* dld,
@@ -488,9 +454,3 @@ int launch_backward_gdn_chunks(const sla_params& p, const void* q, const void* k
 }
 
 }  // namespace sla
-
-extern "C" size_t sla_backward_gdn_chunks_workspace_bytes(const sla_params* p, int packed) {
-    const size_t least = packed ? sla_backward_gdn_varlen_workspace_bytes(p) : sla_backward_gdn_workspace_bytes(p);
-    if (least == 0) return 0;
-    return std::max(least, sla::backward_gdn_chunks_workspace_floats(*p, packed != 0) * sizeof(float));
-}

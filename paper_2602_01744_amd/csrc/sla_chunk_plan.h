@@ -1,0 +1,108 @@
+// Host side of the chunk-parallel backward schedules: how a workspace is divided and which calls they take.
+#pragma once
+#include <stddef.h>
+
+#include <algorithm>
+
+#include "sla.h"
+#include "sla_gdn_block.h"
+
+namespace sla {
+
+constexpr int kChunkTokens = 64;  // tokens per chunk
+
+inline size_t chunk_round4(size_t n) { return (n + 3) & ~(size_t)3; }
+
+// ---- RetNet and GLA (sla_chunk_backward.hip)
+
+// The parts a call is worked off in, one after the other: whole heads of nb sequences or nh heads of one.  Packed batches:
+// nh heads of all sequences.
+struct ChunkParts {
+    int nb, nh, slots;  // of a part; slots: chunks per head
+    size_t floats;      // of its states, both directions
+};
+inline ChunkParts chunk_parts(const sla_params& p, bool packed, size_t budget) {
+    const int nchunk = (p.T + kChunkTokens - 1) / kChunkTokens, all = p.T / kChunkTokens + p.B + 1;
+    const size_t per = (size_t)p.dk * p.dv;  // two bf16 states
+    ChunkParts r;
+    if (packed) {
+        r.nb = p.B;
+        r.slots = all;
+        r.nh = (int)std::min<size_t>(p.H, std::max<size_t>(1, budget / (per * all)));
+    } else {
+        const size_t heads = std::max<size_t>(1, budget / (per * nchunk));
+        r.nh = (int)std::min<size_t>(p.H, heads);
+        r.nb = r.nh == p.H ? (int)std::min<size_t>(p.B, heads / p.H) : 1;
+        r.slots = r.nb * nchunk;
+    }
+    r.floats = (size_t)r.slots * r.nh * per;
+    return r;
+}
+
+// Floats of states a part may hold: as many as the workspace has room for, of which the query asks for no more than
+// kMostStates and the call is content with kLeastStates.  Large parts are better: B=6 T=5690 H=8 128 x 256 RetNet takes
+// 498 us in parts of 1 GiB, 746 in parts of 128 MiB (a launch ends with a partly filled chip, and the intermediate states'
+// stay in the memory-side cache gains less than that); below kLeastStates launches are too small to fill the chip at all.
+constexpr size_t kMostStates = (size_t)1 << 28, kLeastStates = (size_t)1 << 24;
+
+// Gates and their gradients [B,T,H], and behind the states Args::end.
+inline size_t backward_chunks_fixed_floats(const sla_params& p, bool packed) {
+    return 4 * chunk_round4((packed ? (size_t)p.T : (size_t)p.B * p.T) * p.H);
+}
+inline size_t backward_chunks_end_floats(const sla_params& p) {
+    return p.variant == SLA_GLA ? (size_t)p.B * p.H * p.dk * (p.dv / 32) : 0;
+}
+// How a workspace of that many floats is used: Args::end and as many states as there is room for, kMostStates of them at most.
+inline ChunkParts backward_chunks_parts(const sla_params& p, bool packed, size_t floats) {
+    const size_t taken = backward_chunks_fixed_floats(p, packed) + backward_chunks_end_floats(p);
+    return chunk_parts(p, packed, floats > taken ? std::min(kMostStates, floats - taken) : 0);
+}
+inline size_t backward_chunks_floats(const sla_params& p, bool packed, const ChunkParts& parts) {
+    return backward_chunks_fixed_floats(p, packed) + backward_chunks_end_floats(p) + parts.floats;
+}
+inline size_t backward_chunks_workspace_floats(const sla_params& p, bool packed) {
+    return backward_chunks_floats(p, packed, chunk_parts(p, packed, kMostStates));
+}
+// Whether a workspace of that many floats is enough for the chunk-parallel pass.
+inline bool backward_chunks_fit(const sla_params& p, bool packed, size_t floats) {
+    if (p.dtype != SLA_BF16 || p.T == 0) return false;
+    const size_t least = backward_chunks_fixed_floats(p, packed) + kLeastStates;
+    return backward_chunks_floats(p, packed, backward_chunks_parts(p, packed, least)) <= floats;
+}
+
+// ---- delta rule (sla_chunk_gdn.hip)
+
+struct GdnChunkSizes {
+    size_t rows, n, slots, state, rest, wide, ends;  // n: floats of a [rows,H] array; state: of S or X; wide: of res, half of du
+    size_t floats;
+};
+inline GdnChunkSizes gdn_chunk_sizes(const sla_params& p, bool packed) {
+    GdnChunkSizes z;
+    z.rows = packed ? (size_t)p.T : (size_t)p.B * p.T;
+    z.n = chunk_round4(z.rows * p.H);
+    z.slots = packed ? (size_t)p.T / kGdnChunk + p.B + 1 : (size_t)p.B * ((p.T + kGdnChunk - 1) / kGdnChunk);
+    z.state = z.slots * p.H * p.dk * p.dv / 2;
+    z.wide = z.rows * p.H * p.dv / 2;
+    z.rest = gdn_anchor_count(z.rows) * p.H * p.dk * p.dv / 2;
+    z.ends = gdn_anchor_count(z.rows) * p.H * (kGdnAnchor / kGdnChunk) + (size_t)p.B * p.H * (p.dv / 16);
+    z.floats = 5 * z.n + z.ends + 2 * (z.state + z.rest) + 3 * z.wide + gdn_pair_workspace_floats(p.B, p.T, p.H, packed);
+    return z;
+}
+
+// Long rows whose sweeps have a workgroup for each of 256 compute units, or nearly, in every round gain nothing: B=8 H=16
+// 128 x 128 T=4096 1761 -> 1771 us a training step, T=2048 561 -> 564, T=512 171 -> 155; three quarters of the chip (H=12 T=4096)
+// 1110 -> 1012.  Packed sequences end at different times and leave it idle whatever their number.
+inline bool sweeps_fill_the_chip(const sla_params& p, bool packed) {
+    const size_t cus = 256, wgs = (size_t)p.B * p.H * (p.dk < p.dv ? p.dk : p.dv) / 64, rounds = (wgs + cus - 1) / cus;
+    return !packed && p.T >= 1024 && wgs >= cus && 16 * wgs >= 15 * cus * rounds;
+}
+
+// 0: this call does not run chunk-parallel (heads of width 32 are padded by sla_backward_narrow.hip, which runs the sweeps).
+// Its states may take a GiB, as in sla_chunk_backward.hip.
+inline size_t backward_gdn_chunks_workspace_floats(const sla_params& p, bool packed) {
+    if (p.dtype != SLA_BF16 || p.dk < 64 || p.T == 0 || p.B == 0 || sweeps_fill_the_chip(p, packed)) return 0;
+    const GdnChunkSizes z = gdn_chunk_sizes(p, packed);
+    return 2 * z.state <= (size_t)1 << 28 ? z.floats : 0;
+}
+
+}  // namespace sla

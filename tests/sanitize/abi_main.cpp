@@ -18,6 +18,9 @@ static int reached(const char* what) {
 }
 int launch_forward(const sla_params&, int, int, int, const void*, const void*, const void*, const float*, const float*,
                    const void*, const float*, const float*, void*, float*, float*, const int*, hipStream_t) { return reached("forward"); }
+int launch_forward_pieces(const sla_params&, int, int, int, int, const void*, const void*, const void*, const float*,
+                          const float*, const void*, const float*, const float*, void*, float*, float*, const int*,
+                          hipStream_t) { return reached("forward in pieces"); }
 size_t segment_workspace_floats(const sla_params& p, int nseg) {
     return nseg <= 1 ? 0 : (size_t)p.B * p.H * ((size_t)nseg * p.dk * p.dv + (size_t)(nseg - 1) * 8 * p.dk);
 }
@@ -25,6 +28,17 @@ size_t backward_workspace_floats(const sla_params& p, bool) { return (size_t)p.B
 int launch_backward(const sla_params&, const void*, const void*, const void*, const float*, const float*, const void*,
                     const float*, const void*, const float*, void*, void*, void*, float*, float*, void*, float*, float*,
                     const int*, hipStream_t) { return reached("backward"); }
+int launch_backward_chunks(const sla_params&, const void*, const void*, const void*, const float*, const float*, const void*,
+                           const float*, const void*, const float*, void*, void*, void*, float*, float*, void*, float*,
+                           float*, size_t, const int*, bool, hipStream_t) { return reached("backward chunks"); }
+int launch_backward_gdn_chunks(const sla_params&, const void*, const void*, const void*, const float*, const float*,
+                               const float*, const float*, const float*, const void*, const float*, void*, void*, void*,
+                               float*, float*, float*, float*, float*, float*, const int*, bool, hipStream_t) {
+    return reached("backward gdn chunks");
+}
+size_t gdn_pair_workspace_floats(int B, int T, int H, bool packed) {
+    return ((packed ? 0 : (size_t)B * ((T + 31) / 32)) + (packed ? (size_t)T / 32 + B + 1 : 0)) * H * 768;
+}
 size_t backward_segment_extra_floats(const sla_params& p, int nseg) { return (size_t)p.B * nseg * p.H * p.dk * p.dv * 3; }
 sla_params packed_segments(const sla_params& p, int nseg) { sla_params q = p; q.B = p.B * nseg; q.T = p.B * p.T; return q; }
 int launch_backward_segments(const sla_params&, int, int, int, const void*, const void*, const void*, const float*,
@@ -91,7 +105,14 @@ int main() {
             (void)sla_gate_logits_backward_workspace_bytes(&p);
             (void)sla_default_dv_split(&p, 256);
             (void)sla_kernel_name(&p);
-            calls += 10;
+            (void)sla_forward_workspace_bytes(&p, 256);
+            for (int packed = 0; packed < 2; ++packed) {
+                // never less than the plain queries
+                const size_t n = sla_backward_chunks_workspace_bytes(&p, packed), m = sla_backward_gdn_chunks_workspace_bytes(&p, packed);
+                failures += n < (packed ? sla_backward_varlen_workspace_bytes(&p) : sla_backward_workspace_bytes(&p));
+                failures += m < (packed ? sla_backward_gdn_varlen_workspace_bytes(&p) : sla_backward_gdn_workspace_bytes(&p));
+            }
+            calls += 15;
         }
     for (int s : splits) for (int g : segs) for (int T : sizes) {
         sla_params p = ok;
@@ -114,12 +135,16 @@ int main() {
     EXPECT(sla_forward_static(&big, A, A, A, F, F, A, nullptr, nullptr, A, F, nullptr), SLA_ERR_SCRATCH);
     EXPECT(sla_forward_ws(&big, A, A, A, F, F, A, nullptr, nullptr, A, F, A, 16, nullptr), SLA_ERR_WORKSPACE);
     EXPECT(sla_backward(&ok, A, A, A, F, F, A, nullptr, A, nullptr, A, A, A, F, F, A, nullptr, A, 15, nullptr), SLA_ERR_WORKSPACE);
+    EXPECT(sla_backward_chunks_workspace_bytes(&ok, 0) > 0 && sla_backward_gdn_chunks_workspace_bytes(&ok, 0) == 0, 1);
+    EXPECT(sla_backward(&ok, A, A, A, F, F, A, nullptr, A, nullptr, A, A, A, F, F, A, nullptr, A, 16, nullptr), SLA_ERR_WORKSPACE);
+    sla_params gdn = ok; gdn.variant = SLA_GDN;
+    EXPECT(sla_backward_gdn_chunks_workspace_bytes(&gdn, 1) > sla_backward_gdn_varlen_workspace_bytes(&gdn) / 2, 1);
     EXPECT(sla_short_conv_silu_l2(SLA_BF16, 2, 64, 200, 4, 64, 1e-6f, A, F, A, nullptr), SLA_ERR_SHAPE);
     EXPECT(sla_short_conv_silu_l2_backward(SLA_BF16, 2, 100, 256, 4, 64, 1e-6f, A, F, A, A, F, A, 16, nullptr), SLA_ERR_WORKSPACE);
     EXPECT(sla_gate_logits_backward(&ok, A, F, nullptr, A, F, A, (size_t)1 << 30, nullptr), SLA_ERR_NULL);
     for (int code = -9; code <= 1; ++code)
         if (!sla_status_string(code)) ++failures;
     EXPECT(sla_version() >= 100, 1);
-    std::printf("%lld validation calls, %d failures\n", calls + 12, failures);
+    std::printf("%lld validation calls, %d failures\n", calls + 15, failures);
     return failures != 0;
 }
