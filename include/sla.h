@@ -206,7 +206,7 @@ int sla_decode_step_fused(const sla_params* p, const void* q, const void* k, con
  * which run in parallel; the entry state and the end cotangent of every segment come from two pre-passes.  It needs
  * the [B,T,H,d] layout (p->flags == 0) and a larger workspace (sla_backward_workspace_bytes accounts for it); 0 and 1
  * run the single pass.  In a workspace of sla_backward_chunks_workspace_bytes both give way to the chunk-parallel
- * schedule described there, which is the faster one.  fp32 tensors: >= 2 is SLA_ERR_UNSUPPORTED; with 0 and 1 the library itself cuts rectangular
+ * schedule described there wherever that is faster.  fp32 tensors: >= 2 is SLA_ERR_UNSUPPORTED; with 0 and 1 the library itself cuts rectangular
  * batches with few sequences of more than 128 tokens into segments, if the workspace has the room that
  * sla_backward_workspace_bytes asks for, and runs the single pass otherwise.  That room may be larger for a smaller B or T;
  * the single pass takes what sla_backward_varlen_workspace_bytes says for the same B and p->T = B * T, which never grows as
@@ -242,11 +242,13 @@ size_t sla_backward_workspace_bytes(const sla_params* p);
 
 /*
  * Bytes of workspace with which sla_backward (packed == 0) or sla_backward_varlen (packed != 0) runs bf16 tensors
- * chunk-parallel as fast as it can; never less than their own queries.  Every 64-token chunk of a head is then worked on
- * independently, from the states at the chunk boundaries that a first kernel leaves in the workspace (p->segments makes
- * no difference).  A smaller workspace holds the states of a part of the batch at a time (same results); one with less
- * than 64 MiB for them, where that is not all of them, runs the sweeps described at sla_backward.  The gradients of the
- * two agree to the rounding of bf16 operands.  fp32 tensors: the same as the other queries.
+ * fastest; never less than their own queries.  With it most calls run chunk-parallel: every 64-token chunk of a head is
+ * worked on independently, from the states at the chunk boundaries that a first kernel leaves in the workspace, a GiB of them
+ * at most, in parts of the batch where there are more.  A smaller workspace makes the parts smaller (same results).  Calls
+ * for which that is slower run as described at sla_backward, and the query says what these want: long rows with few heads
+ * and p->segments >= 2, parts too small to fill the chip, and always where there is room for less than 64 MiB of states and
+ * not for all.  The gradients of the schedules agree to the rounding of bf16 operands; which one runs depends on *p and
+ * the workspace's size alone.  fp32 tensors: the same as the other queries.
  */
 size_t sla_backward_chunks_workspace_bytes(const sla_params* p, int packed);
 

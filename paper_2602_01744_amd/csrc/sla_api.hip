@@ -455,8 +455,8 @@ static int backward_impl(const sla_params* p, const void* q, const void* k, cons
     int seg_len = 0;
     const int nseg = backward_segments(*p, packed, &seg_len);
     if (nseg > 1 && p->flags != 0) return SLA_ERR_UNSUPPORTED;  // the segments run as a packed batch: [B,T,H,d] only
-    // bf16 tensors: chunk-parallel where the workspace allows it
-    if (sla::backward_chunks_fit(*p, packed, workspace_bytes / sizeof(float)))
+    // bf16 tensors: chunk-parallel where the workspace allows it and it is faster
+    if (sla::backward_chunks_take(*p, packed, nseg, workspace_bytes / sizeof(float)))
         return sla::launch_backward_chunks(*p, q, k, v, q_head_logits, k_head_logits, log_decay, initial_state, d_out,
                                            d_final_state, dq, dk, dv, dq_head_logits, dk_head_logits, dlog_decay,
                                            d_initial_state, (float*)workspace, workspace_bytes / sizeof(float),
@@ -672,7 +672,10 @@ size_t sla_backward_varlen_workspace_bytes(const sla_params* p) {
 size_t sla_backward_chunks_workspace_bytes(const sla_params* p, int packed) {
     const size_t least = packed ? sla_backward_varlen_workspace_bytes(p) : sla_backward_workspace_bytes(p);
     if (least == 0 || p->dtype != SLA_BF16 || p->T == 0 || p->B == 0) return least;
-    return std::max(least, sla::backward_chunks_workspace_floats(*p, packed != 0) * sizeof(float));
+    int len = 0;
+    const size_t floats = sla::backward_chunks_workspace_floats(*p, packed != 0);
+    if (!sla::backward_chunks_take(*p, packed != 0, backward_segments(*p, packed != 0, &len), floats)) return least;
+    return std::max(least, floats * sizeof(float));
 }
 
 size_t sla_backward_gdn_chunks_workspace_bytes(const sla_params* p, int packed) {

@@ -63,11 +63,42 @@ inline size_t backward_chunks_floats(const sla_params& p, bool packed, const Chu
 inline size_t backward_chunks_workspace_floats(const sla_params& p, bool packed) {
     return backward_chunks_floats(p, packed, chunk_parts(p, packed, kMostStates));
 }
-// Whether a workspace of that many floats is enough for the chunk-parallel pass.
-inline bool backward_chunks_fit(const sla_params& p, bool packed, size_t floats) {
-    if (p.dtype != SLA_BF16 || p.T == 0) return false;
+// Whether a call runs chunk-parallel in a workspace of that many floats: they have to be enough, and the schedule has to be
+// faster than what runs otherwise, nseg segments or (nseg == 1) the sweeps in one pass.  A part's states are carried over the
+// chunks one after another, 0.65 us a chunk (RetNet) or 1.15 (GLA) whatever the number of heads, which is what it loses by on
+// long rows with few heads; it wins by 0.6 and 0.9 ns a token and head of 128 x 128, and by the segments' launches.
+//     us, segments -> chunks, B=1 128 x 128      T=4096       8192       16384      32768
+//         RetNet H=2                              97 ->  65  106 -> 108  123 -> 197  167 -> 376
+//                H=8                             111 ->  76  155 -> 135  235 -> 264  435 -> 572
+//                H=16                            151 ->  93  231 -> 179  430 -> 393  819 -> 781
+//         GLA    H=2                             115 -> 105  128 -> 181  148 -> 338  205 -> 661
+//                H=8                             130 -> 111  185 -> 204  301 -> 404  571 -> 830
+//                H=16                            179 -> 137  296 -> 270  567 -> 541 1081 -> 1066
+//     and in parts: GLA B=1 T=16384 H=32 8 segments 1110 -> 2104 (8 parts), B=8 T=4096 H=4 128 x 256 543 -> 498 (4).
+// Against the sweeps, whose own walk takes 8 us in place of a chunk's, a few parts are no matter where those leave compute
+// units idle (RetNet B=4 T=8192 H=16 1027 -> 538 in one part, 562 in four, 1202 in 16); where they fill the chip a part costs
+// its walk (B=16 T=4096 H=16: 1187 -> 1067, 1107 in four parts, 1601 in 16; GLA 1555 -> 1503, 1580 in two).
+inline bool backward_chunks_take(const sla_params& p, bool packed, int nseg, size_t floats) {
+    if (p.dtype != SLA_BF16 || p.T == 0 || p.B == 0) return false;
     const size_t least = backward_chunks_fixed_floats(p, packed) + kLeastStates;
-    return backward_chunks_floats(p, packed, backward_chunks_parts(p, packed, least)) <= floats;
+    if (backward_chunks_floats(p, packed, backward_chunks_parts(p, packed, least)) > floats) return false;
+    const bool gla = p.variant == SLA_GLA;
+    const double heads = (double)p.B * p.H * p.dk * p.dv / (128. * 128.);  // of 128 x 128
+    // Sequences of a 16-token block: the sweeps do one step of their walk, a chunk all its work.  That is slower for numbers
+    // that fill the chip once, for GLA's kernel for keys of 64 also for larger ones.  Packed 12 tokens each, H=8, sweeps ->
+    // chunks: GLA 128 x 128 16 sequences 32 -> 34 us, 32 37 -> 46, 64 58 -> 64; 64 x 64 32 31 -> 30, 128 46 -> 55, 4096 1092 ->
+    // 1350; RetNet 128 x 128 16 31 -> 29, 32 32 -> 36, 128 60 -> 57.  Of 24 tokens: 128 GLA 64 x 64 60 -> 54.
+    if ((packed ? (int64_t)p.T <= (int64_t)16 * p.B : p.T < 16) && p.dk >= 64 && heads >= (gla ? 128. : 256.) &&
+        (heads < (gla ? 1025. : 1024.) || (gla && p.dk == 64)))
+        return false;
+    const ChunkParts parts = backward_chunks_parts(p, packed, floats);
+    const int64_t count = ((int64_t)p.B + parts.nb - 1) / parts.nb * (((int64_t)p.H + parts.nh - 1) / parts.nh);
+    if (nseg > 1) return (double)((p.T + kChunkTokens - 1) / kChunkTokens) * (count - heads / (gla ? 20. : 24.)) <= (gla ? 58. : 90.);
+    if ((int64_t)p.B * p.H * std::min(p.dk, p.dv) / 64 < 256) return count <= 4;
+    // RetNet's values four times as wide as its keys: states as large as the rows they stand for (64 x 256 B=16 T=2048 H=16
+    // 623 -> 650 us; T=512 B=32 341 -> 327)
+    if (!gla && p.dv >= 4 * p.dk && !packed && p.T >= 1024) return false;
+    return (double)(count - 1) <= heads / (gla ? 400. : 92.);
 }
 
 // ---- delta rule (sla_chunk_gdn.hip)

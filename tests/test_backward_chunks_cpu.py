@@ -38,3 +38,29 @@ def test_where_the_other_queries_hold():
     assert sla.sla_backward_chunks_workspace_bytes(_params(sla.GDN)) == 0
     assert sla.sla_backward_chunks_workspace_bytes(_params(dk=96)) == 0
     assert sla.sla_backward_chunks_workspace_bytes(_params(dk=32, segments=2)) == 0
+
+
+@pytest.mark.parametrize("variant", [sla.RETNET, sla.GLA])
+def test_which_calls_run_chunk_parallel(variant):
+    """A call that the other schedules are faster for is told so by the query, which then asks for what these want."""
+    def chunks(B, T, H, dk=128, dv=128, segments=0, packed=False):
+        p = _params(variant, B=B, T=T, H=H, dk=dk, dv=dv)
+        if segments == 0 and not packed:
+            segments = sla.sla_backward_segments(p, 256)
+        p.segments = max(segments, 1)
+        least = sla.sla_backward_varlen_workspace_bytes if packed else sla.sla_backward_workspace_bytes
+        return sla.sla_backward_chunks_workspace_bytes(p, packed) > least(p)
+
+    # few heads: up to a length that grows with their number
+    assert chunks(1, 2048, 2) and not chunks(1, 16384, 2)
+    assert chunks(1, 4096, 8) and not chunks(1, 32768, 8)
+    assert chunks(4, 16384, 8) and chunks(4, 32768, 8)
+    assert not chunks(1, 131072, 8, 64, 64) and not chunks(1, 65536, 4) and not chunks(1, 65536, 32, segments=8)
+    assert chunks(1, 131072, 8, 64, 64, segments=1)  # the sweeps would be slower still
+    # one part however long, or as many as the chip is full in; not one for each of a few heads
+    assert chunks(1, 65536, 32, segments=1) and not chunks(1, 1 << 20, 5, segments=1)
+    assert chunks(8, 4096, 16) and chunks(128, 1024, 16) and chunks(8, 4096, 4, 128, 256)
+    # sequences of a block: not in numbers that fill the chip once
+    assert chunks(32, 32 * 40, 16, packed=True) and not chunks(32, 32 * 12, 16, packed=True)
+    assert chunks(2, 2 * 12, 16, packed=True)
+    assert chunks(4096, 4096 * 12, 16, packed=True)

@@ -110,7 +110,7 @@ def test_many_packed_sequences(monkeypatch, variant, B):
     lens = r.integers(0, 4, B) * r.integers(0, 3, B)
     lens[r.integers(0, B, 3)] = [64, 65, 200]
     cu = np.concatenate([[5], 5 + np.cumsum(lens)])
-    T, H, dk, dv = int(cu[-1]) + 9, 2, 64, 64
+    T, H, dk, dv = int(cu[-1]) + 9, 2, 128, 64
     q, k, v, ql, kl, ld, do = (t[0].contiguous() if t.dim() > 1 else t for t in _tensors(min(variant, GLA), 1, T, H, dk, dv, 3801))
     cu = torch.tensor(cu, dtype=torch.int32, device="cuda")
     if variant == GDN:
