@@ -314,6 +314,19 @@ def forward_varlen(variant: int, q, k, v, q_head_logits, k_head_logits, log_deca
     return out, fin
 
 
+def _workspace(device, most: int, least):
+    """Memory for one call: the ``most`` bytes that it runs fastest with, or the ``least()`` it needs where there is no room."""
+    import torch
+
+    try:
+        return torch.empty(max(most, 16), dtype=torch.uint8, device=device)
+    except torch.cuda.OutOfMemoryError:
+        need = least()
+        if need >= most:
+            raise
+        return torch.empty(max(need, 16), dtype=torch.uint8, device=device)
+
+
 def backward_varlen(variant: int, q, k, v, q_head_logits, k_head_logits, log_decay, d_out, cu_seqlens,
                     initial_state=None, d_final_state=None, *, want_d_initial_state: bool = False):
     """Gradients of ``forward_varlen`` (RetNet, GLA; bfloat16 or float32); tensors packed as there.  Returns a dict
@@ -335,8 +348,8 @@ def backward_varlen(variant: int, q, k, v, q_head_logits, k_head_logits, log_dec
         "d_initial_state": torch.empty((B, H, dk, dv), dtype=torch.float32, device=dev) if want_d_initial_state else None,
     }
     params = SlaParams(variant, BF16 if q.dtype == torch.bfloat16 else F32, B, T, H, dk, dv, 0, 0, 1)
-    need = sla_backward_chunks_workspace_bytes(params, packed=True)
-    workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
+    workspace = _workspace(dev, sla_backward_chunks_workspace_bytes(params, packed=True),
+                           lambda: sla_backward_varlen_workspace_bytes(params))
     ptr = lambda t: None if t is None else t.data_ptr()
     rc = sla_backward_varlen(
         params, ptr(q), ptr(k), ptr(v), ptr(q_head_logits), ptr(k_head_logits), ptr(log_decay), ptr(cu_seqlens),
@@ -544,9 +557,8 @@ def backward(variant: int, q, k, v, q_head_logits, k_head_logits, log_decay, d_o
     if int(segments) == 0:
         cus = torch.cuda.get_device_properties(q.device).multi_processor_count
         params.segments = max(sla_backward_segments(params, cus), 1)
-    need = sla_backward_chunks_workspace_bytes(params)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
+        workspace = _workspace(dev, sla_backward_chunks_workspace_bytes(params), lambda: sla_backward_workspace_bytes(params))
     ptr = lambda t: None if t is None else t.data_ptr()
     rc = sla_backward(
         params, ptr(q), ptr(k), ptr(v), ptr(q_head_logits), ptr(k_head_logits), ptr(log_decay), ptr(initial_state),
@@ -624,8 +636,8 @@ def backward_gdn_varlen(q, k, v, q_head_logits, k_head_logits, log_decay, beta, 
         "d_initial_state": torch.empty((B, H, dk, dv), dtype=torch.float32, device=dev) if want_d_initial_state else None,
     }
     params = SlaParams(GDN, BF16 if q.dtype == torch.bfloat16 else F32, B, T, H, dk, dv, 0, 0, 1)
-    need = sla_backward_gdn_chunks_workspace_bytes(params, packed=True)
-    workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
+    workspace = _workspace(dev, sla_backward_gdn_chunks_workspace_bytes(params, packed=True),
+                           lambda: sla_backward_gdn_varlen_workspace_bytes(params))
     ptr = lambda t: None if t is None else t.data_ptr()
     rc = sla_backward_gdn_varlen(
         params, ptr(q), ptr(k), ptr(v), ptr(q_head_logits), ptr(k_head_logits), ptr(log_decay), ptr(beta),
@@ -667,9 +679,9 @@ def backward_gdn(q, k, v, q_head_logits, k_head_logits, log_decay, beta, d_out, 
         "d_initial_state": torch.empty((B, H, dk, dv), dtype=torch.float32, device=dev) if want_d_initial_state else None,
     }
     params = SlaParams(GDN, BF16 if q.dtype == torch.bfloat16 else F32, B, T, H, dk, dv, 0, 0, 1)
-    need = sla_backward_gdn_chunks_workspace_bytes(params)
     if workspace is None:
-        workspace = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
+        workspace = _workspace(dev, sla_backward_gdn_chunks_workspace_bytes(params),
+                               lambda: sla_backward_gdn_workspace_bytes(params))
     ptr = lambda t: None if t is None else t.data_ptr()
     rc = sla_backward_gdn(
         params, ptr(q), ptr(k), ptr(v), ptr(q_head_logits), ptr(k_head_logits), ptr(log_decay), ptr(beta),
@@ -799,7 +811,7 @@ def forward(
     else:
         need = sla_forward_workspace_bytes(params, _compute_units(q.device))
         if workspace is None and need > 0:
-            workspace = torch.empty(need, dtype=torch.uint8, device=q.device)
+            workspace = _workspace(q.device, need, lambda: sla_workspace_bytes(params, _compute_units(q.device)))
         ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
         rc = sla_forward_ws(
             params, ptr(q), ptr(k), ptr(v), ptr(q_head_logits), ptr(k_head_logits), ptr(log_decay), ptr(beta),
