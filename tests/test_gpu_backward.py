@@ -10,7 +10,7 @@ import oracle
 from gpu_util import GLA, RETNET, TOL, rel_err, to_device, worst_slice_err
 from oracle import sla_backward as ob
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("backward_workspace")]
 
 NAMES = {"dq": "dq", "dk": "dk", "dv": "dv", "dq_head_logits": "dq_logits", "dk_head_logits": "dk_logits",
          "dlog_decay": "dlog_decay", "d_initial_state": "dinitial_state"}
@@ -169,7 +169,8 @@ def test_long_sequences_keep_the_decay_gradient_accurate(T, dv, states):
 @pytest.mark.parametrize("T,segments,states", [(700, 2, True), (1000, 3, False), (2048 + 37, 4, True), (512, 2, True)])
 def test_segment_schedule(variant, T, segments, states):
     """Batch rows cut into segments that run as packed sequences: entry states from the forward's pre-pass, end
-    cotangents from a dv-sweep pre-pass and a combine kernel.  Same answers as the single pass, to the same bar."""
+    cotangents from a dv-sweep pre-pass and a combine kernel (with the plain workspace; these rows are short enough for
+    the chunk-parallel schedule in the larger one).  Same answers as the single pass, to the same bar."""
     B, H, dk, dv = 2, 2, 128, 128
     d = si.custom(variant, "bf16", B=B, T=T, H=H, dk=dk, dv=dv, seed=990 + T + variant)
     cot = si.cotangents(B, T, H, dk, dv, seed=991 + T, final_state=states)
@@ -201,7 +202,7 @@ def test_segment_schedule_on_the_paper_shape():
 
 @pytest.mark.parametrize("name", ["gla_train", "retnet_train"])
 def test_full_size(name):
-    """The bench workload, in the launch configuration bench.py times; every batch row against the C gradient oracle."""
+    """The bench workload, in both workspaces; every batch row against the C gradient oracle."""
     w = si.workload(name)
     d = si.generate(w)
     cot = si.cotangents(w.B, w.T, w.H, w.dk, w.dv, seed=w.seed + 50)
@@ -213,3 +214,15 @@ def test_full_size(name):
     for n in ("dq_head_logits", "dk_head_logits"):
         scale = np.max(np.abs(got[n]))
         assert np.max(np.abs(got[n].sum(axis=-1))) <= 1e-5 * scale * w.H, n
+
+
+@pytest.mark.parametrize("variant", [RETNET, GLA])
+def test_the_workspace_and_segments_choose_the_schedule(backward_workspace, variant):
+    """What the tests above rely on: with the plain workspace the segments asked for run, in the larger one the same kernels
+    whatever is asked for.  Every schedule rounds differently, so that equal bits tell them apart."""
+    B, T, H, dk, dv = 2, 1000, 2, 128, 128
+    d = si.custom(variant, "bf16", B=B, T=T, H=H, dk=dk, dv=dv, seed=998)
+    cot = si.cotangents(B, T, H, dk, dv, seed=999)
+    one, three = (run_backward(variant, d, cot, segments=n) for n in (1, 3))
+    same = all(np.array_equal(one[n], three[n]) for n in ("dq", "dk", "dv"))
+    assert same == (backward_workspace == "largest workspace")

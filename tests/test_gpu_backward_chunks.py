@@ -55,6 +55,49 @@ def test_parts_give_the_same_bits(variant, B, T, H, dk, dv):
 
 
 @pytest.mark.parametrize("variant", [RETNET, GLA])
+@pytest.mark.parametrize("layout", ["packed", "head-major"])
+def test_parts_of_packed_and_head_major_batches(monkeypatch, variant, layout):
+    """The same in the other two layouts: some heads of all sequences at a time, and rows of [B,H,T,d] tensors; with and
+    without the states' gradients, which GLA's decay gradient takes another area of the workspace for."""
+    import torch
+    import paper_2602_01744_amd as sla
+    from paper_2602_01744_amd import binding
+
+    B, T, H, dk, dv = 3, 1500, 24, 128, 128
+    q, k, v, ql, kl, ld, do = _tensors(variant, B, T, H, dk, dv, seed=3150)
+    ds = torch.randn(B, H, dk, dv, device="cuda")
+    if layout == "packed":
+        x = [t.reshape(B * T, *t.shape[2:]) if t.dim() > 2 else t for t in (q, k, v, ql, kl, ld, do)]
+        cu = torch.tensor([0, 1000, 1007, B * T], dtype=torch.int32, device="cuda")
+        call = lambda: sla.backward_varlen(variant, *x, cu, None, ds, want_d_initial_state=True)
+    else:
+        hm = lambda t: t.transpose(1, 2).contiguous() if t.dim() == 4 else t
+        x = [hm(t) for t in (q, k, v)] + [ql, kl] + [hm(t) for t in (ld, do)]
+        call = lambda: sla.backward(variant, *x, None, ds, want_d_initial_state=True, head_major=True)
+    whole = call()
+    least, plain = 4 * 4 * B * T * H + (64 << 20), binding.sla_backward_chunks_workspace_bytes
+    p = sla.SlaParams(variant, sla.BF16, B, B * T if layout == "packed" else T, H, dk, dv, 0, 0, 1)
+    assert least < plain(p, layout == "packed")
+    monkeypatch.setattr(binding, "sla_backward_chunks_workspace_bytes", lambda p, packed=False: least)
+    parts = call()
+    for n, t in whole.items():
+        assert t is None or torch.equal(t, parts[n]), n
+
+
+@pytest.mark.parametrize("T,dk,dv", [(100, 64, 64), (64, 128, 128), (200, 128, 256), (130, 32, 64)])
+def test_strongest_decay_with_states(T, dk, dv):
+    """Log-decay down to the bound of -5 a token, whole blocks of it among them, with states in and out."""
+    d = si.custom(GLA, "bf16", B=2, T=T, H=2, dk=dk, dv=dv, seed=3900 + T)
+    r = np.random.default_rng(3901)
+    ld = (-5.0 * r.random(size=d["log_decay"].shape)).astype(np.float32)
+    ld[:, 16:48, :, : dk // 2] = -5.0
+    ld[:, :, :, 0] = -5.0
+    d["log_decay"] = si.round_to_bf16(ld)
+    cot = si.cotangents(2, T, 2, dk, dv, seed=3902, final_state=True)
+    check_backward(GLA, d, cot, si.initial_state(2, 2, dk, dv, seed=3903), want_ds0=True, label=f"decay in [-5, 0] T={T} {dk}x{dv}")
+
+
+@pytest.mark.parametrize("variant", [RETNET, GLA])
 def test_layouts_and_packing_give_the_same_bits(variant):
     """[B,H,T,d] tensors, and the rows as a packed batch with empty sequences in between, against the rectangular call."""
     import torch

@@ -10,7 +10,7 @@ import sla_inputs as si
 from gpu_util import GDN, TOL, rel_err, to_device
 from oracle import sla_backward as ob
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("backward_workspace")]
 
 NAMES = {"dq": "dq", "dk": "dk", "dv": "dv", "dq_head_logits": "dq_logits", "dk_head_logits": "dk_logits",
          "dlog_decay": "dlog_decay", "dbeta": "dbeta", "d_initial_state": "dinitial_state"}
@@ -167,3 +167,17 @@ def test_full_size():
         assert x is None or np.all(np.isfinite(x)), n
     for n in ("dq_head_logits", "dk_head_logits"):
         assert np.max(np.abs(got[n].sum(axis=-1))) <= 1e-5 * np.max(np.abs(got[n])) * w.H, n
+
+
+def test_the_workspace_chooses_the_schedule(monkeypatch, backward_workspace):
+    """What the tests above rely on: the sweeps in the plain workspace, the chunk-parallel schedule in the larger one.  They
+    round differently, so that equal bits tell them apart."""
+    from paper_2602_01744_amd import binding
+    import paper_2602_01744_amd as sla
+
+    B, T, H, dk, dv = 2, 200, 3, 128, 128
+    d = si.custom(GDN, "bf16", B=B, T=T, H=H, dk=dk, dv=dv, seed=3990)
+    cot = si.cotangents(B, T, H, dk, dv, seed=3991)
+    got = run_backward_gdn(d, cot)
+    monkeypatch.setattr(binding, "sla_backward_gdn_chunks_workspace_bytes", lambda p, packed=False: sla.sla_backward_gdn_workspace_bytes(p))
+    assert np.array_equal(got["dq"], run_backward_gdn(d, cot)["dq"]) == (backward_workspace == "plain workspace")

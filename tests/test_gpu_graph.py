@@ -15,12 +15,12 @@ def _forward_args(variant, d, dtype):
     return g
 
 
-@pytest.mark.parametrize("variant,segments", [(GLA, 1), (RETNET, 3), (GDN, 1)])
-def test_forward_replays_identically(variant, segments):
+@pytest.mark.parametrize("variant,segments,T", [(GLA, 1, 900), (RETNET, 3, 900), (GDN, 1, 900), (GLA, 2, 1100)])
+def test_forward_replays_identically(variant, segments, T):
     import torch
     import paper_2602_01744_amd as sla
 
-    B, T, H, dk, dv = 2, 900, 4, 128, 128
+    B, H, dk, dv = 2, 4, 128, 128  # 1100 tokens in two segments: the pre-pass works on pieces of them
     d = si.custom(variant, "bf16", B=B, T=T, H=H, dk=dk, dv=dv, seed=2700 + variant)
     g = _forward_args(variant, d, "bf16")
     s0 = torch.from_numpy(si.initial_state(B, H, dk, dv, seed=27)).cuda()
@@ -32,7 +32,7 @@ def test_forward_replays_identically(variant, segments):
     fin = torch.empty_like(ref_fin)
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     p = sla.SlaParams(variant, sla.BF16, B, T, H, dk, dv, 0, 0, segments)
-    ws = torch.empty(max(sla.sla_workspace_bytes(p, cus), 16), dtype=torch.uint8, device="cuda")
+    ws = torch.empty(max(sla.sla_forward_workspace_bytes(p, cus), 16), dtype=torch.uint8, device="cuda")
     side = torch.cuda.Stream()
     side.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(side):  # one eager call on the capture stream first (one-time kernel set-up)
@@ -86,14 +86,15 @@ def test_decode_steps_replay_identically():
     assert torch.equal(state, eager_state) and torch.equal(out, eager_out)
 
 
+@pytest.mark.parametrize("chunks", [False, True])
 @pytest.mark.parametrize("variant", [RETNET, GLA, GDN])
-def test_training_step_replays_identically(variant):
+def test_training_step_replays_identically(variant, chunks):
     """Gate logits, forward and backward captured as one graph (raw entry points, buffers allocated up front); the
     workspace is dirtied between replays."""
     import torch
     import paper_2602_01744_amd as sla
 
-    B, T, H, dk, dv = 2, 300, 4, 128, 128
+    B, T, H, dk, dv = 2, 600 if chunks else 300, 4, 128, 128
     d = si.custom(variant, "bf16", B=B, T=T, H=H, dk=dk, dv=dv, seed=2900 + variant)
     g = _forward_args(variant, d, "bf16")
     gw = si.gate_weights(H, dk, seed=2901)
@@ -108,7 +109,10 @@ def test_training_step_replays_identically(variant):
              torch.empty_like(kl)]
     dld = torch.empty_like(g["log_decay"]) if variant != RETNET else None
     dbeta = torch.empty_like(g["beta"]) if variant == GDN else None
-    need = sla.sla_backward_gdn_workspace_bytes(p) if variant == GDN else sla.sla_backward_workspace_bytes(p)
+    if chunks:
+        need = (sla.sla_backward_gdn_chunks_workspace_bytes if variant == GDN else sla.sla_backward_chunks_workspace_bytes)(p)
+    else:
+        need = sla.sla_backward_gdn_workspace_bytes(p) if variant == GDN else sla.sla_backward_workspace_bytes(p)
     ws = torch.empty(need, dtype=torch.uint8, device="cuda")
     ptr = lambda t: None if t is None else t.data_ptr()
 

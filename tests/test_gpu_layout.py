@@ -51,7 +51,7 @@ def test_head_major_widths_and_ragged_length():
 
 @pytest.mark.parametrize("variant", [RETNET, GLA])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-def test_backward_head_major_matches_token_major(variant, dtype):
+def test_backward_head_major_matches_token_major(backward_workspace, variant, dtype):
     import torch
     import paper_2602_01744_amd as sla
 

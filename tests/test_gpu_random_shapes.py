@@ -39,7 +39,7 @@ def test_forward(variant, seed):
 
 @pytest.mark.parametrize("seed", range(3100, 3112))
 @pytest.mark.parametrize("variant", [RETNET, GLA])
-def test_backward(variant, seed):
+def test_backward(backward_workspace, variant, seed):
     c = draw(seed + 100 * variant)
     dtype = "bf16" if seed % 3 else "f32"
     d = si.custom(variant, dtype, B=c["B"], T=c["T"], H=c["H"], dk=c["dk"], dv=c["dv"], seed=seed)
@@ -54,7 +54,7 @@ def test_backward(variant, seed):
 
 
 @pytest.mark.parametrize("seed", range(3200, 3212))
-def test_backward_gdn(seed):
+def test_backward_gdn(backward_workspace, seed):
     c = draw(seed)
     dtype = "bf16" if seed % 3 else "f32"
     d = si.custom(GDN, dtype, B=c["B"], T=c["T"], H=c["H"], dk=c["dk"], dv=c["dv"], seed=seed)

@@ -8,6 +8,9 @@ import sla_inputs as si
 from gpu_util import GLA, RETNET, check, rel_err
 
 # T, segments: segments of 576 tokens in 2 pieces (288), 768 in 3 (256), 1088 in 4 (272), 2048 in 8 (256); ragged ends
+# pieces in several segments: three segments of 576 in 2, four of 768 in 3 (the chain takes four pieces at a time, so that
+# segments end inside of a group)
+CHAINS = [(3 * 576 - 9, 3), (4 * 768 - 7, 4)]
 SHAPES = [(1100, 2), (2 * 768 - 1, 2), (2065, 2), (2 * 2048 - 3, 2)]
 
 
@@ -59,7 +62,7 @@ def test_slice_width_keeps_the_bits(variant, dtype, B, T, H, dk, dv, segments):
 @pytest.mark.gpu
 @pytest.mark.parametrize("variant", [RETNET, GLA])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("T,segments", SHAPES)
+@pytest.mark.parametrize("T,segments", SHAPES + CHAINS)
 def test_pieces(variant, dtype, T, segments):
     d = si.custom(variant, dtype, B=1, T=T, H=2, dk=64, dv=64, seed=1700 + T)
     s0 = si.initial_state(1, 2, 64, 64, seed=1701)

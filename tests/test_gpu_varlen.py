@@ -60,7 +60,7 @@ def test_forward_varlen(variant, dtype):
 
 @pytest.mark.parametrize("variant", [RETNET, GLA])
 @pytest.mark.parametrize("dtype,dk", [("bf16", 128), ("f32", 128), ("bf16", 32)])
-def test_backward_varlen(variant, dtype, dk):
+def test_backward_varlen(backward_workspace, variant, dtype, dk):
     import torch
     import paper_2602_01744_amd as sla
 
@@ -96,7 +96,7 @@ def test_backward_varlen(variant, dtype, dk):
             assert e <= TOL[dtype], (i, n, e)
 
 
-def test_backward_varlen_gdn():
+def test_backward_varlen_gdn(backward_workspace):
     import torch
     import paper_2602_01744_amd as sla
 
@@ -149,8 +149,9 @@ def test_varlen_equals_batch_for_equal_lengths():
     assert torch.equal(fl(out), out2) and torch.equal(fin, fin2)
 
 
+@pytest.mark.parametrize("chunks", [False, True])
 @pytest.mark.parametrize("variant", [GLA, GDN])
-def test_tokens_outside_every_sequence_are_left_untouched(variant):
+def test_tokens_outside_every_sequence_are_left_untouched(variant, chunks):
     """cu_seqlens[0] > 0 and cu_seqlens[B] < T: the tokens before the first and after the last sequence belong to no
     sequence.  Forward and backward must neither read them into a result nor write their rows: every output tensor
     is pre-filled with a canary, which must survive there, while the sequences still agree with the oracle."""
@@ -181,14 +182,15 @@ def test_tokens_outside_every_sequence_are_left_untouched(variant):
     gr = {n: can(t) for n, t in (("dq", q), ("dk", k), ("dv", v), ("dql", ql), ("dkl", kl))}
     if variant == GLA:
         gr["dld"] = can(ld)
-        need = sla.sla_backward_varlen_workspace_bytes(params)
+        need = sla.sla_backward_chunks_workspace_bytes(params, True) if chunks else sla.sla_backward_varlen_workspace_bytes(params)
         ws = torch.empty(max(need, 16), dtype=torch.uint8, device="cuda")
         rc = sla.sla_backward_varlen(params, ptr(q), ptr(k), ptr(v), ptr(ql), ptr(kl), ptr(ld), ptr(cud), None, ptr(dout),
                                      None, ptr(gr["dq"]), ptr(gr["dk"]), ptr(gr["dv"]), ptr(gr["dql"]), ptr(gr["dkl"]),
                                      ptr(gr["dld"]), None, ptr(ws), need, st)
     else:
         gr["dld"], gr["dbeta"] = can(ld), can(beta)
-        need = sla.sla_backward_gdn_varlen_workspace_bytes(params)
+        need = (sla.sla_backward_gdn_chunks_workspace_bytes(params, True) if chunks
+                else sla.sla_backward_gdn_varlen_workspace_bytes(params))
         ws = torch.empty(max(need, 16), dtype=torch.uint8, device="cuda")
         rc = sla.sla_backward_gdn_varlen(params, ptr(q), ptr(k), ptr(v), ptr(ql), ptr(kl), ptr(ld), ptr(beta), ptr(cud),
                                          None, ptr(dout), None, ptr(gr["dq"]), ptr(gr["dk"]), ptr(gr["dv"]),
