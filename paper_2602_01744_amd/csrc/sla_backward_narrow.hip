@@ -2,7 +2,8 @@
 // width).  The backward sweeps slice the key dimension 64 columns to a workgroup, so a 32-wide head runs as a 64-wide
 // one whose upper 32 key dimensions are zero: q, k, the GLA log-decay and the states are copied into zero-padded
 // buffers in the workspace, the 64-wide pass runs on them, and dq, dk, the decay gradient and the state gradient are
-// copied back.  Padded dimensions contribute nothing (q . k over them is zero, their decay factor is exp(0) = 1, their
+// copied back: fp32 tensors and the delta rule.  (RetNet and GLA on bf16 tensors run chunk-parallel, whose kernels take 32-wide
+// keys as they are and whose workspace is never more than the padded copies'.)  Padded dimensions contribute nothing (q . k over them is zero, their decay factor is exp(0) = 1, their
 // state rows stay zero), so the results are those of the 32-wide problem; the price is twice the key-side work and
 // the copies.  Value heads are untouched.
 #include <hip/hip_runtime.h>

@@ -82,13 +82,14 @@ inline bool backward_chunks_take(const sla_params& p, bool packed, int nseg, siz
     if (p.dtype != SLA_BF16 || p.T == 0 || p.B == 0) return false;
     const size_t least = backward_chunks_fixed_floats(p, packed) + kLeastStates;
     if (backward_chunks_floats(p, packed, backward_chunks_parts(p, packed, least)) > floats) return false;
+    if (p.dk < 64) return true;  // the others run them on copies padded to 64 (GLA B=1 T=16384 H=8 32 x 64 1997 -> 210 us)
     const bool gla = p.variant == SLA_GLA;
     const double heads = (double)p.B * p.H * p.dk * p.dv / (128. * 128.);  // of 128 x 128
     // Sequences of a 16-token block: the sweeps do one step of their walk, a chunk all its work.  That is slower for numbers
     // that fill the chip once, for GLA's kernel for keys of 64 also for larger ones.  Packed 12 tokens each, H=8, sweeps ->
     // chunks: GLA 128 x 128 16 sequences 32 -> 34 us, 32 37 -> 46, 64 58 -> 64; 64 x 64 32 31 -> 30, 128 46 -> 55, 4096 1092 ->
     // 1350; RetNet 128 x 128 16 31 -> 29, 32 32 -> 36, 128 60 -> 57.  Of 24 tokens: 128 GLA 64 x 64 60 -> 54.
-    if ((packed ? (int64_t)p.T <= (int64_t)16 * p.B : p.T < 16) && p.dk >= 64 && heads >= (gla ? 128. : 256.) &&
+    if ((packed ? (int64_t)p.T <= (int64_t)16 * p.B : p.T < 16) && heads >= (gla ? 128. : 256.) &&
         (heads < (gla ? 1025. : 1024.) || (gla && p.dk == 64)))
         return false;
     const ChunkParts parts = backward_chunks_parts(p, packed, floats);

@@ -64,3 +64,19 @@ def test_which_calls_run_chunk_parallel(variant):
     assert chunks(32, 32 * 40, 16, packed=True) and not chunks(32, 32 * 12, 16, packed=True)
     assert chunks(2, 2 * 12, 16, packed=True)
     assert chunks(4096, 4096 * 12, 16, packed=True)
+
+
+@pytest.mark.parametrize("variant", [sla.RETNET, sla.GLA])
+@pytest.mark.parametrize("packed", [False, True])
+def test_narrow_keys_never_need_more_than_the_plain_workspace(variant, packed):
+    """bf16 calls with keys of 32 run chunk-parallel in any workspace that is accepted at all: the states fit into what the
+    plain query asks for."""
+    least = sla.sla_backward_varlen_workspace_bytes if packed else sla.sla_backward_workspace_bytes
+    for B in (1, 3, 64, 16384):
+        for T in (1, 63, 64, 65, 1000, 65536):
+            for H, dv in ((1, 64), (4, 256), (64, 128)):
+                p = _params(variant, B=B, T=T, H=H, dk=32, dv=dv)
+                rows, slots = (T, T // 64 + B + 1) if packed else (B * T, B * ((T + 63) // 64))
+                need = 16 * ((rows * H + 3) // 4 * 4) + 4 * slots * H * 32 * dv + (4 * B * H * dv if variant == sla.GLA else 0)
+                if least(p) > 0:  # 0: tensors beyond what the library takes
+                    assert need <= least(p) == sla.sla_backward_chunks_workspace_bytes(p, packed)

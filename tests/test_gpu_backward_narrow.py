@@ -1,5 +1,6 @@
 """GPU parity of the backward passes for key heads of width 32 (dk = 32, dv = 64: the H = 16 point of the head-count
-ablation at fixed width), which run zero-padded to width 64: same oracle, same bars as the other widths."""
+ablation at fixed width), which run zero-padded to width 64 or (RetNet and GLA, bf16) chunk-parallel: same oracle, same bars
+as the other widths."""
 import numpy as np
 import pytest
 
