@@ -14,12 +14,12 @@
 // at their ends (kGdnAnchor in sla_gdn_block.h), which has nothing to average a rounding over: both states are
 // taken there as two bf16 parts, 2^-17 off fp32, and at the sequence's end in fp32 by the state sweep.  (From the bf16 states
 // alone the last token's gradient was 2.0e-3 off at T = 8 with states in and out, 2.3e-4 from the sweeps.)
-// Against the four sweeps of sla_backward_gdn_block.hip, a training step with its convolutions and projections: few sequences 1.6 to
-// 3 times (B=2 T=4096 H=4 128 x 256 1142 -> 381 us, B=2 T=1000 H=8 128 x 128 256 -> 120, B=1 T=300 H=4 113 -> 65, 4096 packed
-// tokens H=8 303 -> 162), where the sweeps leave some compute units idle 1.1 to 1.25 times (B=8 T=4096 H=12 1110 -> 1012, 64 x 128
-// heads H=16 959 -> 774); where they fill the chip see sweeps_fill_the_chip().  Two sweeps 420 us and this kernel 430 for 3.6 GB
-// in all at B=8 T=4096 H=16 128 x 128.  No output is further from fp32 tensors than theirs (dk 5.2e-3 -> 4.8e-3, dv 4.7e-3 -> 4.4e-3,
-// dlog_decay 3.7e-2 -> 3.3e-2, dbeta the same): du stays in fp32, so that dbeta and w are what they were.
+// Against the four sweeps of sla_backward_gdn_block.hip, a backward call: few sequences 1.6 to 3.8 times (B=2 T=4096 H=4 128 x 256
+// 1020 -> 266 us, B=2 T=1000 H=8 128 x 128 227 -> 94, B=1 T=300 H=4 104 -> 53, 4096 packed tokens H=8 141 -> 86), where the sweeps
+// leave some compute units idle 1.1 to 1.25 times (B=8 T=4096 H=12 866 -> 783, 64 x 128 heads H=16 832 -> 674); where they fill the
+// chip see gdn_sweeps_are_faster().  Two sweeps 424 us and this kernel 439 at B=8 T=4096 H=16 128 x 128.  No output is
+// further from fp32 tensors than theirs (dk 4.1e-3 -> 3.4e-3, dv 3.4e-3 -> 3.0e-3, dlog_decay
+// 3.0e-2 -> 2.2e-2, dbeta the same): du stays in fp32, so that dbeta and w are what they were.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

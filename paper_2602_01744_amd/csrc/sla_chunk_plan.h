@@ -121,18 +121,27 @@ inline GdnChunkSizes gdn_chunk_sizes(const sla_params& p, bool packed) {
     return z;
 }
 
-// Long rows whose sweeps have a workgroup for each of 256 compute units, or nearly, in every round gain nothing: B=8 H=16
-// 128 x 128 T=4096 1761 -> 1771 us a training step, T=2048 561 -> 564, T=512 171 -> 155; three quarters of the chip (H=12 T=4096)
-// 1110 -> 1012.  Packed sequences end at different times and leave it idle whatever their number.
-inline bool sweeps_fill_the_chip(const sla_params& p, bool packed) {
-    const size_t cus = 256, wgs = (size_t)p.B * p.H * (p.dk < p.dv ? p.dk : p.dv) / 64, rounds = (wgs + cus - 1) / cus;
-    return !packed && p.T >= 1024 && wgs >= cus && 16 * wgs >= 15 * cus * rounds;
+// Where the sweeps have a workgroup for each of 256 compute units in every round, or nearly, the schedules are close, and heads
+// of 256 values are cheaper in the sweeps (the chunk kernel takes 256 registers for them, and spills).  Backward call, us,
+// sweeps -> chunks:
+//     128 x 256  B=6 H=16 T=1024 389 -> 371   B=7 403 -> 445   B=8 415 -> 500   B=10 663 -> 587   B=12 674 -> 699   B=16 839 -> 948
+//                B=7 T=256 140 -> 120         B=8 T=512 225 -> 258              32 packed rows of 256 488 -> 524
+//     64 x 256   B=16 H=16 T=1024 618 -> 645  B=24 951 -> 894  B=32 1220 -> 1229
+//     128 x 128  B=8 H=15 T=2048 492 -> 468   B=8 H=16 489 -> 500, T=1024 261 -> 251, T=4096 942 -> 940; two rounds, B=16 T=4096
+//                1873 -> 1790, three, B=24 T=2048, 1426 -> 1343
+//     others     64 x 128 B=8 H=32 T=2048 749 -> 703, 128 x 64 B=16 H=16 T=4096 1261 -> 1158, 64 x 64 B=16 942 -> 821
+inline bool gdn_sweeps_are_faster(const sla_params& p, bool packed) {
+    const int64_t cus = 256, wgs = (int64_t)p.B * p.H * std::min(p.dk, p.dv) / 64, rounds = (wgs + cus - 1) / cus;
+    const int64_t mean = packed ? p.T / p.B : p.T;  // tokens of a sequence
+    if (p.dv == 256 && p.dk == 128) return mean >= (rounds > 1 ? 256 : 384) && 16 * wgs >= 12 * cus * rounds;
+    if (p.dv == 256) return !packed && mean >= 256 && 16 * wgs >= 15 * cus * rounds;
+    return !packed && p.dk == 128 && p.dv == 128 && mean >= 1536 && wgs <= cus && 32 * wgs > 31 * cus;
 }
 
 // 0: this call does not run chunk-parallel (heads of width 32 are padded by sla_backward_narrow.hip, which runs the sweeps).
 // Its states may take a GiB, as in sla_chunk_backward.hip.
 inline size_t backward_gdn_chunks_workspace_floats(const sla_params& p, bool packed) {
-    if (p.dtype != SLA_BF16 || p.dk < 64 || p.T == 0 || p.B == 0 || sweeps_fill_the_chip(p, packed)) return 0;
+    if (p.dtype != SLA_BF16 || p.dk < 64 || p.T == 0 || p.B == 0 || gdn_sweeps_are_faster(p, packed)) return 0;
     const GdnChunkSizes z = gdn_chunk_sizes(p, packed);
     return 2 * z.state <= (size_t)1 << 28 ? z.floats : 0;
 }

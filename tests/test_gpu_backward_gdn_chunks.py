@@ -34,6 +34,22 @@ def test_size(packed):
     assert (sla.sla_backward_gdn_chunks_workspace_bytes(full, packed) == least(full)) == (not packed)
 
 
+def test_which_calls_run_chunk_parallel():
+    def chunks(B, T, H, dk=128, dv=128, packed=False):
+        p = _params(B=B, T=T, H=H, dk=dk, dv=dv)
+        least = sla.sla_backward_gdn_varlen_workspace_bytes if packed else sla.sla_backward_gdn_workspace_bytes
+        return sla.sla_backward_gdn_chunks_workspace_bytes(p, packed) > least(p)
+
+    # one full round of the sweeps' workgroups on long rows; not a round and a part, nor two, nor short rows
+    assert not chunks(8, 4096, 16) and chunks(8, 4096, 15) and chunks(10, 4096, 16) and chunks(16, 4096, 16) and chunks(8, 1024, 16)
+    assert chunks(16, 4096, 16, 128, 64) and chunks(8, 2048, 32, 64, 128) and chunks(16, 4096, 16, 64, 64)
+    # heads of 256 values: where the sweeps fill three quarters of the chip in every round
+    assert chunks(5, 1024, 16, 128, 256) and not chunks(7, 1024, 16, 128, 256) and not chunks(8, 512, 16, 128, 256)
+    assert chunks(10, 1024, 16, 128, 256) and not chunks(16, 1024, 16, 128, 256) and chunks(7, 256, 16, 128, 256)
+    assert not chunks(32, 32 * 256, 16, 128, 256, packed=True) and chunks(32, 32 * 64, 16, 128, 256, packed=True)
+    assert not chunks(16, 1024, 16, 64, 256) and chunks(24, 1024, 16, 64, 256) and chunks(16, 16384, 16, 64, 256, packed=True)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("T,dk,dv", [(1, 128, 128), (16, 64, 64), (31, 128, 64), (33, 64, 128), (48, 128, 256), (63, 64, 256),
                                      (64, 128, 128), (65, 64, 64), (96, 128, 128), (97, 128, 128), (129, 64, 128), (200, 128, 256)])
