@@ -77,6 +77,16 @@ def traffic_fields(key: str) -> dict:
     return out
 
 
+def backward_workspace(params, gdn: bool):
+    """Bytes of workspace as the binding allocates them, and whether the call runs chunk-parallel in them (key heads of
+    width 32, RetNet and GLA: always)."""
+    import paper_2602_01744_amd as sla
+
+    least = (sla.sla_backward_gdn_workspace_bytes if gdn else sla.sla_backward_workspace_bytes)(params)
+    need = (sla.sla_backward_gdn_chunks_workspace_bytes if gdn else sla.sla_backward_chunks_workspace_bytes)(params)
+    return need, need > least or (params.dk < 64 and not gdn)
+
+
 MFMA_BF16_PEAK_TFLOPS = 2500.0  # MI355X dense bf16, published
 BLOCK = 16                      # tokens per state step in the kernels (for the causal flop count)
 
@@ -152,7 +162,7 @@ def bench_backward(args, w, sla, si, torch, np) -> int:
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     nseg = 1 if (gdn or hm) else (args.segments if args.segments > 0 else max(sla.sla_backward_segments(params, cus), 1))
     params.segments = nseg
-    need = sla.sla_backward_gdn_workspace_bytes(params) if gdn else sla.sla_backward_workspace_bytes(params)
+    need, chunks = backward_workspace(params, gdn)
     ws = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
     gr = {
         "dq": torch.empty_like(g["q"]), "dk": torch.empty_like(g["k"]), "dv": torch.empty_like(g["v"]),
@@ -208,8 +218,12 @@ def bench_backward(args, w, sla, si, torch, np) -> int:
             "workload": f"{w.name}: backward of SLA-{si.VARIANT_NAMES[w.variant].upper()} B={w.B} T={w.T} H={w.H} "
                         f"dk={w.dk} dv={w.dv} bf16 in/out, dual head-softmax gates, no state cotangents"
                         + (", wide tensors laid out [B,H,T,d]" if hm else "")
-                        + (f", {nseg} segments per batch row" if nseg > 1 else ""),
-            "kernel": ("sla_backward_gdn (block form): sla_bwd_gates_kernel, gdn_blk_pre_kernel, gdn_blk_state_kernel, "
+                        + (", chunk-parallel" if chunks else f", {nseg} segments per batch row" if nseg > 1 else ""),
+            "kernel": ("sla_backward_gdn: sla_bwd_gates_kernel, gdn_blk_pre_kernel, gdn_blk_pair_kernel, sla_chunk_gdn_kernel, "
+                       "gdn_bwd_decay_scan_kernel, sla_bwd_logits_kernel") if gdn and chunks else
+                      ("sla_backward: sla_bwd_gates_kernel, sla_chunk_state_kernel, sla_chunk_backward_kernel, "
+                       "sla_bwd_logits_kernel") if chunks else
+                      ("sla_backward_gdn (block form): sla_bwd_gates_kernel, gdn_blk_pre_kernel, gdn_blk_state_kernel, "
                        "gdn_blk_cotangent_kernel, gdn_blk_key_kernel, gdn_blk_query_kernel, "
                        "gdn_bwd_finish_kernel, gdn_bwd_decay_scan_kernel") if gdn else
                       "sla_backward: sla_bwd_gates_kernel, sla_bwd_dq_kernel, sla_bwd_dv_kernel, sla_bwd_dk_kernel, "
@@ -227,9 +241,9 @@ def bench_backward(args, w, sla, si, torch, np) -> int:
             "kernel_us": call_ms * 1e3,
             "kernel_us_min": float(np.min(per_call_ms)) * 1e3,
             "algorithmic_bytes": abytes,
-            "note": "whole call (%s launches); achieved = algorithmic bytes / call time"
-                    % ("nine" if gdn else "six" if nseg == 1 else "thirteen")
-                    + ("; the sweeps pass res, w, the 32 x 32 block matrices and part of dk through the workspace, "
+            "note": "whole call; achieved = algorithmic bytes / call time"
+                    + ("; the states at the chunk boundaries pass through the workspace" if chunks else
+                       "; the sweeps pass res, w, the 32 x 32 block matrices and part of dk through the workspace, "
                        "about five times the algorithmic bytes, and run at the memory system's speed on those" if gdn else ""),
         },
     }
@@ -295,7 +309,7 @@ def bench_train_step(args, w, sla, si, torch, np) -> int:
              torch.empty_like(kl)]
     dld = torch.empty_like(g["log_decay"]) if w.variant != 0 else None
     dbeta = torch.empty_like(g["beta"]) if gdn else None
-    need = sla.sla_backward_gdn_workspace_bytes(pb) if gdn else sla.sla_backward_workspace_bytes(pb)
+    need, chunks = backward_workspace(pb, gdn)
     ws = torch.empty(max(need, 16), dtype=torch.uint8, device=dev)
     dwq, dwk = torch.empty_like(wq), torch.empty_like(wk)
     gneed = sla.sla_gate_logits_backward_workspace_bytes(pf)
@@ -361,7 +375,8 @@ def bench_train_step(args, w, sla, si, torch, np) -> int:
         "config": {
             "workload": f"{w.name}: gate logits, forward and backward of SLA-{si.VARIANT_NAMES[w.variant].upper()} "
                         f"B={w.B} T={w.T} H={w.H} dk={w.dk} dv={w.dv} bf16"
-                        + (f", backward in {nseg} segments per batch row" if nseg > 1 else ""),
+                        + (", backward chunk-parallel" if chunks else
+                           f", backward in {nseg} segments per batch row" if nseg > 1 else ""),
             "kernel": "sla_gate_logits + sla_forward + " + ("sla_backward_gdn" if gdn else "sla_backward")
                       + " + 2 x sla_gate_logits_backward",
         },
@@ -751,7 +766,7 @@ def measure_config(name, sla, si, torch, np, steps, warmup, settle):
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     params = sla.SlaParams(w.variant, 1 if w.dtype == "bf16" else 0, w.B, w.T, w.H, w.dk, w.dv, 0, 0, 0)
     nseg = sla.sla_segments(params, cus)
-    ws_bytes = sla.sla_workspace_bytes(params, cus)
+    ws_bytes = sla.sla_forward_workspace_bytes(params, cus)
     ws = torch.empty(ws_bytes, dtype=torch.uint8, device=dev) if ws_bytes else None
     params.segments = nseg
     ptr = lambda t: None if t is None else t.data_ptr()
@@ -893,7 +908,7 @@ def main() -> int:
     if nseg < 1:
         print(f"bench.py: {sla.sla_status_string(nseg)}", file=sys.stderr)
         return 2
-    ws_bytes = sla.sla_workspace_bytes(params, cus)
+    ws_bytes = sla.sla_forward_workspace_bytes(params, cus)
     ws = torch.empty(ws_bytes, dtype=torch.uint8, device=dev) if ws_bytes else None
 
     # The timed call is the raw C-ABI entry point with addresses taken once: the Python wrapper's argument
