@@ -6,36 +6,30 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "sla.h"
 #include "sla_chunk_plan.h"
+#include "sla_lane_ops.h"
 
 namespace sla {
 namespace chk {
 
-typedef __attribute__((ext_vector_type(4))) float f4;
-typedef __attribute__((ext_vector_type(4))) uint32_t u4;
-typedef __attribute__((ext_vector_type(2))) uint32_t u2;
-typedef __attribute__((ext_vector_type(4))) short s4;
-typedef __attribute__((ext_vector_type(8))) short s8;
-typedef __attribute__((ext_vector_type(2))) __bf16 bf2;
-typedef __attribute__((ext_vector_type(8))) __bf16 bf8;
-typedef __attribute__((address_space(3))) s4 lds_s4;
+using namespace lane_ops;
 
 constexpr int kChunk = kChunkTokens;  // tokens per chunk: four 16-token blocks, the unit within which GLA's decay products are formed
-constexpr float kLog2e = 1.4426950408889634f;
 
 struct Args {
     const uint16_t* q;
     const uint16_t* k;
     const uint16_t* v;
-    const uint16_t* dout;    // backward; null: forward states only
+    const uint16_t* dout;
     const uint16_t* ld;      // GLA: [B,T,H,dk]
     const float* ld_head;    // RetNet: [H]
     const float* gq;         // gates [B,T,H]
     const float* gk;
     const float* s0;         // [B,H,dk,dv] or null
     const float* dsf;        // cotangent of the final state or null
-    float* sT;               // final state or null
     float* ds0;              // gradient of the initial state or null
     float* end;              // GLA with dsf: [B,H][dv/32][dk] rowsum(dsf * S) over 32 value columns each, S entering the last chunk
     u4* S;                   // operand pieces of the state entering a chunk, see piece()
@@ -92,43 +86,13 @@ __device__ __forceinline__ bool chunk_of(const Args& a, int slot, int& b, int& c
     return chunk >= 0 && chunk < (s.T + kChunk - 1) / kChunk;
 }
 
-__device__ __forceinline__ float bf_lo(uint32_t p) { return __uint_as_float(p << 16); }
-__device__ __forceinline__ float bf_hi(uint32_t p) { return __uint_as_float(p & 0xffff0000u); }
 __device__ __forceinline__ float bf_at(const u4& x, int i) { return (i & 1) ? bf_hi(x[i >> 1]) : bf_lo(x[i >> 1]); }
-__device__ __forceinline__ uint32_t pack2(float lo, float hi) {
-    bf2 t;
-    t.x = (__bf16)lo;
-    t.y = (__bf16)hi;
-    return __builtin_bit_cast(uint32_t, t);
-}
-__device__ __forceinline__ u2 pack4(f4 x) { return u2{pack2(x[0], x[1]), pack2(x[2], x[3])}; }
 __device__ __forceinline__ u4 pack8(f4 x, f4 y) {
     return u4{pack2(x[0], x[1]), pack2(x[2], x[3]), pack2(y[0], y[1]), pack2(y[2], y[3])};
 }
 __device__ __forceinline__ float ex2(float x) { return __builtin_amdgcn_exp2f(x); }
 __device__ __forceinline__ s8 op(u4 x) { return __builtin_bit_cast(s8, x); }
-__device__ __forceinline__ s8 join(s4 a, s4 b) { return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7); }
-// 16x16x32: lane (r = lane % 16, g = lane / 16) holds row r of A / column r of B, contraction slots 8g..8g+7 (any
-// assignment of indices to slots that A and B share); D[4g + i][r] in register i.  The only matrix opcode used here.
-__device__ __forceinline__ void mma(f4& c, s8 a, s8 b) {
-    c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
-}
-// Transposing LDS read: lane l of a group of 16 addresses row l / 4, piece l % 4 (four columns), and receives column
-// l (element l % 4 of piece l / 4) of the four rows.
-__device__ __forceinline__ s4 lds_tr(const uint16_t* p) { return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4*)p); }
-
-template <int CTRL>
-__device__ __forceinline__ float dpp(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
-// inclusive sums over the 16 lanes of a row (tokens): from lane 0 up / from lane 15 down
-__device__ __forceinline__ float row_prefix(float x) {
-    x += dpp<0x111>(x);
-    x += dpp<0x112>(x);
-    x += dpp<0x114>(x);
-    x += dpp<0x118>(x);
-    return x;
-}
+// inclusive sums over the 16 lanes of a row (tokens), from lane 15 down
 __device__ __forceinline__ float row_suffix(float x) {
     x += dpp<0x101>(x);
     x += dpp<0x102>(x);
@@ -138,21 +102,6 @@ __device__ __forceinline__ float row_suffix(float x) {
 }
 __device__ __forceinline__ float row_last(float x) { return dpp<0x15F>(x); }   // lane 15 of the row, to all
 __device__ __forceinline__ float row_first(float x) { return dpp<0x150>(x); }  // lane 0 of the row, to all
-__device__ __forceinline__ float row_all(float x) {                            // sum over the 16 lanes, to all
-    x += dpp<0x128>(x);
-    x += dpp<0x124>(x);
-    x += dpp<0x122>(x);
-    x += dpp<0x121>(x);
-    return x;
-}
-// Sum over the four 16-lane rows of a wave, returned in every lane.
-__device__ __forceinline__ float all_groups(float x) {
-    const uint32_t xi = __float_as_uint(x);
-    const u2 a = __builtin_amdgcn_permlane16_swap(xi, xi, false, false);
-    const uint32_t yi = __float_as_uint(__uint_as_float(a[0]) + __uint_as_float(a[1]));
-    const u2 b = __builtin_amdgcn_permlane32_swap(yi, yi, false, false);
-    return __uint_as_float(b[0]) + __uint_as_float(b[1]);
-}
 
 // Rows of one sequence and head through a buffer descriptor that ends with the sequence: tokens past it read as zero.
 constexpr uint32_t kRsrcWord3 = 0x00020000u;  // raw buffer, 32-bit data format
@@ -161,9 +110,6 @@ struct Rows {
     int off, step;  // bytes: column 0 of token 0, and from token to token
     __device__ __forceinline__ u4 load(int t, int col) const {
         return __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(d, off + t * step + 2 * col, 0, 0));
-    }
-    __device__ __forceinline__ u4 stream(int t, int col) const {  // read once: non-temporal
-        return __builtin_bit_cast(u4, __builtin_amdgcn_raw_buffer_load_b128(d, off + t * step + 2 * col, 0, 2));
     }
     __device__ __forceinline__ void put(int t, int col, u4 x) const {  // tokens past the end are dropped
         __builtin_amdgcn_raw_buffer_store_b128(x, d, off + t * step + 2 * col, 0, 0);
@@ -205,6 +151,25 @@ __device__ __forceinline__ int unit_at(int row, int u) {
     if constexpr (U == 16) return row * U + (u ^ (row & 15));
     if constexpr (U == 8) return row * U + (u ^ ((row >> 1) & 7));
     return row * U + (u ^ ((row >> 2) & 3));
+}
+
+// Lets KERNEL use that much dynamic LDS: once per device and kernel (bit d = done on device d); not a stream operation.
+template <auto KERNEL>
+static bool allow_lds(int bytes) {
+    static std::atomic<uint64_t> configured{0};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (!((configured.load(std::memory_order_acquire) >> dev) & 1u)) {
+        if (hipFuncSetAttribute((const void*)KERNEL, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        configured.fetch_or(uint64_t(1) << dev, std::memory_order_release);
+    }
+    return true;
 }
 
 }  // namespace chk

@@ -19,8 +19,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <algorithm>
-#include <atomic>
 
 #include "sla.h"
 #include "sla_chunk.h"
@@ -242,10 +240,11 @@ __global__ __launch_bounds__(kThreads, 2) void sla_chunk_backward_kernel(const A
                 put(L::oQ32, r, f[5]);
             }
             if (m == 2 && WT < 4) {  // block 3's rows are in registers still
+                constexpr int kLast = TB - 1;
                 float c3[8];
-                scan(lx[WT == 1 ? 3 : 1], tri, c3);
+                scan(lx[kLast], tri, c3);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) f[5][e] = bf_at(qx[WT == 1 ? 3 : 1], e) * ex2(c3[e]) * A[2][e];
+                for (int e = 0; e < 8; ++e) f[5][e] = bf_at(qx[kLast], e) * ex2(c3[e]) * A[2][e];
                 put(L::oQ32, r, f[5]);
             }
             if (r == 0) {
@@ -630,23 +629,9 @@ __global__ __launch_bounds__(kThreads, 2) void sla_chunk_backward_kernel(const A
 template <int VAR, int DK, int DV>
 static int launch_chunks(const Args& a, hipStream_t stream) {
     typedef Lds<VAR, DK> L;
-    auto kernel = sla_chunk_backward_kernel<VAR, DK, DV>;
-    // once per device and instantiation (bit d = done on device d); not a stream operation
-    static std::atomic<uint64_t> configured{0};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) {
-        (void)hipGetLastError();
-        return SLA_ERR_HIP;
-    }
-    if (!((configured.load(std::memory_order_acquire) >> dev) & 1u)) {
-        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, L::total) != hipSuccess) {
-            (void)hipGetLastError();
-            return SLA_ERR_HIP;
-        }
-        configured.fetch_or(uint64_t(1) << dev, std::memory_order_release);
-    }
+    if (!allow_lds<sla_chunk_backward_kernel<VAR, DK, DV>>(L::total)) return SLA_ERR_HIP;
     const unsigned n = ((unsigned)a.slots * a.nh + 7u) / 8u * 8u;
-    hipLaunchKernelGGL(kernel, dim3(n), dim3(kThreads), (size_t)L::total, stream, a);
+    hipLaunchKernelGGL((sla_chunk_backward_kernel<VAR, DK, DV>), dim3(n), dim3(kThreads), (size_t)L::total, stream, a);
     return hipGetLastError() == hipSuccess ? SLA_OK : SLA_ERR_HIP;
 }
 template <int VAR, int DK>

@@ -23,8 +23,6 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
-#include <algorithm>
-#include <atomic>
 
 #include "sla.h"
 #include "sla_chunk.h"
@@ -377,23 +375,9 @@ __global__ __launch_bounds__(kThreads, 2) void sla_chunk_gdn_kernel(const GdnArg
 
 template <int DK, int DV>
 static int launch_gdn_chunks(const GdnArgs& ga, hipStream_t stream) {
-    auto kernel = sla_chunk_gdn_kernel<DK, DV>;
-    // once per device and instantiation (bit d = done on device d); not a stream operation
-    static std::atomic<uint64_t> configured{0};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) {
-        (void)hipGetLastError();
-        return SLA_ERR_HIP;
-    }
-    if (!((configured.load(std::memory_order_acquire) >> dev) & 1u)) {
-        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, GLds<DK>::total) != hipSuccess) {
-            (void)hipGetLastError();
-            return SLA_ERR_HIP;
-        }
-        configured.fetch_or(uint64_t(1) << dev, std::memory_order_release);
-    }
+    if (!allow_lds<sla_chunk_gdn_kernel<DK, DV>>(GLds<DK>::total)) return SLA_ERR_HIP;
     const unsigned n = ((unsigned)ga.a.slots * ga.a.H + 7u) / 8u * 8u;
-    hipLaunchKernelGGL(kernel, dim3(n), dim3(kThreads), (size_t)GLds<DK>::total, stream, ga);
+    hipLaunchKernelGGL((sla_chunk_gdn_kernel<DK, DV>), dim3(n), dim3(kThreads), (size_t)GLds<DK>::total, stream, ga);
     return hipGetLastError() == hipSuccess ? SLA_OK : SLA_ERR_HIP;
 }
 template <int DK>

@@ -224,14 +224,13 @@ __global__ __launch_bounds__(kStateThreads, 3) void sla_chunk_state_kernel(const
             if (it + 1 < nc) turn(it + 1, pb, pa);
         }
     }
-    float* out = rev ? a.ds0 : a.sT;
-    if (out) {
+    if (rev && a.ds0) {
 #pragma unroll
         for (int i = 0; i < NI; ++i)
 #pragma unroll
             for (int n = 0; n < 2; ++n) {
                 const int d = kt0 + 32 * wp + key_of(ti(i), r), v = vt0 + 32 * cg + 8 * g + 4 * n;
-                *(f4*)(out + (((size_t)b * a.H + h) * DK + d) * DV + v) = acc[i][n];
+                *(f4*)(a.ds0 + (((size_t)b * a.H + h) * DK + d) * DV + v) = acc[i][n];
             }
     }
 }
@@ -239,7 +238,7 @@ __global__ __launch_bounds__(kStateThreads, 3) void sla_chunk_state_kernel(const
 template <int VAR, int DK, int DV>
 static int launch_tiles(const Args& a, hipStream_t stream) {
     const dim3 block(kStateThreads);
-    const unsigned pairs8 = ((unsigned)(a.nb * a.nh) + 7u) / 8u * 8u, dirs = a.dout ? 2 : 1;
+    const unsigned pairs8 = ((unsigned)(a.nb * a.nh) + 7u) / 8u * 8u, dirs = 2;
     if constexpr (DK == 32) {
         hipLaunchKernelGGL((sla_chunk_state_kernel<VAR, DK, DV, 32>), dim3(pairs8 * (DV / kTileV), dirs), block, 0, stream, a);
     } else {
