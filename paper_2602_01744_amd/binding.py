@@ -522,10 +522,13 @@ def backward(variant: int, q, k, v, q_head_logits, k_head_logits, log_decay, d_o
              segments: int = 1):
     """Gradients of ``forward`` (RetNet, GLA; bfloat16 or float32) on the current CUDA(HIP) device and stream.  Returns a
     dict of new tensors: dq, dk, dv, dq_head_logits, dk_head_logits (None without k_head_logits), dlog_decay (GLA only,
-    else None) and d_initial_state (None unless asked for).  bfloat16: ``segments`` >= 2 cuts every batch row into that
-    many segments that run in parallel (for batches with few sequences); 0 asks ``sla_backward_segments`` for the count
-    that fills this device.  float32: ``segments`` must be 0 or 1; the library cuts rows over 128 tokens of batches with few
-    sequences by itself, unless a ``workspace`` is given that only has the room of the single pass."""
+    else None) and d_initial_state (None unless asked for).
+
+    bfloat16: most calls run chunk-parallel in the workspace that is allocated here, whatever ``segments`` says; long rows with
+    few heads, and calls given a ``workspace`` of sla_backward_workspace_bytes, run in that many segments per row that work in
+    parallel (>= 2), or in one pass (1); 0 asks ``sla_backward_segments`` for the count that fills this device.  float32:
+    ``segments`` must be 0 or 1; the library cuts rows over 128 tokens of batches with few sequences by itself, unless a
+    ``workspace`` is given that only has the room of the single pass.  The schedules differ in the rounding of operands."""
     import torch
 
     assert q.is_cuda and q.dtype in (torch.bfloat16, torch.float32)

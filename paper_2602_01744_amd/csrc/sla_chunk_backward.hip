@@ -13,9 +13,10 @@
 // tokens (T = 2085 128 x 128: 5.3e-3 of its norm against the oracle, the sweeps' 1.6e-2; for the tokens next to the sweeps'
 // fp32 anchors 2.8e-3 against 3.8e-3).  In a row's last chunk S and X are taken in fp32 for the first term, see end.
 // Against the sweeps of sla_backward.hip, which carry the states through all tokens of a sequence (a call, all launches):
-// few sequences 2 to 4 times (B=4 T=500 H=8 128 x 128 GLA 109 -> 45 us; B=8 T=4096 H=4 128 x 256 GLA 522, in four segments,
-// -> 330 us), B=8 T=2048 H=16 128 x 128 GLA 398 -> 390 us, RetNet 306 -> 290 us: there the memory system bounds it, 0.84 GB in
-// and 0.3 GB out in 216 us (GLA).  Small batches are bound by one workgroup's own latency, 19 us.
+// few sequences 2 to 4 times (B=4 T=500 H=8 128 x 128 GLA 109 -> 45 us; B=8 T=4096 H=4 128 x 256 GLA 514, in four segments,
+// -> 312 us), B=8 T=2048 H=16 128 x 128 GLA 406 -> 393 us, RetNet 300 -> 282 us: there the memory system bounds it, 0.84 GB in
+// and 0.31 GB out in 221 us (GLA).  Small batches are bound by one workgroup's own latency, 19 us.  Which calls it takes:
+// backward_chunks_take() in sla_chunk_plan.h.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -69,8 +70,8 @@ template <int VAR, int DK, int DV>
 __global__ __launch_bounds__(kThreads, 2) void sla_chunk_backward_kernel(const Args a) {
     typedef Lds<VAR, DK> L;
     constexpr bool GLA = VAR == SLA_GLA;
-    // GLA at width 128: q, k and the decay are loaded a second time for the last part; kept, they would spill (291 us a call
-    // against 260, B=8 T=2048 H=16)
+    // GLA at width 128: q, k and the decay are loaded a second time for the last part; kept, they would spill (this
+    // launch, B=8 T=2048 H=16: 291 us against 260 when the choice was made, 221 now)
     constexpr bool kReload = GLA && DK == 128;
     constexpr int WD = L::WD, WT = L::WT, TB = L::TB, U = DK / 8, NS = DV / 32, NM = 3;
     extern __shared__ __align__(16) unsigned char smem[];

@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kThreads, 2) void sla_chunk_gdn_kernel(const GdnArg
     const Rows rq = rows_of<DK>(a, a.q, s, b, h), rk = rows_of<DK>(a, a.k, s, b, h);
     const Rows rv = rows_of<DV>(a, a.v, s, b, h), ro = rows_of<DV>(a, a.dout, s, b, h);
     const Rows rr = rows_of<DV>(a, ga.res, s, b, h);
-    // (under 2^31 bytes: the states of this schedule, dk / 32 and more times as many, take a GiB at most)
+    // (under 2^31 bytes: a sequence's states of both kinds are dk / 64 times as many and more, a GiB at most)
     const Rows rd = {__builtin_amdgcn_make_buffer_rsrc((void*)(ga.du + s.tok0 * a.H * DV), 0, s.T * a.H * DV * 4, kRsrcWord3),
                      h * DV * 4, a.H * DV * 4};
     const Rows rdv = rows_of<DV>(a, a.dv, s, b, h);
