@@ -300,11 +300,11 @@ size_t sla_backward_gdn_varlen_workspace_bytes(const sla_params* p);
 
 /*
  * Bytes of workspace with which sla_backward_gdn (packed == 0) or sla_backward_gdn_varlen (packed != 0) runs bf16 tensors
- * chunk-parallel; never less than their own queries.  The states of both directions at the boundaries of 64-token chunks
- * then lie in the workspace, a GiB of them at most (larger batches, and long rows enough to fill the chip without, run the
- * sweeps in the plain workspace), and every chunk
- * of a head is worked on independently.  A smaller workspace runs the sweeps; the gradients of the two agree to the rounding
- * of bf16 operands.  Key heads of width 32 and fp32 tensors: the same as the other queries.
+ * fastest; never less than their own queries.  With it most calls run chunk-parallel: the states of both directions at the
+ * boundaries of 64-token chunks then lie in the workspace, a GiB of them at most, and every chunk of a head is worked on
+ * independently.  Larger batches, and calls whose sweeps fill the chip and are as fast, run the sweeps in the plain workspace,
+ * as any call does in a smaller one; the gradients of the two agree to the rounding of bf16 operands, and which one runs
+ * depends on *p and the workspace's size alone.  Key heads of width 32 and fp32 tensors: the same as the other queries.
  */
 size_t sla_backward_gdn_chunks_workspace_bytes(const sla_params* p, int packed);
 
