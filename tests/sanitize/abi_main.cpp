@@ -138,7 +138,7 @@ int main() {
     EXPECT(sla_backward_chunks_workspace_bytes(&ok, 0) > 0 && sla_backward_gdn_chunks_workspace_bytes(&ok, 0) == 0, 1);
     EXPECT(sla_backward(&ok, A, A, A, F, F, A, nullptr, A, nullptr, A, A, A, F, F, A, nullptr, A, 16, nullptr), SLA_ERR_WORKSPACE);
     sla_params gdn = ok; gdn.variant = SLA_GDN;
-    EXPECT(sla_backward_gdn_chunks_workspace_bytes(&gdn, 1) > sla_backward_gdn_varlen_workspace_bytes(&gdn) / 2, 1);
+    EXPECT(sla_backward_gdn_chunks_workspace_bytes(&gdn, 1) >= sla_backward_gdn_varlen_workspace_bytes(&gdn), 1);
     EXPECT(sla_short_conv_silu_l2(SLA_BF16, 2, 64, 200, 4, 64, 1e-6f, A, F, A, nullptr), SLA_ERR_SHAPE);
     EXPECT(sla_short_conv_silu_l2_backward(SLA_BF16, 2, 100, 256, 4, 64, 1e-6f, A, F, A, A, F, A, 16, nullptr), SLA_ERR_WORKSPACE);
     EXPECT(sla_gate_logits_backward(&ok, A, F, nullptr, A, F, A, (size_t)1 << 30, nullptr), SLA_ERR_NULL);
