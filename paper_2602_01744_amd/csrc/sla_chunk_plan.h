@@ -85,20 +85,29 @@ inline bool backward_chunks_take(const sla_params& p, bool packed, int nseg, siz
     if (p.dk < 64) return true;  // the others run them on copies padded to 64 (GLA B=1 T=16384 H=8 32 x 64 1997 -> 210 us)
     const bool gla = p.variant == SLA_GLA;
     const double heads = (double)p.B * p.H * p.dk * p.dv / (128. * 128.);  // of 128 x 128
+    const int64_t rows = (int64_t)p.B * p.H;
     // Sequences of a 16-token block: the sweeps do one step of their walk, a chunk all its work.  That is slower for numbers
-    // that fill the chip once, for GLA's kernel for keys of 64 also for larger ones.  Packed 12 tokens each, H=8, sweeps ->
-    // chunks: GLA 128 x 128 16 sequences 32 -> 34 us, 32 37 -> 46, 64 58 -> 64; 64 x 64 32 31 -> 30, 128 46 -> 55, 4096 1092 ->
-    // 1350; RetNet 128 x 128 16 31 -> 29, 32 32 -> 36, 128 60 -> 57.  Of 24 tokens: 128 GLA 64 x 64 60 -> 54.
-    if ((packed ? (int64_t)p.T <= (int64_t)16 * p.B : p.T < 16) && heads >= (gla ? 128. : 256.) &&
-        (heads < (gla ? 1025. : 1024.) || (gla && p.dk == 64)))
+    // that fill the chip about once, and GLA's kernel pays for it in larger numbers too, but for keys of 128 with up to 128 values.
+    // Packed, 3 and 14 tokens each, H=8, sweeps -> chunks:
+    //     GLA     64 x 128   32 sequences 30 -> 34, 31 -> 34   64 34 -> 50, 36 -> 50   256 92 -> 109, 104 -> 109   1024 327 -> 367, 377 -> 381
+    //             128 x 128  16 31 -> 32, 31 -> 34   64 54 -> 68, 58 -> 65   128 94 -> 99, 103 -> 98   256 172 -> 164, 199 -> 168
+    //             128 x 256  16 31 -> 42, 32 -> 47   64 69 -> 91, 77 -> 91   256 235 -> 260, 278 -> 266   1024 917 -> 1027, 1088 -> 1114
+    //     RetNet  64 x 256   16 25 -> 27, 26 -> 28   64 35 -> 48, 38 -> 43   128 58 -> 63, 63 -> 61   256 102 -> 95, 118 -> 101
+    //             128 x 128  16 25 -> 27, 25 -> 28   32 29 -> 35, 31 -> 35   64 46 -> 52, 50 -> 47   128 80 -> 67, 87 -> 65
+    if ((packed ? (int64_t)p.T <= (int64_t)16 * p.B : p.T < 16) && heads >= 128. &&
+        (gla ? p.dk == 64 || p.dv == 256 || rows < 1536 : rows < (p.dk == 64 ? 1536 : 768)))
         return false;
     const ChunkParts parts = backward_chunks_parts(p, packed, floats);
     const int64_t count = ((int64_t)p.B + parts.nb - 1) / parts.nb * (((int64_t)p.H + parts.nh - 1) / parts.nh);
     if (nseg > 1) return (double)((p.T + kChunkTokens - 1) / kChunkTokens) * (count - heads / (gla ? 20. : 24.)) <= (gla ? 58. : 90.);
-    if ((int64_t)p.B * p.H * std::min(p.dk, p.dv) / 64 < 256) return count <= 4;
-    // RetNet's values four times as wide as its keys: states as large as the rows they stand for (64 x 256 B=16 T=2048 H=16
-    // 623 -> 650 us; T=512 B=32 341 -> 327)
-    if (!gla && p.dv >= 4 * p.dk && !packed && p.T >= 1024) return false;
+    if (rows * std::min(p.dk, p.dv) / 64 < 240) return count <= 4;
+    // RetNet's 64 x 256 keeps states as large as the rows they stand for.  Where the sweeps fill the chip in every round it loses on
+    // all but short rows: B=16 H=16 T=448 139 -> 131, T=576 169 -> 179, T=1024 305 -> 328; two rounds, B=32, T=704 444 -> 437,
+    // T=2500 1517 -> 1595; one and a quarter, B=20, T=1024 470 -> 394.
+    if (!gla && !packed && p.dk == 64 && p.dv == 256) {
+        const int64_t rounds = (rows + 255) / 256;
+        if (16 * rows >= 15 * 256 * rounds && p.T >= (rounds == 1 ? 576 : 1024)) return false;
+    }
     return (double)(count - 1) <= heads / (gla ? 400. : 92.);
 }
 

@@ -63,6 +63,11 @@ def test_which_calls_run_chunk_parallel(variant):
     # sequences of a block: not in numbers that fill the chip once
     assert chunks(32, 32 * 40, 16, packed=True) and not chunks(32, 32 * 12, 16, packed=True)
     assert chunks(2, 2 * 12, 16, packed=True)
+    assert chunks(64, 64 * 12, 16, 128, 256, packed=True) == (variant == sla.RETNET)
+    assert chunks(1024, 1024 * 12, 16, 64, 128, packed=True) == (variant == sla.RETNET)
+    # RetNet's widest values, where the sweeps fill the chip in every round
+    assert chunks(16, 640, 16, 64, 256) == chunks(32, 2048, 16, 64, 256) == (variant == sla.GLA)
+    assert chunks(16, 448, 16, 64, 256) and chunks(24, 2048, 16, 64, 256) and chunks(16, 1024, 16, 64, 128)
     assert chunks(4096, 4096 * 12, 16, packed=True)
 
 
